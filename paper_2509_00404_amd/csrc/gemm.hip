@@ -26,6 +26,19 @@ struct Fp4Operand {
     int64_t rows;
 };
 
+// Vector loads at any byte address (rows start on 16-byte code and 8-byte scale boundaries only when K % 128 == 0;
+// the hardware loads unaligned vectors in one instruction, it only touches one cache line more now and then).
+typedef uint32_t uvec4_u __attribute__((ext_vector_type(4), aligned(1)));
+typedef uint32_t uvec2_u __attribute__((ext_vector_type(2), aligned(1)));
+__device__ __forceinline__ uint4 load16_any(const uint8_t* p) {
+    const uvec4_u v = *reinterpret_cast<const uvec4_u*>(p);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ uint2 load8_any(const uint8_t* p) {
+    const uvec2_u v = *reinterpret_cast<const uvec2_u*>(p);
+    return make_uint2(v.x, v.y);
+}
+
 // One thread's share of a stage of ROWS rows x 64 B of codes: V = ROWS*4/NT 16-byte code vectors.
 // NT = threads per workgroup.
 template <int V>
@@ -40,9 +53,11 @@ struct ScaleRegs {
     uint2 s[V];
 };
 
-template <int BM, int BN, int NT, bool VEC>
+// `whole`: all 128 contraction elements of the stage exist (uniform; a constant where PART is false); otherwise the
+// missing ones read as zero
+template <int BM, int BN, int NT>
 __device__ __forceinline__ void scale_load(const Fp4Operand& A, const Fp4Operand& B, int64_t m0, int64_t n0, int64_t K,
-                                           int64_t k0, ScaleRegs<(BM + BN + NT - 1) / NT>& rg, int tid) {
+                                           int64_t k0, bool whole, ScaleRegs<(BM + BN + NT - 1) / NT>& rg, int tid) {
     constexpr int V = (BM + BN + NT - 1) / NT;
     const int64_t sstride = K / 16;
 #pragma unroll
@@ -54,8 +69,8 @@ __device__ __forceinline__ void scale_load(const Fp4Operand& A, const Fp4Operand
             int64_t gr = isa ? m0 + e : n0 + (e - BM);
             if (gr >= op.rows) gr = op.rows - 1;
             const uint8_t* src = op.scales + gr * sstride + k0 / 16;
-            if (VEC) {
-                rg.s[v] = *reinterpret_cast<const uint2*>(src);
+            if (whole) {
+                rg.s[v] = load8_any(src);
             } else {
                 uint32_t w[2] = {0, 0};
                 for (int i = 0; i < 8; ++i)
@@ -85,11 +100,11 @@ __device__ __forceinline__ void scale_store(const ScaleRegs<(BM + BN + NT - 1) /
     }
 }
 
-template <int ROWS, int NT, bool VEC>
-__device__ __forceinline__ void stage_load(const Fp4Operand& op, int64_t r0, int64_t K, int64_t k0,
+template <int ROWS, int NT>
+__device__ __forceinline__ void stage_load(const Fp4Operand& op, int64_t r0, int64_t K, int64_t k0, bool whole,
                                            StageRegs<ROWS * 4 / NT>& rg, int tid) {
     constexpr int T = ROWS * 4 / NT;
-    const int64_t cstride = K / 2, sstride = K / 16;
+    const int64_t cstride = K / 2;
 #pragma unroll
     for (int v = 0; v < T; ++v) {
         int e = tid + NT * v;
@@ -97,8 +112,8 @@ __device__ __forceinline__ void stage_load(const Fp4Operand& op, int64_t r0, int
         int64_t gr = r0 + row;
         if (gr >= op.rows) gr = op.rows - 1;
         const uint8_t* src = op.codes + gr * cstride + k0 / 2 + 16 * seg;
-        if (VEC) {
-            rg.c[v] = *reinterpret_cast<const uint4*>(src);
+        if (whole) {
+            rg.c[v] = load16_any(src);
         } else {
             uint32_t w[4] = {0, 0, 0, 0};
             for (int b = 0; b < 16; ++b) {
@@ -156,7 +171,9 @@ __host__ __device__ __forceinline__ int64_t ext_chunk(int64_t row_block, int ste
 
 // One output tile by a workgroup of WMW x WNW waves, each wave TM x TN tiles of 32x32 (BM = 32 TM WMW,
 // BN = 32 TN WNW), over the contraction stages [it0, niter).
-template <int TM, int TN, int WMW, int WNW, bool VEC, typename OUT>
+// PART: the last stage may end past K.  (A template parameter: the test costs the wait counts of every stage, 5 % of a
+// small product.)
+template <int TM, int TN, int WMW, int WNW, bool PART, typename OUT>
 __device__ __forceinline__ void
 gemm_nt_tile(const Fp4Operand& A, const Fp4Operand& B, int64_t K, const bf16_t* __restrict__ Aext,
              const bf16_t* __restrict__ Bext, int Ke, float alpha, OUT* __restrict__ C, int64_t ldc, int tile_m, int tile_n,
@@ -183,9 +200,14 @@ gemm_nt_tile(const Fp4Operand& A, const Fp4Operand& B, int64_t K, const bf16_t* 
     StageRegs<BM * 4 / NT> ra;
     StageRegs<BN * 4 / NT> rb;
     ScaleRegs<(BM + BN + NT - 1) / NT> rs;
-    stage_load<BM, NT, VEC>(A, m0, K, it0 * G_KI, ra, tid);
-    stage_load<BN, NT, VEC>(B, n0, K, it0 * G_KI, rb, tid);
-    scale_load<BM, BN, NT, VEC>(A, B, m0, n0, K, it0 * G_KI, rs, tid);
+    auto load = [&](int64_t it) {
+        const int64_t k0 = it * G_KI;
+        const bool whole = !PART || k0 + G_KI <= K;
+        stage_load<BM, NT>(A, m0, K, k0, whole, ra, tid);
+        stage_load<BN, NT>(B, n0, K, k0, whole, rb, tid);
+        scale_load<BM, BN, NT>(A, B, m0, n0, K, k0, whole, rs, tid);
+    };
+    load(it0);
     stage_store<BM, NT>(ra, lds, tid);
     stage_store<BN, NT>(rb, lds + OFF_CB, tid);
     scale_store<BM, BN, NT>(rs, lds + OFF_SA, lds + OFF_SB, tid);
@@ -193,11 +215,7 @@ gemm_nt_tile(const Fp4Operand& A, const Fp4Operand& B, int64_t K, const bf16_t* 
     for (int64_t it = it0; it < niter; ++it) {
         const int cur = (int)((it - it0) & 1);
         const bool more = it + 1 < niter;
-        if (more) {
-            stage_load<BM, NT, VEC>(A, m0, K, (it + 1) * G_KI, ra, tid);
-            stage_load<BN, NT, VEC>(B, n0, K, (it + 1) * G_KI, rb, tid);
-            scale_load<BM, BN, NT, VEC>(A, B, m0, n0, K, (it + 1) * G_KI, rs, tid);
-        }
+        if (more) load(it + 1);
         const uint8_t* bufc = lds + cur * BUF;
         uint8_t* bufn = lds + (cur ^ 1) * BUF;
         const uint8_t* ca = bufc + (wm + li) * G_CROW + 4 * half;
@@ -267,14 +285,15 @@ gemm_nt_tile(const Fp4Operand& A, const Fp4Operand& B, int64_t K, const bf16_t* 
         }
 }
 
-// 1-D grid of ceil(M / BM) * ceil(N / BN) workgroups; workgroup -> tile by TileMap
-template <int TM, int TN, int WMW, int WNW, bool VEC, typename OUT>
+// 1-D grid of ceil(M / BM) * ceil(N / BN) workgroups; workgroup -> tile by TileMap; the first niter stages of the
+// contraction (all of them, unless the last, partial one is among the extra columns)
+template <int TM, int TN, int WMW, int WNW, bool PART, typename OUT>
 __global__ void __launch_bounds__(64 * WMW * WNW)
-k_fp4_gemm_nt(Fp4Operand A, Fp4Operand B, int64_t K, const bf16_t* __restrict__ Aext,
+k_fp4_gemm_nt(Fp4Operand A, Fp4Operand B, int64_t K, int64_t niter, const bf16_t* __restrict__ Aext,
               const bf16_t* __restrict__ Bext, int Ke, float alpha, OUT* __restrict__ C, int64_t ldc, TileMap tmap) {
     int tile_m, tile_n;
     tile_coords(tmap, tile_m, tile_n);
-    gemm_nt_tile<TM, TN, WMW, WNW, VEC, OUT>(A, B, K, Aext, Bext, Ke, alpha, C, ldc, tile_m, tile_n, 0, (K + G_KI - 1) / G_KI);
+    gemm_nt_tile<TM, TN, WMW, WNW, PART, OUT>(A, B, K, Aext, Bext, Ke, alpha, C, ldc, tile_m, tile_n, 0, niter);
 }
 
 // Up to three skinny products in one launch, each cut along the contraction into `splits` parts that are written
@@ -293,7 +312,7 @@ struct SkinnyBatch {
     int count;
 };
 
-template <bool VEC>
+template <bool PART>
 __global__ void __launch_bounds__(256)
 k_fp4_skinny_batch(SkinnyBatch batch, int64_t K) {
     int q = 0;
@@ -307,7 +326,7 @@ k_fp4_skinny_batch(SkinnyBatch batch, int64_t K) {
     const int64_t niter_all = (K + G_KI - 1) / G_KI;
     const int64_t it0 = (int64_t)z * pr.ips;
     const int64_t niter = it0 + pr.ips < niter_all ? it0 + pr.ips : niter_all;
-    gemm_nt_tile<2, 1, 2, 2, VEC, float>(pr.A, pr.B, K, nullptr, nullptr, 0, pr.alpha,
+    gemm_nt_tile<2, 1, 2, 2, PART, float>(pr.A, pr.B, K, nullptr, nullptr, 0, pr.alpha,
                                          pr.P + (size_t)z * pr.A.rows * pr.B.rows, pr.B.rows, t / pr.tiles_n, t % pr.tiles_n,
                                          it0, niter);
 }
@@ -323,7 +342,8 @@ k_fp4_skinny_batch(SkinnyBatch batch, int64_t K) {
 //    workgroup barrier sits at the start of step 6, and steps 6 and 7 already read and expand the
 //    next stage's first two steps, so no MFMA waits for a barrier, an LDS round trip or a global load.
 // The stage body is branch-free and the same for every stage (the last one stages and expands data
-// that nobody uses), which keeps the whole loop one scheduling region.  Needs K % 128 == 0.
+// that nobody uses), which keeps the whole loop one scheduling region.  It covers the K / 128 whole stages; the
+// elements past the last whole stage are among the extra columns (see k_assemble_ext).
 template <typename OUT>
 __global__ void __launch_bounds__(256)
 k_fp4_gemm_nt_pipe(Fp4Operand A, Fp4Operand B, int64_t K, const bf16_t* __restrict__ Aext,
@@ -404,12 +424,12 @@ k_fp4_gemm_nt_pipe(Fp4Operand A, Fp4Operand B, int64_t K, const bf16_t* __restri
     uint2 rsa, rsb;
     // st = stage index within this workgroup's range, clamped by the caller
     auto load_codes = [&](int st, int v) {
-        ra[v] = *reinterpret_cast<const uint4*>(pa[v] + st * (G_KI / 2));
-        rb[v] = *reinterpret_cast<const uint4*>(pb[v] + st * (G_KI / 2));
+        ra[v] = load16_any(pa[v] + st * (G_KI / 2));
+        rb[v] = load16_any(pb[v] + st * (G_KI / 2));
     };
     auto load_scales = [&](int st) {
-        rsa = *reinterpret_cast<const uint2*>(psa + st * (G_KI / 16));
-        rsb = *reinterpret_cast<const uint2*>(psb + st * (G_KI / 16));
+        rsa = load8_any(psa + st * (G_KI / 16));
+        rsb = load8_any(psb + st * (G_KI / 16));
     };
     auto load_stage = [&](int st) {
 #pragma unroll
@@ -685,55 +705,54 @@ int launch_gemm_pipe(hipStream_t s, const Fp4Operand& a, const Fp4Operand& b, in
 }
 
 template <int TM, int TN, int WMW, int WNW, typename OUT>
-int launch_gemm_tile(hipStream_t s, const Fp4Operand& a, const Fp4Operand& b, int64_t K, bool vec, const bf16_t* Aext,
+int launch_gemm_tile(hipStream_t s, const Fp4Operand& a, const Fp4Operand& b, int64_t K, int64_t niter, const bf16_t* Aext,
                      const bf16_t* Bext, int Ke, float alpha, OUT* C, int64_t ldc) {
     constexpr int BM = 32 * TM * WMW, BN = 32 * TN * WNW, NT = 64 * WMW * WNW;
     static_assert(BM * 4 >= NT && BN * 4 >= NT, "every thread stages at least one code vector");
     const int64_t tm = ceil_div64(a.rows, BM), tn = ceil_div64(b.rows, BN);
     if (tm * tn > 0x7FFFFFFF) return METIS_UNSUPPORTED;
     constexpr size_t lds = gemm_lds_bytes<BM, BN>();
-    dim3 grid((unsigned)(tm * tn));
-    if (vec) {
-        auto kern = k_fp4_gemm_nt<TM, TN, WMW, WNW, true, OUT>;
-        static LdsLimitCache lds_set;
-        if (!ensure_dyn_lds((const void*)kern, lds, lds_set)) return METIS_HIP_ERROR;
-        hipLaunchKernelGGL(kern, grid, dim3(NT), lds, s, a, b, K, Aext, Bext, Ke, alpha, C, ldc, make_tile_map(tm, tn));
-    } else {
-        auto kern = k_fp4_gemm_nt<TM, TN, WMW, WNW, false, OUT>;
-        static LdsLimitCache lds_set;
-        if (!ensure_dyn_lds((const void*)kern, lds, lds_set)) return METIS_HIP_ERROR;
-        hipLaunchKernelGGL(kern, grid, dim3(NT), lds, s, a, b, K, Aext, Bext, Ke, alpha, C, ldc, make_tile_map(tm, tn));
-    }
+    const bool part = niter * G_KI > K;
+    auto kern = part ? k_fp4_gemm_nt<TM, TN, WMW, WNW, true, OUT> : k_fp4_gemm_nt<TM, TN, WMW, WNW, false, OUT>;
+    static LdsLimitCache lds_set[2];
+    if (!ensure_dyn_lds((const void*)kern, lds, lds_set[part])) return METIS_HIP_ERROR;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn)), dim3(NT), lds, s, a, b, K, niter, Aext, Bext, Ke, alpha, C, ldc,
+                       make_tile_map(tm, tn));
     METIS_LAUNCH_CHECK();
     return METIS_OK;
 }
 
+// Shapes whose last, partial contraction stage travels as extra bf16 columns (exact: grid * e4m3 has at most 6
+// significant bits) so that the software-pipelined kernel's branch-free stages serve any K: large outputs with K % 128.
+// (The byte-wise staging it replaced took 798 us for the 4096 x 4096 weight gradient over 6000 tokens, 2.2 times the
+// two aligned products of that step together; the whole step went from 2718 to 2029 us.)
+bool tail_as_columns(int64_t M, int64_t N, int64_t K) { return M >= 1024 && N >= 1024 && K > G_KI && K % G_KI != 0; }
+
+// ext_tail: the elements past the last whole stage are among the extra columns
 template <typename OUT>
 int launch_gemm(hipStream_t s, const metis_fp4& A, const metis_fp4& B, const bf16_t* Aext, const bf16_t* Bext, int Ke,
-                float alpha, OUT* C, int64_t ldc, float* partial = nullptr, size_t partial_bytes = 0) {
+                bool ext_tail, float alpha, OUT* C, int64_t ldc, float* partial = nullptr, size_t partial_bytes = 0) {
     const int64_t M = A.rows, N = B.rows, K = A.cols;
-    Fp4Operand a = {A.codes, A.scales, M}, b = {B.codes, B.scales, N};
-    const bool vec = (K % G_KI) == 0 && reinterpret_cast<uintptr_t>(A.codes) % 16 == 0 &&
-                     reinterpret_cast<uintptr_t>(B.codes) % 16 == 0 && reinterpret_cast<uintptr_t>(A.scales) % 8 == 0 &&
-                     reinterpret_cast<uintptr_t>(B.scales) % 8 == 0;
+    const Fp4Operand a = {A.codes, A.scales, M}, b = {B.codes, B.scales, N};
+    const int64_t niter = ext_tail ? K / G_KI : ceil_div64(K, G_KI);
     if (M >= 1024 && N >= 1024) {
-        // 256x256 tile, 4 waves of 128x128, software-pipelined (needs whole 128-deep stages and aligned rows); the
-        // tiles of a partly filled last round are cut along the contraction when the caller brought room for the parts
+        // 256x256 tile, 4 waves of 128x128, software-pipelined (whole 128-deep stages); the tiles of a partly filled
+        // last round are cut along the contraction when the caller brought room for the parts
+        const bool whole = K % G_KI == 0 || ext_tail;
         const size_t tail_need = gemm_tail_bytes(M, N, K);
         const bool can_split = tail_need > 0 && partial && partial_bytes >= tail_need;
-        if (vec && (can_split || ceil_div64(M, 256) * ceil_div64(N, 256) > 128))
+        const int64_t tiles = ceil_div64(M, 256) * ceil_div64(N, 256);
+        if (whole && (can_split || tiles > 128))
             return launch_gemm_pipe<OUT>(s, a, b, K, Aext, Bext, Ke, alpha, C, ldc, partial, partial_bytes);
         // an output of at most 128 tiles of 256 x 256 would leave half the CUs without work: 128 x 128 tiles
         // (four times as many workgroups, each less efficient) finish sooner
-        if (ceil_div64(M, 256) * ceil_div64(N, 256) <= 128)
-            return launch_gemm_tile<2, 2, 2, 2, OUT>(s, a, b, K, vec, Aext, Bext, Ke, alpha, C, ldc);
-        if (vec) return launch_gemm_pipe<OUT>(s, a, b, K, Aext, Bext, Ke, alpha, C, ldc, partial, partial_bytes);
-        // otherwise 8 waves of 128x64 with bounds-checked staging
-        return launch_gemm_tile<4, 2, 2, 4, OUT>(s, a, b, K, vec, Aext, Bext, Ke, alpha, C, ldc);
+        if (tiles <= 128) return launch_gemm_tile<2, 2, 2, 2, OUT>(s, a, b, K, niter, Aext, Bext, Ke, alpha, C, ldc);
+        // a partial stage that could not become extra columns (no workspace): 8 waves of 128x64, bounds-checked staging
+        return launch_gemm_tile<4, 2, 2, 4, OUT>(s, a, b, K, niter, Aext, Bext, Ke, alpha, C, ldc);
     }
-    if (N > 64 && M > 64) return launch_gemm_tile<2, 2, 2, 2, OUT>(s, a, b, K, vec, Aext, Bext, Ke, alpha, C, ldc);
-    if (N <= 64) return launch_gemm_tile<2, 1, 2, 2, OUT>(s, a, b, K, vec, Aext, Bext, Ke, alpha, C, ldc);
-    return launch_gemm_tile<1, 2, 2, 2, OUT>(s, a, b, K, vec, Aext, Bext, Ke, alpha, C, ldc);
+    if (N > 64 && M > 64) return launch_gemm_tile<2, 2, 2, 2, OUT>(s, a, b, K, niter, Aext, Bext, Ke, alpha, C, ldc);
+    if (N <= 64) return launch_gemm_tile<2, 1, 2, 2, OUT>(s, a, b, K, niter, Aext, Bext, Ke, alpha, C, ldc);
+    return launch_gemm_tile<1, 2, 2, 2, OUT>(s, a, b, K, niter, Aext, Bext, Ke, alpha, C, ldc);
 }
 
 // value of one FP4 element without the tensor scale: grid[code] * e4m3(scale)
@@ -751,6 +770,8 @@ __device__ __forceinline__ float fp4_elem_nog(const uint8_t* codes, const uint8_
 //   Aext[m, kb:kb+ka] = Ua[m,:] without its tensor scale (exact in bf16)
 //   Bext[n, 0:kb]     = Ub[n,:] without its tensor scale (exact in bf16)
 //   Bext[n, kb:kb+ka] = E2[n,:] * Sa * gUa / (gRa gRb)
+//   Aext[m, Kep:Kep+Kt] = Ra[m, K-Kt:K] and Bext[n, Kep:Kep+Kt] = Rb[n, K-Kt:K] without tensor scales (exact in bf16):
+//                       the contraction elements past the last whole stage, when they are taken as columns
 // T1, E2 and Mk arrive as n1, n2, n3 contraction parts that are added here in ascending order.
 // Blocks [0, ceil(Ma/32)) build 32 rows of Aext each: the dequantized factor rows U_a and the small matrix
 // Sa Mk sit in LDS; thread (row t/8, column group t%8) owns the columns 64 h + 8 (t%8) + 0..7 of its row.  The
@@ -811,6 +832,28 @@ __device__ __forceinline__ void decode_factor_rows(const uint8_t* __restrict__ c
     }
 }
 
+// The last Kt contraction elements of rows r0 .. r0 + 31 of a residual as bf16 columns from column Kep on: thread
+// (row rr, column group cg) decodes 8 elements = 4 code bytes and one scale at a time.
+__device__ __forceinline__ uint4 pack8_bf16(const float (&v)[8]);
+__device__ __forceinline__ void tail_columns(const Fp4Operand& R, int64_t K, int Kt, int64_t row, int rr, int cg, int Kep,
+                                             int nsteps, bf16_t* __restrict__ ext) {
+    const float grid[8] = {0.0f, 0.5f, 1.0f, 1.5f, 2.0f, 3.0f, 4.0f, 6.0f};
+    for (int c0 = 8 * cg; c0 < Kt; c0 += 64) {
+        const int64_t k = K - Kt + c0;
+        const uint8_t* c = R.codes + row * (K / 2) + k / 2;
+        const float sc = e4m3_decode(R.scales[row * (K / 16) + k / 16]);
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t byte = c[i >> 1], nib = (i & 1) ? (byte >> 4) : (byte & 15u);
+            const float x = grid[nib & 7u] * sc;
+            v[i] = (nib & 8u) ? -x : x;
+        }
+        const int col = Kep + c0;
+        *reinterpret_cast<uint4*>(ext + ext_chunk(row >> 5, col >> 4, (col >> 3) & 1, rr, nsteps)) = pack8_bf16(v);
+    }
+}
+
 __device__ __forceinline__ uint4 pack8_bf16(const float (&v)[8]) {
     uint4 o;
     o.x = (uint32_t)f32_to_bf16_rne(v[0]) | (uint32_t)f32_to_bf16_rne(v[1]) << 16;
@@ -823,7 +866,7 @@ __device__ __forceinline__ uint4 pack8_bf16(const float (&v)[8]) {
 // NCH = ceil(kb / 64): column groups of a row that hold T1-type columns
 template <int NCH>
 __global__ void __launch_bounds__(256)
-k_assemble_ext(int64_t Ma, int64_t Nb, int ka, int kb, int Kep, const float* __restrict__ T1, int n1,
+k_assemble_ext(int64_t Ma, int64_t Nb, int ka, int kb, int Kep, Fp4Operand Ra, Fp4Operand Rb, int64_t K, int Kt, const float* __restrict__ T1, int n1,
                const float* __restrict__ Mk, int n3, const float* __restrict__ E2, int n2,
                const uint8_t* __restrict__ ua_codes, const uint8_t* __restrict__ ua_scales, float g_ua,
                const float* __restrict__ Sa, const uint8_t* __restrict__ ub_codes,
@@ -831,7 +874,7 @@ k_assemble_ext(int64_t Ma, int64_t Nb, int ka, int kb, int Kep, const float* __r
                float inv_grr, bf16_t* __restrict__ Aext, bf16_t* __restrict__ Bext) {
     extern __shared__ __attribute__((aligned(16))) float ax_sm[];
     const int nblk_a = (int)((Ma + AX_ROWS - 1) / AX_ROWS);
-    const int tid = threadIdx.x, rr = tid >> 3, cg = tid & 7;
+    const int tid = threadIdx.x, rr = tid >> 3, cg = tid & 7, nsteps = (Kep + Kt) >> 4;
     if ((int)blockIdx.x < nblk_a) {
         float* ua = ax_sm;                                          // [AX_ROWS][ka + 1]
         float* mk = ax_sm + (AX_ROWS * (ka + 1) + 3) / 4 * 4;       // [ka][kb] (+ 8 floats of slack)
@@ -863,6 +906,7 @@ k_assemble_ext(int64_t Ma, int64_t Nb, int ka, int kb, int Kep, const float* __r
         decode_factor_rows(ua_codes, ua_scales, Ma, ka, r0, ua, tid);
         __syncthreads();
         if (!in) return;
+        tail_columns(Ra, K, Kt, row, rr, cg, Kep, nsteps, Aext);
         const bool vecmk = kb % 4 == 0;
         const float gs = g_ub * inv_grr;
 #pragma unroll
@@ -897,7 +941,7 @@ k_assemble_ext(int64_t Ma, int64_t Nb, int ka, int kb, int Kep, const float* __r
                 for (int i = 0; i < 8; ++i)
                     if (c0 + i < kb) v[i] = acc[i] * Sb[c0 + i] * gs;
             }
-            *reinterpret_cast<uint4*>(Aext + ext_chunk(row >> 5, c0 >> 4, (c0 >> 3) & 1, rr, Kep >> 4)) = pack8_bf16(v);
+            *reinterpret_cast<uint4*>(Aext + ext_chunk(row >> 5, c0 >> 4, (c0 >> 3) & 1, rr, nsteps)) = pack8_bf16(v);
         }
         return;
     }
@@ -923,6 +967,7 @@ k_assemble_ext(int64_t Ma, int64_t Nb, int ka, int kb, int Kep, const float* __r
     decode_factor_rows(ub_codes, ub_scales, Nb, kb, r0, ub, tid);
     __syncthreads();
     if (!in) return;
+    tail_columns(Rb, K, Kt, row, rr, cg, Kep, nsteps, Bext);
     const float gs = g_ua * inv_grr;
 #pragma unroll
     for (int h = 0; h < 4; ++h) {
@@ -944,7 +989,7 @@ k_assemble_ext(int64_t Ma, int64_t Nb, int ka, int kb, int Kep, const float* __r
             }
             v[i] = x;
         }
-        *reinterpret_cast<uint4*>(Bext + ext_chunk(row >> 5, c0 >> 4, (c0 >> 3) & 1, rr, Kep >> 4)) = pack8_bf16(v);
+        *reinterpret_cast<uint4*>(Bext + ext_chunk(row >> 5, c0 >> 4, (c0 >> 3) & 1, rr, nsteps)) = pack8_bf16(v);
     }
 }
 
@@ -956,7 +1001,8 @@ struct NtOperand {            // one side of Abar Bbar^T: Abar = U diag(S) V^T +
 
 struct LinWs {
     size_t off_t1, off_mk, off_e2, off_aext, off_bext, off_tail, tail_bytes, total;
-    int Kep;
+    int Kep;                 // low-rank columns, padded to 16
+    int Kt;                  // columns of the last, partial contraction stage (0: none or not taken as columns)
     int s1, s2, s3;          // contraction parts of T1, E2, Mk
 };
 
@@ -977,6 +1023,7 @@ LinWs lin_layout(int64_t Ma, int64_t Nb, int ka, int kb, int64_t Kc) {
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
     w.Kep = (ka + kb + 15) / 16 * 16;
+    w.Kt = tail_as_columns(Ma, Nb, Kc) ? (int)(Kc % G_KI) : 0;
     // (the assembly kernel adds the parts up, two rounds of four loads at most)
     w.s1 = kb > 0 ? skinny_parts(Ma, kb, Kc, 8) : 1;
     w.s2 = ka > 0 ? skinny_parts(Nb, ka, Kc, 8) : 1;
@@ -984,9 +1031,9 @@ LinWs lin_layout(int64_t Ma, int64_t Nb, int ka, int kb, int64_t Kc) {
     w.off_t1 = take((size_t)w.s1 * Ma * (kb > 0 ? kb : 1) * 4);
     w.off_mk = take((size_t)w.s3 * (ka > 0 ? ka : 1) * (kb > 0 ? kb : 1) * 4);
     w.off_e2 = take((size_t)w.s2 * Nb * (ka > 0 ? ka : 1) * 4);
-    w.off_aext = take((size_t)((Ma + 31) / 32 * 32) * (w.Kep > 0 ? w.Kep : 16) * 2);       // rows padded to whole 32-row blocks
-    w.off_bext = take((size_t)((Nb + 31) / 32 * 32) * (w.Kep > 0 ? w.Kep : 16) * 2);
-    w.tail_bytes = (Ma >= 1024 && Nb >= 1024 && Kc % G_KI == 0) ? gemm_tail_bytes(Ma, Nb, Kc) : 0;
+    w.off_aext = take((size_t)((Ma + 31) / 32 * 32) * (w.Kep + w.Kt > 0 ? w.Kep + w.Kt : 16) * 2);       // rows padded to whole 32-row blocks
+    w.off_bext = take((size_t)((Nb + 31) / 32 * 32) * (w.Kep + w.Kt > 0 ? w.Kep + w.Kt : 16) * 2);
+    w.tail_bytes = (Ma >= 1024 && Nb >= 1024 && (Kc % G_KI == 0 || w.Kt > 0)) ? gemm_tail_bytes(Ma, Nb, Kc) : 0;
     w.off_tail = take(w.tail_bytes);
     w.total = o;
     return w;
@@ -1014,11 +1061,17 @@ int linear_nt(hipStream_t s, const NtOperand& a, const NtOperand& b, metis_mat* 
     const float grr = a.R.tscale * b.R.tscale;
     int Ke = 0;
     const bf16_t *Aext = nullptr, *Bext = nullptr;
+    bool ext_tail = false;
     int st;
+    const LinWs w = lin_layout(Ma, Nb, ka, kb, Kc);
+    const bool ws_fits = workspace && workspace_bytes >= w.off_tail;                        // the tail region is optional
+    const bool ws_aligned = reinterpret_cast<uintptr_t>(workspace) % 16 == 0;
     if (ka > 0 || kb > 0) {
-        const LinWs w = lin_layout(Ma, Nb, ka, kb, Kc);
-        if (!workspace || workspace_bytes < w.off_tail) return METIS_WORKSPACE_TOO_SMALL;   // the tail region is optional
-        if (reinterpret_cast<uintptr_t>(workspace) % 16) return METIS_INVALID_ARG;
+        if (!ws_fits) return METIS_WORKSPACE_TOO_SMALL;
+        if (!ws_aligned) return METIS_INVALID_ARG;
+    }
+    // (two unsplit operands work without a workspace: a partial last stage then takes the bounds-checked kernel)
+    if (ka > 0 || kb > 0 || (w.Kt > 0 && ws_fits && ws_aligned)) {
         char* ws = (char*)workspace;
         float* T1 = (float*)(ws + w.off_t1);
         float* Mk = (float*)(ws + w.off_mk);
@@ -1032,7 +1085,6 @@ int linear_nt(hipStream_t s, const NtOperand& a, const NtOperand& b, metis_mat* 
             sb.count = 0;
             int wgs = 0;
             const int64_t iters = ceil_div64(Kc, G_KI);
-            bool vec = Kc % G_KI == 0;
             auto add = [&](const metis_fp4& X, const metis_fp4& Y, float* P, int parts) {
                 SkinnyProblem& q = sb.p[sb.count++];
                 q.A = {X.codes, X.scales, X.rows};
@@ -1044,25 +1096,19 @@ int linear_nt(hipStream_t s, const NtOperand& a, const NtOperand& b, metis_mat* 
                 q.ips = (int)ceil_div64(iters, parts);
                 q.first = wgs;
                 wgs += q.tiles * parts;
-                vec = vec && reinterpret_cast<uintptr_t>(X.codes) % 16 == 0 && reinterpret_cast<uintptr_t>(Y.codes) % 16 == 0 &&
-                      reinterpret_cast<uintptr_t>(X.scales) % 8 == 0 && reinterpret_cast<uintptr_t>(Y.scales) % 8 == 0;
             };
             if (ceil_div64(Ma, 128) * 64 * w.s1 + ceil_div64(Nb, 128) * 64 * w.s2 > 0x3FFFFFFF) return METIS_UNSUPPORTED;
             if (kb > 0) add(a.R, b.Vt, T1, w.s1);
             if (ka > 0) add(b.R, a.Vt, E2, w.s2);
             if (ka > 0 && kb > 0) add(a.Vt, b.Vt, Mk, w.s3);
-            for (int i = sb.count; i < 3; ++i) sb.p[i] = sb.p[0];
-            {
+            for (int i = sb.count; i < 3; ++i) sb.p[i] = sb.count ? sb.p[0] : SkinnyProblem{};
+            if (sb.count > 0) {
                 constexpr size_t lds = gemm_lds_bytes<128, 64>();
-                if (vec) {
-                    static LdsLimitCache lds_set;
-                    if (!ensure_dyn_lds((const void*)k_fp4_skinny_batch<true>, lds, lds_set)) return METIS_HIP_ERROR;
-                    hipLaunchKernelGGL(k_fp4_skinny_batch<true>, dim3((unsigned)wgs), dim3(256), lds, s, sb, Kc);
-                } else {
-                    static LdsLimitCache lds_set;
-                    if (!ensure_dyn_lds((const void*)k_fp4_skinny_batch<false>, lds, lds_set)) return METIS_HIP_ERROR;
-                    hipLaunchKernelGGL(k_fp4_skinny_batch<false>, dim3((unsigned)wgs), dim3(256), lds, s, sb, Kc);
-                }
+                const bool part = Kc % G_KI != 0;
+                auto skinny = part ? k_fp4_skinny_batch<true> : k_fp4_skinny_batch<false>;
+                static LdsLimitCache lds_set[2];
+                if (!ensure_dyn_lds((const void*)skinny, lds, lds_set[part])) return METIS_HIP_ERROR;
+                hipLaunchKernelGGL(skinny, dim3((unsigned)wgs), dim3(256), lds, s, sb, Kc);
                 METIS_LAUNCH_CHECK();
             }
             const int64_t nblk = ceil_div64(Ma, AX_ROWS) + ceil_div64(Nb, AX_ROWS);
@@ -1071,30 +1117,29 @@ int linear_nt(hipStream_t s, const NtOperand& a, const NtOperand& b, metis_mat* 
             static LdsLimitCache ax_set[2];
             if (ax_lds > 48 * 1024 && !ensure_dyn_lds((const void*)assemble, ax_lds, ax_set[kb > 64])) return METIS_HIP_ERROR;
             hipLaunchKernelGGL(assemble, dim3((unsigned)nblk), dim3(256), ax_lds, s, Ma, Nb, ka, kb, w.Kep,
-                               T1, w.s1, Mk, w.s3, E2, w.s2, a.Ut.codes, a.Ut.scales, ka > 0 ? a.Ut.tscale : 1.0f, a.S, b.Ut.codes,
+                               Fp4Operand{a.R.codes, a.R.scales, Ma}, Fp4Operand{b.R.codes, b.R.scales, Nb}, Kc, w.Kt, T1,
+                               w.s1, Mk, w.s3, E2, w.s2, a.Ut.codes, a.Ut.scales, ka > 0 ? a.Ut.tscale : 1.0f, a.S, b.Ut.codes,
                                b.Ut.scales, kb > 0 ? b.Ut.tscale : 1.0f, b.S, 1.0f / grr, ae, be);
             METIS_LAUNCH_CHECK();
         }
-        Ke = w.Kep;
+        Ke = w.Kep + w.Kt;
+        ext_tail = w.Kt > 0;
         Aext = ae;
         Bext = be;
     }
     // room for the partial tiles of a split last round, when the workspace has it
     float* partial = nullptr;
     size_t partial_bytes = 0;
-    {
-        const LinWs w = lin_layout(Ma, Nb, ka, kb, Kc);
-        if (w.tail_bytes > 0 && workspace && workspace_bytes >= w.total && reinterpret_cast<uintptr_t>(workspace) % 16 == 0) {
-            partial = (float*)((char*)workspace + w.off_tail);
-            partial_bytes = w.tail_bytes;
-        }
+    if (w.tail_bytes > 0 && workspace && workspace_bytes >= w.total && ws_aligned) {
+        partial = (float*)((char*)workspace + w.off_tail);
+        partial_bytes = w.tail_bytes;
     }
     if (!do_main) return METIS_OK;
     const int pi = metis_prof_begin(METIS_PROF_GEMM, s);
     if (out->dtype == METIS_BF16)
-        st = launch_gemm<bf16_t>(s, a.R, b.R, Aext, Bext, Ke, grr, (bf16_t*)out->ptr, out->ld, partial, partial_bytes);
+        st = launch_gemm<bf16_t>(s, a.R, b.R, Aext, Bext, Ke, ext_tail, grr, (bf16_t*)out->ptr, out->ld, partial, partial_bytes);
     else
-        st = launch_gemm<float>(s, a.R, b.R, Aext, Bext, Ke, grr, (float*)out->ptr, out->ld, partial, partial_bytes);
+        st = launch_gemm<float>(s, a.R, b.R, Aext, Bext, Ke, ext_tail, grr, (float*)out->ptr, out->ld, partial, partial_bytes);
     metis_prof_end(METIS_PROF_GEMM, pi, s);
     return st;
 }
