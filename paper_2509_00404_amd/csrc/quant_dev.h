@@ -116,22 +116,62 @@ __device__ __forceinline__ float sr_pick(float x, float y, float step, uint32_t 
     return __builtin_copysignf(v, y);
 }
 
+// The same choice without the exact remainder, for all but one draw in 2^17.  With e = max(floor(log2 a), 0), the cell
+// width w = 2^(e-1) and p = a - u w, the element goes up iff p > lo, so it becomes ceil(p / w) w.  One fused
+// multiply-add forms S = p + 8 w, which for 0 <= p < 4 w lies in one binade of fp32 with 2^20 units per w: the low 20
+// bits of S say how far p is above a multiple of w.  What can be wrong with them: y = fl(x r) is off by at most a 2^-23 <= 1/2 unit
+// (a < 4 w), u lacks its last bit (2^-24 w = 1/16 unit), the factor 4 - u / 2 and S round to at most 1/2 unit each: less
+// than two units.  S is formed SR_BIAS = 4 units high; when its low bits are at least 2 SR_BIAS, p is truly more than
+// two units above one multiple of w and more than two below the next, and the decision stands; otherwise the caller
+// takes sr_pick.  (An a that rounding moved across a power of two puts p next to a multiple of w unless u decides the
+// same way on both sides.)  S - 7.5 w, exact, is then a value whose rounding to the nearest grid point is the
+// result -- except that the spacing halves below 2^e, hence the clamp to 2^floor(log2 a), a grid point or,
+// below 1/2, nothing above the first midpoint -- so the packed converter finishes the job.
+// 12 instructions per element instead of 28; rows of 8192 x 14336: 118 -> 82 us, with the Hadamard rotation
+// 8192 x 4096: 33 -> 25 us, both bound by vector issue.
+#define SR_BIAS 4
+__device__ __forceinline__ float sr_fast(float x, float r, uint32_t word, uint32_t& low_bits) {
+    const float a = fminf(fabsf(x) * r, 6.0f);
+    const float e2 = __uint_as_float(__float_as_uint(a) & 0x7F800000u);         // 2^floor(log2 a)
+    const float wh = fmaxf(e2, 1.0f);                                           // 2 w
+    const float u1 = __uint_as_float(__builtin_amdgcn_alignbit(0x7Fu, word, 9));  // 1 + u, the last bit of u dropped
+    const float S = __builtin_fmaf(__builtin_fmaf(u1, -0.5f, 4.5f + SR_BIAS * 4.76837158203125e-07f /* 2^-21 */), wh, a);
+    low_bits = __float_as_uint(S) & 0xFFFFFu;
+    return __builtin_copysignf(fmaxf(__builtin_fmaf(wh, -3.75f, S), e2), x);
+}
+
 __device__ __forceinline__ uint32_t quantize_block16_sr(const float (&v)[16], QuantParams qp, uint2& codes, uint64_t seed,
-                                                        uint32_t stream, uint64_t first_word /* multiple of 4 */) {
-    float amax = 0.0f;
+                                                        uint32_t stream, uint64_t first_word /* multiple of 16 */) {
+    float amax = 0.0f, amax_nan = 0.0f;           // the second one keeps a NaN, the first one ignores it
 #pragma unroll
-    for (int i = 0; i < 16; i += 2) amax = fmaxf(amax, fmaxf(fabsf(v[i]), fabsf(v[i + 1])));
+    for (int i = 0; i < 16; i += 2)
+        amax_nan = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(v[i]), fabsf(v[i + 1])), amax_nan);
+    amax = amax_nan;
+    // a block whose largest magnitude is not finite, enormous or tiny takes the exact path (the argument above needs
+    // normal steps and reciprocals); a zero block does not: its products are zeros
+    bool slow = !(amax_nan < 1e30f && (amax_nan >= 1e-30f || amax_nan == 0.0f));
+    if (slow) {
+        amax = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 16; i += 2) amax = fmaxf(amax, fmaxf(fabsf(v[i]), fabsf(v[i + 1])));
+    }
     const uint32_t sc = e4m3_scale_round_up(amax, qp);
     const float step = e4m3_decode(sc) * qp.g;
     const float r = sc == 0u ? 0.0f : recip_rn(step);
+    uint32_t w[16];
+    philox_4blocks(seed, stream, first_word >> 2, w);
     float y[16];
+    uint32_t low = 0xFFFFFu;
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
-        const u32x4 rw = philox_block(seed, stream, (first_word >> 2) + b);
-        y[4 * b + 0] = sr_pick(v[4 * b + 0], quot_rn(v[4 * b + 0], step, r), step, rw.x);
-        y[4 * b + 1] = sr_pick(v[4 * b + 1], quot_rn(v[4 * b + 1], step, r), step, rw.y);
-        y[4 * b + 2] = sr_pick(v[4 * b + 2], quot_rn(v[4 * b + 2], step, r), step, rw.z);
-        y[4 * b + 3] = sr_pick(v[4 * b + 3], quot_rn(v[4 * b + 3], step, r), step, rw.w);
+    for (int i = 0; i < 16; i += 2) {
+        uint32_t l0, l1;
+        y[i] = sr_fast(v[i], r, w[i], l0);
+        y[i + 1] = sr_fast(v[i + 1], r, w[i + 1], l1);
+        low = min(low, min(l0, l1));
+    }
+    if (slow || low < 2u * SR_BIAS) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) y[i] = sr_pick(v[i], quot_rn(v[i], step, r), step, w[i]);
     }
     uint32_t w0 = 0u, w1 = 0u;
     w0 = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w0, y[0], y[1], 1.0f, 0);

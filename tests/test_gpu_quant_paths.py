@@ -1,0 +1,84 @@
+"""The 128 x 128 two-orientation quantizer and the draw-by-draw short cut of stochastic rounding, bit-exact against the
+oracle: sizes around the tile and its 256-tile threshold, and inputs (zeros, ties, saturated, huge and tiny blocks,
+non-finite values) on both sides of the short cut's conditions."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import quant as oq
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def metis():
+    from paper_2509_00404_amd import metis as m
+    assert torch.cuda.is_available()
+    m.lib()
+    return m
+
+
+def _compare(got, ref):
+    c, s = ref
+    assert np.array_equal(got.scales.cpu().numpy(), s)
+    assert np.array_equal(got.codes.cpu().numpy(), c)
+
+
+# 16 x 16 tiles at (2048, 2048); one tile row or column partly filled; one row of tiles; padded rows (ld > N)
+@pytest.mark.parametrize("M,N,pad", [(2048, 2048, 0), (1936, 2064, 0), (16, 32768, 0), (32768, 16, 8), (1952, 2160, 24)])
+@pytest.mark.parametrize("sr", [False, True])
+@pytest.mark.parametrize("rows", [False, True])
+def test_both_orientations(metis, M, N, pad, sr, rows):
+    g0 = torch.Generator(device="cuda").manual_seed(M + N)
+    x = torch.randn((M, N + pad), device="cuda", generator=g0)
+    x *= torch.exp(torch.empty((M, 1), device="cuda").uniform_(-6, 6, generator=g0))
+    x = x.to(torch.bfloat16)[:, :N]
+    g = oq.tensor_scale_for(float(x.abs().max()))
+    out, out_t = metis.Fp4Tensor(M, N, g) if rows else None, metis.Fp4Tensor(N, M, g)
+    if sr:
+        metis.quantize_sr(x, 91, out, out_t)
+    else:
+        metis.quantize(x, out, out_t)
+    torch.cuda.synchronize()
+    xn = x.double().cpu().numpy()
+    xt = np.ascontiguousarray(xn.T)
+    _compare(out_t, oq.quantize_sr(xt, g, 91, oq.STREAM_SR_T) if sr else oq.quantize(xt, g))
+    if rows:
+        _compare(out, oq.quantize_sr(xn, g, 91, oq.STREAM_SR) if sr else oq.quantize(xn, g))
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("scale,g", [(1.0, 2.0 ** -8), (1.0, 2.0 ** -14), (2.0 ** 104, 2.0 ** 96), (2.0 ** -100, 2.0 ** -108),
+                                     (2.0 ** -60, 2.0 ** 40)])
+def test_stochastic_short_cut(metis, dtype, scale, g):
+    # grid values, midpoints and values a few ulp from both times every power of two of a block's range, zero blocks,
+    # and random blocks: 4M draws, of which ~30 fall in the window that takes the exact path
+    rs = np.random.default_rng(7)
+    M, N = 2048, 2048
+    x = rs.standard_normal((M, N)) * np.exp(rs.uniform(-8, 2, (M, 1)))
+    grid = np.array([0, .25, .5, .75, 1, 1.25, 1.5, 1.75, 2, 2.5, 3, 3.5, 4, 5, 6, 7])
+    x[:256] = rs.choice(grid, (256, N)) * rs.choice([-1.0, 1.0], (256, N)) * 2.0 ** rs.integers(-6, 3, (256, 1))
+    x[256:512] = x[:256] * (1.0 + rs.integers(-3, 4, (256, N)) * 2.0 ** (-8 if dtype == torch.bfloat16 else -23))
+    x[512:520] = 0.0
+    t = torch.from_numpy(x * scale).to(dtype)
+    out = metis.Fp4Tensor(M, N, g)
+    metis.quantize_sr(t.cuda(), 5, out)
+    torch.cuda.synchronize()
+    _compare(out, oq.quantize_sr(t.double().numpy(), g, 5, oq.STREAM_SR))
+
+
+@pytest.mark.parametrize("special", [np.inf, -np.inf, np.nan])
+def test_non_finite_values_take_the_exact_path(metis, special):
+    # fp32 takes the generic kernel, bf16 the row kernel: both must give a saturated code and leave other blocks alone
+    x = torch.randn((64, 256))
+    x[3, 37] = float(special)
+    ref = metis.Fp4Tensor(64, 256, 2.0 ** -9)
+    metis.quantize_sr(torch.nan_to_num(x, nan=0.0, posinf=0.0, neginf=0.0).cuda(), 11, ref)
+    got = metis.Fp4Tensor(64, 256, 2.0 ** -9)
+    metis.quantize_sr(x.cuda(), 11, got)
+    torch.cuda.synchronize()
+    a, b = got.codes.cpu().numpy(), ref.codes.cpu().numpy()
+    code = (a[3, 18] >> 4) & 7
+    assert code == 7                                          # magnitude 6
+    a[3, 16:24] = b[3, 16:24]
+    assert np.array_equal(a, b)
