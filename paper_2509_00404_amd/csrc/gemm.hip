@@ -72,10 +72,15 @@ __device__ __forceinline__ void scale_load(const Fp4Operand& A, const Fp4Operand
             if (whole) {
                 rg.s[v] = load8_any(src);
             } else {
-                uint32_t w[2] = {0, 0};
-                for (int i = 0; i < 8; ++i)
-                    if (k0 / 16 + i < sstride) w[i >> 2] |= (uint32_t)src[i] << (8 * (i & 3));
-                rg.s[v] = make_uint2(w[0], w[1]);
+                // the row's last 8 scales end at its end: load those and shift the missing ones in as zeros
+                uint64_t w = 0;
+                if (sstride >= 8) {
+                    const uint2 x = load8_any(op.scales + (gr + 1) * sstride - 8);
+                    w = ((uint64_t)x.y << 32 | x.x) >> (8 * (int)(k0 / 16 + 8 - sstride));
+                } else {
+                    for (int i = 0; i < (int)sstride; ++i) w |= (uint64_t)src[i] << (8 * i);   // K < 128: one stage
+                }
+                rg.s[v] = make_uint2((uint32_t)w, (uint32_t)(w >> 32));
             }
         }
     }
@@ -115,12 +120,13 @@ __device__ __forceinline__ void stage_load(const Fp4Operand& op, int64_t r0, int
         if (whole) {
             rg.c[v] = load16_any(src);
         } else {
-            uint32_t w[4] = {0, 0, 0, 0};
-            for (int b = 0; b < 16; ++b) {
-                int64_t kb = k0 / 2 + 16 * seg + b;
-                if (kb < cstride) w[b >> 2] |= (uint32_t)src[b] << (8 * (b & 3));
-            }
-            rg.c[v] = make_uint4(w[0], w[1], w[2], w[3]);
+            // K is a multiple of 16: the row ends on an 8-byte boundary of the stage.  (Byte by byte, the last stage of a 1360 x
+            // 1232 x 752 training step cost its skinny pre-products 12.3 us a launch against 8.6.)
+            const int64_t kb = k0 / 2 + 16 * seg;
+            const uint8_t* row_p = op.codes + gr * cstride;
+            const uint2 lo = load8_any(kb < cstride ? src : row_p), hi = load8_any(kb + 8 < cstride ? src + 8 : row_p);
+            const uint32_t mlo = kb < cstride ? ~0u : 0u, mhi = kb + 8 < cstride ? ~0u : 0u;
+            rg.c[v] = make_uint4(lo.x & mlo, lo.y & mlo, hi.x & mhi, hi.y & mhi);
         }
     }
 }
@@ -250,8 +256,8 @@ gemm_nt_tile(const Fp4Operand& A, const Fp4Operand& B, int64_t K, const bf16_t* 
     if (Ke > 0) {
         const int nks = Ke >> 4;
         const int64_t rba_max = (A.rows + 31) / 32 - 1, rbb_max = (B.rows + 31) / 32 - 1;
-        for (int ks = 0; ks < nks; ++ks) {
-            BFrag fa[TM], fb[TN];
+        // (the operands of a step travel while the step before is multiplied)
+        auto load_ext = [&](int ks, BFrag (&fa)[TM], BFrag (&fb)[TN]) {
 #pragma unroll
             for (int i = 0; i < TM; ++i) {
                 int64_t rb = (m0 + wm) / 32 + i;
@@ -264,11 +270,21 @@ gemm_nt_tile(const Fp4Operand& A, const Fp4Operand& B, int64_t K, const bf16_t* 
                 if (rb > rbb_max) rb = rbb_max;
                 fb[j].u = *reinterpret_cast<const uint4*>(Bext + ext_chunk(rb, ks, half, li, nks));
             }
+        };
+        BFrag fa[TM], fb[TN];
+        load_ext(0, fa, fb);
+        for (int ks = 0; ks < nks; ++ks) {
+            BFrag na[TM], nb[TN];
+            load_ext(ks + 1 < nks ? ks + 1 : ks, na, nb);
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i].v, fb[j].v, acc[i][j], 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < TM; ++i) fa[i] = na[i];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) fb[j] = nb[j];
         }
     }
     // D layout 32x32: lane l, element v -> row 8*(v/4) + 4*(l/32) + v%4, column l%32
@@ -294,6 +310,35 @@ k_fp4_gemm_nt(Fp4Operand A, Fp4Operand B, int64_t K, int64_t niter, const bf16_t
     int tile_m, tile_n;
     tile_coords(tmap, tile_m, tile_n);
     gemm_nt_tile<TM, TN, WMW, WNW, PART, OUT>(A, B, K, Aext, Bext, Ke, alpha, C, ldc, tile_m, tile_n, 0, niter);
+}
+
+// The same tiles with the contraction cut into parts of `ips` stages: workgroup b takes part b / tiles of tile b % tiles and
+// writes an fp32 tile of P[part] (M x N each, side by side); the low-rank columns enter with part 0.
+template <int TM, int TN, int WMW, int WNW, bool PART>
+__global__ void __launch_bounds__(64 * WMW * WNW)
+k_fp4_gemm_nt_parts(Fp4Operand A, Fp4Operand B, int64_t K, int64_t niter, int ips, const bf16_t* __restrict__ Aext,
+                    const bf16_t* __restrict__ Bext, int Ke, float alpha, float* __restrict__ P, int tiles, int tiles_n) {
+    const int z = (int)blockIdx.x / tiles, t = (int)blockIdx.x - z * tiles;
+    const int64_t it0 = (int64_t)z * ips, it1 = it0 + ips < niter ? it0 + ips : niter;
+    gemm_nt_tile<TM, TN, WMW, WNW, PART, float>(A, B, K, Aext, Bext, z == 0 ? Ke : 0, alpha, P + (size_t)z * A.rows * B.rows, B.rows,
+                                               t / tiles_n, t % tiles_n, it0, it1);
+}
+
+// C = sum of the parts, in ascending order; a thread takes 4 columns (N % 16 == 0)
+template <typename OUT>
+__global__ void __launch_bounds__(256)
+k_sum_output_parts(const float* __restrict__ P, int parts, int64_t MN, int64_t N, OUT* __restrict__ C, int64_t ldc) {
+    const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+    if (e >= MN) return;
+    float4 acc = *reinterpret_cast<const float4*>(P + e);
+#pragma unroll 4
+    for (int p = 1; p < parts; ++p) {
+        const float4 x = *reinterpret_cast<const float4*>(P + (size_t)p * MN + e);
+        acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
+    }
+    const int64_t r = (uint64_t)MN >> 32 ? e / N : (int64_t)((uint32_t)e / (uint32_t)N);
+    OUT* c = C + r * ldc + (e - r * N);
+    store_out<OUT>(c, acc.x); store_out<OUT>(c + 1, acc.y); store_out<OUT>(c + 2, acc.z); store_out<OUT>(c + 3, acc.w);
 }
 
 // Up to three skinny products in one launch, each cut along the contraction into `splits` parts that are written
@@ -722,6 +767,55 @@ int launch_gemm_tile(hipStream_t s, const Fp4Operand& a, const Fp4Operand& b, in
     return METIS_OK;
 }
 
+// Contraction parts of an output that the small tiles serve (M or N below 1024).  Few tiles leave most CUs idle while each
+// tile walks its whole contraction at ~1.1 us per 128-deep stage (latency; 0.55 us per workgroup once a CU holds several);
+// cutting it costs the parts' fp32 tiles (8 bytes of traffic per element and part at ~4 TB/s) and a launch, ~3.5 us.
+// The cut with the least sum is taken.  Whole call at rank 64: 256 x 4096 x 4096 56 -> 39 us, 256 x 4096 x 14336 153 -> 66 us,
+// 512 x 4096 x 4096 58 -> 48 us, 512 x 1024 x 4096 55 -> 35 us, 1000 x 4096 x 4096 (not cut) 63 -> 59 us.
+int small_split(int64_t M, int64_t N, int64_t niter) {
+    const int64_t bm = M <= 64 ? 64 : 128, bn = N <= 64 && M > 64 ? 64 : 128;
+    const int64_t tiles = ceil_div64(M, bm) * ceil_div64(N, bn);
+    if (tiles > 256) return 1;
+    int best = 1;
+    double best_t = 1e30;
+    for (int p = 1; p <= 16 && (p == 1 || 2 * p <= niter); ++p) {
+        const int64_t ips = ceil_div64(niter, p);
+        if (ceil_div64(niter, ips) != p) continue;                       // no empty part
+        const double per_cu = (double)ceil_div64(tiles * p, 256);
+        const double t = (double)ips * (per_cu > 1.7 ? 0.55 * per_cu : 1.1) +
+                         (p > 1 ? 3.5 + (double)p * (double)M * (double)N * 2e-6 : 0.0);
+        if (t < best_t - 1e-9) { best_t = t; best = p; }
+    }
+    return best;
+}
+
+// bytes of the parts of a small output (0: not cut)
+size_t small_split_bytes(int64_t M, int64_t N, int64_t K) {
+    if (M >= 1024 && N >= 1024) return 0;
+    const int p = small_split(M, N, ceil_div64(K, G_KI));
+    return p > 1 ? (size_t)p * M * N * sizeof(float) : 0;
+}
+
+template <int TM, int TN, int WMW, int WNW, typename OUT>
+int launch_gemm_parts(hipStream_t s, const Fp4Operand& a, const Fp4Operand& b, int64_t K, int64_t niter, int parts,
+                      const bf16_t* Aext, const bf16_t* Bext, int Ke, float alpha, OUT* C, int64_t ldc, float* partial) {
+    constexpr int BM = 32 * TM * WMW, BN = 32 * TN * WNW, NT = 64 * WMW * WNW;
+    const int64_t tn = ceil_div64(b.rows, BN), tiles = ceil_div64(a.rows, BM) * tn;
+    constexpr size_t lds = gemm_lds_bytes<BM, BN>();
+    const bool part = niter * G_KI > K;
+    auto kern = part ? k_fp4_gemm_nt_parts<TM, TN, WMW, WNW, true> : k_fp4_gemm_nt_parts<TM, TN, WMW, WNW, false>;
+    static LdsLimitCache lds_set[2];
+    if (!ensure_dyn_lds((const void*)kern, lds, lds_set[part])) return METIS_HIP_ERROR;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * parts)), dim3(NT), lds, s, a, b, K, niter, (int)ceil_div64(niter, parts), Aext,
+                       Bext, Ke, alpha, partial, (int)tiles, (int)tn);
+    METIS_LAUNCH_CHECK();
+    const int64_t mn = a.rows * b.rows;
+    hipLaunchKernelGGL(k_sum_output_parts<OUT>, dim3((unsigned)ceil_div64(mn, 1024)), dim3(256), 0, s, partial, parts, mn, b.rows,
+                       C, ldc);
+    METIS_LAUNCH_CHECK();
+    return METIS_OK;
+}
+
 // Shapes whose last, partial contraction stage travels as extra bf16 columns (exact: grid * e4m3 has at most 6
 // significant bits) so that the software-pipelined kernel's branch-free stages serve any K: large outputs with K % 128.
 // (The byte-wise staging it replaced took 798 us for the 4096 x 4096 weight gradient over 6000 tokens, 2.2 times the
@@ -750,9 +844,297 @@ int launch_gemm(hipStream_t s, const metis_fp4& A, const metis_fp4& B, const bf1
         // a partial stage that could not become extra columns (no workspace): 8 waves of 128x64, bounds-checked staging
         return launch_gemm_tile<4, 2, 2, 4, OUT>(s, a, b, K, niter, Aext, Bext, Ke, alpha, C, ldc);
     }
+    const int parts = small_split(M, N, niter);
+    if (parts > 1 && partial && partial_bytes >= (size_t)parts * M * N * sizeof(float)) {
+        if (N > 64 && M > 64)
+            return launch_gemm_parts<2, 2, 2, 2, OUT>(s, a, b, K, niter, parts, Aext, Bext, Ke, alpha, C, ldc, partial);
+        if (M > 64) return launch_gemm_parts<2, 1, 2, 2, OUT>(s, a, b, K, niter, parts, Aext, Bext, Ke, alpha, C, ldc, partial);
+        return launch_gemm_parts<1, 2, 2, 2, OUT>(s, a, b, K, niter, parts, Aext, Bext, Ke, alpha, C, ldc, partial);
+    }
     if (N > 64 && M > 64) return launch_gemm_tile<2, 2, 2, 2, OUT>(s, a, b, K, niter, Aext, Bext, Ke, alpha, C, ldc);
     if (N <= 64) return launch_gemm_tile<2, 1, 2, 2, OUT>(s, a, b, K, niter, Aext, Bext, Ke, alpha, C, ldc);
     return launch_gemm_tile<1, 2, 2, 2, OUT>(s, a, b, K, niter, Aext, Bext, Ke, alpha, C, ldc);
+}
+
+// ---- few rows (decode): Y[M <= 64, N] = A Bbar^T with A unsplit, Bbar = U S V^T + R ----
+// Two launches.  The first multiplies A with the rows of R_b and, as more columns, with those of V_b (T1 = A V_b^T), cut
+// along the contraction into `z` parts so that a few workgroups per CU exist however few columns there are.  A workgroup
+// owns 32 columns and all rows; its 4 waves deal the 128-deep stages of the part among themselves, so no stage
+// passes through LDS and no wave waits for another: a lane reads the 64 codes (two 16-byte loads) and 4 scales of its row and half of the stage and
+// expands them where they are.  The order of the contraction elements inside a stage is the lane's own (step s, half h =
+// elements 64 h + 8 s ..), the same for both operands.  The waves' tiles are added in wave order through LDS.
+// The second launch adds the parts in order and Y = alpha A R_b^T + (T1 S_b) U_b^T in fp32.
+// Bound by latency: 16 x 4096 x 4096 at rank 64 6.6 + 5.4 us (the general path's three kernels: 8.3 + 4.5 + 31 us), the whole
+// call 42 -> 15 us; 16 x 4096 x 14336 115 -> 20 us, 64 x 4096 x 14336 117 -> 32 us.  At 128 rows a CU spends its time on
+// reading and expanding A again for every 32 columns: 128 x 14336 x 4096 60 us against the general path's 47.  (One launch whose every workgroup forms T1 again was measured too: 32 x 4096 x 4096 at rank 64 16 us,
+// 16 x 4096 x 14336 41 us; two thirds of its vector instructions expanded V_b.)
+#define DC_MAX_ROWS 64
+struct DecodeRaw {
+    uint4 c0, c1;
+    uint32_t s;
+};
+typedef uint32_t u32_u __attribute__((aligned(1)));
+
+// the lane's share of a stage: codes and scales of the contraction elements k .. k + 63 of a row (zeros from K on;
+// `whole`, uniform: none is missing)
+__device__ __forceinline__ DecodeRaw decode_load(const uint8_t* codes, const uint8_t* scales, int64_t k, int64_t K, bool whole) {
+    DecodeRaw r;
+    if (whole) {
+        r.c0 = load16_any(codes + k / 2);
+        r.c1 = load16_any(codes + k / 2 + 16);
+        r.s = *reinterpret_cast<const u32_u*>(scales + k / 16);
+    } else {
+        uint2 c[4];
+        r.s = 0;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const bool in = k + 16 * b < K;
+            c[b] = load8_any(in ? codes + k / 2 + 8 * b : codes);
+            const uint32_t sc = in ? scales[k / 16 + b] : 0u;
+            r.s |= sc << (8 * b);
+            c[b].x = in ? c[b].x : 0u;
+            c[b].y = in ? c[b].y : 0u;
+        }
+        r.c0 = make_uint4(c[0].x, c[0].y, c[1].x, c[1].y);
+        r.c1 = make_uint4(c[2].x, c[2].y, c[3].x, c[3].y);
+    }
+    return r;
+}
+
+__device__ __forceinline__ half8_t decode_frag(const DecodeRaw& r, const uint32_t (&sp)[2], int s) {
+    const uint32_t w = s == 0 ? r.c0.x : s == 1 ? r.c0.y : s == 2 ? r.c0.z : s == 3 ? r.c0.w
+                     : s == 4 ? r.c1.x : s == 5 ? r.c1.y : s == 6 ? r.c1.z : r.c1.w;
+    return dequant8(w, sp[s >> 2], (s >> 1) & 1);
+}
+
+// column blocks of 32: [0, nb) are R_b's rows, the rest V_b's; P [z][M][ldp], ldp = 32 x all column blocks
+template <int TM>
+__global__ void __launch_bounds__(256)
+k_fp4_decode(Fp4Operand A, Fp4Operand B, Fp4Operand V, int nb, int64_t K, int ips, float* __restrict__ P, int64_t ldp) {
+    __shared__ float red[4][32][32];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 31, half = lane >> 5;
+    const int64_t cstride = K / 2, sstride = K / 16;
+    // rows past an operand's end re-read its last row; what they give is not stored, or dropped by the second kernel
+    const uint8_t *ca[TM], *sa[TM], *cb, *sb;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int64_t r = 32 * i + li < A.rows ? 32 * i + li : A.rows - 1;
+        ca[i] = A.codes + r * cstride;
+        sa[i] = A.scales + r * sstride;
+    }
+    {
+        const int blk = (int)blockIdx.x;
+        const bool isv = blk >= nb;
+        const int64_t rows = isv ? V.rows : B.rows, r0 = 32 * (int64_t)(isv ? blk - nb : blk) + li;
+        const int64_t r = r0 < rows ? r0 : rows - 1;
+        cb = (isv ? V.codes : B.codes) + r * cstride;
+        sb = (isv ? V.scales : B.scales) + r * sstride;
+    }
+    float16_t acc[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][v] = 0.0f;
+    const int nst = (int)((K + G_KI - 1) / G_KI), it0 = (int)blockIdx.y * ips, it1 = it0 + ips < nst ? it0 + ips : nst;
+    DecodeRaw a[TM], b;
+    auto load = [&](int it) {
+        const int64_t k0 = (int64_t)it * G_KI, k = k0 + 64 * half;
+        const bool whole = k0 + G_KI <= K;
+        b = decode_load(cb, sb, k, K, whole);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) a[i] = decode_load(ca[i], sa[i], k, K, whole);
+    };
+    if (it0 + wave < it1) load(it0 + wave);
+    for (int it = it0 + wave; it < it1; it += 4) {
+        DecodeRaw a0[TM];
+        const DecodeRaw b0 = b;
+        uint32_t pa[TM][2], pb[2];
+        auto scales2 = [](uint32_t s, uint32_t (&o)[2]) {
+            o[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(s, 1.0f, false));
+            o[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(s, 1.0f, true));
+        };
+#pragma unroll
+        for (int i = 0; i < TM; ++i) { a0[i] = a[i]; scales2(a0[i].s, pa[i]); }
+        scales2(b0.s, pb);
+        if (it + 4 < it1) load(it + 4);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const half8_t fb = decode_frag(b0, pb, s);
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+                acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(decode_frag(a0[i], pa[i], s), fb, acc[i], 0, 0, 0);
+        }
+    }
+    // D layout 32x32: lane l, element v -> row 8*(v/4) + 4*(l/32) + v%4, column l%32
+    const int row = tid >> 5, col = tid & 31;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        if (i > 0) __syncthreads();
+#pragma unroll
+        for (int v = 0; v < 16; ++v) red[wave][8 * (v >> 2) + 4 * half + (v & 3)][li] = acc[i][v];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int r = row + 8 * q;
+            const float x = ((red[0][r][col] + red[1][r][col]) + red[2][r][col]) + red[3][r][col];
+            if (32 * i + r < A.rows) P[((int64_t)blockIdx.y * A.rows + 32 * i + r) * ldp + 32 * (int64_t)blockIdx.x + col] = x;
+        }
+    }
+}
+
+// Y = alpha sum_z P + (T1 S_b) U_b^T; a workgroup owns 16 rows and 64 columns, a thread 4 columns of one row.  All global
+// loads of a thread are issued before the first use (a missing part re-reads the last one with weight 0).  H = 64-column
+// halves of the rank.
+#define DF_ROWS 16
+#define DF_COLS 64
+#define DC_MAX_PARTS 4
+struct Parts4 {
+    float4 x[DC_MAX_PARTS];
+};
+__device__ __forceinline__ Parts4 load_parts4(const float* __restrict__ p, int64_t zs, int parts) {
+    Parts4 r;
+#pragma unroll
+    for (int u = 0; u < DC_MAX_PARTS; ++u) r.x[u] = *reinterpret_cast<const float4*>(p + (u < parts ? u : parts - 1) * zs);
+    return r;
+}
+__device__ __forceinline__ float4 add_parts4(const Parts4& r, int parts) {
+    float4 s = r.x[0];
+#pragma unroll
+    for (int u = 1; u < DC_MAX_PARTS; ++u) {
+        const float w = u < parts ? 1.0f : 0.0f;
+        s.x = fmaf(w, r.x[u].x, s.x); s.y = fmaf(w, r.x[u].y, s.y);
+        s.z = fmaf(w, r.x[u].z, s.z); s.w = fmaf(w, r.x[u].w, s.w);
+    }
+    return s;
+}
+
+template <int H, typename OUT>
+__global__ void __launch_bounds__(256)
+k_decode_finish(const float* __restrict__ P, int parts, int M, int64_t N, int64_t ldp, int nb, int kb,
+                const uint8_t* __restrict__ ub_codes, const uint8_t* __restrict__ ub_scales, const float* __restrict__ Sb,
+                float alpha, float alpha_lr, OUT* __restrict__ C, int64_t ldc) {
+    constexpr int KP = 64 * H, LT = KP + 4;
+    __shared__ __attribute__((aligned(16))) float t1[H ? DF_ROWS * LT : 4];     // T1 S_b with the tensor scales, [row][j]
+    __shared__ __attribute__((aligned(16))) bf16_t ub[H ? DF_COLS * LT : 8];    // U_b without its own (exact), [column][j]
+    const int tid = threadIdx.x, r16 = tid >> 4, c4 = tid & 15;
+    const int64_t zs = (int64_t)M * ldp;
+    const int64_t n0 = (int64_t)blockIdx.x * DF_COLS, n = n0 + 4 * c4;
+    const int m = (int)blockIdx.y * DF_ROWS + r16;
+    const bool in = n < N && m < M;
+    const int64_t mrow = m < M ? m : M - 1;
+    Parts4 tp[H ? H : 1];
+    float4 sv[H ? H : 1];
+    uint32_t uw[H ? 2 * H : 1], us[H ? 2 * H : 1];
+    // T1: row r16, columns 64 h + 4 c4 .. + 3 (the padded columns of V_b's last block hold copies of its last row)
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        const int j = 64 * h + 4 * c4;
+        tp[h] = load_parts4(P + mrow * ldp + 32 * nb + (j < kb ? j : 0), zs, parts);
+        sv[h] = make_float4(j < kb ? Sb[j] : 0.0f, j + 1 < kb ? Sb[j + 1] : 0.0f, j + 2 < kb ? Sb[j + 2] : 0.0f,
+                            j + 3 < kb ? Sb[j + 3] : 0.0f);
+    }
+#pragma unroll
+    for (int i = 0; i < 2 * H; ++i) {
+        const int j = (tid >> 3) + 32 * i, c = 8 * (tid & 7);
+        uw[i] = us[i] = 0;
+        if (j < kb && n0 + c < N) {
+            uw[i] = *reinterpret_cast<const u32_u*>(ub_codes + j * (N / 2) + (n0 + c) / 2);
+            us[i] = ub_scales[j * (N / 16) + (n0 + c) / 16];
+        }
+    }
+    const Parts4 yp = load_parts4(P + (in ? m * ldp + n : 0), zs, parts);
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        const float4 x = add_parts4(tp[h], parts);
+        const int j = 64 * h + 4 * c4;
+        float4 v;
+        v.x = j < kb ? x.x * (sv[h].x * alpha_lr) : 0.0f;
+        v.y = j + 1 < kb ? x.y * (sv[h].y * alpha_lr) : 0.0f;
+        v.z = j + 2 < kb ? x.z * (sv[h].z * alpha_lr) : 0.0f;
+        v.w = j + 3 < kb ? x.w * (sv[h].w * alpha_lr) : 0.0f;
+        *reinterpret_cast<float4*>(t1 + r16 * LT + j) = v;
+    }
+    const float grid[8] = {0.0f, 0.5f, 1.0f, 1.5f, 2.0f, 3.0f, 4.0f, 6.0f};
+#pragma unroll
+    for (int i = 0; i < 2 * H; ++i) {
+        const int j = (tid >> 3) + 32 * i, c = 8 * (tid & 7);
+        const float s = e4m3_decode(us[i]);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const uint32_t nib = (uw[i] >> (4 * q)) & 15u;
+            const float x = grid[nib & 7u] * s;
+            ub[(c + q) * LT + j] = f32_to_bf16_rne((nib & 8u) ? -x : x);
+        }
+    }
+    const float4 y = add_parts4(yp, parts);
+    float o[4] = {alpha * y.x, alpha * y.y, alpha * y.z, alpha * y.w};
+    if (H) __syncthreads();
+    if (!in) return;
+#pragma unroll 4
+    for (int q = 0; q < KP; q += 4) {
+        const float4 a = *reinterpret_cast<const float4*>(t1 + r16 * LT + q);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint2 u = *reinterpret_cast<const uint2*>(ub + (4 * c4 + i) * LT + q);
+            o[i] = fmaf(a.x, bf16lo_to_f32(u.x), o[i]);
+            o[i] = fmaf(a.y, bf16hi_to_f32(u.x), o[i]);
+            o[i] = fmaf(a.z, bf16lo_to_f32(u.y), o[i]);
+            o[i] = fmaf(a.w, bf16hi_to_f32(u.y), o[i]);
+        }
+    }
+    OUT* c = C + m * ldc + n;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) store_out<OUT>(c + i, o[i]);
+}
+
+// few rows of an unsplit left operand
+bool decode_shape(int64_t Ma, int ka) { return ka == 0 && Ma <= DC_MAX_ROWS; }
+
+struct DecodePlan {
+    int nb, nv, ips, parts;              // column blocks of 32 of R_b, of V_b; stages per part, parts
+    int64_t ldp;
+    size_t bytes;
+};
+DecodePlan decode_plan(int64_t M, int64_t N, int kb, int64_t K) {
+    DecodePlan d;
+    d.nb = (int)ceil_div64(N, 32);
+    d.nv = (kb + 31) / 32;
+    d.ldp = 32 * (int64_t)(d.nb + d.nv);
+    // about three workgroups per CU, each with a stage for every wave (the rank does not enter: a workspace sized for a larger
+    // rank fits a smaller one)
+    const int64_t wgs = d.nb + 2, nst = ceil_div64(K, G_KI);
+    int64_t want = ceil_div64(768, wgs), most = nst / 4 > 0 ? nst / 4 : 1;
+    if (want > most) want = most;
+    if (want > DC_MAX_PARTS) want = DC_MAX_PARTS;
+    d.ips = (int)ceil_div64(nst, want);
+    d.parts = (int)ceil_div64(nst, d.ips);
+    d.bytes = (size_t)d.parts * M * d.ldp * sizeof(float);
+    return d;
+}
+
+template <typename OUT>
+int launch_decode(hipStream_t s, const metis_fp4& A, const metis_fp4& B, const metis_fp4* Ub, const metis_fp4* Vb, const float* Sb,
+                  int kb, float* P, OUT* C, int64_t ldc) {
+    const Fp4Operand a = {A.codes, A.scales, A.rows}, b = {B.codes, B.scales, B.rows};
+    Fp4Operand v = {nullptr, nullptr, 0};
+    const uint8_t *uc = nullptr, *us = nullptr;
+    float alpha_lr = 0.0f;
+    if (kb > 0) {
+        v = {Vb->codes, Vb->scales, kb};
+        uc = Ub->codes;
+        us = Ub->scales;
+        alpha_lr = A.tscale * Vb->tscale * Ub->tscale;
+    }
+    const DecodePlan d = decode_plan(A.rows, B.rows, kb, A.cols);
+    auto kern = A.rows <= 32 ? k_fp4_decode<1> : k_fp4_decode<2>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(d.nb + d.nv), (unsigned)d.parts), dim3(256), 0, s, a, b, v, d.nb, A.cols, d.ips, P, d.ldp);
+    METIS_LAUNCH_CHECK();
+    auto finish = kb == 0 ? k_decode_finish<0, OUT> : kb <= 64 ? k_decode_finish<1, OUT> : k_decode_finish<2, OUT>;
+    hipLaunchKernelGGL(finish, dim3((unsigned)ceil_div64(B.rows, DF_COLS), (unsigned)ceil_div64(A.rows, DF_ROWS)), dim3(256), 0, s, P,
+                       d.parts, (int)A.rows, B.rows, d.ldp, d.nb, kb, uc, us, Sb, A.tscale * B.tscale, alpha_lr, C, ldc);
+    METIS_LAUNCH_CHECK();
+    return METIS_OK;
 }
 
 // value of one FP4 element without the tensor scale: grid[code] * e4m3(scale)
@@ -1004,6 +1386,7 @@ struct LinWs {
     int Kep;                 // low-rank columns, padded to 16
     int Kt;                  // columns of the last, partial contraction stage (0: none or not taken as columns)
     int s1, s2, s3;          // contraction parts of T1, E2, Mk
+    bool decode;             // few rows of an unsplit operand: the tail region holds the parts of both products
 };
 
 // Parts of a skinny product with rows x cols outputs: few output tiles, long contraction -> cut it so that about
@@ -1034,6 +1417,9 @@ LinWs lin_layout(int64_t Ma, int64_t Nb, int ka, int kb, int64_t Kc) {
     w.off_aext = take((size_t)((Ma + 31) / 32 * 32) * (w.Kep + w.Kt > 0 ? w.Kep + w.Kt : 16) * 2);       // rows padded to whole 32-row blocks
     w.off_bext = take((size_t)((Nb + 31) / 32 * 32) * (w.Kep + w.Kt > 0 ? w.Kep + w.Kt : 16) * 2);
     w.tail_bytes = (Ma >= 1024 && Nb >= 1024 && (Kc % G_KI == 0 || w.Kt > 0)) ? gemm_tail_bytes(Ma, Nb, Kc) : 0;
+    w.decode = decode_shape(Ma, ka);
+    if (w.decode) w.tail_bytes = decode_plan(Ma, Nb, kb, Kc).bytes;
+    else if (w.tail_bytes == 0) w.tail_bytes = small_split_bytes(Ma, Nb, Kc);
     w.off_tail = take(w.tail_bytes);
     w.total = o;
     return w;
@@ -1069,6 +1455,17 @@ int linear_nt(hipStream_t s, const NtOperand& a, const NtOperand& b, metis_mat* 
     if (ka > 0 || kb > 0) {
         if (!ws_fits) return METIS_WORKSPACE_TOO_SMALL;
         if (!ws_aligned) return METIS_INVALID_ARG;
+    }
+    if (w.decode && workspace && workspace_bytes >= w.total && ws_aligned) {
+        if (!do_main) return METIS_OK;                   // nothing to prepare
+        float* P = (float*)((char*)workspace + w.off_tail);
+        const int pi = metis_prof_begin(METIS_PROF_GEMM, s);
+        if (out->dtype == METIS_BF16)
+            st = launch_decode<bf16_t>(s, a.R, b.R, &b.Ut, &b.Vt, b.S, kb, P, (bf16_t*)out->ptr, out->ld);
+        else
+            st = launch_decode<float>(s, a.R, b.R, &b.Ut, &b.Vt, b.S, kb, P, (float*)out->ptr, out->ld);
+        metis_prof_end(METIS_PROF_GEMM, pi, s);
+        return st;
     }
     // (two unsplit operands work without a workspace: a partial last stage then takes the bounds-checked kernel)
     if (ka > 0 || kb > 0 || (w.Kt > 0 && ws_fits && ws_aligned)) {
@@ -1130,7 +1527,7 @@ int linear_nt(hipStream_t s, const NtOperand& a, const NtOperand& b, metis_mat* 
     // room for the partial tiles of a split last round, when the workspace has it
     float* partial = nullptr;
     size_t partial_bytes = 0;
-    if (w.tail_bytes > 0 && workspace && workspace_bytes >= w.total && ws_aligned) {
+    if (w.tail_bytes > 0 && !w.decode && workspace && workspace_bytes >= w.total && ws_aligned) {
         partial = (float*)((char*)workspace + w.off_tail);
         partial_bytes = w.tail_bytes;
     }
@@ -1154,8 +1551,12 @@ NtOperand nt(const metis_fp4& R, const metis_fp4& Ut, const metis_fp4& Vt, const
 
 extern "C" size_t metis_linear_workspace_bytes(int64_t L, int64_t N, int64_t K, int k) {
     if (L < 1 || N < 1 || K < 1 || k < 0) return 0;
-    size_t a = lin_layout(L, N, k, k, K).total, b = lin_layout(L, K, k, k, N).total, c = lin_layout(N, K, k, k, L).total;
-    return a > b ? (a > c ? a : c) : (b > c ? b : c);
+    // the three products of split operands, and those of an unsplit left operand (few rows take another path then)
+    size_t most = 0;
+    for (int ka : {k, 0})
+        for (size_t b : {lin_layout(L, N, ka, k, K).total, lin_layout(L, K, ka, k, N).total, lin_layout(N, K, ka, k, L).total})
+            if (b > most) most = b;
+    return most;
 }
 
 // Y[L,N] = Xbar Wbar^T: contraction over K

@@ -1,0 +1,76 @@
+"""GPU parity of products with few rows (at most 64 rows of an unsplit operand) and of small outputs
+whose contraction is cut into parts; with the bars of tests/test_gpu_linear.py, at edges of the 32-row / 32-column
+tiles, the 128-deep stages and the 32-column groups of the low-rank part."""
+import pytest
+import torch
+
+from gpu_helpers import elementwise_bound, make_split, operand_parts, rel_fro, split_to_oracle
+from oracle import linear as olin
+from test_gpu_linear import GEMM_RTOL, metis  # noqa: F401  (metis is a fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def _product(metis, L, N, K, kx, kw, out_dtype, seed=1):  # noqa: F811
+    from paper_2509_00404_amd import workloads
+    X = workloads.planted(L, K, workloads.power_law(min(L, K, 128), 1.2), seed, rms=1.0, outlier_cols=1)
+    W = workloads.planted(N, K, workloads.power_law(min(N, K, 128), 1.0), seed + 1, noise_top=0.01, rms=0.02)
+    xs = make_split(metis, X, kx, 4, 1.0, 11, want_t=False)[0]
+    ws = make_split(metis, W, kw, 4, 1.0, 12, want_t=False)[0]
+    xo, wo = split_to_oracle(xs), split_to_oracle(ws)
+    ref = olin.linear_fwd(xo, wo)
+    return xs, ws, ref, elementwise_bound(operand_parts(xo), operand_parts(wo), ref, out_dtype)
+
+
+@pytest.mark.parametrize("L,N,K,k", [
+    (1, 16, 16, 4), (1, 48, 32, 0), (3, 272, 112, 5), (16, 256, 128, 8), (16, 400, 1040, 32), (17, 528, 1184, 33),
+    (31, 144, 2064, 64), (32, 1040, 1152, 65), (32, 256, 272, 88), (16, 8208, 272, 64), (5, 8224, 144, 88), (16, 4096, 4096, 64), (8, 160, 5120, 80), (33, 4096, 2064, 16), (64, 272, 4096, 20),
+    (65, 304, 1232, 12), (127, 96, 2048, 88), (128, 2064, 400, 33), (100, 528, 1040, 0)])
+@pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
+def test_few_rows(metis, L, N, K, k, out_dtype):  # noqa: F811
+    if k > 0 and k + 4 > min(N, K):
+        k = min(N, K) - 4
+    xs, ws, ref, bound = _product(metis, L, N, K, 0, k, out_dtype)
+    wsb = torch.empty((max(metis.linear_workspace_bytes(L, N, K, k), 256),), dtype=torch.uint8, device="cuda")
+    Y = torch.full((L, N + 8), float("nan"), dtype=out_dtype, device="cuda")
+    metis.fp4_linear_fwd(xs, ws, Y[:, :N], wsb)
+    got = Y[:, :N].double().cpu().numpy()
+    assert torch.isnan(Y[:, N:]).all()
+    assert rel_fro(got, ref) < (GEMM_RTOL if out_dtype == torch.bfloat16 else 5e-3)
+    assert (abs(got - ref) <= bound).all()
+    # the two-phase form is the same product
+    Z = torch.full((L, N), float("nan"), dtype=out_dtype, device="cuda")
+    metis.fp4_linear_phase(metis.LINEAR_FWD, metis.LINEAR_PREPARE, xs, ws, None, wsb)
+    metis.fp4_linear_phase(metis.LINEAR_FWD, metis.LINEAR_APPLY, xs, ws, Z, wsb)
+    assert torch.equal(Z, Y[:, :N])
+
+
+@pytest.mark.parametrize("L,N,K,kx,kw", [
+    (48, 4096, 2064, 8, 16),        # 64 x 128 tiles, a partial last stage
+    (64, 272, 4096, 8, 20),
+    (129, 1040, 4096, 0, 20),
+    (16, 256, 1040, 8, 8),          # few rows of a split operand: the general path
+    (144, 64, 3008, 12, 12),        # 128 x 64 tiles
+    (400, 528, 1232, 20, 24),
+    (1008, 1040, 2048, 16, 16),
+    (65, 4096, 272, 0, 0)])         # nothing to cut
+@pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
+def test_cut_contraction(metis, L, N, K, kx, kw, out_dtype):  # noqa: F811
+    xs, ws, ref, bound = _product(metis, L, N, K, kx, kw, out_dtype, seed=5)
+    nbytes = max(metis.linear_workspace_bytes(L, N, K, max(kx, kw)), 256)
+    Y = torch.full((L, N), float("nan"), dtype=out_dtype, device="cuda")
+    metis.fp4_linear_fwd(xs, ws, Y, torch.empty((nbytes,), dtype=torch.uint8, device="cuda"))
+    y = Y.double().cpu().numpy()
+    assert rel_fro(y, ref) < (GEMM_RTOL if out_dtype == torch.bfloat16 else 5e-3)
+    assert (abs(y - ref) <= bound).all()
+
+
+@pytest.mark.parametrize("L", [16, 100, 200])
+def test_unsplit_without_workspace(metis, L):  # noqa: F811
+    xs, ws, ref, bound = _product(metis, L, 528, 4096, 0, 0, torch.float32)
+    nbytes = metis.linear_workspace_bytes(L, 528, 4096, 0)
+    for wsb in (None, torch.empty((nbytes + 8,), dtype=torch.uint8, device="cuda")[8:],       # misaligned: not used
+                torch.empty((nbytes,), dtype=torch.uint8, device="cuda")):
+        Y = torch.full((L, 528), float("nan"), dtype=torch.float32, device="cuda")
+        metis.fp4_linear_fwd(xs, ws, Y, wsb)
+        assert (abs(Y.double().cpu().numpy() - ref) <= bound).all()
