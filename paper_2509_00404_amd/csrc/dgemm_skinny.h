@@ -9,36 +9,37 @@
 #pragma once
 #include "dgemm.h"
 
-__device__ __forceinline__ double bf16_bits_to_f64(uint16_t h) {
-    return (double)__uint_as_float(((uint32_t)h) << 16);
-}
+__device__ __forceinline__ double skinny_to_f64(bf16_t h) { return (double)__uint_as_float(((uint32_t)h) << 16); }
+__device__ __forceinline__ double skinny_to_f64(float x) { return (double)x; }
 
 // ---------------------------------------------------------------------------------------
 // Sketch: Z[m][j] += sum_k A[rowmap[m]][k] * Om[k][j],  m < Ms, j < r, k in the split's chunk.
-//   A   bf16, row stride lda (multiple of 8, base 16-byte aligned), K % 8 == 0
+//   A   bf16 (or fp32: the weight gradient of the factor gradients), rows of whole 16-byte pieces, 16-byte aligned, K % 8 == 0
 //   Om  bf16 [K][r] row-major, r % 8 == 0, base 16-byte aligned
 //   Z   fp64 [ksplit][Ms][r] partial products
 // grid (1, ceil(Ms/64), ksplit), block 256: wave w owns rows 16w..16w+15 and all NT column tiles.
 // ---------------------------------------------------------------------------------------
 #define SK_ROWS 64
-#define SK_KS 64
-#define SK_LDA 72                     // bf16 per LDS row of the A stage (144 B: 16-byte aligned, bank-spread)
-template <int NT>
+#define SK_KS 64                      // unit of the contraction split
+template <int NT, typename TA>
 struct SketchCfg {
+    static constexpr int E = 16 / sizeof(TA);                        // elements per 16-byte piece
+    static constexpr int KS = 8 * E;                                 // stage depth: 64 bf16 or 32 fp32, 8 pieces a row
+    static constexpr int LDA = KS + E;                               // LDS row of the A stage (144 B: 16-byte aligned, bank-spread)
     // LDS row length of the Omega stage, = 16 (mod 32) so that the four k-rows a B fragment
     // touches fall into disjoint bank ranges
     static constexpr int LDO = NT * 16 + ((NT * 16) % 32 == 16 ? 0 : 16);
-    static constexpr int OM_LOADS = (SK_KS * NT * 2 + 255) / 256;    // 16-byte pieces per thread and stage
+    static constexpr int OM_LOADS = (KS * NT * 2 + 255) / 256;    // 16-byte pieces per thread and stage
 };
 
-template <int NT>
+template <int NT, typename TA>
 __global__ void __launch_bounds__(256)
-k_sketch(const bf16_t* __restrict__ A, int64_t lda, const uint32_t* __restrict__ rowmap, int64_t Ms, int64_t K,
+k_sketch(const TA* __restrict__ A, int64_t lda, const uint32_t* __restrict__ rowmap, int64_t Ms, int64_t K,
          const bf16_t* __restrict__ Om, int r, int64_t kchunk, double* __restrict__ Z) {
-    constexpr int LDO = SketchCfg<NT>::LDO;
-    constexpr int OML = SketchCfg<NT>::OM_LOADS;
-    __shared__ __align__(16) uint16_t As[2][SK_ROWS * SK_LDA];
-    __shared__ __align__(16) uint16_t Os[2][SK_KS * LDO];
+    typedef SketchCfg<NT, TA> Cfg;
+    constexpr int LDO = Cfg::LDO, OML = Cfg::OM_LOADS, KS = Cfg::KS, LDA = Cfg::LDA;
+    __shared__ __align__(16) TA As[2][SK_ROWS * LDA];
+    __shared__ __align__(16) uint16_t Os[2][KS * LDO];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t m0 = (int64_t)blockIdx.y * SK_ROWS;
     const int64_t kbeg = (int64_t)blockIdx.z * kchunk;
@@ -46,11 +47,11 @@ k_sketch(const bf16_t* __restrict__ A, int64_t lda, const uint32_t* __restrict__
     if (kbeg >= kend) return;
 
     // the pad columns r .. 16 NT of the Omega stage stay zero
-    for (int e = tid; e < 2 * SK_KS * LDO; e += 256) (&Os[0][0])[e] = 0;
+    for (int e = tid; e < 2 * KS * LDO; e += 256) (&Os[0][0])[e] = 0;
     __syncthreads();
 
-    // A pieces: 64 rows x 8 pieces of 8 bf16, two per thread
-    const bf16_t* arow[2];
+    // A pieces: 64 rows x 8 pieces, two per thread
+    const TA* arow[2];
     bool aok[2];
     int a_lds[2], a_k[2];
 #pragma unroll
@@ -60,10 +61,10 @@ k_sketch(const bf16_t* __restrict__ A, int64_t lda, const uint32_t* __restrict__
         aok[i] = m < Ms;
         const int64_t src = aok[i] ? (rowmap ? (int64_t)rowmap[m] : m) : 0;
         arow[i] = A + src * lda;
-        a_lds[i] = row * SK_LDA + 8 * kc;
-        a_k[i] = 8 * kc;
+        a_lds[i] = row * LDA + Cfg::E * kc;
+        a_k[i] = Cfg::E * kc;
     }
-    // Omega pieces: 64 k-rows x r/8 pieces
+    // Omega pieces: KS k-rows x r/8 pieces
     const int rc = r >> 3;
     int o_k[OML], o_j[OML];
     bool ook[OML];
@@ -72,7 +73,7 @@ k_sketch(const bf16_t* __restrict__ A, int64_t lda, const uint32_t* __restrict__
         const int c = tid + 256 * i;
         o_k[i] = c / rc;
         o_j[i] = 8 * (c - o_k[i] * rc);
-        ook[i] = o_k[i] < SK_KS;
+        ook[i] = o_k[i] < KS;
     }
 
     uint4 ra[2], ro[OML];
@@ -104,17 +105,17 @@ k_sketch(const bf16_t* __restrict__ A, int64_t lda, const uint32_t* __restrict__
     stash(0);
     __syncthreads();
     int buf = 0;
-    const int arow_l = (wave * 16 + (lane & 15)) * SK_LDA;
-    for (int64_t kt = kbeg; kt < kend; kt += SK_KS) {
-        const bool more = kt + SK_KS < kend;
-        if (more) fetch(kt + SK_KS);
+    const int arow_l = (wave * 16 + (lane & 15)) * LDA;
+    for (int64_t kt = kbeg; kt < kend; kt += KS) {
+        const bool more = kt + KS < kend;
+        if (more) fetch(kt + KS);
 #pragma unroll 4
-        for (int s = 0; s < SK_KS / 4; ++s) {
+        for (int s = 0; s < KS / 4; ++s) {
             const int kr = 4 * s + (lane >> 4);
-            const double a = bf16_bits_to_f64(As[buf][arow_l + kr]);
+            const double a = skinny_to_f64(As[buf][arow_l + kr]);
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
-                const double b = bf16_bits_to_f64(Os[buf][kr * LDO + 16 * j + (lane & 15)]);
+                const double b = skinny_to_f64(Os[buf][kr * LDO + 16 * j + (lane & 15)]);
                 acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[j], 0, 0, 0);
             }
         }
@@ -143,26 +144,26 @@ k_sketch(const bf16_t* __restrict__ A, int64_t lda, const uint32_t* __restrict__
 // ---------------------------------------------------------------------------------------
 #define PJ_COLS 64
 #define PJ_KS 32
-#define PJ_LDA 80                     // bf16 per LDS row of the A stage: = 16 (mod 32)
-template <int NT>
+#define PJ_LDA 80                     // elements per LDS row of the A stage: = 16 (mod 32)
+template <int NT, typename TA>
 struct ProjectCfg {
     static constexpr int LDH = NT * 16 + ((NT * 16) % 32 == 16 ? 0 : 16);    // doubles, = 16 (mod 32)
     static constexpr int H_LOADS = (PJ_KS * NT * 8 + 255) / 256;              // double2 pieces per thread and stage
-    static constexpr size_t LDS = 2 * (size_t)PJ_KS * LDH * sizeof(double) + 2 * (size_t)PJ_KS * PJ_LDA * sizeof(uint16_t);
+    static constexpr size_t LDS = 2 * (size_t)PJ_KS * LDH * sizeof(double) + 2 * (size_t)PJ_KS * PJ_LDA * sizeof(TA);
 };
 
-template <int NT>
+template <int NT, typename TA>
 __global__ void __launch_bounds__(256)
 k_project(const double* __restrict__ H_main, const double* __restrict__ H_alt, const int32_t* __restrict__ use_alt, int r,
-          const bf16_t* __restrict__ A, int64_t lda, const uint32_t* __restrict__ rowmap, int64_t Ms, int64_t N,
+          const TA* __restrict__ A, int64_t lda, const uint32_t* __restrict__ rowmap, int64_t Ms, int64_t N,
           int64_t kchunk, double* __restrict__ B) {
     // the orthonormal basis: the second CholeskyQR pass's output, or the first pass's when that was enough
     const double* __restrict__ H = (use_alt && *use_alt) ? H_alt : H_main;
-    constexpr int LDH = ProjectCfg<NT>::LDH;
-    constexpr int HL = ProjectCfg<NT>::H_LOADS;
+    constexpr int LDH = ProjectCfg<NT, TA>::LDH;
+    constexpr int HL = ProjectCfg<NT, TA>::H_LOADS;
     extern __shared__ __align__(16) unsigned char pj_smem[];
     double* Hs = reinterpret_cast<double*>(pj_smem);                                   // [2][PJ_KS * LDH]
-    uint16_t* As = reinterpret_cast<uint16_t*>(pj_smem + 2 * (size_t)PJ_KS * LDH * sizeof(double));   // [2][PJ_KS * PJ_LDA]
+    TA* As = reinterpret_cast<TA*>(pj_smem + 2 * (size_t)PJ_KS * LDH * sizeof(double));   // [2][PJ_KS * PJ_LDA]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t n0 = (int64_t)blockIdx.x * PJ_COLS;
     const int64_t kbeg = (int64_t)blockIdx.z * kchunk;
@@ -183,31 +184,43 @@ k_project(const double* __restrict__ H_main, const double* __restrict__ H_alt, c
         h_j[i] = 2 * (c - h_k[i] * rc);
         hok[i] = h_k[i] < PJ_KS;
     }
-    // A pieces: 32 k-rows x 8 pieces of 8 bf16, one per thread
-    const int a_kr = tid >> 3, a_n = 8 * (tid & 7);
-    const bool a_nok = n0 + a_n < N;
+    // A pieces: 32 k-rows x 64 columns, one (bf16) or two (fp32) per thread
+    constexpr int E = 16 / sizeof(TA), AP = 8 / E;
+    int a_kr[AP], a_n[AP];
+    bool a_nok[AP];
+#pragma unroll
+    for (int i = 0; i < AP; ++i) {
+        const int c = tid + 256 * i;
+        a_kr[i] = c / (PJ_COLS / E);
+        a_n[i] = E * (c % (PJ_COLS / E));
+        a_nok[i] = n0 + a_n[i] < N;
+    }
 
     double2 rh[HL];
-    uint4 ra;
+    uint4 ra[AP];
     auto fetch = [&](int64_t kt) {
 #pragma unroll
         for (int i = 0; i < HL; ++i) {
             const int64_t k = kt + h_k[i];
             rh[i] = (hok[i] && k < kend) ? *reinterpret_cast<const double2*>(H + k * r + h_j[i]) : make_double2(0.0, 0.0);
         }
-        const int64_t k = kt + a_kr;
-        if (a_nok && k < kend) {
-            const int64_t src = rowmap ? (int64_t)rowmap[k] : k;
-            ra = *reinterpret_cast<const uint4*>(A + src * lda + n0 + a_n);
-        } else {
-            ra = make_uint4(0, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < AP; ++i) {
+            const int64_t k = kt + a_kr[i];
+            if (a_nok[i] && k < kend) {
+                const int64_t src = rowmap ? (int64_t)rowmap[k] : k;
+                ra[i] = *reinterpret_cast<const uint4*>(A + src * lda + n0 + a_n[i]);
+            } else {
+                ra[i] = make_uint4(0, 0, 0, 0);
+            }
         }
     };
     auto stash = [&](int buf) {
 #pragma unroll
         for (int i = 0; i < HL; ++i)
             if (hok[i]) *reinterpret_cast<double2*>(&Hs[(size_t)buf * PJ_KS * LDH + h_k[i] * LDH + h_j[i]]) = rh[i];
-        *reinterpret_cast<uint4*>(&As[buf * PJ_KS * PJ_LDA + a_kr * PJ_LDA + a_n]) = ra;
+#pragma unroll
+        for (int i = 0; i < AP; ++i) *reinterpret_cast<uint4*>(&As[buf * PJ_KS * PJ_LDA + a_kr[i] * PJ_LDA + a_n[i]]) = ra[i];
     };
 
     double4_t acc[NT];
@@ -222,11 +235,11 @@ k_project(const double* __restrict__ H_main, const double* __restrict__ H_alt, c
         const bool more = kt + PJ_KS < kend;
         if (more) fetch(kt + PJ_KS);
         const double* hs = Hs + (size_t)buf * PJ_KS * LDH;
-        const uint16_t* as = As + buf * PJ_KS * PJ_LDA;
+        const TA* as = As + buf * PJ_KS * PJ_LDA;
 #pragma unroll 4
         for (int s = 0; s < PJ_KS / 4; ++s) {
             const int kr = 4 * s + (lane >> 4);
-            const double b = bf16_bits_to_f64(as[kr * PJ_LDA + wave * 16 + (lane & 15)]);
+            const double b = skinny_to_f64(as[kr * PJ_LDA + wave * 16 + (lane & 15)]);
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
                 const double a = hs[kr * LDH + 16 * i + (lane & 15)];
@@ -256,8 +269,9 @@ static inline int64_t skinny_kchunk(int64_t K, int64_t tiles, int stage) {
 }
 
 // true when the fast kernels' layout preconditions hold
-static inline bool skinny_ok(const bf16_t* A, int64_t lda, int64_t N, int r) {
-    return r % 8 == 0 && r >= 8 && r <= 128 && N % 8 == 0 && lda % 8 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0;
+template <typename TA>
+static inline bool skinny_ok(const TA* A, int64_t lda, int64_t N, int r) {
+    return r % 8 == 0 && r >= 8 && r <= 128 && N % 8 == 0 && lda % (16 / (int64_t)sizeof(TA)) == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0;
 }
 
 // number of partial products the two kernels write
@@ -269,12 +283,13 @@ static inline int project_parts(int64_t Ms, int64_t N) {
 }
 
 // Z = sketch_parts(Ms, K) partial products [Ms][r]
-static inline int launch_sketch(hipStream_t s, const bf16_t* A, int64_t lda, const uint32_t* rowmap, int64_t Ms, int64_t K,
+template <typename TA>
+static inline int launch_sketch(hipStream_t s, const TA* A, int64_t lda, const uint32_t* rowmap, int64_t Ms, int64_t K,
                                 const bf16_t* Om, int r, double* Z) {
     const int64_t kchunk = skinny_kchunk(K, ceil_div64(Ms, SK_ROWS), SK_KS);
     dim3 grid(1, (unsigned)ceil_div64(Ms, SK_ROWS), (unsigned)ceil_div64(K, kchunk));
 #define SKETCH_CASE(NT)                                                                                          \
-    hipLaunchKernelGGL(k_sketch<NT>, grid, dim3(256), 0, s, A, lda, rowmap, Ms, K, Om, r, kchunk, Z);
+    hipLaunchKernelGGL((k_sketch<NT, TA>), grid, dim3(256), 0, s, A, lda, rowmap, Ms, K, Om, r, kchunk, Z);
     switch ((r + 15) / 16) {
         case 1: SKETCH_CASE(1) break;
         case 2: SKETCH_CASE(2) break;
@@ -291,16 +306,17 @@ static inline int launch_sketch(hipStream_t s, const bf16_t* A, int64_t lda, con
 }
 
 // B = project_parts(Ms, N) partial products [r][N]
+template <typename TA>
 static inline int launch_project(hipStream_t s, const double* H, const double* H_alt, const int32_t* use_alt, int r,
-                                 const bf16_t* A, int64_t lda, const uint32_t* rowmap, int64_t Ms, int64_t N, double* B) {
+                                 const TA* A, int64_t lda, const uint32_t* rowmap, int64_t Ms, int64_t N, double* B) {
     const int64_t kchunk = skinny_kchunk(Ms, ceil_div64(N, PJ_COLS), PJ_KS);
     dim3 grid((unsigned)ceil_div64(N, PJ_COLS), 1, (unsigned)ceil_div64(Ms, kchunk));
 #define PROJECT_CASE(NT)                                                                                         \
     {                                                                                                            \
-        const size_t lds = ProjectCfg<NT>::LDS;                                                                  \
+        const size_t lds = ProjectCfg<NT, TA>::LDS;                                                                  \
         static LdsLimitCache lds_set;                                                                            \
-        if (!ensure_dyn_lds((const void*)k_project<NT>, lds, lds_set)) return METIS_HIP_ERROR;                   \
-        hipLaunchKernelGGL(k_project<NT>, grid, dim3(256), lds, s, H, H_alt, use_alt, r, A, lda, rowmap, Ms, N, kchunk, B);      \
+        if (!ensure_dyn_lds((const void*)k_project<NT, TA>, lds, lds_set)) return METIS_HIP_ERROR;                   \
+        hipLaunchKernelGGL((k_project<NT, TA>), grid, dim3(256), lds, s, H, H_alt, use_alt, r, A, lda, rowmap, Ms, N, kchunk, B);      \
     }
     switch ((r + 15) / 16) {
         case 1: PROJECT_CASE(1) break;

@@ -26,33 +26,48 @@ __global__ void k_dequant_factor(const uint8_t* __restrict__ codes, const uint8_
     out[t] = rowscale ? v * rowscale[j] : v;
 }
 
-// The same values laid out for the skinny kernels: bf16 [cols][k] (exact: a code times an E4M3 scale times a power
-// of two has at most 5 significant bits), or fp64 [cols][k] times rowscale[j]
-template <typename TO>
-__global__ void k_dequant_factor_t(const uint8_t* __restrict__ codes, const uint8_t* __restrict__ scales, int k, int64_t cols,
-                                   float g, const float* __restrict__ rowscale, TO* __restrict__ out) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)k * cols) return;
-    const int64_t c = t / k;
-    const int j = (int)(t - c * k);
+__device__ __forceinline__ float fp4_value(const uint8_t* __restrict__ codes, const uint8_t* __restrict__ scales, int64_t cols, int j,
+                                          int64_t c, float g) {
     const uint32_t byte = codes[j * (cols / 2) + c / 2];
     const uint32_t nib = (c & 1) ? (byte >> 4) : (byte & 15u);
     const float grid[8] = {0.0f, 0.5f, 1.0f, 1.5f, 2.0f, 3.0f, 4.0f, 6.0f};
-    float v = grid[nib & 7u] * e4m3_decode(scales[j * (cols / 16) + c / 16]) * g;
-    if (nib & 8u) v = -v;
-    if constexpr (sizeof(TO) == 2) out[t] = f32_to_bf16_rne(v);
-    else out[t] = (double)v * (double)rowscale[j];
+    const float v = grid[nib & 7u] * e4m3_decode(scales[j * (cols / 16) + c / 16]) * g;
+    return (nib & 8u) ? -v : v;
 }
 
-// out[c][j] = (float) in[j][c]
-__global__ void k_f64_to_f32_t(const double* __restrict__ in, int k, int64_t cols, float* __restrict__ out) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)k * cols) return;
-    const int64_t c = t / k;
-    const int j = (int)(t - c * k);
-    out[t] = (float)in[(int64_t)j * cols + c];
+// The dequantized factors as the skinny kernels read them, in one launch: Vbar as bf16 [K][k] (exact: a code times an E4M3
+// scale times a power of two has at most 5 significant bits), then Ubar S as fp64 [N][k] and Ubar as fp32 [N][k]
+__global__ void __launch_bounds__(256)
+k_fg_prepare(const uint8_t* __restrict__ vc, const uint8_t* __restrict__ vs, float gv, int64_t K, const uint8_t* __restrict__ uc,
+             const uint8_t* __restrict__ us, float gu, int64_t N, int k, const float* __restrict__ S, bf16_t* __restrict__ Vbf,
+             double* __restrict__ UdS, float* __restrict__ Ud) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, nv = K * k, nu = N * k;
+    if (t < nv) {
+        const int64_t c = t / k;
+        Vbf[t] = f32_to_bf16_rne(fp4_value(vc, vs, K, (int)(t - c * k), c, gv));
+    } else if (t < nv + nu) {
+        const int64_t e = t - nv, c = e / k;
+        const int j = (int)(e - c * k);
+        const float v = fp4_value(uc, us, N, j, c, gu);
+        UdS[e] = (double)v * (double)S[j];
+        Ud[e] = v;
+    }
 }
 
+// dU[n][j] = T[n][j] S[j], dV[c][j] = dV64[j][c], dS: the three results rounded to fp32, in one launch
+__global__ void __launch_bounds__(256)
+k_fg_finish(const double* __restrict__ T, int64_t N, const double* __restrict__ dV64, int64_t K, const double* __restrict__ dS64, int k,
+            const float* __restrict__ S, float* __restrict__ dU, float* __restrict__ dV, float* __restrict__ dS) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, nu = N * k, nv = K * k;
+    if (t < nu) {
+        dU[t] = (float)(T[t] * (double)S[t % k]);
+    } else if (t < nu + nv) {
+        const int64_t e = t - nu, c = e / k;
+        dV[e] = (float)dV64[(e - c * k) * K + c];
+    } else if (t < nu + nv + (int64_t)k * k) {
+        dS[t - nu - nv] = (float)dS64[t - nu - nv];
+    }
+}
 
 // out[r][j] = (float)(in[r][j] * colscale[j])  (colscale optional)
 __global__ void k_f64_to_f32_cols(const double* __restrict__ in, int64_t rows, int k, const float* __restrict__ colscale,
@@ -70,7 +85,7 @@ int splits_for(int64_t Kc, int64_t tiles) {
 }
 
 struct FgLayout {
-    size_t off_t, off_dv, off_ds, off_vd, off_ud, off_uds, off_vbf, off_h64, off_parts, total;
+    size_t off_t, off_dv, off_ds, off_vd, off_ud, off_uds, off_vbf, off_h64, off_parts, off_parts2, total;
 };
 
 FgLayout fg_layout(int64_t N, int64_t K, int k) {
@@ -94,6 +109,7 @@ FgLayout fg_layout(int64_t N, int64_t K, int k) {
         size_t need = std::max(tp * (size_t)N * k, vp * (size_t)K * k);
         need = std::max(need, sp * (size_t)k * k);
         L.off_parts = take(need * 8);
+        L.off_parts2 = take((size_t)project_parts(N, K) * K * k * 8);     // the second product's, side by side with the first's
     }
     L.total = o;
     return L;
@@ -132,36 +148,33 @@ int run(hipStream_t s, const TW* dW, int64_t ld, int64_t N, int64_t K, int k, co
     float* UdS = (float*)(ws + L.off_uds);
     double* parts = (double*)(ws + L.off_parts);
     SumList sums;
-    hipLaunchKernelGGL(k_dequant_factor, dim3((unsigned)ceil_div64((int64_t)k * K, 256)), dim3(256), 0, s, W->Vt.codes,
-                       W->Vt.scales, k, K, W->Vt.tscale, (const float*)nullptr, Vd);
-    hipLaunchKernelGGL(k_dequant_factor, dim3((unsigned)ceil_div64((int64_t)k * N, 256)), dim3(256), 0, s, W->Ut.codes,
-                       W->Ut.scales, k, N, W->Ut.tscale, (const float*)nullptr, Ud);
-    hipLaunchKernelGGL(k_dequant_factor, dim3((unsigned)ceil_div64((int64_t)k * N, 256)), dim3(256), 0, s, W->Ut.codes,
-                       W->Ut.scales, k, N, W->Ut.tscale, W->S, UdS);
-    METIS_LAUNCH_CHECK();
     const int64_t tk = ceil_div64(k, 32);
-    // A bf16 dW of aligned rows takes the decomposition's skinny kernels (same shapes as its sketch and projection)
-    bool fast = false;
-    if constexpr (sizeof(TW) == 2) fast = skinny_ok((const bf16_t*)dW, ld, K, k) && N % 8 == 0;
+    // A dW of aligned rows takes the decomposition's skinny kernels (same shapes as its sketch and projection): fp32 4096 x 4096
+    // at rank 64, the two products 262 us on the generic kernel, 120 us there; the whole call in 7 launches instead of 14
+    const bool fast = skinny_ok(dW, ld, K, k) && N % 8 == 0 && (N + K) * (int64_t)k < ((int64_t)1 << 38);
     if (fast) {
         bf16_t* Vbf = (bf16_t*)(ws + L.off_vbf);
         double* H64 = (double*)(ws + L.off_h64);
-        hipLaunchKernelGGL(k_dequant_factor_t<bf16_t>, dim3((unsigned)ceil_div64((int64_t)k * K, 256)), dim3(256), 0, s,
-                           W->Vt.codes, W->Vt.scales, k, K, W->Vt.tscale, (const float*)nullptr, Vbf);
-        hipLaunchKernelGGL(k_dequant_factor_t<double>, dim3((unsigned)ceil_div64((int64_t)k * N, 256)), dim3(256), 0, s,
-                           W->Ut.codes, W->Ut.scales, k, N, W->Ut.tscale, W->S, H64);
+        double* parts2 = (double*)(ws + L.off_parts2);
+        hipLaunchKernelGGL(k_fg_prepare, dim3((unsigned)ceil_div64((N + K) * k, 256)), dim3(256), 0, s, W->Vt.codes, W->Vt.scales,
+                           W->Vt.tscale, K, W->Ut.codes, W->Ut.scales, W->Ut.tscale, N, k, W->S, Vbf, H64, Ud);
         METIS_LAUNCH_CHECK();
         int st;
         // T = dW Vbar                  [N,k], contraction over K
-        if ((st = launch_sketch(s, (const bf16_t*)dW, ld, nullptr, N, K, Vbf, k, parts)) != METIS_OK) return st;
+        if ((st = launch_sketch(s, dW, ld, nullptr, N, K, Vbf, k, parts)) != METIS_OK) return st;
         sums.add(parts, sketch_parts(N, K), N * (int64_t)k, N * (int64_t)k, T);
-        sums.launch(s);
         // dV^T = (Ubar S)^T dW         [k,K], contraction over N
-        if ((st = launch_project(s, H64, nullptr, nullptr, k, (const bf16_t*)dW, ld, nullptr, N, K, parts)) != METIS_OK)
-            return st;
-        sums.add(parts, project_parts(N, K), K * (int64_t)k, K * (int64_t)k, dV64);
+        if ((st = launch_project(s, H64, nullptr, nullptr, k, dW, ld, nullptr, N, K, parts2)) != METIS_OK) return st;
+        sums.add(parts2, project_parts(N, K), K * (int64_t)k, K * (int64_t)k, dV64);
         sums.launch(s);
     } else {
+        hipLaunchKernelGGL(k_dequant_factor, dim3((unsigned)ceil_div64((int64_t)k * K, 256)), dim3(256), 0, s, W->Vt.codes,
+                           W->Vt.scales, k, K, W->Vt.tscale, (const float*)nullptr, Vd);
+        hipLaunchKernelGGL(k_dequant_factor, dim3((unsigned)ceil_div64((int64_t)k * N, 256)), dim3(256), 0, s, W->Ut.codes,
+                           W->Ut.scales, k, N, W->Ut.tscale, (const float*)nullptr, Ud);
+        hipLaunchKernelGGL(k_dequant_factor, dim3((unsigned)ceil_div64((int64_t)k * N, 256)), dim3(256), 0, s, W->Ut.codes,
+                           W->Ut.scales, k, N, W->Ut.tscale, W->S, UdS);
+        METIS_LAUNCH_CHECK();
         // T = dW Vbar                  [N,k], contraction over K
         int want = splits_for(K, ceil_div64(N, 32) * tk);
         launch_dgemm<TW, float, EPI_PART_F64>(s, opnd(dW, ld, 1), opnd(Vd, K, 1), N, k, K, want, epi_part(parts, N, k));
@@ -177,19 +190,22 @@ int run(hipStream_t s, const TW* dW, int64_t ld, int64_t N, int64_t K, int k, co
     // dS = Ubar^T T                    [k,k], contraction over N
     {
         const int want = splits_for(N, tk * tk);
-        launch_dgemm<float, double, EPI_PART_F64>(s, opnd(Ud, N, 1), opnd(T, 1, k), k, k, N, want, epi_part(parts, k, k));
+        launch_dgemm<float, double, EPI_PART_F64>(s, fast ? opnd(Ud, 1, k) : opnd(Ud, N, 1), opnd(T, 1, k), k, k, N, want,
+                                                  epi_part(parts, k, k));
         sums.add(parts, dgemm_parts<EPI_PART_F64>(k, k, N, want), (int64_t)k * k, (int64_t)k * k, dS64);
         sums.launch(s);
     }
     METIS_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_f64_to_f32_cols, dim3((unsigned)ceil_div64(N * k, 256)), dim3(256), 0, s, T, N, k, W->S, dU);
-    if (fast)
-        hipLaunchKernelGGL(k_f64_to_f32_t, dim3((unsigned)ceil_div64(K * k, 256)), dim3(256), 0, s, dV64, k, K, dV);
-    else
+    if (fast) {
+        hipLaunchKernelGGL(k_fg_finish, dim3((unsigned)ceil_div64((N + K + k) * k, 256)), dim3(256), 0, s, T, N, dV64, K, dS64, k, W->S,
+                           dU, dV, dS);
+    } else {
+        hipLaunchKernelGGL(k_f64_to_f32_cols, dim3((unsigned)ceil_div64(N * k, 256)), dim3(256), 0, s, T, N, k, W->S, dU);
         hipLaunchKernelGGL(k_f64_to_f32_cols, dim3((unsigned)ceil_div64(K * k, 256)), dim3(256), 0, s, dV64, K, k,
                            (const float*)nullptr, dV);
-    hipLaunchKernelGGL(k_f64_to_f32_cols, dim3((unsigned)ceil_div64((int64_t)k * k, 256)), dim3(256), 0, s, dS64,
-                       (int64_t)k, k, (const float*)nullptr, dS);
+        hipLaunchKernelGGL(k_f64_to_f32_cols, dim3((unsigned)ceil_div64((int64_t)k * k, 256)), dim3(256), 0, s, dS64,
+                           (int64_t)k, k, (const float*)nullptr, dS);
+    }
     METIS_LAUNCH_CHECK();
     return METIS_OK;
 }
