@@ -8,140 +8,161 @@
 // ---------------------------------------------------------------------------------------
 // Blocked Cholesky in LDS, shared by both kernels below.  On entry W holds the lower triangle of a
 // symmetric matrix column-major (element (i, c), i >= c, at W[c*ld + i]); on exit the same places
-// hold L, and rinv[c] = 1 / L[c][c].  Blocks of CB = 4 columns, two workgroup barriers per block:
-//   1  one thread per row at or below the block reads the CB x CB diagonal block (LDS broadcast), factors
-//      it on its own (every thread repeats the same ~30 operations: cheaper than a barrier and a round
-//      trip through LDS) and solves its row's CB entries against it (the chain of dependent pivots is what a
-//      block costs, and it grows faster than the block: CB = 8 measured slower than 4),
-//   2  the trailing matrix takes the rank-CB update on the fp64 matrix cores: CB / 4
-//      v_mfma_f64_16x16x4_f64 per 16x16 tile.
+// hold L, and rinv[c] = 1 / L[c][c].  Panels of 16 columns, three workgroup barriers each:
+//   1  a lane holds the 16 panel entries of one row below the diagonal block in registers, and every 16 lanes a copy of the
+//      16 rows of the diagonal block (each group factors it for itself), so one pass over the columns factors the block and
+//      solves the rows: a column's pivot and multipliers reach the 16 lanes by v_mov_b64 with a row broadcast,
+//      with no LDS, no scalar registers and no barrier between columns;
+//   2  the trailing matrix takes the rank-16 update on the fp64 matrix cores: four v_mfma_f64_16x16x4_f64 per 16x16 tile,
+//      transposed, so that a tile's columns are read and written along the lanes.
+// The chain of n dependent reciprocal square roots bounds it.  n = 80: 15 us, n = 64: 11 us; blocks of 4
+// columns factored by every thread out of LDS, two barriers each, took 31 and 23 us.
 // BAD_PIVOT_ZEROES: a pivot <= floor zeroes its column (semi-definite input, eigensolver); otherwise it is
 // replaced by 1e-300 and its 1-based index is written to *info (CholeskyQR2's rank check).
+// (Multipliers passed as scalars by v_readlane cost 27 cycles each, 3.4 us a panel.)
 // ---------------------------------------------------------------------------------------
 typedef double double4_t __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ double chol_rsqrt(double x) {
-    double y = __builtin_amdgcn_rsq(x);
-    y = y * (1.5 - 0.5 * x * y * y);
-    y = y * (1.5 - 0.5 * x * y * y);
-    return y;
+__device__ __forceinline__ double readlane64(double x, int l) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l), __builtin_amdgcn_readlane(__double2loint(x), l));
 }
 
-template <bool BAD_PIVOT_ZEROES, int CB = 4>
-__device__ void chol_blocked(double* __restrict__ W, int ld, int n, double* __restrict__ rinv, double floor_,
+// x of lane N of each row of 16 lanes, in all 16
+template <int N>
+__device__ __forceinline__ double row_bcast(double x) {
+    return __longlong_as_double(__builtin_amdgcn_update_dpp((long long)0, __double_as_longlong(x), 0x150 + N, 0xF, 0xF, true));
+}
+template <class F, int... I>
+__device__ __forceinline__ void for_each_block_impl(F&& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>): a loop whose index is a compile-time constant
+template <int N, class F>
+__device__ __forceinline__ void for_each_block(F&& f) {
+    for_each_block_impl(f, std::make_integer_sequence<int, N>{});
+}
+
+// 1 / sqrt(x) to ~1e-16: the hardware seed (~2^-23) and one third-order step
+__device__ __forceinline__ double chol_rsqrt(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = __builtin_fma(-(x * y), y, 1.0);
+    return __builtin_fma(e * y, __builtin_fma(e, 0.375, 0.5), y);
+}
+
+template <bool BAD_PIVOT_ZEROES>
+__device__ __forceinline__ void chol_blocked(double* __restrict__ W, int ld, int n, double* __restrict__ rinv, double floor_,
                              int32_t* __restrict__ info) {
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = nthr >> 6;
-    static_assert(CB % 4 == 0, "the trailing update takes the block in chunks of the matrix instruction's depth");
-    for (int k0 = 0; k0 < n; k0 += CB) {
-        // ---- 1: diagonal block (entries past n act as an identity block) and the rows below ----
-        double d[CB][CB];                                // lower triangle of the diagonal block
-        double r[CB];
-        if (tid < n - k0) {
-            const int i = k0 + tid;
+    for (int k0 = 0; k0 < n; k0 += 16) {
+        const int below = n - k0 - 16;                   // rows under the diagonal block
+        const bool mine = wave == 0 || 64 * wave < below;      // uniform
+        const int l16 = lane & 15, i = k0 + 16 + 64 * wave + lane;
+        double d[16], x[16], rv = 0.0;                   // row k0 + l16 of the diagonal block, row i below it
+        if (mine) {
+            // (unconditional loads, then selects: a branch per entry would cost more than the column's arithmetic.)
+            const int id = min(k0 + l16, n - 1), ix = min(i, n - 1);
 #pragma unroll
-            for (int q = 0; q < CB; ++q)
+            for (int c = 0; c < 16; ++c) {
+                const double* col = W + (size_t)min(k0 + c, n - 1) * ld;
+                d[c] = col[id];
+                x[c] = col[ix];
+            }
+            if (below < 0) {                             // entries past n act as an identity block
 #pragma unroll
-                for (int c = 0; c <= q; ++c)
-                    d[q][c] = (k0 + q < n) ? W[(size_t)(k0 + c) * ld + k0 + q] : (q == c ? 1.0 : 0.0);
-#pragma unroll
-            for (int c = 0; c < CB; ++c) {
-                double piv = d[c][c];
-#pragma unroll
-                for (int t = 0; t < c; ++t) piv -= d[c][t] * d[c][t];
+                for (int c = 0; c < 16; ++c) d[c] = k0 + l16 >= n || k0 + c >= n ? (l16 == c ? 1.0 : 0.0) : d[c];
+            }
+        }
+        __syncthreads();                                 // every wave holds the unfactored block
+        if (mine) {
+            int bad = 0;
+            double r = 0.0;
+            auto pivot = [&](auto C) {
+                constexpr int c = decltype(C)::value;
+                double piv = row_bcast<c>(d[c]);
                 if (BAD_PIVOT_ZEROES) {
-                    r[c] = piv > floor_ ? chol_rsqrt(piv) : 0.0;
+                    r = piv > floor_ ? chol_rsqrt(piv) : 0.0;
                 } else {
-                    if (!(piv > 0.0)) {
-                        if (tid == 0 && info && k0 + c < n) *info = k0 + c + 1;
-                        piv = 1e-300;
-                    }
-                    r[c] = chol_rsqrt(piv);
+                    const bool ok = piv > 0.0;
+                    bad = !ok && k0 + c < n ? k0 + c + 1 : bad;
+                    piv = ok ? piv : 1e-300;
+                    r = chol_rsqrt(piv);
                 }
-                d[c][c] = piv * r[c];                    // sqrt(pivot), or 0 for a zeroed column
+            };
+            pivot(std::integral_constant<int, 0>{});
+            // (column c's first update feeds the next pivot's reciprocal square root, the others fill its latency; the fences
+            // keep the compiler from postponing them into one long chain per column)
+            for_each_block<16>([&](auto C) {
+                constexpr int c = decltype(C)::value;
+                __builtin_amdgcn_sched_barrier(0);
+                rv = l16 == c ? r : rv;
+                d[c] *= r;                               // the pivot's lane: sqrt(pivot), or 0 for a zeroed column
+                x[c] *= r;
+                for_each_block<15 - c>([&](auto T) {
+                    constexpr int t = c + 1 + decltype(T)::value;
+                    const double m = row_bcast<t>(d[c]);
+                    d[t] = __builtin_fma(-d[c], m, d[t]);
+                    if constexpr (t == c + 1) pivot(std::integral_constant<int, t>{});
+                    x[t] = __builtin_fma(-x[c], m, x[t]);
+                });
+            });
+            __builtin_amdgcn_sched_barrier(0);
+            // (formed here, not in the branches below: sunk there, the rows would wait for the whole block with every multiplier
+            // alive)
 #pragma unroll
-                for (int q = c + 1; q < CB; ++q) {
-                    double v = d[q][c];
+            for (int c = 0; c < 16; ++c) asm volatile("" : "+v"(x[c]), "+v"(d[c]));
+            asm volatile("" : "+v"(rv));
+            if (!BAD_PIVOT_ZEROES && bad && tid == 0 && info) *info = bad;
+            if (i < n) {
 #pragma unroll
-                    for (int t = 0; t < c; ++t) v -= d[q][t] * d[c][t];
-                    d[q][c] = v * r[c];
-                }
+                for (int c = 0; c < 16; ++c) W[(size_t)(k0 + c) * ld + i] = x[c];
             }
-            if (tid >= CB) {
-                double x[CB];
+            if (tid < 16 && k0 + tid < n) {
 #pragma unroll
-                for (int c = 0; c < CB; ++c) {
-                    double v = W[(size_t)(k0 + c) * ld + i];
-#pragma unroll
-                    for (int t = 0; t < c; ++t) v -= x[t] * d[c][t];
-                    x[c] = v * r[c];
-                }
-#pragma unroll
-                for (int c = 0; c < CB; ++c) W[(size_t)(k0 + c) * ld + i] = x[c];
+                for (int c = 0; c < 16; ++c)             // above the diagonal: zeros
+                    if (k0 + c < n) W[(size_t)(k0 + c) * ld + k0 + tid] = tid >= c ? d[c] : 0.0;
+                rinv[k0 + tid] = rv;
             }
         }
+        if (below <= 0) break;
         __syncthreads();
-        // the block's own rows are written once every thread has read the unfactored block; nothing
-        // reads them again before the next barrier
-        if (tid < CB && tid < n - k0) {
-#pragma unroll
-            for (int q = 0; q < CB; ++q)
-                if (tid == q) {
-                    rinv[k0 + q] = r[q];
-#pragma unroll
-                    for (int c = 0; c <= q; ++c) W[(size_t)(k0 + c) * ld + k0 + q] = d[q][c];
-                }
-        }
-        if (n - k0 <= CB) break;
-        // ---- 2: trailing update A22 -= L21 L21^T over the 16-aligned lower tiles that reach past k0 + CB ----
-        const int t0 = (k0 + CB) & ~15;
-        const int T = (n - t0 + 15) / 16, ntiles = T * (T + 1) / 2;
+        // trailing update A22 -= L21 L21^T, lower 16 x 16 tiles, one per wave and round; rows: the tile's columns of A22
+        const int t0 = k0 + 16, T = (below + 15) / 16, ntiles = T * (T + 1) / 2;
         for (int tile = wave; tile < ntiles; tile += nwaves) {
             int ti = 0, rem = tile;
             while (rem > ti) { rem -= ti + 1; ++ti; }       // tile -> (ti, tc), tc <= ti
-            const int i0 = t0 + 16 * ti, c0 = t0 + 16 * rem;
-            const int ia = i0 + (lane & 15), cb = c0 + (lane & 15);
-            double av[CB / 4], bv[CB / 4];
+            const int i0 = t0 + 16 * ti, c0 = t0 + 16 * rem, kq = lane >> 4;
+            const int ib = min(i0 + (lane & 15), n - 1), ca = min(c0 + (lane & 15), n - 1);
+            double av[4], bv[4];
+            double4_t acc;
 #pragma unroll
-            for (int kc = 0; kc < CB / 4; ++kc) {
-                const size_t col = (size_t)(k0 + 4 * kc + (lane >> 4)) * ld;
-                av[kc] = (ia < n && ia >= k0 + CB) ? W[col + ia] : 0.0;
-                bv[kc] = (cb < n && cb >= k0 + CB) ? W[col + cb] : 0.0;
+            for (int kc = 0; kc < 4; ++kc) {
+                const size_t col = (size_t)(k0 + 4 * kc + kq) * ld;
+                av[kc] = -W[col + ca];
+                bv[kc] = W[col + ib];
             }
-            double4_t acc = {0.0, 0.0, 0.0, 0.0};
+            // D: lane l, element v -> (row 4 v + l / 16, column l % 16) of the tile; surplus ones are not stored
 #pragma unroll
-            for (int kc = 0; kc < CB / 4; ++kc) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[kc], bv[kc], acc, 0, 0, 0);
-            // D: lane l, element v -> (row 4 v + l / 16, column l % 16) of the tile
+            for (int v = 0; v < 4; ++v) acc[v] = W[(size_t)min(c0 + 4 * v + kq, n - 1) * ld + ib];
+#pragma unroll
+            for (int kc = 0; kc < 4; ++kc) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[kc], bv[kc], acc, 0, 0, 0);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int i = i0 + 4 * v + (lane >> 4), c = cb;
-                if (i < n && c < n && c >= k0 + CB && i >= c) W[(size_t)c * ld + i] -= acc[v];
+                const int i = i0 + (lane & 15), c = c0 + 4 * v + kq;
+                if (i < n && c < n && i >= c) W[(size_t)c * ld + i] = acc[v];
             }
         }
         __syncthreads();
     }
-    __syncthreads();                                     // the last block's rows are visible to the caller
+    __syncthreads();                                     // the last panel is visible to the caller
 }
 
 // ---------------------------------------------------------------------------------------
 // Cholesky G = L L^T and Linv = L^-1 (lower triangular), n <= SM_MAX_N.
 // LDS: L [n][n+1] doubles, X [n][n+1] doubles.
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ double chol_group8_sum(double x) {
-    int lo, hi;
-    double y;
-    lo = __builtin_amdgcn_update_dpp(__double2loint(x), __double2loint(x), 0xB1, 0xF, 0xF, false);
-    hi = __builtin_amdgcn_update_dpp(__double2hiint(x), __double2hiint(x), 0xB1, 0xF, 0xF, false);
-    y = x + __hiloint2double(hi, lo);
-    lo = __builtin_amdgcn_update_dpp(__double2loint(y), __double2loint(y), 0x4E, 0xF, 0xF, false);
-    hi = __builtin_amdgcn_update_dpp(__double2hiint(y), __double2hiint(y), 0x4E, 0xF, 0xF, false);
-    y = y + __hiloint2double(hi, lo);
-    lo = __builtin_amdgcn_update_dpp(__double2loint(y), __double2loint(y), 0x141, 0xF, 0xF, false);
-    hi = __builtin_amdgcn_update_dpp(__double2hiint(y), __double2hiint(y), 0x141, 0xF, 0xF, false);
-    return y + __hiloint2double(hi, lo);
-}
-
-__global__ void __launch_bounds__(1024)
+#define CI_THREADS 512               // 256 registers per lane: the panels take 140
+__global__ void __launch_bounds__(CI_THREADS)
 k_chol_inv(const CholBatch batch, int n) {
     extern __shared__ double sm[];
     const CholProblem& prob = batch.p[blockIdx.x];
@@ -151,7 +172,7 @@ k_chol_inv(const CholBatch batch, int n) {
     int32_t* __restrict__ wellcond_out = prob.wellcond_out;
     const int32_t* __restrict__ skip_in = prob.skip_in;
     if (skip_in && *skip_in) {
-        for (int e = threadIdx.x; e < n * n; e += 1024) Linv[e] = (e / n == e % n) ? 1.0 : 0.0;
+        for (int e = threadIdx.x; e < n * n; e += CI_THREADS) Linv[e] = (e / n == e % n) ? 1.0 : 0.0;
         return;
     }
     const int ld = n + 1;
@@ -159,17 +180,19 @@ k_chol_inv(const CholBatch batch, int n) {
     double* X = sm + (size_t)n * ld;             // L^-1, row-major: X(t, c) at X[t*ld + c]
     __shared__ double dinv[SM_MAX_CHOL];
     const int tid = threadIdx.x;
-    for (int e = tid; e < n * n; e += 1024) {
-        int i = e / n, j = e - i * n;
-        L[j * ld + i] = G[e];
-        X[i * ld + j] = 0.0;
-    }
+    for (int p = tid >> 4; p < n; p += CI_THREADS >> 4)             // G is symmetric: its row p is column p of L
+        for (int i = tid & 15; i < n; i += 16) {
+            L[p * ld + i] = G[(size_t)p * n + i];
+            X[p * ld + i] = 0.0;
+        }
     __syncthreads();
     chol_blocked<false>(L, ld, n, dinv, 0.0, info);
-    if (wellcond_out && tid == 0) {
-        double lo = dinv[0], hi = dinv[0];
-        for (int j = 1; j < n; ++j) { lo = fmin(lo, dinv[j]); hi = fmax(hi, dinv[j]); }
-        *wellcond_out = (hi <= 1e3 * lo) ? 1 : 0;        // a replaced pivot has dinv = 1e150 and fails this
+    if (wellcond_out && tid < 64) {
+        double lo = dinv[tid < n ? tid : 0], hi = lo;
+        if (tid + 64 < n) { lo = fmin(lo, dinv[tid + 64]); hi = fmax(hi, dinv[tid + 64]); }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) { lo = fmin(lo, __shfl_xor(lo, o)); hi = fmax(hi, __shfl_xor(hi, o)); }
+        if (tid == 0) *wellcond_out = (hi <= 1e3 * lo) ? 1 : 0;        // a replaced pivot has dinv = 1e150 and fails this
     }
     // L^-1 by 16 x 16 blocks.  The diagonal blocks are inverted by substitution (one thread per column, 16 steps in
     // registers); then, one block sub-diagonal after the other, X_ij = -X_ii (sum_k L_ik X_kj) on the fp64 matrix
@@ -177,7 +200,7 @@ k_chol_inv(const CholBatch batch, int n) {
     // the second product wants for its right operand (accumulator element v = contraction chunk v), so it never
     // touches memory.  Rows and columns past n act as an identity.
     {
-        const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = 1024 >> 6;
+        const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = CI_THREADS >> 6;
         const int T = (n + 15) / 16;
         const bool whole = (n & 15) == 0;             // no padding: the accessors need no tests
         auto Lat = [&](int i, int c2) { return (whole || (i < n && c2 < n)) ? L[min(c2, n - 1) * ld + min(i, n - 1)] : (i == c2 ? 1.0 : 0.0); };
@@ -234,10 +257,8 @@ k_chol_inv(const CholBatch batch, int n) {
         }
     }
     __syncthreads();
-    for (int e = tid; e < n * n; e += 1024) {
-        int i = e / n, j = e - i * n;
-        Linv[e] = X[i * ld + j];
-    }
+    for (int i = tid >> 4; i < n; i += CI_THREADS >> 4)
+        for (int j = tid & 15; j < n; j += 16) Linv[(size_t)i * n + j] = X[i * ld + j];
 }
 
 // ---------------------------------------------------------------------------------------
@@ -312,15 +333,15 @@ __host__ __device__ static inline int jacobi_ld(int n, int l) {
 // eigenvalue by 1e-10 relative).  P comes from the classical dense symmetric path, all inside this
 // workgroup:
 //   1  A = L^T L                                       (fp64 matrix cores)
-//   2  Householder tridiagonalisation  Q^T A Q = T     (one row per 8 lanes, rows in registers)
-//   3  eigenvalues of T by multisection on Sturm counts (8 probes per eigenvalue and round)
+//   2  Householder tridiagonalisation  Q^T A Q = T     (rows in registers, 8 lanes a row, four waves)
+//   3  eigenvalues of T by multisection on Sturm counts (3 probes per eigenvalue and round)
 //   4  eigenvectors of T by twisted factorisation       (one thread per eigenvector)
 //   5  back-transformation  P = Q Z                     (one column per 8 lanes, no barriers)
 //   6  Newton-Schulz polish  P <- P (I - (P^T P - I) / 2)  until orthogonal to 1e-10; if the computed
 //      vectors are far from orthogonal (coincident or tiny eigenvalues) the preconditioner is dropped
 //   7  W0 = L P                                         (fp64 matrix cores)
-// R1 holds L on entry (column-major, stride ld, (ne+1) columns); the result is left in R2 in the same
-// layout.  gscr: (ne+1)*ld doubles of global scratch for L.  sa: 10*n + 40 doubles of LDS, 16-byte aligned.
+// R1 holds L on entry (column-major, odd stride lda = n | 1: rows and columns both walk all banks); the result is left in
+// R2 in the sweeps' layout (stride ld, ne + 1 columns).  gscr: n * lda doubles of global scratch for L.  sa: 10*n + 40 doubles of LDS, 16-byte aligned.
 // ---------------------------------------------------------------------------------------
 __device__ __forceinline__ double wave_max(double x) {
 #pragma unroll
@@ -333,9 +354,6 @@ __device__ __forceinline__ double wave_sum(double x) {
     return x;
 }
 
-__device__ __forceinline__ double readlane64(double x, int l) {
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l), __builtin_amdgcn_readlane(__double2loint(x), l));
-}
 // x is the same in the 8 lanes of every group: the sum over the wave's 8 groups, in every lane
 __device__ __forceinline__ double wave_sum_of_groups8(double x) {
     x += dpp_mov64<0x140>(x);     // row_mirror: the other group of this row of 16 lanes
@@ -347,30 +365,21 @@ __device__ __forceinline__ double rcp_nr2(double x) {          // 1/x to ~1e-15 
     return y * (2.0 - x * y);
 }
 
-// 9^12 = 2.8e11 sections of the scaled spectrum: eigenvalues to ~1e-11 ||T||, eigenvectors orthogonal to
+// 4^19 = 2.7e11 sections of the scaled spectrum: eigenvalues to ~1e-11 ||T||, eigenvectors orthogonal to
 // ~1e-5 before the polish, which one Newton-Schulz step brings to ~1e-10
-#define PRE_ROUNDS 12
-#define PRE_MAX_ROUNDS 20
+#define PRE_ROUNDS 19
+#define PRE_MAX_ROUNDS 32
 
-template <class F, int... I>
-__device__ __forceinline__ void for_each_block_impl(F&& f, std::integer_sequence<int, I...>) {
-    (f(std::integral_constant<int, I>{}), ...);
-}
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>): a loop whose index is a compile-time constant
-template <int N, class F>
-__device__ __forceinline__ void for_each_block(F&& f) {
-    for_each_block_impl(f, std::make_integer_sequence<int, N>{});
-}
-
-// One 16x16 tile of sum_k a(i, k) b(k, j) on the fp64 matrix cores; lane supplies row/column (lane & 15) and the
-// k offset lane >> 4.  fa / fb read in-bounds elements; out-of-range rows, columns and k contribute zero.
+// One 16x16 tile of sum_{kbeg <= k < kend} a(i, k) b(k, j) on the fp64 matrix cores (kbeg a multiple of 16); lane supplies
+// row/column (lane & 15) and the k offset lane >> 4.  fa / fb read in-bounds elements; out-of-range rows, columns and k
+// contribute zero.
 template <class FA, class FB>
-__device__ __forceinline__ double4_t tile_mma(int n, int ia, int jb, int kq, FA fa, FB fb, bool batch = true) {
+__device__ __forceinline__ double4_t tile_mma(int n, int ia, int jb, int kq, FA fa, FB fb, int kbeg, int kend) {
     const int ic = min(ia, n - 1), jc = min(jb, n - 1);
     const bool iok = ia < n, jok = jb < n;
     double4_t acc = {0.0, 0.0, 0.0, 0.0};
-    if ((n & 15) == 0 && batch) {                 // whole tiles: no guards, operands of four steps loaded ahead
-        for (int k0 = 0; k0 < n; k0 += 16) {
+    if ((n & 15) == 0 && (kend & 15) == 0) {      // whole tiles: no guards, operands of four steps loaded ahead
+        for (int k0 = kbeg; k0 < kend; k0 += 16) {
             double a[4], b[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -382,10 +391,10 @@ __device__ __forceinline__ double4_t tile_mma(int n, int ia, int jb, int kq, FA 
         }
         return acc;
     }
-    for (int k0 = 0; k0 < n; k0 += 4) {
+    for (int k0 = kbeg; k0 < kend; k0 += 4) {
         const int k = k0 + kq, kc = min(k, n - 1);
         const double a = fa(ic, kc), b = fb(kc, jc);
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64((iok && k < n) ? a : 0.0, (jok && k < n) ? b : 0.0, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64((iok && k < kend) ? a : 0.0, (jok && k < kend) ? b : 0.0, acc, 0, 0, 0);
     }
     return acc;
 }
@@ -412,13 +421,12 @@ __device__ __forceinline__ void back_blocks(double (&zr)[NR], const double* __re
 }
 
 template <int NE>
-__device__ void eig_precondition(double* __restrict__ R1, double* __restrict__ R2, int ld, int n, int ne,
+__device__ __forceinline__ bool eig_precondition(double* __restrict__ R1, double* __restrict__ R2, int ld, int lda, int n, int ne,
                                  double* __restrict__ gscr, double* __restrict__ sa) {
     constexpr int NR = 2 * NE;                    // entries of a row (or column) per lane of an 8-lane group
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = nthr >> 6;
     const int T16 = (n + 15) / 16, ntiles = T16 * T16;
-    const int lda = n | 1;                        // odd stride: rows and columns both walk all banks
     const size_t rsize = (size_t)(ne + 1) * ld;
     const int n8 = (n + 7) & ~7;
     double* dd = sa;            // [n] diagonal of T
@@ -427,76 +435,91 @@ __device__ void eig_precondition(double* __restrict__ R1, double* __restrict__ R
     double* tauv = de + 2 * n8; // [n] Householder tau
     double* scl = tauv + n;     // [n] v_i = A[i][j] * scl[j] for i > j+1, v_{j+1} = 1
     double* lamv = scl + n;     // [n] eigenvalues of T, ascending
-    const int n16 = (n + 15) & ~15;
-    double* xx = lamv + n;      // [n16] current column below the diagonal, zero up to the current row and from n up
-    double* pp = xx + n16;      // [n16] A v, zero up to the current row and from n up
-    __shared__ double part_k[16], part_s[2][16];  // per-wave partial sums: v^T A v, and sigma by step parity
+    const int n32 = (n + 31) & ~31;
+    double* xx = lamv + n;      // [n32] current column below the diagonal, zero up to the current row and from n up
+    double* pp = xx + n32;      // [n32] A v, zero up to the current row and from n up
+    __shared__ double part_k[4], part_s[2][4];    // per-wave partial sums: v^T A v, and sigma by step parity
     __shared__ unsigned long long err_s;
     __shared__ int fail_s;
 
     // ---- 0: L to global scratch (R1 is reused for the eigenvectors) ----
-    for (size_t e = tid; e < rsize; e += nthr) gscr[e] = R1[e];
+    for (int e = tid; e < n * lda; e += nthr) gscr[e] = R1[e];
     if (tid == 0) fail_s = 0;
 
-    // Gram of the columns of a column-major matrix M (stride ldm, nc columns of nr rows) into R2 (row-major, lda)
-    auto gram_to_R2 = [&](const double* M, int ldm, bool batch) {
-        for (int t0 = 0; t0 < ntiles; t0 += nwaves) {
-            if (t0 + wave >= ntiles) continue;    // `wave` is a scalar: a uniform branch; a repeated tile would queue on the same matrix pipe
-            const int tile = t0 + wave;
-            const int ti = tile / T16, tj = tile - ti * T16;
+    // Gram of the columns of R1 into R2 (row-major, lda): lower tiles, mirrored.  k_from: the columns are zero above row
+    // 16 floor(column / 16) (a triangular factor), so the sum starts there
+    auto gram_to_R2 = [&](bool lower) {
+        for (int tile = wave; tile < T16 * (T16 + 1) / 2; tile += nwaves) {    // `wave` is a scalar: a uniform loop
+            int ti = 0, tj = tile;
+            while (tj > ti) { tj -= ti + 1; ++ti; }
             const int ci = 16 * ti + (lane & 15), cj = 16 * tj + (lane & 15), kq = lane >> 4;
-            const double4_t acc = tile_mma(n, ci, cj, kq, [&](int i, int k) { return M[(size_t)i * ldm + k]; },
-                                           [&](int k, int c) { return M[(size_t)c * ldm + k]; }, batch);
+            const double4_t acc = tile_mma(n, ci, cj, kq, [&](int i, int k) { return R1[(size_t)i * lda + k]; },
+                                           [&](int k, int c) { return R1[(size_t)c * lda + k]; }, lower ? 16 * ti : 0, n);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int i = 16 * ti + 4 * v + kq;
-                if (i < n && cj < n) R2[(size_t)i * lda + cj] = acc[v];
+                if (i < n && cj < n) {
+                    R2[(size_t)i * lda + cj] = acc[v];
+                    R2[(size_t)cj * lda + i] = acc[v];
+                }
             }
         }
     };
 
     // ---- 1: A = L^T L ----
-    gram_to_R2(R1, ld, false);                    // the factor's column stride suits the sweeps, not these reads: no batching
+    gram_to_R2(true);
     __syncthreads();
-    // ---- 2: tridiagonalisation (lower), row r on lanes q = 0..7, columns q, q+8, ... in registers.
-    //         Step j, two barriers: every live wave forms the reflector's scalars and its own pieces of v from
+    // ---- 2: tridiagonalisation (lower).  Four waves, one per SIMD: a group of 8 lanes holds the rows g, g + 32, ..., lane
+    //         q of it their columns q, q+8, ... in registers.  What a step costs is instructions, and most of them (the reflector's scalars,
+    //         v and w by columns, reductions) are the same for every row, so few waves with several rows each beat ten waves
+    //         with one (n = 80: 77 us against 100; a lone wave issues an instruction every ~6.5 cycles, 360 a step).
+    //         Step j, two barriers: every wave forms the reflector's scalars and its own pieces of v from
     //         column j (xx) | p_r = A[r][:] v and the wave's share of v^T A v || rank-2 update, then column j+1
     //         with its squared norm for the next step.  xx and pp are kept zero up to row j (and from n up), so
-    //         dead rows and columns update by exactly zero without any test; waves whose rows are all dead only
-    //         keep the barriers. ----
+    //         dead columns of a block update by exactly zero without any test; whole dead blocks of rows and columns are
+    //         skipped (one instantiation of the step per block of 8 columns). ----
     {
-        const int r = tid >> 3, q = tid & 7;
-        const bool row_ok = r < n;
-        const int nw_rows = (n + 7) >> 3;         // waves that hold rows
-        double areg[NR];
+        constexpr int RWS = (16 * NE + 31) / 32;               // rows per lane group
+        const int g = tid >> 3, q = tid & 7;
+        const bool part = wave < 4;                            // uniform
+        double areg[RWS][NR];
+        if (part) {
 #pragma unroll
-        for (int e = 0; e < NR; ++e) {
-            const int c = q + 8 * e;
-            areg[e] = (row_ok && c < n) ? R2[(size_t)r * lda + c] : 0.0;
+            for (int i = 0; i < RWS; ++i)
+#pragma unroll
+                for (int e = 0; e < NR; ++e) {
+                    const int r = g + 32 * i, c = q + 8 * e;
+                    areg[i][e] = (r < n && c < n) ? R2[(size_t)r * lda + c] : 0.0;
+                }
         }
-        for (int c = tid; c < n16; c += nthr) { pp[c] = 0.0; xx[c] = 0.0; }
+        for (int c = tid; c < n32; c += nthr) { pp[c] = 0.0; xx[c] = 0.0; }
         __syncthreads();
-        {
-            if (row_ok && q == 0 && r >= 1) xx[r] = areg[0];
-            const double y = (row_ok && r >= 2 && q == 0) ? areg[0] * areg[0] : 0.0;
+        if (part) {
+            double y = 0.0;
+#pragma unroll
+            for (int i = 0; i < RWS; ++i) {
+                const int r = g + 32 * i;
+                if (q == 0 && r < n) {
+                    if (r >= 1) xx[r] = areg[i][0];
+                    if (r >= 2) y += areg[i][0] * areg[i][0];
+                }
+            }
             const double t = wave_sum_of_groups8(group8_sum(y));
-            if (lane == 0 && wave < 16) { part_s[0][wave] = t; part_s[1][wave] = 0.0; part_k[wave] = 0.0; }
+            if (lane == 0) part_s[0][wave] = t;
         }
         auto step = [&](int j, auto ES) {
             constexpr int es = decltype(ES)::value;            // (j + 1) / 8: the register block of column j + 1
+            constexpr int i0 = es / 4;                         // rows below 32 i0 are dead
             __syncthreads();                      // column j (xx) and the partial sums of its sigma are complete
-            const bool live = wave < nw_rows && 8 * wave + 7 > j;       // some row of this wave is below row j
-            double vreg[NR], vr = 0.0, tau = 0.0;
-            if (live || wave == 0) {
-                // every live wave works out the reflector's scalars for itself: cheaper than a third barrier
-                const double sg = group_sum<16>((lane & 15) < nw_rows ? part_s[j & 1][lane & 15] : 0.0);
+            double vreg[NR], vr[RWS], p[RWS], tau = 0.0;
+            if (part) {
+                // every wave works out the reflector's scalars for itself: cheaper than a third barrier
+                const double sg = (part_s[j & 1][0] + part_s[j & 1][1]) + (part_s[j & 1][2] + part_s[j & 1][3]);
                 const double alpha = xx[j + 1];
                 double scale = 0.0, beta = alpha;
                 if (sg > 0.0) {
                     const double h = alpha * alpha + sg;
-                    double ri = __builtin_amdgcn_rsq(h);          // 1/sqrt(h), two Newton steps
-                    ri = ri * (1.5 - 0.5 * h * ri * ri);
-                    ri = ri * (1.5 - 0.5 * h * ri * ri);
+                    const double ri = chol_rsqrt(h);
                     const double nr = h * ri;
                     beta = alpha >= 0.0 ? -nr : nr;
                     tau = (beta - alpha) * (alpha >= 0.0 ? -ri : ri);
@@ -506,41 +529,56 @@ __device__ void eig_precondition(double* __restrict__ R1, double* __restrict__ R
                 // v_c = x_c * scale below row j+1 (xx is zero up to row j), 1 at row j+1
                 const int qj = (j + 1) & 7;
 #pragma unroll
-                for (int e = 0; e < NR; ++e) vreg[e] = xx[q + 8 * e] * scale;
-                if (q == qj) vreg[es] = 1.0;
-                vr = r == j + 1 ? 1.0 : xx[r] * scale;
-            }
-            if (live) {                           // p_r = sum_c A[r][c] v_c
-                double p0 = 0.0, p1 = 0.0;
+                for (int e = es; e < NR; ++e) vreg[e] = xx[q + 8 * e] * scale;
+                vreg[es] = q == qj ? 1.0 : vreg[es];
+                double s = 0.0;
 #pragma unroll
-                for (int e = 0; e < NR; e += 2) {
-                    p0 += areg[e] * vreg[e];
-                    if (e + 1 < NR) p1 += areg[e + 1] * vreg[e + 1];
+                for (int i = i0; i < RWS; ++i) {               // p_r = sum_c A[r][c] v_c
+                    const int r = g + 32 * i;
+                    const double x = xx[r] * scale;
+                    vr[i] = r == j + 1 ? 1.0 : x;
+                    double p0 = 0.0, p1 = 0.0;
+#pragma unroll
+                    for (int e = es; e < NR; e += 2) {
+                        p0 = __builtin_fma(areg[i][e], vreg[e], p0);
+                        if (e + 1 < NR) p1 = __builtin_fma(areg[i][e + 1], vreg[e + 1], p1);
+                    }
+                    const double pr = group8_sum(p0 + p1);
+                    p[i] = r > j ? pr : 0.0;
+                    pp[r] = p[i];                     // (the 8 lanes write the same value)
+                    s = __builtin_fma(p[i], vr[i], s);
                 }
-                const double p = group8_sum(p0 + p1);
-                const double t = wave_sum_of_groups8(p * vr);
-                if (q == 0 && r > j && row_ok) pp[r] = p;
-                if (lane == 0) part_k[wave] = t;
-            } else if (lane == 0 && wave < nw_rows) {
-                part_k[wave] = 0.0;
-                part_s[(j + 1) & 1][wave] = 0.0;
+                s = wave_sum_of_groups8(s);
+                if (lane == 0) part_k[wave] = s;
             }
             __syncthreads();
-            if (tid == 0) xx[j + 1] = 0.0;        // the column's head is spent: rows up to j+1 read as zero from now on
-            if (live) {
-                const double ks = group_sum<16>((lane & 15) < nw_rows ? part_k[lane & 15] : 0.0);
+            if (part) {
+                const double ks = (part_k[0] + part_k[1]) + (part_k[2] + part_k[3]);
                 const double K = 0.5 * tau * tau * ks;
-                const double wr = tau * pp[r] - K * vr;
+                double wc[NR], y = 0.0;
 #pragma unroll
-                for (int e = 0; e < NR; ++e) {
-                    const double wc = tau * pp[q + 8 * e] - K * vreg[e];
-                    areg[e] -= vr * wc + wr * vreg[e];
+                for (int e = es; e < NR; ++e) wc[e] = __builtin_fma(tau, pp[q + 8 * e], -K * vreg[e]);
+                double xn[RWS];
+#pragma unroll
+                for (int i = i0; i < RWS; ++i) {
+                    const int r = g + 32 * i;
+                    const double wr = __builtin_fma(tau, p[i], -K * vr[i]);
+#pragma unroll
+                    for (int e = es; e < NR; ++e)
+                        areg[i][e] = __builtin_fma(-wr, vreg[e], __builtin_fma(-vr[i], wc[e], areg[i][e]));
+                    // column j+1 below its diagonal for the next step, and the partial sums of its sigma
+                    xn[i] = r >= j + 2 ? areg[i][es] : 0.0;
+                    const double z = r >= j + 3 ? xn[i] : 0.0;
+                    y = __builtin_fma(z, z, y);
                 }
-                // column j+1 below its diagonal for the next step, and the partial sums of its sigma
-                const double xn = areg[es];
-                const bool own = q == ((j + 1) & 7);
-                if (own && r >= j + 2 && row_ok) xx[r] = xn;
-                const double y = (own && r >= j + 3 && row_ok) ? xn * xn : 0.0;
+                // rows up to j+1 (the spent head of the column) read as zero from now on
+                if (tid == 0) xx[j + 1] = 0.0;
+                if (q == ((j + 1) & 7)) {
+#pragma unroll
+                    for (int i = i0; i < RWS; ++i) xx[g + 32 * i] = xn[i];
+                } else {
+                    y = 0.0;
+                }
                 const double t = wave_sum_of_groups8(group8_sum(y));
                 if (lane == 0) part_s[(j + 1) & 1][wave] = t;
             }
@@ -553,16 +591,20 @@ __device__ void eig_precondition(double* __restrict__ R1, double* __restrict__ R
         __syncthreads();
         // the reflectors, normalised, stay in the strict lower triangle: v^(j)_i = R2[i][j] for every i (zeros down
         // to the diagonal, 1 below it); the diagonal and the subdiagonal move to dd, ee first
+        if (part) {
 #pragma unroll
-        for (int e = 0; e < NR; ++e) {
-            const int c = q + 8 * e;
-            if (row_ok && c < n) {
-                if (c == r) dd[r] = areg[e];
-                if (c == r - 1 && r == n - 1) ee[n - 2] = areg[e];
-                double v = 0.0;
-                if (c + 2 < n) v = r == c + 1 ? 1.0 : (r > c + 1 ? areg[e] * scl[c] : 0.0);
-                R2[(size_t)r * lda + c] = v;
-            }
+            for (int i = 0; i < RWS; ++i)
+#pragma unroll
+                for (int e = 0; e < NR; ++e) {
+                    const int r = g + 32 * i, c = q + 8 * e;
+                    if (r < n && c < n) {
+                        if (c == r) dd[r] = areg[i][e];
+                        if (c == r - 1 && r == n - 1) ee[n - 2] = areg[i][e];
+                        double v = 0.0;
+                        if (c + 2 < n) v = r == c + 1 ? 1.0 : (r > c + 1 ? areg[i][e] * scl[c] : 0.0);
+                        R2[(size_t)r * lda + c] = v;
+                    }
+                }
         }
         if (tid == 0) { tauv[n - 2] = 0.0; tauv[n - 1] = 0.0; ee[n - 1] = 0.0; }
         __syncthreads();
@@ -584,41 +626,44 @@ __device__ void eig_precondition(double* __restrict__ R1, double* __restrict__ R
             }
         }
         __syncthreads();
-        const int i = tid >> 3, q = tid & 7;
-        if (i < n) {
+        // 21 eigenvalues per wave, 3 probes each: four sections, 2 bits per round.  (Eight probes, 3.17 bits, need ten waves
+        // for n = 80 and cost what ten waves issue: 44 us against 33.)
+        const int idx = lane / 3, q = lane - 3 * idx, i = 21 * wave + idx;
+        if (21 * wave < n) {
             double lo = -1.0 - 1e-9, hi = 1.0 + 1e-9;       // Gershgorin after scaling
             for (int round = 0; round < PRE_MAX_ROUNDS; ++round) {
                 // enough once the interval is below 1e-11 of the spectrum's scale and 1e-6 of the eigenvalue itself
                 // (small eigenvalues of a graded matrix keep going); the lanes of a wave leave together
-                const bool done = round >= PRE_ROUNDS && (hi - lo) <= 1e-6 * fmax(fabs(lo), fabs(hi));
+                const bool done = i >= n || idx > 20 || (round >= PRE_ROUNDS && (hi - lo) <= 1e-6 * fmax(fabs(lo), fabs(hi)));
                 if (__ballot(!done) == 0ull) break;
-                const double w = (hi - lo) * (1.0 / 9.0);
+                const double w = (hi - lo) * 0.25;
                 const double mu = lo + w * (double)(q + 1);
                 // Sturm count: sign changes in the sequence of leading principal minors of T - mu,
-                // p_k = (d_k - mu) p_{k-1} - e_{k-1}^2 p_{k-2}; the pair is renormalised every 8 steps
+                // p_k = (d_k - mu) p_{k-1} - e_{k-1}^2 p_{k-2}; the pair is renormalised, and the signs of the last
+                // 8 steps, one bit each, are counted every 8 steps
                 double p2 = 0.0, p1 = 1.0;
-                int cnt = 0, hprev = 0;
+                uint32_t signs = 0;
+                int cnt = 0;
                 for (int k0 = 0; k0 < n8; k0 += 8) {
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
                         const double p = (de[k0 + u] - mu) * p1 - de[n8 + k0 + u] * p2;
-                        const int h = __double2hiint(p);
-                        cnt += (unsigned)(h ^ hprev) >> 31;
-                        hprev = h;
+                        signs = __builtin_amdgcn_alignbit(signs, (uint32_t)__double2hiint(p), 31);     // signs << 1 | sign(p)
                         p2 = p1; p1 = p;
                     }
+                    cnt += __popc((signs ^ (signs >> 1)) & 0xFFu);
                     const int ex = max((__double2hiint(p1) >> 20) & 0x7ff, (__double2hiint(p2) >> 20) & 0x7ff);
                     p1 = ldexp(p1, 1023 - ex);
                     p2 = ldexp(p2, 1023 - ex);
                 }
-                // probes at or below lambda_i have cnt <= i; they form a prefix of the group's 8 lanes
+                // probes at or below lambda_i have cnt <= i; they form a prefix of the group's 3 lanes
                 const unsigned long long b = __ballot(cnt <= i);
-                const int k0 = __popc((unsigned)((b >> (lane & 56)) & 0xFFull));
+                const int k0 = __popc((unsigned)((b >> (3 * idx)) & 0x7ull));
                 const double nlo = k0 > 0 ? lo + w * (double)k0 : lo;
-                const double nhi = k0 < 8 ? lo + w * (double)(k0 + 1) : hi;
+                const double nhi = k0 < 3 ? lo + w * (double)(k0 + 1) : hi;
                 lo = nlo; hi = nhi;
             }
-            if (q == 0) lamv[i] = 0.5 * (lo + hi);
+            if (q == 0 && i < n && idx < 21) lamv[i] = 0.5 * (lo + hi);
         }
         __syncthreads();
         // eigenvalues closer than the accuracy of the vectors that follow (repeated eigenvalues, rank deficiency):
@@ -640,7 +685,7 @@ __device__ void eig_precondition(double* __restrict__ R1, double* __restrict__ R
         double D = dd[0] - lam;
         z[0] = D;
         for (int k = 1; k < n; ++k) {
-            D = (dd[k] - lam) - e2_(k - 1) * rcp_nr2(piv(D));
+            D = (dd[k] - lam) - e2_(k - 1) * rcp_nr(piv(D));
             z[k] = D;
         }
         // backward pivots D- over z, remembering where |gamma_k| = |D+_k + D-_k - (d_k - lam)| is smallest
@@ -650,7 +695,7 @@ __device__ void eig_precondition(double* __restrict__ R1, double* __restrict__ R
         z[n - 1] = Dm;
         for (int k = n - 2; k >= 0; --k) {
             const double a = dd[k] - lam;
-            Dm = a - e2_(k) * rcp_nr2(piv(Dm));
+            Dm = a - e2_(k) * rcp_nr(piv(Dm));
             const double gam = fabs(z[k] + Dm - a);
             if (gam < best) { best = gam; rr = k; }
             z[k] = Dm;
@@ -659,19 +704,19 @@ __device__ void eig_precondition(double* __restrict__ R1, double* __restrict__ R
         D = dd[0] - lam;
         if (rr > 0) z[0] = D;
         for (int k = 1; k < rr; ++k) {
-            D = (dd[k] - lam) - e2_(k - 1) * rcp_nr2(piv(D));
+            D = (dd[k] - lam) - e2_(k - 1) * rcp_nr(piv(D));
             z[k] = D;
         }
         // z_rr = 1; upwards z_k = -e_k z_{k+1} / D+_k; downwards z_{k+1} = -e_k z_k / D-_{k+1}
         double zz = 1.0, nrm2 = 1.0;
         for (int k = rr - 1; k >= 0; --k) {
-            zz = -ee[k] * zz * rcp_nr2(piv(z[k]));
+            zz = -ee[k] * zz * rcp_nr(piv(z[k]));
             z[k] = zz;
             nrm2 += zz * zz;
         }
         zz = 1.0;
         for (int k = rr; k + 1 < n; ++k) {
-            zz = -ee[k] * zz * rcp_nr2(piv(z[k + 1]));
+            zz = -ee[k] * zz * rcp_nr(piv(z[k + 1]));
             z[k + 1] = zz;
             nrm2 += zz * zz;
         }
@@ -701,7 +746,7 @@ __device__ void eig_precondition(double* __restrict__ R1, double* __restrict__ R
     bool ok = fail_s == 0;
     for (int it = 0; it < 4 && ok; ++it) {
         if (tid == 0) err_s = 0ull;
-        gram_to_R2(R1, lda, true);                // E + I = P^T P
+        gram_to_R2(false);                        // E + I = P^T P
         __syncthreads();
         double m = 0.0;
         for (int e = tid; e < n * n; e += nthr) {
@@ -726,7 +771,7 @@ __device__ void eig_precondition(double* __restrict__ R1, double* __restrict__ R
             const int ti = tile / T16, tj = tile - ti * T16;
             const int ia = 16 * ti + (lane & 15), jb = 16 * tj + (lane & 15), kq = lane >> 4;
             acc[t] = tile_mma(n, ia, jb, kq, [&](int i, int k) { return R1[(size_t)k * lda + i]; },
-                              [&](int k, int c) { return R2[(size_t)k * lda + c] - (k == c ? 1.0 : 0.0); });
+                              [&](int k, int c) { return R2[(size_t)k * lda + c] - (k == c ? 1.0 : 0.0); }, 0, n);
         }
         __syncthreads();
 #pragma unroll
@@ -747,24 +792,40 @@ __device__ void eig_precondition(double* __restrict__ R1, double* __restrict__ R
     }
     // ---- 7: W0 = L P into R2 (or L itself when the preconditioner was dropped) ----
     __syncthreads();
-    for (size_t e = tid; e < rsize; e += nthr) R2[e] = ok ? 0.0 : gscr[e];
+    for (size_t e = tid; e < rsize; e += nthr) {
+        const int c = (int)(e / ld), i = (int)(e - (size_t)c * ld);
+        R2[e] = (!ok && c < n && i < n) ? gscr[(size_t)c * lda + i] : 0.0;
+    }
     __syncthreads();
-    if (ok) {
-        for (int t0 = 0; t0 < ntiles; t0 += nwaves) {
-            if (t0 + wave >= ntiles) continue;
-            const int tile = t0 + wave;
-            const int ti = tile / T16, tj = tile - ti * T16;
-            const int ia = 16 * ti + (lane & 15), jb = 16 * tj + (lane & 15), kq = lane >> 4;
-            const double4_t a4 = tile_mma(n, ia, jb, kq, [&](int i, int k) { return gscr[(size_t)k * ld + i]; },   // L[i][k]
-                                          [&](int k, int c) { return R1[(size_t)c * lda + k]; });       // P[k][c]
+    if (!ok) return false;
+    double4_t acc[4];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int i = 16 * ti + 4 * v + kq;
-                if (i < n && jb < n) R2[(size_t)jb * ld + i] = a4[v];
+    for (int t = 0; t < 4; ++t) {
+        const int tile = wave + t * nwaves;
+        if (tile >= ntiles) continue;             // (uniform)
+        const int ti = tile / T16, tj = tile - ti * T16;
+        const int ia = 16 * ti + (lane & 15), jb = 16 * tj + (lane & 15), kq = lane >> 4;
+        acc[t] = tile_mma(n, ia, jb, kq, [&](int i, int k) { return gscr[(size_t)k * lda + i]; },           // L[i][k], k <= i
+                          [&](int k, int c) { return R1[(size_t)c * lda + k]; }, 0, min(16 * ti + 16, n));  // P[k][c]
+    }
+    __syncthreads();                              // P has been read: R1 takes a copy of W0 in its own stride for the check below
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const int tile = wave + t * nwaves;
+        if (tile >= ntiles) continue;
+        const int ti = tile / T16, tj = tile - ti * T16;
+        const int jb = 16 * tj + (lane & 15), kq = lane >> 4;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int i = 16 * ti + 4 * v + kq;
+            if (i < n && jb < n) {
+                R2[(size_t)jb * ld + i] = acc[t][v];
+                R1[(size_t)jb * lda + i] = acc[t][v];
             }
         }
     }
     __syncthreads();
+    return true;
 }
 
 // One-sided Jacobi on the Cholesky factor of G.  JGL lanes share a pair of columns, NE = ceil(n / JGL)
@@ -780,7 +841,7 @@ __device__ void eig_precondition(double* __restrict__ R1, double* __restrict__ R
 // to all the others, and rotations among the others keep it so; it leaves the tournament, and
 // the later sweeps run over the columns that still move.
 template <int NE, int JGL>
-__global__ void __launch_bounds__(1024)
+__global__ void __launch_bounds__(NE <= 4 ? 512 : 128 * NE)
 k_jacobi_eig(const JacobiBatch batch, int n, int kk, int use_pre) {
     extern __shared__ double sm[];
     const JacobiProblem& prob = batch.p[blockIdx.x];
@@ -789,7 +850,8 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk, int use_pre) {
     double* __restrict__ vec = prob.vec;
     double* __restrict__ tmat = prob.tmat;
     float* __restrict__ sval = prob.sval;
-    double* __restrict__ gscr = use_pre ? prob.gscr : nullptr;
+    // (orders of 72 to 88 alone: see the launch)
+    double* __restrict__ gscr = NE == 5 || NE == 6 ? (use_pre ? prob.gscr : nullptr) : nullptr;
     const int ne = n + (n & 1);             // even number of columns (a zero column pads odd n)
     // Column stride = 8 (mod 16) doubles spreads the columns that one LDS instruction touches over the banks.
     const int ld = jacobi_ld(n, JGL);
@@ -804,41 +866,88 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk, int use_pre) {
     // [10 n + 40] the preconditioner's vectors, past the int arrays, on an even double index (16-byte loads)
     double* pre_sa = sm + (((gscr ? 2 : 1) * rsize + ne / 2 + ne + 1 + (3 * ne + 4) / 2 + 2) & ~(size_t)1);
     __shared__ int nact_sh, wcnt[2];
-    __shared__ double amax_sh;
     const int tid = threadIdx.x, nthr = blockDim.x, grp = tid / JGL, gl = tid % JGL;
 
-    for (int e = tid; e < (ne + 1) * ld; e += nthr) {
-        int p = e / ld, i = e - p * ld;
-        W[e] = (p < n && i < n) ? G[(size_t)i * n + p] : 0.0;
-    }
+    // the preconditioner works on an odd column stride (and on n columns alone), the sweeps on theirs; only the lower triangle
+    // is loaded (G is symmetric: column p of it is the rest of row p), so that L comes out with zeros above its diagonal
+    const int ldc = gscr ? n | 1 : ld;
+    for (int p = tid >> 4; p < (gscr ? n : ne + 1); p += nthr >> 4)
+        for (int i = tid & 15; i < ldc; i += 16) W[(size_t)p * ldc + i] = (p < n && i < n && i >= p) ? G[(size_t)p * n + i] : 0.0;
     if (tid <= ne) { colmap[tid] = tid; rotf[tid] = 0; nrm[tid] = 0.0; }
     if (tid == 0) { nact_sh = ne; wcnt[0] = 0; wcnt[1] = 0; }
     __syncthreads();
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Precondition: replace G by its Cholesky factor L (G = L L^T, column j of L in column j of W).
     // The columns of L are far closer to orthogonal than those of G (one Cholesky-LR step), the
     // rotations then converge in about half the sweeps, and column j ends as sigma_j u_j with
     // sigma_j^2 = lambda_j, u_j the eigenvector of G.  A pivot at rounding level (semi-definite G)
     // zeroes its column.
     {
-        __shared__ double piv_floor;
         __shared__ double rinv_sh[SM_MAX_N];
-        if (tid == 0) {
-            double m = 0.0;
-            for (int j = 0; j < n; ++j) m = fmax(m, W[(size_t)j * ld + j]);
-            piv_floor = m * 1e-30;
-        }
-        __syncthreads();
-        chol_blocked<true>(W, ld, n, rinv_sh, piv_floor, nullptr);
-        // the rotations work on whole columns: clear the part above the diagonal
-        for (int e = tid; e < n * n; e += nthr) {
-            const int c = e / n, i = e - c * n;
-            if (i < c) W[(size_t)c * ld + i] = 0.0;
-        }
-        __syncthreads();
+        double m = 0.0;                           // every wave finds the largest diagonal entry for itself
+        for (int j = lane; j < n; j += 64) m = fmax(m, W[(size_t)j * ldc + j]);
+        chol_blocked<true>(W, ldc, n, rinv_sh, wave_max(m) * 1e-30, nullptr);
     }
-    if (gscr) {
-        eig_precondition<NE>(sm, sm + rsize, ld, n, ne, gscr, pre_sa);
-        W = sm + rsize;
+    const double tol2 = 1e-14, floor2 = 1e-28;
+    double amax = 0.0;
+    // keep the columns that have to rotate (rotf set), in slot order; returns their number
+    auto compact = [&](int m) {
+        int myc = -1, f = 0;
+        __syncthreads();
+        if (tid < m) { myc = colmap[tid]; f = rotf[myc]; }
+        const unsigned long long bal = __ballot(f);
+        if (lane == 0 && wave < 2) wcnt[wave] = __popcll(bal);
+        __syncthreads();
+        const int total = wcnt[0] + wcnt[1];
+        if (f) {
+            colmap[__popcll(bal & ((1ull << lane) - 1ull)) + (wave == 1 ? wcnt[0] : 0)] = myc;
+            rotf[myc] = 0;
+        }
+        if (tid == 0) {
+            if (total & 1) colmap[total] = ne;
+            nact_sh = total + (total & 1);
+        }
+        __syncthreads();
+        return total;
+    };
+    bool checked = false;
+    if constexpr (NE == 5 || NE == 6) {
+        if (gscr) {
+            W = sm + rsize;
+            checked = eig_precondition<NE>(sm, W, ld, ldc, n, ne, gscr, pre_sa);
+        }
+    }
+    if (checked) {
+        // The preconditioned columns are (nearly) orthogonal: which of them still have to rotate is decided on their
+        // Gram matrix, all pairs at once on the matrix cores, instead of in a sweep (n = 80: 32 us) that
+        // would leave nearly all of them alone.
+        const double* C = sm;
+        for (int c = tid >> 3; c < n; c += nthr >> 3) {
+            double s = 0.0;
+            for (int i = tid & 7; i < n; i += 8) s += C[(size_t)c * ldc + i] * C[(size_t)c * ldc + i];
+            s = group8_sum(s);
+            if ((tid & 7) == 0) nrm[c] = s;
+        }
+        __syncthreads();
+        for (int j = lane; j < n; j += 64) amax = fmax(amax, nrm[j]);
+        amax = wave_max(amax);
+        const int T16 = (n + 15) / 16;
+        for (int tile = wave; tile < T16 * (T16 + 1) / 2; tile += nthr >> 6) {
+            int ti = 0, tj = tile;
+            while (tj > ti) { tj -= ti + 1; ++ti; }
+            const int ci = 16 * ti + (lane & 15), cj = 16 * tj + (lane & 15), kq = lane >> 4;
+            const double4_t acc = tile_mma(n, ci, cj, kq, [&](int i, int k) { return C[(size_t)i * ldc + k]; },
+                                           [&](int k, int c) { return C[(size_t)c * ldc + k]; }, 0, n);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = 16 * ti + 4 * v + kq;
+                if (i < n && cj < n && i != cj) {
+                    const double a = nrm[i], b = nrm[cj];
+                    if (acc[v] * acc[v] > tol2 * a * b + floor2 * amax * (a + b)) { rotf[i] = 1; rotf[cj] = 1; }
+                }
+            }
+        }
+        compact(ne);
     }
 
     // Rotate while gamma^2 > tol^2 alpha beta + (c eps)^2 amax (alpha + beta), tol = 1e-7: the
@@ -846,8 +955,6 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk, int use_pre) {
     // the rounding floor of a dot product of two columns that each carry an absolute error of
     // ~eps * lambda_max (the columns are lambda_j v_j, formed from O(lambda_max) entries): below it
     // a rotation only reshuffles noise and the sweeps would never end.
-    const double tol2 = 1e-14, floor2 = 1e-28;
-    double amax = 0.0;
     double X[NE], Y[NE];
     double nX = 0.0, nY = 0.0;
 
@@ -902,6 +1009,7 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk, int use_pre) {
 
     for (int sweep = 0; sweep < 40; ++sweep) {
         const int m = nact_sh, gs = m / 2;           // even number of slots, groups this sweep
+        if (m == 0) break;
         const bool act = grp < gs, inner = grp < gs - 1;
         int idX = ne, idY = ne;
         if (act) {
@@ -923,16 +1031,11 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk, int use_pre) {
         // a full sweep reverses the slot order: the columns this group ends up with
         const int endX = act ? colmap[m - 1 - 2 * grp] : ne, endY = act ? colmap[m - 2 - 2 * grp] : ne;
         __syncthreads();                          // every column is in registers before the first mailbox write
-        if (sweep == 0) {
+        if (sweep == 0 && !checked) {
             if (act && gl == 0) { nrm[idX] = nX; nrm[idY] = nY; }
             __syncthreads();
-            if (tid == 0) {
-                double mx = 0.0;
-                for (int j = 0; j < ne; ++j) mx = fmax(mx, nrm[j]);
-                amax_sh = mx;
-            }
-            __syncthreads();
-            amax = amax_sh;
+            for (int j = lane; j < ne; j += 64) amax = fmax(amax, nrm[j]);
+            amax = wave_max(amax);
         }
         for (int s2 = 0; s2 < gs; ++s2) {
             // even step: slots (2g, 2g+1) are (X, Y); afterwards Y moves down to group g-1
@@ -972,25 +1075,7 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk, int use_pre) {
                 if (__double2hiint(nY) < 0) rotf[endY] = 1;
             }
         }
-        // keep the columns that rotated, in slot order
-        int myc = -1, f = 0;
-        __syncthreads();
-        if (tid < m) { myc = colmap[tid]; f = rotf[myc]; }
-        const unsigned long long bal = __ballot(f);
-        const int wv = tid >> 6, ln = tid & 63;
-        if (ln == 0 && wv < 2) wcnt[wv] = __popcll(bal);
-        __syncthreads();
-        const int total = wcnt[0] + wcnt[1];
-        if (f) {
-            colmap[__popcll(bal & ((1ull << ln) - 1ull)) + (wv == 1 ? wcnt[0] : 0)] = myc;
-            rotf[myc] = 0;
-        }
-        if (tid == 0) {
-            if (total & 1) colmap[total] = ne;
-            nact_sh = total + (total & 1);
-        }
-        __syncthreads();
-        if (total == 0) break;
+        if (compact(m) == 0) break;               // keep the columns that rotated
     }
     // column norms = singular values of L = square roots of the eigenvalues
     for (int pp = grp; pp < ne; pp += nthr / JGL) {
@@ -1007,13 +1092,29 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk, int use_pre) {
         order[r] = tid;
     }
     __syncthreads();
-    for (int e = tid; e < n * n; e += nthr) {
-        int i = e / n, j = e - i * n;
-        int pp = order[j];
-        double l = nrm[pp];
-        double v = l > 0.0 ? W[(size_t)pp * ld + i] / l : (i == j ? 1.0 : 0.0);
-        if (vec) vec[e] = v;
-        if (tmat && j < kk) tmat[(size_t)i * kk + j] = l > 0.0 ? v / l : 0.0;
+    {
+        // a thread's columns stay the same for all its rows
+        constexpr int NJ = (NE * JGL + 15) / 16;
+        int pp[NJ];
+        double rl[NJ];
+        bool zero[NJ];
+#pragma unroll
+        for (int q = 0; q < NJ; ++q) {
+            const int j = min((tid & 15) + 16 * q, n - 1);
+            pp[q] = order[j];
+            const double l = nrm[pp[q]];
+            zero[q] = !(l > 0.0);
+            rl[q] = zero[q] ? 0.0 : rcp_nr2(l);
+        }
+        for (int i = tid >> 4; i < n; i += nthr >> 4)
+#pragma unroll
+            for (int q = 0; q < NJ; ++q) {
+                const int j = (tid & 15) + 16 * q;
+                if (j >= n) continue;
+                const double v = zero[q] ? (i == j ? 1.0 : 0.0) : W[(size_t)pp[q] * ld + i] * rl[q];
+                if (vec) vec[(size_t)i * n + j] = v;
+                if (tmat && j < kk) tmat[(size_t)i * kk + j] = v * rl[q];
+            }
     }
     if (tid < n) {
         double l = nrm[order[tid]];              // sigma_j = sqrt(lambda_j)
@@ -1031,7 +1132,7 @@ int launch_chol_inv_batch(hipStream_t s, const CholProblem* probs, int count, in
         const int nb = count - b0 < SM_MAX_BATCH ? count - b0 : SM_MAX_BATCH;
         CholBatch batch;
         for (int i = 0; i < SM_MAX_BATCH; ++i) batch.p[i] = probs[b0 + (i < nb ? i : 0)];
-        hipLaunchKernelGGL(k_chol_inv, dim3(nb), dim3(1024), lds, s, batch, n);
+        hipLaunchKernelGGL(k_chol_inv, dim3(nb), dim3(CI_THREADS), lds, s, batch, n);
         METIS_LAUNCH_CHECK();
     }
     return METIS_OK;
@@ -1043,8 +1144,8 @@ int launch_jacobi_eig_batch(hipStream_t s, const JacobiProblem* probs, int count
     const int ne = n + (n & 1), ld = jacobi_ld(n, jgl);
     const size_t rsize = (size_t)(ne + 1) * ld;
     const size_t small = ((size_t)ne / 2 + ne + 1) * sizeof(double) + (size_t)(3 * ne + 4) * sizeof(int) + 16;
-    // the preconditioner needs two matrix-sized regions and 10 n + 40 doubles; it pays from n ~ 72 on (about 250 us
-    // against 7 of 9 sweeps of 46 us at n = 80; at n = 64 the plain sweeps win), and its second region fits in
+    // the preconditioner needs two matrix-sized regions and 10 n + 40 doubles; it pays from n ~ 72 on (about 170 us
+    // against 8 of 9 sweeps of 46 us at n = 80; at n = 64 the plain sweeps, 120 to 170 us, are no slower), and its second region fits in
     // the 160 KB of LDS up to n = 88.  It runs when every problem of the batch brings scratch.
     size_t lds = rsize * sizeof(double) + small;
     const size_t lds_pre = 2 * rsize * sizeof(double) + small + (10 * (size_t)n + 44) * sizeof(double);
@@ -1055,7 +1156,7 @@ int launch_jacobi_eig_batch(hipStream_t s, const JacobiProblem* probs, int count
     // one group of jgl lanes per column pair, in whole waves and at least 512 threads (the Cholesky pre-pass, the
     // bookkeeping and the preconditioner's 8 lanes per row use them); no idle waves beyond that: every wave of
     // the workgroup takes part in every barrier
-    const int need = (ne / 2 * jgl + 63) / 64 * 64;
+    const int need = (ne / 2 * jgl + 63) / 64 * 64;               // at most 128 ceil(n / 16): the kernel's launch bound
     const int threads = need > 512 ? need : 512;
     if (ne / 2 * jgl > threads) return METIS_UNSUPPORTED;
     for (int b0 = 0; b0 < count; b0 += SM_MAX_BATCH) {

@@ -1,0 +1,37 @@
+"""The small factorizations at the orders where their tiles end: Cholesky panels of 16 columns (one below, at, and one
+above a multiple), the eigenvector preconditioner's range of 72 to 88, its neighbours, and the largest orders; repeated and
+vanishing singular values (the preconditioner's fallback).  Bars of tests/test_gpu_decompose.py."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import decompose as odec
+from test_gpu_decompose import _compare, _planted_bf16, _run, metis  # noqa: F401  (metis is a fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("k,p", [(1, 1), (8, 7), (16, 1), (17, 14), (31, 2), (48, 16), (49, 16), (63, 8), (64, 8), (65, 8),
+                                 (64, 15), (65, 15), (65, 16), (72, 15), (80, 8), (81, 8), (90, 5), (95, 1)])
+def test_orders_at_the_edges_of_tiles(metis, k, p):  # noqa: F811
+    M, N = 512, 256
+    s = 50.0 * np.arange(1, N + 1) ** -1.1 + 0.02
+    A = _planted_bf16(M, N, s, seed=k + 7 * p)
+    got = _run(metis, A, k, p, 0.5, seed=5)
+    _compare(A, got, odec.decompose(A.double().numpy(), k, p, 0.5, seed=5), k)
+
+
+@pytest.mark.parametrize("k,p", [(20, 12), (60, 20), (72, 16)])
+def test_repeated_singular_values(metis, k, p):  # noqa: F811
+    # pairs of equal singular values down to the last kept one: the subspaces are determined up to the pair, so compare
+    # the singular values and the projector
+    M, N = 512, 256
+    s = 20.0 * 0.9 ** (np.arange(N) // 2)
+    s[k + p - 2:] *= 0.01
+    A = _planted_bf16(M, N, s, seed=3)
+    U, S, V, _ = _run(metis, A, k, p, 1.0, seed=8)
+    Ur, Sr, Vr = odec.decompose(A.double().numpy(), k, p, 1.0, seed=8)
+    assert np.max(np.abs(S - Sr) / Sr) < 1e-3
+    assert np.abs(V.T @ V - np.eye(k)).max() < 1e-4
+    An = A.double().numpy()
+    assert np.linalg.norm((U * S) @ V.T - (Ur * Sr) @ Vr.T) / np.linalg.norm(An) < 1e-3
