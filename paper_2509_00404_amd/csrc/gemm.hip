@@ -767,33 +767,45 @@ int launch_gemm_tile(hipStream_t s, const Fp4Operand& a, const Fp4Operand& b, in
     return METIS_OK;
 }
 
-// Contraction parts of an output that the small tiles serve (M or N below 1024).  Few tiles leave most CUs idle while each
-// tile walks its whole contraction at ~1.1 us per 128-deep stage (latency; 0.55 us per workgroup once a CU holds several);
-// cutting it costs the parts' fp32 tiles (8 bytes of traffic per element and part at ~4 TB/s) and a launch, ~3.5 us.
-// The cut with the least sum is taken.  Whole call at rank 64: 256 x 4096 x 4096 56 -> 39 us, 256 x 4096 x 14336 153 -> 66 us,
-// 512 x 4096 x 4096 58 -> 48 us, 512 x 1024 x 4096 55 -> 35 us, 1000 x 4096 x 4096 (not cut) 63 -> 59 us.
-int small_split(int64_t M, int64_t N, int64_t niter) {
+// How an output of at most 256 tiles of the bounds-checked kernel is produced, by estimates (in us) that were fitted to
+// measurements at rank 64:
+//   - small tiles (128 x 128 for large sides): a 128-deep stage takes 1.4 us (expansion bound, 1.15 per workgroup once a CU holds
+//     several), the rest 8.  Few tiles leave most CUs idle while each walks its whole contraction: the contraction is cut into parts
+//     where that costs less than it saves, a launch of 3.5 and 6 bytes of traffic per element and part at ~4 TB/s;
+//   - both sides at least 1024: the pipelined kernel's 256 x 256 tiles, 3.3 per stage of a tile cut into `pipe_parts`, the rest 13,
+//     a launch of 3 and the sum of its parts.
+// 4096 x 1024: K = 1024 43 -> 20 (small tiles, whole), K = 4096 59 -> 52, K = 14336 stays pipelined (119; small tiles 157);
+// 1024 x 1024: K = 4096 45 -> 31, K = 14336 89 -> 53 (4 parts); 1360 x 1232 x 768 35 -> 13.  Whole calls with one side below 1024:
+// 256 x 4096 x 4096 56 -> 39, 256 x 4096 x 14336 153 -> 66, 512 x 4096 x 4096 58 -> 48, 512 x 1024 x 4096 55 -> 35.
+struct SmallPlan {
+    bool small;              // small tiles (otherwise: too many of them, or the pipelined kernel with its own cut is faster)
+    int parts;               // their contraction parts
+};
+SmallPlan small_plan(int64_t M, int64_t N, int64_t niter, int pipe_parts) {
+    SmallPlan best = {false, 1};
     const int64_t bm = M <= 64 ? 64 : 128, bn = N <= 64 && M > 64 ? 64 : 128;
     const int64_t tiles = ceil_div64(M, bm) * ceil_div64(N, bn);
-    if (tiles > 256) return 1;
-    int best = 1;
-    double best_t = 1e30;
+    if (tiles > 256) return best;
+    const double mn = (double)M * (double)N;
+    double best_t = pipe_parts > 0 ? 16.0 + 3.3 * (double)ceil_div64(niter, pipe_parts) + pipe_parts * mn * 1e-6 : 1e30;
     for (int p = 1; p <= 16 && (p == 1 || 2 * p <= niter); ++p) {
         const int64_t ips = ceil_div64(niter, p);
         if (ceil_div64(niter, ips) != p) continue;                       // no empty part
         const double per_cu = (double)ceil_div64(tiles * p, 256);
-        const double t = (double)ips * (per_cu > 1.7 ? 0.55 * per_cu : 1.1) +
-                         (p > 1 ? 3.5 + (double)p * (double)M * (double)N * 2e-6 : 0.0);
-        if (t < best_t - 1e-9) { best_t = t; best = p; }
+        const double t = 8.0 + (double)ips * (per_cu > 1.5 ? 1.15 * per_cu : 1.4) + (p > 1 ? 3.5 + p * mn * 1.5e-6 : 0.0);
+        if (t < best_t - 1e-9) {
+            best_t = t;
+            best = {true, p};
+        }
     }
     return best;
 }
 
-// bytes of the parts of a small output (0: not cut)
-size_t small_split_bytes(int64_t M, int64_t N, int64_t K) {
-    if (M >= 1024 && N >= 1024) return 0;
-    const int p = small_split(M, N, ceil_div64(K, G_KI));
-    return p > 1 ? (size_t)p * M * N * sizeof(float) : 0;
+// The plan of an M x N output over `niter` stages; whole: every stage is a whole one
+SmallPlan gemm_plan(int64_t M, int64_t N, int64_t niter, bool whole) {
+    int pipe_parts = 0;
+    if (M >= 1024 && N >= 1024 && whole && gemm_tail_bytes(M, N, niter * G_KI, &pipe_parts) == 0) pipe_parts = 0;
+    return small_plan(M, N, niter, pipe_parts);
 }
 
 template <int TM, int TN, int WMW, int WNW, typename OUT>
@@ -836,6 +848,13 @@ int launch_gemm(hipStream_t s, const metis_fp4& A, const metis_fp4& B, const bf1
         const size_t tail_need = gemm_tail_bytes(M, N, K);
         const bool can_split = tail_need > 0 && partial && partial_bytes >= tail_need;
         const int64_t tiles = ceil_div64(M, 256) * ceil_div64(N, 256);
+        const SmallPlan plan = gemm_plan(M, N, niter, whole);
+        const bool room = partial && partial_bytes >= (size_t)plan.parts * M * N * sizeof(float);
+        // few tiles: small ones, whole or in parts (without the room for those the call works too, on the kernels below)
+        if (whole && plan.small && (plan.parts == 1 || room)) {
+            if (plan.parts == 1) return launch_gemm_tile<2, 2, 2, 2, OUT>(s, a, b, K, niter, Aext, Bext, Ke, alpha, C, ldc);
+            return launch_gemm_parts<2, 2, 2, 2, OUT>(s, a, b, K, niter, plan.parts, Aext, Bext, Ke, alpha, C, ldc, partial);
+        }
         if (whole && (can_split || tiles > 128))
             return launch_gemm_pipe<OUT>(s, a, b, K, Aext, Bext, Ke, alpha, C, ldc, partial, partial_bytes);
         // an output of at most 128 tiles of 256 x 256 would leave half the CUs without work: 128 x 128 tiles
@@ -844,7 +863,7 @@ int launch_gemm(hipStream_t s, const metis_fp4& A, const metis_fp4& B, const bf1
         // a partial stage that could not become extra columns (no workspace): 8 waves of 128x64, bounds-checked staging
         return launch_gemm_tile<4, 2, 2, 4, OUT>(s, a, b, K, niter, Aext, Bext, Ke, alpha, C, ldc);
     }
-    const int parts = small_split(M, N, niter);
+    const int parts = gemm_plan(M, N, niter, false).parts;
     if (parts > 1 && partial && partial_bytes >= (size_t)parts * M * N * sizeof(float)) {
         if (N > 64 && M > 64)
             return launch_gemm_parts<2, 2, 2, 2, OUT>(s, a, b, K, niter, parts, Aext, Bext, Ke, alpha, C, ldc, partial);
@@ -1416,10 +1435,14 @@ LinWs lin_layout(int64_t Ma, int64_t Nb, int ka, int kb, int64_t Kc) {
     w.off_e2 = take((size_t)w.s2 * Nb * (ka > 0 ? ka : 1) * 4);
     w.off_aext = take((size_t)((Ma + 31) / 32 * 32) * (w.Kep + w.Kt > 0 ? w.Kep + w.Kt : 16) * 2);       // rows padded to whole 32-row blocks
     w.off_bext = take((size_t)((Nb + 31) / 32 * 32) * (w.Kep + w.Kt > 0 ? w.Kep + w.Kt : 16) * 2);
-    w.tail_bytes = (Ma >= 1024 && Nb >= 1024 && (Kc % G_KI == 0 || w.Kt > 0)) ? gemm_tail_bytes(Ma, Nb, Kc) : 0;
     w.decode = decode_shape(Ma, ka);
+    const bool large = Ma >= 1024 && Nb >= 1024, whole = Kc % G_KI == 0 || w.Kt > 0;
+    const int64_t niter = w.Kt > 0 ? Kc / G_KI : ceil_div64(Kc, G_KI);
+    const SmallPlan plan = gemm_plan(Ma, Nb, niter, whole);
+    const size_t parts_bytes = plan.parts > 1 ? (size_t)plan.parts * Ma * Nb * sizeof(float) : 0;
     if (w.decode) w.tail_bytes = decode_plan(Ma, Nb, kb, Kc).bytes;
-    else if (w.tail_bytes == 0) w.tail_bytes = small_split_bytes(Ma, Nb, Kc);
+    else if (large) w.tail_bytes = !whole ? 0 : plan.small ? parts_bytes : gemm_tail_bytes(Ma, Nb, Kc);
+    else w.tail_bytes = parts_bytes;
     w.off_tail = take(w.tail_bytes);
     w.total = o;
     return w;

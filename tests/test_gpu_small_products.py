@@ -65,6 +65,25 @@ def test_cut_contraction(metis, L, N, K, kx, kw, out_dtype):  # noqa: F811
     assert (abs(y - ref) <= bound).all()
 
 
+@pytest.mark.parametrize("L,N,K,kx,kw", [
+    (2320, 2064, 1280, 16, 24),     # pipelined kernel, its 90 tiles in two parts each, ragged edges
+    (2320, 2064, 1296, 0, 24),      # the same with extra columns for the last 16 elements
+    (2048, 2048, 1024, 8, 8),       # 256 small tiles, whole
+    (1104, 1040, 2192, 16, 20),     # small tiles in parts, extra columns
+    (1024, 3600, 1152, 0, 0)])      # 70 large tiles, 232 small ones
+@pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
+def test_large_sides_few_tiles(metis, L, N, K, kx, kw, out_dtype):  # noqa: F811
+    xs, ws, ref, bound = _product(metis, L, N, K, kx, kw, out_dtype, seed=9)
+    nbytes = metis.linear_workspace_bytes(L, N, K, max(kx, kw))
+    for size in ((nbytes,) if kx + kw else (0, nbytes)):
+        Y = torch.full((L, N + 16), float("nan"), dtype=out_dtype, device="cuda")
+        metis.fp4_linear_fwd(xs, ws, Y[:, :N], torch.empty((size,), dtype=torch.uint8, device="cuda") if size else None)
+        assert torch.isnan(Y[:, N:]).all()
+        y = Y[:, :N].double().cpu().numpy()
+        assert rel_fro(y, ref) < (GEMM_RTOL if out_dtype == torch.bfloat16 else 5e-3)
+        assert (abs(y - ref) <= bound).all()
+
+
 @pytest.mark.parametrize("L", [16, 100, 200])
 def test_unsplit_without_workspace(metis, L):  # noqa: F811
     xs, ws, ref, bound = _product(metis, L, 528, 4096, 0, 0, torch.float32)
