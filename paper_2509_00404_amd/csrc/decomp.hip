@@ -55,7 +55,7 @@ Layout make_layout(int64_t M, int64_t N, int k, int p, int64_t Ms) {
         const size_t bp = std::max(project_parts(Ms, N), dgemm_parts<EPI_PART_F64>(L.r, N, Ms, split_for(Ms, ceil_div64(L.r, 32) * ceil_div64(N, 32))));
         const size_t g1p = dgemm_parts<EPI_PART_F64>(L.r, L.r, Ms, split_for(Ms, tiles_rr));
         const size_t g2p = dgemm_parts<EPI_PART_F64>(L.r, L.r, N, split_for(N, tiles_rr));
-        const size_t g3p = std::max((int)ceil_div64(M, GR_ROWS), dgemm_parts<EPI_PART_F64>(k, k, M, split_for(M, tiles_kk)));
+        const size_t g3p = std::max((int)gram_blocks(M), dgemm_parts<EPI_PART_F64>(k, k, M, split_for(M, tiles_kk)));
         size_t need = zp * (size_t)Ms * r;
         need = std::max(need, bp * r * (size_t)N);
         need = std::max(need, std::max(g1p, g2p) * r * r);
@@ -463,7 +463,7 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
         if (j.gram_fast) {
             // sums the broadcast's partial products into C (part 0) on the way
             if ((st = launch_gram_parts(s, j.C, k, j.M, j.cparts, cstride, j.C, j.parts)) != METIS_OK) return st;
-            sums.add(j.parts, (int)ceil_div64(j.M, GR_ROWS), (int64_t)k * k, (int64_t)k * k, j.G3);
+            sums.add(j.parts, (int)gram_blocks(j.M), (int64_t)k * k, (int64_t)k * k, j.G3);
         } else {
             const int want = split_for(j.M, tiles_kk);
             launch_dgemm<float, float, EPI_PART_F64>(s, op_parts(j.C, 1, k, j.cparts, cstride), op_parts(j.C, 1, k, j.cparts, cstride),

@@ -336,23 +336,26 @@ static inline int launch_project(hipStream_t s, const double* H, const double* H
 // ---------------------------------------------------------------------------------------
 // Gram matrix of a tall skinny matrix given as a sum of partial arrays (the broadcast's per-split
 // partial products):  S = sum_p C_p  (M x r, fp32),  G_b = S_b^T S_b  (r x r, fp64) for the rows S_b of workgroup b:
-// G holds ceil(M / GR_ROWS) partial Gram matrices, added in a fixed order afterwards (k_sum_parts_batch).
+// G holds gram_blocks(M) partial Gram matrices, added in a fixed order afterwards (k_sum_parts_batch).
 // The summed matrix is written back as fp32 (sum_out, may alias part 0) for the later U = S T.
 //   r % 4 == 0, C 16-byte aligned.
-// grid (ceil(M / GR_ROWS)), block 256; wave w owns row tiles w, w+4 of G and all NT column tiles.
+// grid gram_blocks(M), block 256; wave w owns row tiles w, w+4 of G and all NT column tiles.
 // ---------------------------------------------------------------------------------------
-#define GR_ROWS 64                    // rows of C per workgroup
 #define GR_KS 32                      // rows per stage
+// Rows of C per workgroup: one stage while that leaves at most 256 partial matrices (bound by the latency of the parts'
+// loads), two beyond, where the partial matrices' own traffic counts (k = 64: 32 KB each).  4096 rows: 11.5 -> 7.2 us against two.
+static inline int gram_rows(int64_t M) { return M <= 256 * GR_KS ? GR_KS : 2 * GR_KS; }
+static inline int64_t gram_blocks(int64_t M) { return ceil_div64(M, gram_rows(M)); }
 template <int NT>
 __global__ void __launch_bounds__(256)
-k_gram_parts(const float* C, int r, int64_t M, int nparts, int64_t part_stride, float* sum_out,
+k_gram_parts(const float* C, int r, int64_t M, int rows, int nparts, int64_t part_stride, float* sum_out,
              double* __restrict__ G) {
     constexpr int LDC = NT * 16 + ((NT * 16) % 32 == 16 ? 0 : 16);      // doubles, = 16 (mod 32)
     constexpr int PIECES = (GR_KS * NT * 4 + 255) / 256;                // float4 pieces per thread and stage
     constexpr int RT = (NT + 3) / 4;                                     // row tiles per wave
     __shared__ double Cs[GR_KS * LDC];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t m0 = (int64_t)blockIdx.x * GR_ROWS;
+    const int64_t m0 = (int64_t)blockIdx.x * rows;
     const int rc = r >> 2;
     for (int e = tid; e < GR_KS * LDC; e += 256) Cs[e] = 0.0;           // pad columns r .. 16 NT stay zero
     double4_t acc[RT][NT];
@@ -361,7 +364,7 @@ k_gram_parts(const float* C, int r, int64_t M, int nparts, int64_t part_stride, 
 #pragma unroll
         for (int j = 0; j < NT; ++j) acc[i][j] = (double4_t){0.0, 0.0, 0.0, 0.0};
     __syncthreads();
-    for (int64_t mt = m0; mt < m0 + GR_ROWS && mt < M; mt += GR_KS) {
+    for (int64_t mt = m0; mt < m0 + rows && mt < M; mt += GR_KS) {
 #pragma unroll
         for (int i = 0; i < PIECES; ++i) {
             const int c = tid + 256 * i, row = c / rc, col = 4 * (c - row * rc);
@@ -371,12 +374,12 @@ k_gram_parts(const float* C, int r, int64_t M, int nparts, int64_t part_stride, 
                 if (m < M) {
                     const float* src = C + m * r + col;
                     int p = 0;
-                    for (; p + 4 <= nparts; p += 4) {          // four loads in flight
-                        float4 v[4];
+                    for (; p + 8 <= nparts; p += 8) {          // eight loads in flight
+                        float4 v[8];
 #pragma unroll
-                        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const float4*>(src + (p + u) * part_stride);
+                        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(src + (p + u) * part_stride);
 #pragma unroll
-                        for (int u = 0; u < 4; ++u) {
+                        for (int u = 0; u < 8; ++u) {
                             s0 += (double)v[u].x;
                             s1 += (double)v[u].y;
                             s2 += (double)v[u].z;
@@ -436,8 +439,8 @@ k_gram_parts(const float* C, int r, int64_t M, int nparts, int64_t part_stride, 
 
 static inline int launch_gram_parts(hipStream_t s, const float* C, int r, int64_t M, int nparts, int64_t part_stride,
                                     float* sum_out, double* G) {
-    dim3 grid((unsigned)ceil_div64(M, GR_ROWS));
-#define GRAM_CASE(NT) hipLaunchKernelGGL(k_gram_parts<NT>, grid, dim3(256), 0, s, C, r, M, nparts, part_stride, sum_out, G);
+    dim3 grid((unsigned)gram_blocks(M));
+#define GRAM_CASE(NT) hipLaunchKernelGGL(k_gram_parts<NT>, grid, dim3(256), 0, s, C, r, M, gram_rows(M), nparts, part_stride, sum_out, G);
     switch ((r + 15) / 16) {
         case 1: GRAM_CASE(1) break;
         case 2: GRAM_CASE(2) break;
