@@ -195,21 +195,61 @@ k_quantize_both_bf16(const bf16_t* __restrict__ A, int64_t ld, int64_t M, int64_
     }
 }
 
-// The transposed quantization of the two fp32 factors of a split, U [M, k] -> Q(U^T) [k, M] and V [N, k] -> Q(V^T)
-// [k, N], and the copy of S, in one launch (three tiny launches otherwise): blocks [0, tiles of U) take U, the rest V.
+// The factors of a split in one launch, read once: the transposed quantization U [M, k] -> Q(U^T) [k, M] and V [N, k] ->
+// Q(V^T) [k, N], the copy of S, and (us_hi not null) the residual kernel's operands, -(U diag(S)) and V as bf16 hi / lo parts
+// with the rank padded to kp (a multiple of 16, at most 64 ceil(k / 64)).  Blocks [0, tiles of U) take U, the rest V.
 template <bool SR>
 __global__ void __launch_bounds__(256)
 k_quantize_factors_t(const float* __restrict__ U, int64_t M, const float* __restrict__ V, int64_t N, int k, QuantParams qu,
                      QuantParams qv, uint8_t* __restrict__ ut_codes, uint8_t* __restrict__ ut_scales,
                      uint8_t* __restrict__ vt_codes, uint8_t* __restrict__ vt_scales, uint64_t seed_u, uint64_t seed_v,
-                     const float* __restrict__ S_src, float* __restrict__ S_dst) {
+                     const float* __restrict__ S_src, float* __restrict__ S_dst, int kp, bf16_t* __restrict__ us_hi,
+                     bf16_t* __restrict__ us_lo, bf16_t* __restrict__ v_hi, bf16_t* __restrict__ v_lo) {
+    __shared__ float tile[64][65];
     const int64_t gx = (k + 63) / 64, tiles_u = gx * ((M + 63) / 64);
     const int64_t b = blockIdx.x;
-    if (b == 0 && S_src && (int)threadIdx.x < k) S_dst[threadIdx.x] = S_src[threadIdx.x];
+    const int tid = threadIdx.x;
+    if (b == 0 && S_dst && tid < k) S_dst[tid] = S_src[tid];
     const bool u = b < tiles_u;
-    const int64_t t = u ? b : b - tiles_u;
-    quantize_tile_body<float, SR>(u ? U : V, k, u ? M : N, k, u ? qu : qv, u ? qu : qv, nullptr, nullptr, u ? ut_codes : vt_codes,
-                                  u ? ut_scales : vt_scales, u ? seed_u : seed_v, t % gx, t / gx);
+    const int64_t t = u ? b : b - tiles_u, rows = u ? M : N;
+    const int64_t m0 = t / gx * 64;
+    const int c0 = (int)(t % gx) * 64, c = c0 + (tid & 63);
+    const float* __restrict__ F = u ? U : V;
+    bf16_t* __restrict__ hi = u ? us_hi : v_hi;
+    bf16_t* __restrict__ lo = u ? us_lo : v_lo;
+    const float s = hi && u && c < k ? -S_src[c] : 1.0f;
+    float x[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int64_t m = m0 + (tid >> 6) + 4 * i;
+        x[i] = m < rows && c < k ? F[m * k + c] : 0.0f;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int r = (tid >> 6) + 4 * i;
+        tile[r][tid & 63] = x[i];
+        if (hi && m0 + r < rows && c < kp) {
+            const float y = x[i] * s;
+            const bf16_t h = f32_to_bf16_rne(y);
+            hi[(m0 + r) * kp + c] = h;
+            lo[(m0 + r) * kp + c] = f32_to_bf16_rne(y - bf16_to_f32(h));
+        }
+    }
+    __syncthreads();
+    const int line = tid >> 2, blk = tid & 3;      // 64 columns x 4 blocks of 16 rows
+    const int64_t m = m0 + blk * 16;
+    if (c0 + line < k && m < rows) {
+        float v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = tile[blk * 16 + i][line];
+        uint2 cd;
+        const int64_t n = c0 + line;
+        const QuantParams qp = u ? qu : qv;
+        const uint32_t sc = SR ? quantize_block16_sr(v, qp, cd, u ? seed_u : seed_v, SR_STREAM_T, (uint64_t)(n * rows + m))
+                               : quantize_block16(v, qp, cd);
+        *reinterpret_cast<uint2*>((u ? ut_codes : vt_codes) + n * (rows / 2) + m / 2) = cd;
+        (u ? ut_scales : vt_scales)[n * (rows / 16) + m / 16] = (uint8_t)sc;
+    }
 }
 
 static bool pow2(float g) {
@@ -306,19 +346,18 @@ extern "C" int metis_quantize_rht_sr(void* stream, const metis_mat* A, uint64_t 
     return METIS_OK;
 }
 
-// Q(U^T), Q(V^T) and S of a split in one launch (see k_quantize_factors_t); M % 16 == 0, N % 16 == 0, S_src null for no copy
+// Q(U^T), Q(V^T), S and (us_hi not null) the bf16 operands of a split in one launch (see k_quantize_factors_t);
+// M % 16 == 0, N % 16 == 0, S_dst null for no copy
 int launch_quantize_factors_t(hipStream_t s, const float* U, int64_t M, const float* V, int64_t N, int k, const metis_fp4& Ut,
-                              const metis_fp4& Vt, bool sr, uint64_t seed_u, uint64_t seed_v, const float* S_src, float* S_dst) {
+                              const metis_fp4& Vt, bool sr, uint64_t seed_u, uint64_t seed_v, const float* S_src, float* S_dst,
+                              int kp, bf16_t* us_hi, bf16_t* us_lo, bf16_t* v_hi, bf16_t* v_lo) {
     if (!pow2(Ut.tscale) || !pow2(Vt.tscale) || k < 1 || k > 256) return METIS_INVALID_ARG;
     const int64_t gx = (k + 63) / 64, blocks = gx * (ceil_div64(M, 64) + ceil_div64(N, 64));
     if (blocks > 0x7FFFFFFF) return METIS_UNSUPPORTED;
     const QuantParams qu = make_quant_params(Ut.tscale), qv = make_quant_params(Vt.tscale);
-    if (sr)
-        hipLaunchKernelGGL(k_quantize_factors_t<true>, dim3((unsigned)blocks), dim3(256), 0, s, U, M, V, N, k, qu, qv, Ut.codes,
-                           Ut.scales, Vt.codes, Vt.scales, seed_u, seed_v, S_src, S_dst);
-    else
-        hipLaunchKernelGGL(k_quantize_factors_t<false>, dim3((unsigned)blocks), dim3(256), 0, s, U, M, V, N, k, qu, qv, Ut.codes,
-                           Ut.scales, Vt.codes, Vt.scales, seed_u, seed_v, S_src, S_dst);
+    auto kern = sr ? k_quantize_factors_t<true> : k_quantize_factors_t<false>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, s, U, M, V, N, k, qu, qv, Ut.codes, Ut.scales, Vt.codes,
+                       Vt.scales, seed_u, seed_v, S_src, S_dst, kp, us_hi, us_lo, v_hi, v_lo);
     METIS_LAUNCH_CHECK();
     return METIS_OK;
 }

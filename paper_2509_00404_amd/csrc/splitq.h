@@ -25,7 +25,10 @@ int launch_residual_quant(hipStream_t s, const bf16_t* A, int64_t lda, int64_t M
 int quantize_factors(hipStream_t s, const float* U, const float* S, const float* V, int64_t M, int64_t N, int k,
                      metis_split* out, bool sr, uint64_t seed);
 
-// quant.hip: the two transposed factor quantizations (and the copy of S when S_src is not null) in one launch.
+// quant.hip: the two transposed factor quantizations (and the copy of S when S_dst is not null; and, when us_hi is not null, the
+// bf16 hi / lo operands -(U S) [M, kp] and V [N, kp] of the residual kernel) in one launch.
 // U [M, k] and V [N, k] fp32 contiguous; Ut [k, M] and Vt [k, N] with M % 16 == 0 and N % 16 == 0
 int launch_quantize_factors_t(hipStream_t s, const float* U, int64_t M, const float* V, int64_t N, int k, const metis_fp4& Ut,
-                              const metis_fp4& Vt, bool sr, uint64_t seed_u, uint64_t seed_v, const float* S_src, float* S_dst);
+                              const metis_fp4& Vt, bool sr, uint64_t seed_u, uint64_t seed_v, const float* S_src, float* S_dst,
+                              int kp = 0, bf16_t* us_hi = nullptr, bf16_t* us_lo = nullptr, bf16_t* v_hi = nullptr,
+                              bf16_t* v_lo = nullptr);

@@ -18,31 +18,17 @@ union Frag {
     bf16x8_t v;
 };
 
-// -(U diag(S)) and V as bf16 hi/lo, row-major with the rank padded to kp (a multiple of 16)
-__global__ void k_split_factors(const float* __restrict__ U, const float* __restrict__ S, const float* __restrict__ V,
-                                int64_t M, int64_t N, int k, int kp, bf16_t* __restrict__ us_hi,
-                                bf16_t* __restrict__ us_lo, bf16_t* __restrict__ v_hi, bf16_t* __restrict__ v_lo,
-                                float* __restrict__ S_out) {
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < k && S_out) S_out[t] = S[t];
-    if (t >= (M + N) * kp) return;
-    int64_t row = t / kp;
-    int c = (int)(t - row * kp);
-    float x = 0.0f;
-    bf16_t *hi, *lo;
-    if (row < M) {
-        if (c < k) x = -(U[row * k + c] * S[c]);
-        hi = us_hi + row * kp + c;
-        lo = us_lo + row * kp + c;
-    } else {
-        row -= M;
-        if (c < k) x = V[row * k + c];
-        hi = v_hi + row * kp + c;
-        lo = v_lo + row * kp + c;
-    }
-    bf16_t h = f32_to_bf16_rne(x);
-    *hi = h;
-    *lo = f32_to_bf16_rne(x - bf16_to_f32(h));
+// V as bf16 hi/lo, row-major with the rank padded to kp (a multiple of 16)
+__global__ void k_split_v(const float* __restrict__ V, int64_t N, int k, int kp, bf16_t* __restrict__ v_hi,
+                          bf16_t* __restrict__ v_lo) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= N * kp) return;
+    const int64_t row = t / kp;
+    const int c = (int)(t - row * kp);
+    const float x = c < k ? V[row * k + c] : 0.0f;
+    const bf16_t h = f32_to_bf16_rne(x);
+    v_hi[t] = h;
+    v_lo[t] = f32_to_bf16_rne(x - bf16_to_f32(h));
 }
 
 // 16 bytes of codes (two neighbouring blocks) to an 8-byte aligned address in one store
@@ -402,9 +388,7 @@ k_band_factors(const float* __restrict__ parts, int nparts, int64_t part_stride,
 }  // namespace
 
 int launch_v_factors(hipStream_t s, const float* V, int64_t N, int k, int kp, bf16_t* v_hi, bf16_t* v_lo) {
-    hipLaunchKernelGGL(k_split_factors, dim3((unsigned)ceil_div64(N * kp, 256)), dim3(256), 0, s, (const float*)nullptr,
-                       (const float*)nullptr, V, (int64_t)0, N, k, kp, (bf16_t*)nullptr, (bf16_t*)nullptr, v_hi, v_lo,
-                       (float*)nullptr);
+    hipLaunchKernelGGL(k_split_v, dim3((unsigned)ceil_div64(N * kp, 256)), dim3(256), 0, s, V, N, k, kp, v_hi, v_lo);
     METIS_LAUNCH_CHECK();
     return METIS_OK;
 }
@@ -434,12 +418,15 @@ int check_split_out(int64_t M, int64_t N, int k, const metis_split* out) {
 int launch_residual_quant(hipStream_t s, const bf16_t* Ap, int64_t lda, int64_t M, int64_t N, int64_t Mt, int64_t row_off,
                           const bf16_t* us_hi, const bf16_t* us_lo, const bf16_t* v_hi, const bf16_t* v_lo, int kp, float g,
                           uint8_t* codes, uint8_t* scales, uint8_t* ct, uint8_t* st_, float* R_debug, bool sr, uint64_t seed) {
-    // two workgroups per CU at a time; every workgroup walks at least four 64-column steps; the number of column
-    // chunks that fills the last round of workgroups best
-    const int64_t row_blocks = ceil_div64(M, RQ_ROWS);
-    const int64_t want = balanced_split(row_blocks, ceil_div64(N, 4 * RQ_COLS), 512);
-    int64_t cchunk = ceil_div64(ceil_div64(N, want), RQ_COLS) * RQ_COLS;
-    if (cchunk < 4 * RQ_COLS) cchunk = 4 * RQ_COLS;
+    // Two workgroups per CU at a time, the number of column chunks that fills the last round of workgroups best.  Every workgroup
+    // walks at least four 64-column steps (whole output lines, and the factors' fragments loaded once for them) while that leaves
+    // one for each CU, fewer in small matrices: 1360 x 1232 at rank 20, both orientations, 15.8 -> 7.4 us, 1024 x 4096 at rank 64 16 -> 11.
+    const int64_t row_blocks = ceil_div64(M, RQ_ROWS), steps = ceil_div64(N, RQ_COLS);
+    int64_t run = 4;
+    while (run > 1 && row_blocks * ceil_div64(steps, run) < 256) run /= 2;
+    const int64_t want = balanced_split(row_blocks, ceil_div64(steps, run), 512);
+    int64_t cchunk = ceil_div64(steps, want) * RQ_COLS;
+    if (cchunk < run * RQ_COLS) cchunk = run * RQ_COLS;
     dim3 grid((unsigned)row_blocks, (unsigned)ceil_div64(N, cchunk));
     const QuantParams qp = make_quant_params(g);
     const bool want_t = ct != nullptr;
@@ -478,7 +465,7 @@ int quantize_factors(hipStream_t s, const float* U, const float* S, const float*
     // factors: Q(U^T) [k,M], Q(V^T) [k,N], blocks along the long axis; with stochastic rounding the two draw under
     // their own keys so that no two tensors share draws
     return launch_quantize_factors_t(s, U, M, V, N, k, out->Ut, out->Vt, sr, seed + 1, seed + 2,
-                                     S && out->S != S ? S : nullptr, out->S);
+                                     S, S && out->S != S ? out->S : nullptr);
 }
 
 template <bool SR>
@@ -506,18 +493,15 @@ static int split_quantize_impl(void* stream, const metis_mat* A, const float* U,
     bf16_t* us_lo = (bf16_t*)(ws + ub);
     bf16_t* v_hi = (bf16_t*)(ws + 2 * ub);
     bf16_t* v_lo = (bf16_t*)(ws + 2 * ub + vb);
-    int64_t tot = (M + N) * kp;
-    hipLaunchKernelGGL(k_split_factors, dim3((unsigned)ceil_div64(tot, 256)), dim3(256), 0, s, U, S, V, M, N, k, kp,
-                       us_hi, us_lo, v_hi, v_lo, out->S);
+    // the factors' quantization and the residual's operands from one read of them
+    const int fs = launch_quantize_factors_t(s, U, M, V, N, k, out->Ut, out->Vt, SR, seed + 1, seed + 2, S,
+                                             out->S != S ? out->S : nullptr, kp, us_hi, us_lo, v_hi, v_lo);
+    if (fs != METIS_OK) return fs;
     const bf16_t* Ap = (const bf16_t*)A->ptr;
     uint8_t* ct = want_t ? out->Rt.codes : nullptr;
     uint8_t* st_ = want_t ? out->Rt.scales : nullptr;
-    {
-        const int rs = launch_residual_quant(s, Ap, A->ld, M, N, M, 0, us_hi, us_lo, v_hi, v_lo, kp, out->R.tscale,
-                                             out->R.codes, out->R.scales, ct, st_, R_debug, SR, seed);
-        if (rs != METIS_OK) return rs;
-    }
-    return quantize_factors(s, U, nullptr, V, M, N, k, out, SR, seed);
+    return launch_residual_quant(s, Ap, A->ld, M, N, M, 0, us_hi, us_lo, v_hi, v_lo, kp, out->R.tscale, out->R.codes,
+                                 out->R.scales, ct, st_, R_debug, SR, seed);
 }
 
 extern "C" int metis_split_quantize(void* stream, const metis_mat* A, const float* U, const float* S, const float* V,
@@ -552,7 +536,7 @@ extern "C" int metis_split_quantize_static(void* stream, const metis_mat* A, con
         if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return METIS_HIP_ERROR;
         g_scratch_ptr[dev] = ptr;
     }
-    // every byte the kernels read is rewritten by k_split_factors first: nothing has to start at zero
+    // every byte the kernels read is rewritten by k_quantize_factors_t first: nothing has to start at zero
     return split_quantize_impl<false>(stream, A, U, S, V, k, 0, out, R_debug, g_scratch_ptr[dev], need);
 }
 
