@@ -123,16 +123,16 @@ __host__ __device__ __forceinline__ u32x4 philox4x32_10(u32x4 c, uint32_t k0, ui
 __device__ __forceinline__ void philox_4blocks(uint64_t seed, uint32_t stream, uint64_t blk, uint32_t (&w)[16]) {
     const uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u, W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;
     const uint32_t key0 = (uint32_t)seed, key1 = (uint32_t)(seed >> 32);
-    const uint64_t p1s = (uint64_t)M1 * stream;                               // round 1, third counter word
-    const uint32_t x1 = (uint32_t)(p1s >> 32) ^ (uint32_t)(blk >> 32) ^ key0;  // after round 1: counter word 0 ...
+    const uint64_t p1s = (uint64_t)M1 * stream;                               // first round, third counter word
+    const uint32_t x1 = (uint32_t)(p1s >> 32) ^ (uint32_t)(blk >> 32) ^ key0;  // after the first round: counter word 0 ...
     const uint32_t y1 = (uint32_t)p1s;                                        // ... and 1, the same for the four blocks
     const uint64_t p0r2 = (uint64_t)M0 * x1;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-        // round 1: M0 (blk + b), the low word of blk + b never carries
+        // first round: M0 (blk + b), the low word of blk + b never carries
         const uint64_t p0r1 = (uint64_t)M0 * ((uint32_t)blk + b);
         uint32_t z = (uint32_t)(p0r1 >> 32) ^ key1, q = (uint32_t)p0r1;
-        // round 2
+        // second round
         const uint64_t p1r2 = (uint64_t)M1 * z;
         uint32_t x = __builtin_amdgcn_bitop3_b32((uint32_t)(p1r2 >> 32), y1, key0 + W0, 0x96);
         uint32_t y = (uint32_t)p1r2;
