@@ -324,19 +324,30 @@ k_fp4_gemm_nt_parts(Fp4Operand A, Fp4Operand B, int64_t K, int64_t niter, int ip
                                                t / tiles_n, t % tiles_n, it0, it1);
 }
 
-// C = sum of the parts, in ascending order; a thread takes 4 columns (N % 16 == 0)
+// C = sum of the parts, in ascending order; a thread takes 4 consecutive elements.  They lie in one row, 16-byte aligned in every
+// part, when N % 4 == 0; an unsplit right operand may have any number of rows, and then each element finds its own row.
 template <typename OUT>
 __global__ void __launch_bounds__(256)
 k_sum_output_parts(const float* __restrict__ P, int parts, int64_t MN, int64_t N, OUT* __restrict__ C, int64_t ldc) {
     const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (e >= MN) return;
+    auto row_of = [&](int64_t x) { return (uint64_t)MN >> 32 ? x / N : (int64_t)((uint32_t)x / (uint32_t)N); };
+    if (N % 4 != 0) {                                    // (uniform)
+        for (int64_t x = e; x < e + 4 && x < MN; ++x) {
+            float acc = P[x];
+            for (int p = 1; p < parts; ++p) acc += P[(size_t)p * MN + x];
+            const int64_t r = row_of(x);
+            store_out<OUT>(C + r * ldc + (x - r * N), acc);
+        }
+        return;
+    }
     float4 acc = *reinterpret_cast<const float4*>(P + e);
 #pragma unroll 4
     for (int p = 1; p < parts; ++p) {
         const float4 x = *reinterpret_cast<const float4*>(P + (size_t)p * MN + e);
         acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
     }
-    const int64_t r = (uint64_t)MN >> 32 ? e / N : (int64_t)((uint32_t)e / (uint32_t)N);
+    const int64_t r = row_of(e);
     OUT* c = C + r * ldc + (e - r * N);
     store_out<OUT>(c, acc.x); store_out<OUT>(c + 1, acc.y); store_out<OUT>(c + 2, acc.z); store_out<OUT>(c + 3, acc.w);
 }
@@ -1102,9 +1113,11 @@ k_decode_finish(const float* __restrict__ P, int parts, int M, int64_t N, int64_
             o[i] = fmaf(a.w, bf16hi_to_f32(u.y), o[i]);
         }
     }
+    // (without factors the right operand may have any number of rows: the last group of a row can be a partial one)
     OUT* c = C + m * ldc + n;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) store_out<OUT>(c + i, o[i]);
+    for (int i = 0; i < 4; ++i)
+        if (n + i < N) store_out<OUT>(c + i, o[i]);
 }
 
 // few rows of an unsplit left operand

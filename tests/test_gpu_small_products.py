@@ -4,8 +4,9 @@ tiles, the 128-deep stages and the 32-column groups of the low-rank part."""
 import pytest
 import torch
 
-from gpu_helpers import elementwise_bound, make_split, operand_parts, rel_fro, split_to_oracle
+from gpu_helpers import elementwise_bound, fp4_to_oracle, make_split, operand_parts, rel_fro, split_to_oracle
 from oracle import linear as olin
+from oracle import quant as oq
 from test_gpu_linear import GEMM_RTOL, metis  # noqa: F401  (metis is a fixture)
 
 pytestmark = pytest.mark.gpu
@@ -93,3 +94,55 @@ def test_unsplit_without_workspace(metis, L):  # noqa: F811
         Y = torch.full((L, 528), float("nan"), dtype=torch.float32, device="cuda")
         metis.fp4_linear_fwd(xs, ws, Y, wsb)
         assert (abs(Y.double().cpu().numpy() - ref) <= bound).all()
+
+
+def _guarded(rows, cols, ld, dtype):
+    """[rows, cols] view with row stride ld into NaN-filled storage that goes on for 64 elements behind it."""
+    flat = torch.full((rows * ld + 64,), float("nan"), dtype=dtype, device="cuda")
+    return flat, flat[:rows * ld].view(rows, ld)[:, :cols]
+
+
+def _check_guarded(flat, view, ref, bound):
+    rows, cols = view.shape
+    ld = view.stride(0)
+    assert torch.isnan(flat[rows * ld:]).all()                                  # nothing behind the output
+    assert torch.isnan(flat[:rows * ld].view(rows, ld)[:, cols:]).all()         # nor in the caller's columns beside it
+    assert (abs(view.double().cpu().numpy() - ref) <= bound).all()
+
+
+# an unsplit right operand may have any number of rows: output widths that are no multiple of 4, contiguous (the next row
+# begins where one ends) and padded
+@pytest.mark.parametrize("L,N,K,kx", [
+    (1, 1, 272, 0), (3, 50, 16, 0), (16, 257, 4096, 0), (16, 1001, 1040, 0), (64, 258, 2064, 0), (33, 1003, 128, 0),     # few rows
+    (65, 50, 4096, 0), (100, 250, 4096, 0), (129, 257, 2064, 0), (256, 1001, 4096, 0), (1040, 1041, 4096, 0),     # contraction cut
+    (16, 257, 2048, 8), (208, 1002, 3008, 8), (1040, 1041, 2192, 16),                                              # split left operand
+    (80, 49, 96, 0), (1024, 1025, 256, 0)])                                                                        # uncut
+@pytest.mark.parametrize("pad", [0, 7])
+@pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
+def test_widths_of_any_size(metis, L, N, K, kx, pad, out_dtype):  # noqa: F811
+    xs, ws, ref, bound = _product(metis, L, N, K, kx, 0, out_dtype, seed=13)
+    wsb = torch.empty((max(metis.linear_workspace_bytes(L, N, K, kx), 256),), dtype=torch.uint8, device="cuda")
+    flat, Y = _guarded(L, N, N + pad, out_dtype)
+    metis.fp4_linear_fwd(xs, ws, Y, wsb)
+    _check_guarded(flat, Y, ref, bound)
+
+
+@pytest.mark.parametrize("L,N,K", [(2048, 33, 250), (4096, 257, 101), (2064, 1041, 1042)])
+@pytest.mark.parametrize("pad", [0, 7])
+def test_weight_gradient_of_any_size(metis, L, N, K, pad):  # noqa: F811
+    # dW[N, K] = G^T X of unsplit operands: only the contraction has to come in blocks of 16
+    from paper_2509_00404_amd import workloads
+    out_dtype = torch.float32
+    t = [workloads.gaussian(L, c, s) for c, s in ((N, 31), (K, 32))]
+    ops = []
+    for a in t:
+        sp = metis.SplitTensor(L, a.shape[1], 0, 1.0, 1.0, 2.0 ** -8, want_t=True)
+        metis.quantize(a.cuda(), None, sp.Rt)
+        ops.append(sp)
+    g, x = (oq.dequantize(*fp4_to_oracle(sp.Rt)) for sp in ops)
+    ref = g @ x.T
+    bound = elementwise_bound((g, None, None, None), (x, None, None, None), ref, out_dtype)
+    wsb = torch.empty((max(metis.linear_workspace_bytes(L, N, K, 0), 256),), dtype=torch.uint8, device="cuda")
+    flat, dW = _guarded(N, K, K + pad, out_dtype)
+    metis.fp4_linear_wgrad(ops[0], ops[1], dW, wsb)
+    _check_guarded(flat, dW, ref, bound)
