@@ -298,7 +298,7 @@ int metis_split_from_parts_sr(void* stream, const metis_mat* W_R, const float* U
 
 /* ---- FP4 GEMMs on split operands (Eq. 2, Eq. 3, and the W_R gradient after Eq. 3) ------ */
 
-/* Bytes of device workspace the three GEMM calls need (max over them). */
+/* Bytes of device workspace the three GEMM calls need (max over them) for operands of ranks up to k, equal or not. */
 size_t metis_linear_workspace_bytes(int64_t L, int64_t N, int64_t K, int k);
 
 /* Y[L,N]  = Xbar Wbar^T   uses X.R [L,K], W.R [N,K]                       (Eq. 2) */

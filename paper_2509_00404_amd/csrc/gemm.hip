@@ -1632,11 +1632,14 @@ NtOperand nt(const metis_fp4& R, const metis_fp4& Ut, const metis_fp4& Vt, const
 
 extern "C" size_t metis_linear_workspace_bytes(int64_t L, int64_t N, int64_t K, int k) {
     if (L < 1 || N < 1 || K < 1 || k < 0) return 0;
-    // the three products of split operands, and those of an unsplit left operand (few rows take another path then)
+    // The operands' ranks may be any two up to k.  A layout grows with each of them, except that a skinny product of up to 64
+    // columns is cut into more parts than one of 65 to 128, and that unsplit operands take other kernels: the largest is at one of these.
+    const int ranks[3] = {0, k < 64 ? k : 64, k};
     size_t most = 0;
-    for (int ka : {k, 0})
-        for (size_t b : {lin_layout(L, N, ka, k, K).total, lin_layout(L, K, ka, k, N).total, lin_layout(N, K, ka, k, L).total})
-            if (b > most) most = b;
+    for (int ka : ranks)
+        for (int kb : ranks)
+            for (size_t b : {lin_layout(L, N, ka, kb, K).total, lin_layout(L, K, ka, kb, N).total, lin_layout(N, K, ka, kb, L).total})
+                if (b > most) most = b;
     return most;
 }
 

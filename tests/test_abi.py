@@ -47,6 +47,41 @@ def test_host_side_argument_checks_need_no_gpu():
     assert L.metis_quantize_sr(None, None, 0, None, None) == -1
 
 
+@pytest.mark.parametrize("L,N,K", [(8192, 4096, 4096), (16, 4096, 4096), (64, 1040, 4096), (2048, 1024, 4096), (1360, 1232, 752),
+                                   (128, 256, 512), (4096, 64, 14336), (48, 48, 4096), (3056, 1520, 1040)])
+def test_linear_workspace_covers_every_smaller_rank(L, N, K):
+    """A workspace of linear_workspace_bytes(..., k) serves operands of any ranks up to k, equal or not: none of the three products
+    finds it too small.  The workspace pointer is misaligned, so that a call whose size suffices is refused right after the size
+    was looked at and nothing is enqueued (status -1), with or without a GPU."""
+    from paper_2509_00404_amd import metis
+    if not os.path.exists(metis.LIB_PATH):
+        pytest.skip("library not built")
+    lib = metis.lib()
+    fake = 1 << 20                                          # never read: the call ends before anything is enqueued
+
+    def fp4(rows, cols):
+        return metis.Fp4(fake, fake, 1.0, rows, cols)
+
+    def split(M, N_, k):
+        f = (fp4(k, M), fp4(k, N_)) if k else (metis.Fp4(None, None, 1.0, 0, 0),) * 2
+        return metis.Split(*f, fp4(M, N_), fp4(N_, M), fake, k)
+
+    for k in (1, 16, 64, 65, 80, 128):
+        size = metis.linear_workspace_bytes(L, N, K, k)
+        ranks = sorted({r for r in (0, 1, 8, 20, 63, 64, 65, 72, 80, 127, 128) if r <= k} | {k})
+        for ka in ranks:
+            for kb in ranks:
+                if ka + kb == 0:
+                    continue                                # two unsplit operands need no workspace
+                for fn, a, b, (rows, cols) in ((lib.metis_fp4_linear_fwd, (L, K), (N, K), (L, N)),
+                                               (lib.metis_fp4_linear_dgrad, (L, N), (N, K), (L, K)),
+                                               (lib.metis_fp4_linear_wgrad, (L, N), (L, K), (N, K))):
+                    sa, sb = split(*a, ka), split(*b, kb)
+                    out = metis.Mat(fake, rows, cols, cols, metis.F32)
+                    st = fn(None, ctypes.byref(sa), ctypes.byref(sb), ctypes.byref(out), fake + 8, size)
+                    assert st == -1, (fn.__name__, k, ka, kb, st)
+
+
 def test_tensor_scale_helper_is_the_smallest_covering_power_of_two():
     from paper_2509_00404_amd import metis
     if not os.path.exists(metis.LIB_PATH):
