@@ -319,7 +319,9 @@ int metis_fp4_linear_wgrad(void* stream, const metis_split* G, const metis_split
  *   phase    METIS_LINEAR_PREPARE writes only the workspace; METIS_LINEAR_APPLY reads what PREPARE of the same
  *            product, operands and workspace left there and writes `out`; METIS_LINEAR_ALL = both, which is what
  *            the three calls above do.  `out` may be null for PREPARE.
- * Between PREPARE and APPLY the workspace must not be used by anything else (one workspace per product in flight).
+ * The factors (Ut, Vt, S) are read by PREPARE alone; APPLY reads the residuals and the workspace, given with the same
+ * workspace_bytes.  Between PREPARE and APPLY the workspace must not be used by anything else (one workspace per product in
+ * flight).
  * Same argument rules, workspace size and errors as the three calls above; METIS_INVALID_ARG for an unknown
  * product or phase.  Asynchronous on `stream`.
  */

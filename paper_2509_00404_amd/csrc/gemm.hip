@@ -940,11 +940,12 @@ __device__ __forceinline__ half8_t decode_frag(const DecodeRaw& r, const uint32_
 // column blocks of 32: [0, nb) are R_b's rows, the rest V_b's; P [z][M][ldp], ldp = 32 x all column blocks
 template <int TM>
 __global__ void __launch_bounds__(256)
-k_fp4_decode(Fp4Operand A, Fp4Operand B, Fp4Operand V, int nb, int64_t K, int ips, float* __restrict__ P, int64_t ldp) {
+k_fp4_decode(Fp4Operand A, Fp4Operand B, Fp4Operand V, int blk0, int nb, int64_t K, int ips, float* __restrict__ P, int64_t ldp) {
     __shared__ float red[4][32][32];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 31, half = lane >> 5;
     const int64_t cstride = K / 2, sstride = K / 16;
+    const int blk = blk0 + (int)blockIdx.x;
     // rows past an operand's end re-read its last row; what they give is not stored, or dropped by the second kernel
     const uint8_t *ca[TM], *sa[TM], *cb, *sb;
 #pragma unroll
@@ -954,7 +955,6 @@ k_fp4_decode(Fp4Operand A, Fp4Operand B, Fp4Operand V, int nb, int64_t K, int ip
         sa[i] = A.scales + r * sstride;
     }
     {
-        const int blk = (int)blockIdx.x;
         const bool isv = blk >= nb;
         const int64_t rows = isv ? V.rows : B.rows, r0 = 32 * (int64_t)(isv ? blk - nb : blk) + li;
         const int64_t r = r0 < rows ? r0 : rows - 1;
@@ -1008,7 +1008,7 @@ k_fp4_decode(Fp4Operand A, Fp4Operand B, Fp4Operand V, int nb, int64_t K, int ip
         for (int q = 0; q < 4; ++q) {
             const int r = row + 8 * q;
             const float x = ((red[0][r][col] + red[1][r][col]) + red[2][r][col]) + red[3][r][col];
-            if (32 * i + r < A.rows) P[((int64_t)blockIdx.y * A.rows + 32 * i + r) * ldp + 32 * (int64_t)blockIdx.x + col] = x;
+            if (32 * i + r < A.rows) P[((int64_t)blockIdx.y * A.rows + 32 * i + r) * ldp + 32 * (int64_t)blk + col] = x;
         }
     }
 }
@@ -1145,23 +1145,52 @@ DecodePlan decode_plan(int64_t M, int64_t N, int kb, int64_t K) {
     return d;
 }
 
+// U_b^T (k x N FP4, N % 16 == 0) and S_b as PREPARE leaves them for APPLY, in `keep`: codes, scales, S on a 16-byte boundary
+size_t decode_keep_scales(int64_t N, int kb) { return (size_t)kb * N / 2; }
+size_t decode_keep_s(int64_t N, int kb) { return align_up(decode_keep_scales(N, kb) + (size_t)kb * N / 16, 16); }
+__global__ void __launch_bounds__(256)
+k_decode_keep(const uint8_t* __restrict__ codes, const uint8_t* __restrict__ scales, const float* __restrict__ S, int64_t N, int kb,
+              uint8_t* __restrict__ kc, uint8_t* __restrict__ ks, float* __restrict__ kS) {
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;       // 16 elements: 8 code bytes, one scale
+    if (t < kb * N / 16) {
+        const uint2 c = load8_any(codes + 8 * t);
+        *reinterpret_cast<uint2*>(kc + 8 * t) = c;
+        ks[t] = scales[t];
+    }
+    if (t < kb) kS[t] = S[t];
+}
+
+// One phase of the product, or both.  What PREPARE leaves is what depends on the right operand's factors, as on the general path:
+// their columns of P (the parts of T1), and U_b and S_b, which the second kernel wants, copied to `keep`.
 template <typename OUT>
 int launch_decode(hipStream_t s, const metis_fp4& A, const metis_fp4& B, const metis_fp4* Ub, const metis_fp4* Vb, const float* Sb,
-                  int kb, float* P, OUT* C, int64_t ldc) {
+                  int kb, float* P, uint8_t* keep, int phase, OUT* C, int64_t ldc) {
+    if (phase == METIS_LINEAR_PREPARE && kb == 0) return METIS_OK;
     const Fp4Operand a = {A.codes, A.scales, A.rows}, b = {B.codes, B.scales, B.rows};
     Fp4Operand v = {nullptr, nullptr, 0};
     const uint8_t *uc = nullptr, *us = nullptr;
     float alpha_lr = 0.0f;
+    uint8_t* keep_us = keep + decode_keep_scales(B.rows, kb);
+    float* keep_s = (float*)(keep + decode_keep_s(B.rows, kb));
     if (kb > 0) {
         v = {Vb->codes, Vb->scales, kb};
-        uc = Ub->codes;
-        us = Ub->scales;
+        uc = phase == METIS_LINEAR_APPLY ? keep : Ub->codes;
+        us = phase == METIS_LINEAR_APPLY ? keep_us : Ub->scales;
+        if (phase == METIS_LINEAR_APPLY) Sb = keep_s;
         alpha_lr = A.tscale * Vb->tscale * Ub->tscale;
     }
     const DecodePlan d = decode_plan(A.rows, B.rows, kb, A.cols);
     auto kern = A.rows <= 32 ? k_fp4_decode<1> : k_fp4_decode<2>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(d.nb + d.nv), (unsigned)d.parts), dim3(256), 0, s, a, b, v, d.nb, A.cols, d.ips, P, d.ldp);
+    const int blk0 = phase == METIS_LINEAR_PREPARE ? d.nb : 0, blk1 = phase == METIS_LINEAR_APPLY ? d.nb : d.nb + d.nv;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(blk1 - blk0), (unsigned)d.parts), dim3(256), 0, s, a, b, v, blk0, d.nb, A.cols, d.ips, P,
+                       d.ldp);
     METIS_LAUNCH_CHECK();
+    if (phase == METIS_LINEAR_PREPARE) {
+        hipLaunchKernelGGL(k_decode_keep, dim3((unsigned)ceil_div64((int64_t)kb * B.rows / 16, 256)), dim3(256), 0, s, Ub->codes,
+                           Ub->scales, Sb, B.rows, kb, keep, keep_us, keep_s);
+        METIS_LAUNCH_CHECK();
+        return METIS_OK;
+    }
     auto finish = kb == 0 ? k_decode_finish<0, OUT> : kb <= 64 ? k_decode_finish<1, OUT> : k_decode_finish<2, OUT>;
     hipLaunchKernelGGL(finish, dim3((unsigned)ceil_div64(B.rows, DF_COLS), (unsigned)ceil_div64(A.rows, DF_ROWS)), dim3(256), 0, s, P,
                        d.parts, (int)A.rows, B.rows, d.ldp, d.nb, kb, uc, us, Sb, A.tscale * B.tscale, alpha_lr, C, ldc);
@@ -1538,13 +1567,15 @@ int linear_nt(hipStream_t s, const NtOperand& a, const NtOperand& b, metis_mat* 
         if (!ws_aligned) return METIS_INVALID_ARG;
     }
     if (w.decode && workspace && workspace_bytes >= w.total && ws_aligned) {
-        if (!do_main) return METIS_OK;                   // nothing to prepare
         float* P = (float*)((char*)workspace + w.off_tail);
+        // the kept factors, 9/16 byte per element of U_b and 4 per singular value, take the place of Bext: 2 bytes per element
+        uint8_t* keep = (uint8_t*)workspace + w.off_bext;
+        if (!do_main) return launch_decode<float>(s, a.R, b.R, &b.Ut, &b.Vt, b.S, kb, P, keep, phase, (float*)nullptr, 0);
         const int pi = metis_prof_begin(METIS_PROF_GEMM, s);
         if (out->dtype == METIS_BF16)
-            st = launch_decode<bf16_t>(s, a.R, b.R, &b.Ut, &b.Vt, b.S, kb, P, (bf16_t*)out->ptr, out->ld);
+            st = launch_decode<bf16_t>(s, a.R, b.R, &b.Ut, &b.Vt, b.S, kb, P, keep, phase, (bf16_t*)out->ptr, out->ld);
         else
-            st = launch_decode<float>(s, a.R, b.R, &b.Ut, &b.Vt, b.S, kb, P, (float*)out->ptr, out->ld);
+            st = launch_decode<float>(s, a.R, b.R, &b.Ut, &b.Vt, b.S, kb, P, keep, phase, (float*)out->ptr, out->ld);
         metis_prof_end(METIS_PROF_GEMM, pi, s);
         return st;
     }

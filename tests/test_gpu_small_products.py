@@ -146,3 +146,26 @@ def test_weight_gradient_of_any_size(metis, L, N, K, pad):  # noqa: F811
     flat, dW = _guarded(N, K, K + pad, out_dtype)
     metis.fp4_linear_wgrad(ops[0], ops[1], dW, wsb)
     _check_guarded(flat, dW, ref, bound)
+
+
+@pytest.mark.parametrize("L,N,K,kx,kw", [(16, 400, 1040, 0, 32), (1, 48, 272, 0, 3), (64, 1040, 2064, 0, 65), (33, 16, 128, 0, 8),      # few rows
+                                         (128, 272, 1040, 0, 16), (48, 528, 1040, 16, 24), (1040, 1072, 1264, 16, 24)])   # general path
+@pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
+def test_apply_does_not_read_the_factors(metis, L, N, K, kx, kw, out_dtype):  # noqa: F811
+    """What depends on the factors is in the workspace after PREPARE: a program may quantize new ones into their place before APPLY."""
+    if kw + 4 > min(N, K):
+        kw = min(N, K) - 4
+    xs, ws, _, _ = _product(metis, L, N, K, kx, kw, out_dtype, seed=17)
+    wsb = torch.full((max(metis.linear_workspace_bytes(L, N, K, max(kx, kw)), 256),), 0xA5, dtype=torch.uint8, device="cuda")
+    Y = torch.empty((L, N), dtype=out_dtype, device="cuda")
+    metis.fp4_linear_fwd(xs, ws, Y, wsb)
+    wsb.fill_(0x5A)
+    metis.fp4_linear_phase(metis.LINEAR_FWD, metis.LINEAR_PREPARE, xs, ws, None, wsb)
+    for sp in (xs, ws):
+        if sp.k:
+            sp.S.fill_(float("nan"))
+            for t in (sp.Ut.codes, sp.Vt.codes, sp.Ut.scales, sp.Vt.scales):
+                t.fill_(0x33)
+    Z = torch.full((L, N), float("nan"), dtype=out_dtype, device="cuda")
+    metis.fp4_linear_phase(metis.LINEAR_FWD, metis.LINEAR_APPLY, xs, ws, Z, wsb)
+    assert torch.equal(Z, Y)
