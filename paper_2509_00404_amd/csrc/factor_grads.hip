@@ -35,8 +35,8 @@ __device__ __forceinline__ float fp4_value(const uint8_t* __restrict__ codes, co
     return (nib & 8u) ? -v : v;
 }
 
-// The dequantized factors as the skinny kernels read them, in one launch: Vbar as bf16 [K][k] (exact: a code times an E4M3
-// scale times a power of two has at most 5 significant bits), then Ubar S as fp64 [N][k] and Ubar as fp32 [N][k]
+// The dequantized factors as the skinny kernels read them, in one launch: Vbar as bf16 [K][k] (exact under bf16_exact below), then
+// Ubar S as fp64 [N][k] and Ubar as fp32 [N][k]
 __global__ void __launch_bounds__(256)
 k_fg_prepare(const uint8_t* __restrict__ vc, const uint8_t* __restrict__ vs, float gv, int64_t K, const uint8_t* __restrict__ uc,
              const uint8_t* __restrict__ us, float gu, int64_t N, int k, const float* __restrict__ S, bf16_t* __restrict__ Vbf,
@@ -137,6 +137,15 @@ bool fp4_ok(const metis_fp4& f, int64_t rows, int64_t cols) {
     return f.codes && f.scales && f.rows == rows && f.cols == cols && cols % 16 == 0 && f.tscale > 0.0f;
 }
 
+// Every value code * e4m3 * g of a factor is a bf16 number: a code times an E4M3 scale has at most 6 significant bits and is a
+// multiple of 2^-10 of at most 2688, so g has to be a power of two that keeps those bits between bf16's smallest subnormal,
+// 2^-133, and its largest number.
+bool bf16_exact(float g) {
+    uint32_t u;
+    __builtin_memcpy(&u, &g, 4);
+    return (u & 0x7FFFFFu) == 0 && g >= 0x1p-123f && g <= 0x1p116f;
+}
+
 template <typename TW>
 int run(hipStream_t s, const TW* dW, int64_t ld, int64_t N, int64_t K, int k, const metis_split* W, float* dU, float* dS,
         float* dV, char* ws, const FgLayout& L) {
@@ -151,7 +160,8 @@ int run(hipStream_t s, const TW* dW, int64_t ld, int64_t N, int64_t K, int k, co
     const int64_t tk = ceil_div64(k, 32);
     // A dW of aligned rows takes the decomposition's skinny kernels (same shapes as its sketch and projection): fp32 4096 x 4096
     // at rank 64, the two products 262 us on the generic kernel, 120 us there; the whole call in 7 launches instead of 14
-    const bool fast = skinny_ok(dW, ld, K, k) && N % 8 == 0 && (N + K) * (int64_t)k < ((int64_t)1 << 38);
+    // (a tensor scale that is no power of two would round Vbar there: the generic kernel holds it in fp32)
+    const bool fast = skinny_ok(dW, ld, K, k) && N % 8 == 0 && (N + K) * (int64_t)k < ((int64_t)1 << 38) && bf16_exact(W->Vt.tscale);
     if (fast) {
         bf16_t* Vbf = (bf16_t*)(ws + L.off_vbf);
         double* H64 = (double*)(ws + L.off_h64);

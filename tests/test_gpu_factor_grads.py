@@ -86,3 +86,18 @@ def test_rejects_bad_arguments(metis):
     small = torch.empty((16,), dtype=torch.uint8, device="cuda")
     with pytest.raises(metis.MetisError):
         metis.fp4_factor_grads(torch.zeros((N, K), dtype=torch.float32, device="cuda"), ws, dU, dS, dV, small)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_tensor_scales_that_round_in_16_bits(metis, dtype):
+    """The entry point takes any positive tensor scale: one that is no power of two (the factors then need more bits than bf16
+    has) gives the same precision."""
+    from paper_2509_00404_amd import workloads
+    N, K, k = 272, 320, 16
+    W = workloads.planted(N, K, workloads.power_law(min(N, K), 1.0), 5, noise_top=0.01, rms=0.02)
+    ws = make_split(metis, W, k, 8, 1.0, 3)[0]
+    ws.Ut.tscale, ws.Vt.tscale = 2.0 ** -11 * 1.3125, float(np.float32(2.0 ** -11 * 1.7))
+    dW = torch.randn((N, K), generator=torch.Generator().manual_seed(9)).to(dtype).cuda()
+    got = _run(metis, dW, ws)
+    for name, a, b in zip(("dU", "dS", "dV"), got, olin.factor_grads(dW.double().cpu().numpy(), split_to_oracle(ws))):
+        assert rel_fro(a, b) < FG_RTOL, (name, rel_fro(a, b))
