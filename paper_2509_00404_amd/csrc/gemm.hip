@@ -1219,34 +1219,29 @@ __device__ __forceinline__ float fp4_elem_nog(const uint8_t* codes, const uint8_
 // Blocks [0, ceil(Ma/32)) build 32 rows of Aext each: the dequantized factor rows U_a and the small matrix
 // Sa Mk sit in LDS; thread (row t/8, column group t%8) owns the columns 64 h + 8 (t%8) + 0..7 of its row.  The
 // remaining blocks build 32 rows of Bext each the same way.  The kernel moves little data and is bound by
-// load latency, so the global loads of a thread are issued before the first use: eight parts of a sum at a time, and for ranks
-// that are multiples of 8 up to 64 those of T1 and Mk together (one trip instead of six: 4096 rows a side, rank 64,
-// 18.8 -> 15.7 us).
+// load latency: the loads of all parts of a sum are issued before the first use, and four workgroups share a CU.  Both count:
+// with the loads of T1 and Mk in one trip as well (220 registers, two workgroups per CU) 4096 rows a side at rank 64 took the
+// same 33.0 us with the skinny products before it, and 100352 rows of an output layer behind 128 tokens 24.6 instead of 18.5.
 #define AX_ROWS 32
 
-// Eight consecutive values of up to eight parts, all loads issued (a missing part re-reads the last one) ...
-struct Parts8 {
-    float4 lo[8], hi[8];
-};
-__device__ __forceinline__ Parts8 load_parts8(const float* __restrict__ base, size_t pstride, int n, size_t off) {
-    Parts8 r;
+// acc[i] += sum over parts p < n <= NP of base[p * pstride + off + i], i < 8, 16-byte aligned: all loads issued, then added in
+// ascending order (a missing part re-reads the last one with weight 0)
+template <int NP>
+__device__ __forceinline__ void sum_parts8_vec(const float* __restrict__ base, size_t pstride, int n, size_t off, float (&acc)[8]) {
+    float4 lo[NP], hi[NP];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < NP; ++u) {
         const float* q = base + (size_t)(u < n ? u : n - 1) * pstride + off;
-        r.lo[u] = *reinterpret_cast<const float4*>(q);
-        r.hi[u] = *reinterpret_cast<const float4*>(q + 4);
+        lo[u] = *reinterpret_cast<const float4*>(q);
+        hi[u] = *reinterpret_cast<const float4*>(q + 4);
     }
-    return r;
-}
-// ... and added in ascending order (missing parts with weight 0)
-__device__ __forceinline__ void add_parts8(const Parts8& r, int n, float (&acc)[8]) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < NP; ++u) {
         const float w = u < n ? 1.0f : 0.0f;
-        acc[0] = fmaf(w, r.lo[u].x, acc[0]); acc[1] = fmaf(w, r.lo[u].y, acc[1]);
-        acc[2] = fmaf(w, r.lo[u].z, acc[2]); acc[3] = fmaf(w, r.lo[u].w, acc[3]);
-        acc[4] = fmaf(w, r.hi[u].x, acc[4]); acc[5] = fmaf(w, r.hi[u].y, acc[5]);
-        acc[6] = fmaf(w, r.hi[u].z, acc[6]); acc[7] = fmaf(w, r.hi[u].w, acc[7]);
+        acc[0] = fmaf(w, lo[u].x, acc[0]); acc[1] = fmaf(w, lo[u].y, acc[1]);
+        acc[2] = fmaf(w, lo[u].z, acc[2]); acc[3] = fmaf(w, lo[u].w, acc[3]);
+        acc[4] = fmaf(w, hi[u].x, acc[4]); acc[5] = fmaf(w, hi[u].y, acc[5]);
+        acc[6] = fmaf(w, hi[u].z, acc[6]); acc[7] = fmaf(w, hi[u].w, acc[7]);
     }
 }
 
@@ -1254,7 +1249,8 @@ __device__ __forceinline__ void add_parts8(const Parts8& r, int n, float (&acc)[
 __device__ __forceinline__ void sum_parts8(const float* __restrict__ base, size_t pstride, int n, size_t off, int cnt,
                                            bool vec, float (&acc)[8]) {
     if (vec) {
-        add_parts8(load_parts8(base, pstride, n, off), n, acc);
+        if (n <= 4) sum_parts8_vec<4>(base, pstride, n, off, acc);       // (uniform)
+        else sum_parts8_vec<8>(base, pstride, n, off, acc);
         return;
     }
     for (int p0 = 0; p0 < n; p0 += 4) {
@@ -1355,41 +1351,23 @@ k_assemble_ext(int64_t Ma, int64_t Nb, int ka, int kb, int Kep, Fp4Operand Ra, F
         for (int h = 0; h < NCH; ++h)
 #pragma unroll
             for (int i = 0; i < 8; ++i) t1[h][i] = 0.0f;
-        if (NCH == 1 && ka > 0 && kb > 0 && kb % 8 == 0 && nmk <= 2 * 8 * 256) {
-            // (uniform) every group of 8 is whole, aligned and inside one row of Mk
-            const int c0 = 8 * cg < kb ? 8 * cg : 0, ea = 8 * tid < nmk ? 8 * tid : 0, eb = 8 * tid + 2048 < nmk ? 8 * tid + 2048 : 0;
-            const Parts8 pt = load_parts8(T1, (size_t)Ma * kb, n1, (size_t)lrow * kb + c0);
-            const Parts8 pa = load_parts8(Mk, (size_t)nmk, n3, (size_t)ea);
-            const Parts8 pb = load_parts8(Mk, (size_t)nmk, n3, (size_t)eb);
-            const float fa = g_ua * Sa[ea / kb], fb = g_ua * Sa[eb / kb];
-            float ma[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f}, mb[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-            add_parts8(pt, n1, t1[0]);
-            add_parts8(pa, n3, ma);
-            add_parts8(pb, n3, mb);
+        // this thread's sums of the T1 parts
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                if (8 * tid < nmk) mk[ea + i] = ma[i] * fa;
-                if (8 * tid + 2048 < nmk) mk[eb + i] = mb[i] * fb;
+        for (int h = 0; h < NCH; ++h) {
+            const int c0 = 64 * h + 8 * cg;
+            if (c0 < kb && n1 > 0) {
+                const int cnt = kb - c0 < 8 ? kb - c0 : 8;
+                sum_parts8(T1, (size_t)Ma * kb, n1, (size_t)lrow * kb + c0, cnt, cnt == 8 && kb % 4 == 0, t1[h]);
             }
-        } else {
-            // this thread's sums of the T1 parts
+        }
+        // Sa Mk (with U_a's tensor scale) into LDS, the parts added on the way
+        for (int e0 = 8 * tid; e0 < nmk; e0 += 8 * 256) {
+            float m[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+            const int cnt = nmk - e0 < 8 ? nmk - e0 : 8;
+            sum_parts8(Mk, (size_t)nmk, n3, (size_t)e0, cnt, cnt == 8 && nmk % 4 == 0, m);
 #pragma unroll
-            for (int h = 0; h < NCH; ++h) {
-                const int c0 = 64 * h + 8 * cg;
-                if (c0 < kb && n1 > 0) {
-                    const int cnt = kb - c0 < 8 ? kb - c0 : 8;
-                    sum_parts8(T1, (size_t)Ma * kb, n1, (size_t)lrow * kb + c0, cnt, cnt == 8 && kb % 4 == 0, t1[h]);
-                }
-            }
-            // Sa Mk (with U_a's tensor scale) into LDS, the parts added on the way
-            for (int e0 = 8 * tid; e0 < nmk; e0 += 8 * 256) {
-                float m[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-                const int cnt = nmk - e0 < 8 ? nmk - e0 : 8;
-                sum_parts8(Mk, (size_t)nmk, n3, (size_t)e0, cnt, cnt == 8 && nmk % 4 == 0, m);
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    if (i < cnt) mk[e0 + i] = m[i] * g_ua * Sa[(e0 + i) / kb];
-            }
+            for (int i = 0; i < 8; ++i)
+                if (i < cnt) mk[e0 + i] = m[i] * g_ua * Sa[(e0 + i) / kb];
         }
         decode_factor_rows(ua_codes, ua_scales, Ma, ka, r0, ua, tid);
         __syncthreads();
