@@ -781,8 +781,10 @@ int launch_gemm_tile(hipStream_t s, const Fp4Operand& a, const Fp4Operand& b, in
 // How an output of at most 256 tiles of the bounds-checked kernel is produced, by estimates (in us) that were fitted to
 // measurements at rank 64:
 //   - small tiles (128 x 128 for large sides): a 128-deep stage takes 1.4 us (expansion bound, 1.15 per workgroup once a CU holds
-//     several), the rest 8.  Few tiles leave most CUs idle while each walks its whole contraction: the contraction is cut into parts
-//     where that costs less than it saves, a launch of 3.5 and 6 bytes of traffic per element and part at ~4 TB/s;
+//     several; 0.85 and 0.66 for tiles with a side of 64), the rest 8.  Few tiles leave most CUs idle while each walks its whole
+//     contraction: the contraction is cut into parts where that costs less than it saves, a launch of 3.5 and 6 bytes of traffic per
+//     element and part at ~4 TB/s.  Where the whole call would be one short launch (lone: no extra columns; a side of 64) the second
+//     one also costs the host 2 us (64 x 4096 x 1024: cut 9.4 us in a graph, 11.5 call after call; whole 10.6 both);
 //   - both sides at least 1024: the pipelined kernel's 256 x 256 tiles, 3.3 per stage of a tile cut into `pipe_parts`, the rest 13,
 //     a launch of 3 and the sum of its parts.
 // 4096 x 1024: K = 1024 43 -> 20 (small tiles, whole), K = 4096 59 -> 52, K = 14336 stays pipelined (119; small tiles 157);
@@ -792,18 +794,20 @@ struct SmallPlan {
     bool small;              // small tiles (otherwise: too many of them, or the pipelined kernel with its own cut is faster)
     int parts;               // their contraction parts
 };
-SmallPlan small_plan(int64_t M, int64_t N, int64_t niter, int pipe_parts) {
+SmallPlan small_plan(int64_t M, int64_t N, int64_t niter, int pipe_parts, bool lone) {
     SmallPlan best = {false, 1};
     const int64_t bm = M <= 64 ? 64 : 128, bn = N <= 64 && M > 64 ? 64 : 128;
     const int64_t tiles = ceil_div64(M, bm) * ceil_div64(N, bn);
     if (tiles > 256) return best;
     const double mn = (double)M * (double)N;
     double best_t = pipe_parts > 0 ? 16.0 + 3.3 * (double)ceil_div64(niter, pipe_parts) + pipe_parts * mn * 1e-6 : 1e30;
+    const bool half = bm * bn < 128 * 128;
+    const double one = half ? 0.85 : 1.4, many = half ? 0.66 : 1.15, launch = lone && half ? 5.5 : 3.5;
     for (int p = 1; p <= 16 && (p == 1 || 2 * p <= niter); ++p) {
         const int64_t ips = ceil_div64(niter, p);
         if (ceil_div64(niter, ips) != p) continue;                       // no empty part
         const double per_cu = (double)ceil_div64(tiles * p, 256);
-        const double t = 8.0 + (double)ips * (per_cu > 1.5 ? 1.15 * per_cu : 1.4) + (p > 1 ? 3.5 + p * mn * 1.5e-6 : 0.0);
+        const double t = 8.0 + (double)ips * (per_cu > 1.5 ? many * per_cu : one) + (p > 1 ? launch + p * mn * 1.5e-6 : 0.0);
         if (t < best_t - 1e-9) {
             best_t = t;
             best = {true, p};
@@ -812,11 +816,11 @@ SmallPlan small_plan(int64_t M, int64_t N, int64_t niter, int pipe_parts) {
     return best;
 }
 
-// The plan of an M x N output over `niter` stages; whole: every stage is a whole one
-SmallPlan gemm_plan(int64_t M, int64_t N, int64_t niter, bool whole) {
+// The plan of an M x N output over `niter` stages; whole: every stage is a whole one; lone: there are no extra columns
+SmallPlan gemm_plan(int64_t M, int64_t N, int64_t niter, bool whole, bool lone) {
     int pipe_parts = 0;
     if (M >= 1024 && N >= 1024 && whole && gemm_tail_bytes(M, N, niter * G_KI, &pipe_parts) == 0) pipe_parts = 0;
-    return small_plan(M, N, niter, pipe_parts);
+    return small_plan(M, N, niter, pipe_parts, lone);
 }
 
 template <int TM, int TN, int WMW, int WNW, typename OUT>
@@ -859,7 +863,7 @@ int launch_gemm(hipStream_t s, const metis_fp4& A, const metis_fp4& B, const bf1
         const size_t tail_need = gemm_tail_bytes(M, N, K);
         const bool can_split = tail_need > 0 && partial && partial_bytes >= tail_need;
         const int64_t tiles = ceil_div64(M, 256) * ceil_div64(N, 256);
-        const SmallPlan plan = gemm_plan(M, N, niter, whole);
+        const SmallPlan plan = gemm_plan(M, N, niter, whole, Ke == 0);
         const bool room = partial && partial_bytes >= (size_t)plan.parts * M * N * sizeof(float);
         // few tiles: small ones, whole or in parts (without the room for those the call works too, on the kernels below)
         if (whole && plan.small && (plan.parts == 1 || room)) {
@@ -874,7 +878,7 @@ int launch_gemm(hipStream_t s, const metis_fp4& A, const metis_fp4& B, const bf1
         // a partial stage that could not become extra columns (no workspace): 8 waves of 128x64, bounds-checked staging
         return launch_gemm_tile<4, 2, 2, 4, OUT>(s, a, b, K, niter, Aext, Bext, Ke, alpha, C, ldc);
     }
-    const int parts = gemm_plan(M, N, niter, false).parts;
+    const int parts = gemm_plan(M, N, niter, false, Ke == 0).parts;
     if (parts > 1 && partial && partial_bytes >= (size_t)parts * M * N * sizeof(float)) {
         if (N > 64 && M > 64)
             return launch_gemm_parts<2, 2, 2, 2, OUT>(s, a, b, K, niter, parts, Aext, Bext, Ke, alpha, C, ldc, partial);
@@ -1120,8 +1124,29 @@ k_decode_finish(const float* __restrict__ P, int parts, int M, int64_t N, int64_
         if (n + i < N) store_out<OUT>(c + i, o[i]);
 }
 
-// few rows of an unsplit left operand
-bool decode_shape(int64_t Ma, int ka) { return ka == 0 && Ma <= DC_MAX_ROWS; }
+// Few rows of an unsplit left operand, where the few-row kernels are the faster ones.  Every workgroup of 32 columns expands all of
+// A's rows again, in blocks of 32, and the parts of the whole output travel through memory; the general path does neither, but
+// has two launches more with factors.  So wide outputs are its own, from fewer elements on when there are two row blocks, when a short
+// contraction gives little to gain, and without factors or above rank 64 (a longer second kernel).  us in a graph, few-row against
+// general, N x K:
+//   rank 64: 64 x 14336 x 4096 33 against 34, 64 x 20480 x 4096 42 against 39, 64 x 12288 x 512 16 against 18, 64 x 50256 x 512 38
+//   against 27, 32 x 50256 x 768 25 against 30; rank 16: 32 x 28672 x 4096 35 against 41, x 512 16.5 against 16.4;
+//   rank 128: 64 x 8192 x 4096 29 against 34, 64 x 14336 x 4096 41 against 37, 32 x 28672 x 1024 28 against 30;
+//   no factors: 64 x 8192 x 4096 17.4 against 17.6, 64 x 16384 x 4096 26 against 23, 17 x 50256 x 4096 37 against 46.
+// Up to 16 rows it is cheap at every width (rank 64, 16 x 50256 x 4096 43 against 63).  Without factors the general path is one launch
+// when its contraction is short, which saves the host 2.6 us (16 x 4096 x 512 5.1 against 6.5, but 11.2 against 8.7 call after
+// call; x 1024 5.3 against 9.8).
+bool decode_shape(int64_t Ma, int64_t Nb, int ka, int kb, int64_t Kc) {
+    if (ka > 0 || Ma > DC_MAX_ROWS) return false;
+    const int64_t niter = ceil_div64(Kc, G_KI);
+    if (kb == 0 && niter <= 6) return false;
+    if (Ma <= 16) return true;
+    const bool low = kb > 0 && kb <= 64;
+    int64_t most;                                   // output elements, in units of 2^16
+    if (Ma <= 32) most = low ? (niter >= 6 ? 32 : 12) : niter >= (kb > 0 ? 6 : 16) ? 16 : 8;
+    else most = low ? (niter >= 12 ? 15 : 12) : 8;
+    return Ma * Nb <= most << 16;
+}
 
 struct DecodePlan {
     int nb, nv, ips, parts;              // column blocks of 32 of R_b, of V_b; stages per part, parts
@@ -1500,10 +1525,10 @@ LinWs lin_layout(int64_t Ma, int64_t Nb, int ka, int kb, int64_t Kc) {
     w.off_e2 = take((size_t)w.s2 * Nb * (ka > 0 ? ka : 1) * 4);
     w.off_aext = take((size_t)((Ma + 31) / 32 * 32) * (w.Kep + w.Kt > 0 ? w.Kep + w.Kt : 16) * 2);       // rows padded to whole 32-row blocks
     w.off_bext = take((size_t)((Nb + 31) / 32 * 32) * (w.Kep + w.Kt > 0 ? w.Kep + w.Kt : 16) * 2);
-    w.decode = decode_shape(Ma, ka);
+    w.decode = decode_shape(Ma, Nb, ka, kb, Kc);
     const bool large = Ma >= 1024 && Nb >= 1024, whole = Kc % G_KI == 0 || w.Kt > 0;
     const int64_t niter = w.Kt > 0 ? Kc / G_KI : ceil_div64(Kc, G_KI);
-    const SmallPlan plan = gemm_plan(Ma, Nb, niter, whole);
+    const SmallPlan plan = gemm_plan(Ma, Nb, niter, whole, w.Kep + w.Kt == 0);
     const size_t parts_bytes = plan.parts > 1 ? (size_t)plan.parts * Ma * Nb * sizeof(float) : 0;
     if (w.decode) w.tail_bytes = decode_plan(Ma, Nb, kb, Kc).bytes;
     else if (large) w.tail_bytes = !whole ? 0 : plan.small ? parts_bytes : gemm_tail_bytes(Ma, Nb, Kc);

@@ -169,3 +169,19 @@ def test_apply_does_not_read_the_factors(metis, L, N, K, kx, kw, out_dtype):  # 
     Z = torch.full((L, N), float("nan"), dtype=out_dtype, device="cuda")
     metis.fp4_linear_phase(metis.LINEAR_FWD, metis.LINEAR_APPLY, xs, ws, Z, wsb)
     assert torch.equal(Z, Y)
+
+
+# both sides of the lines at which few rows leave their own kernels for the general ones: 16 rows, then the output's elements, in
+# steps of 2^16, by rank, contraction (6, 12, 16 stages) and rows (32); without factors 6 stages; contractions for which a lone launch
+# stays whole
+@pytest.mark.parametrize("L,N,K,k", [
+    (16, 32784, 912, 0), (17, 30832, 912, 0), (17, 30848, 912, 0), (33, 15872, 912, 0), (33, 15888, 912, 0), (17, 30848, 2064, 0),
+    (48, 272, 768, 0), (48, 272, 784, 0), (32, 24576, 144, 8), (32, 24592, 144, 8), (32, 24592, 656, 8), (64, 12288, 144, 64),
+    (64, 12304, 144, 64), (64, 15360, 1424, 8), (64, 15376, 1424, 8), (64, 8192, 144, 65), (64, 8208, 144, 65), (31, 16912, 144, 72),
+    (31, 16928, 144, 72), (31, 16928, 656, 72), (80, 272, 1040, 0), (64, 272, 1024, 0), (64, 272, 1280, 0)])
+def test_lines_between_the_paths(metis, L, N, K, k):  # noqa: F811
+    xs, ws, ref, bound = _product(metis, L, N, K, 0, k, torch.float32, seed=21)
+    wsb = torch.empty((max(metis.linear_workspace_bytes(L, N, K, k), 256),), dtype=torch.uint8, device="cuda")
+    flat, Y = _guarded(L, N, N, torch.float32)
+    metis.fp4_linear_fwd(xs, ws, Y, wsb)
+    _check_guarded(flat, Y, ref, bound)
