@@ -112,18 +112,27 @@ k_quantize_tile(const T* __restrict__ A, int64_t ld, int64_t M, int64_t N, Quant
 }
 
 // Both orientations of a bf16 matrix (aligned rows, M % 16 == 0, N % 16 == 0), or the transposed one alone.  128 x 128
-// tile.  A thread takes the blocks of two neighbouring rows straight from two 32-byte loads (8 lanes cover
-// 256 bytes of a row), quantizes them in registers, and packs the two rows' elements into dwords that it stores column by column in LDS, so
-// that a block of the transposed copy (16 rows of one column) is two 16-byte LDS reads.  Bound by vector issue with
-// stochastic rounding, by write requests without; 8 lanes write 64 bytes of codes in a row (the 64 x 64 tiles below write 32).
-// A column of the LDS tile is 64 dwords (row pairs) + 4, and each group of 16 columns is shifted by 8 more: the 64
-// lanes of a store then hit 64 different banks.
-// 8192 x 14336, both orientations, against the 64 x 64 tiles below: nearest 204 -> 91 us (0.34 GB of traffic: 3.8 TB/s),
+// tile.  A thread takes the blocks of two neighbouring rows straight from two 32-byte loads (8 lanes cover 256 bytes of
+// a row), quantizes them in registers, and packs the two rows' elements into dwords that it stores column by column in LDS,
+// so that a block of the transposed copy (16 rows of one column) is two 16-byte LDS reads.  Bound by vector issue with
+// stochastic rounding, by write requests without; 8 lanes write 64 bytes of codes in a row (the 64 x 64 tiles of
+// k_quantize_tile write 32).  A column of the LDS tile is 64 dwords (row pairs) + 4, and each group of 16 columns is shifted
+// by 8 more: the 64 lanes of a store then hit 64 different banks.
+// 8192 x 14336, both orientations, against the 64 x 64 tiles: nearest 204 -> 91 us (0.34 GB of traffic: 3.8 TB/s),
 // stochastic 283 -> 159 us; the transposed copy alone 157 -> 71 and 200 -> 92 us.  Below one tile per CU the
 // small tiles spread better and both take less than a launch costs (2048 x 1024: 9 us either way).
 #define QT_DIM 128
 #define QT_LD (QT_DIM / 2 + 4)
 #define QT_MIN_TILES 256
+// Tiles of a thin matrix are mostly empty, and a thread's two rows then leave most of the workgroup idle: a stochastic transposed copy
+// alone wants 80 rows (us on the small tiles and on these: 48 x 87376 10.3 and 12.4, 80 x 52416 11.5 and 10.1), everything
+// else 48 (32 x 131072 transposed 6.3 and 6.9, 48 x 349520 20.5 and 15.3), and both stochastic copies 32 columns (65536 x 16 11.1
+// and 12.4, 32768 x 32 9.9 and 9.7).
+static bool tile_shape_ok(int64_t M, int64_t N, bool rows, bool sr) {
+    const int64_t tiles = ceil_div64(N, QT_DIM) * ceil_div64(M, QT_DIM);
+    return N % 16 == 0 && tiles >= QT_MIN_TILES && ceil_div64(M, QT_DIM) <= 65535 && M >= (sr && !rows ? 80 : 48) &&
+           N >= (sr && rows ? 32 : 16);
+}
 template <bool SR>
 __global__ void __launch_bounds__(256)
 k_quantize_both_bf16(const bf16_t* __restrict__ A, int64_t ld, int64_t M, int64_t N, QuantParams qp, QuantParams qpt,
@@ -288,8 +297,7 @@ static int quantize_impl(void* stream, const metis_mat* A, metis_fp4* out, metis
     }
     const bool rows_aligned = A->dtype == METIS_BF16 && A->ld % 8 == 0 && reinterpret_cast<uintptr_t>(A->ptr) % 16 == 0;
     // large enough that the 128 x 128 tiles still fill the chip
-    if (out_t && rows_aligned && N % 16 == 0 && ceil_div64(N, QT_DIM) * ceil_div64(M, QT_DIM) >= QT_MIN_TILES &&
-        ceil_div64(M, QT_DIM) <= 65535) {
+    if (out_t && rows_aligned && tile_shape_ok(M, N, out != nullptr, SR)) {
         hipLaunchKernelGGL(k_quantize_both_bf16<SR>, dim3((unsigned)ceil_div64(N, QT_DIM), (unsigned)ceil_div64(M, QT_DIM)),
                            dim3(256), 0, s, (const bf16_t*)A->ptr, A->ld, M, N, make_quant_params(out ? out->tscale : 1.0f),
                            make_quant_params(out_t->tscale), out ? out->codes : nullptr, out ? out->scales : nullptr,

@@ -82,3 +82,23 @@ def test_non_finite_values_take_the_exact_path(metis, special):
     assert code == 7                                          # magnitude 6
     a[3, 16:24] = b[3, 16:24]
     assert np.array_equal(a, b)
+
+
+# thin matrices on both sides of the lines between the two tile kernels: 48 and 80 rows, 32 columns
+@pytest.mark.parametrize("M,N", [(32, 32768), (48, 32768), (64, 32768), (80, 32768), (32768, 16), (32768, 32)])
+@pytest.mark.parametrize("sr", [False, True])
+@pytest.mark.parametrize("rows", [False, True])
+def test_thin_matrices(metis, M, N, sr, rows):
+    x = torch.randn((M, N), generator=torch.Generator().manual_seed(M + 3 * N)).to(torch.bfloat16)
+    g = oq.tensor_scale_for(float(x.abs().max()))
+    out, out_t = metis.Fp4Tensor(M, N, g) if rows else None, metis.Fp4Tensor(N, M, g)
+    if sr:
+        metis.quantize_sr(x.cuda(), 17, out, out_t)
+    else:
+        metis.quantize(x.cuda(), out, out_t)
+    torch.cuda.synchronize()
+    xn = x.double().numpy()
+    xt = np.ascontiguousarray(xn.T)
+    _compare(out_t, oq.quantize_sr(xt, g, 17, oq.STREAM_SR_T) if sr else oq.quantize(xt, g))
+    if rows:
+        _compare(out, oq.quantize_sr(xn, g, 17, oq.STREAM_SR) if sr else oq.quantize(xn, g))
