@@ -49,11 +49,51 @@ __device__ __forceinline__ double chol_rsqrt(double x) {
     return __builtin_fma(e * y, __builtin_fma(e, 0.375, 0.5), y);
 }
 
-template <bool BAD_PIVOT_ZEROES>
+// SMALL: n may be 4 or less.
+template <bool BAD_PIVOT_ZEROES, bool SMALL>
 __device__ __forceinline__ void chol_blocked(double* __restrict__ W, int ld, int n, double* __restrict__ rinv, double floor_,
                              int32_t* __restrict__ info) {
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = nthr >> 6;
+    if (SMALL && n <= 4) {                               // (a 2 x 2 matrix as a panel: 16 columns, 3 us; the same operations on one lane)
+        if (tid == 0) {
+            double l[4][4], rv[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int c = 0; c <= i; ++c) l[i][c] = i < n ? W[(size_t)c * ld + i] : (i == c ? 1.0 : 0.0);
+            int bad = 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                double piv = l[c][c];
+                if (BAD_PIVOT_ZEROES) {
+                    rv[c] = piv > floor_ ? chol_rsqrt(piv) : 0.0;
+                } else {
+                    const bool ok = piv > 0.0;
+                    bad = !ok && c < n ? c + 1 : bad;
+                    piv = ok ? piv : 1e-300;
+                    rv[c] = chol_rsqrt(piv);
+                }
+#pragma unroll
+                for (int i = c; i < 4; ++i) l[i][c] *= rv[c];
+#pragma unroll
+                for (int t = c + 1; t < 4; ++t)
+#pragma unroll
+                    for (int i = t; i < 4; ++i) l[i][t] = __builtin_fma(-l[i][c], l[t][c], l[i][t]);
+            }
+            if (!BAD_PIVOT_ZEROES && bad && info) *info = bad;
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (c < n) {
+                    rinv[c] = rv[c];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (i < n) W[(size_t)c * ld + i] = i >= c ? l[i >= c ? i : c][c] : 0.0;
+                }
+        }
+        __syncthreads();
+        return;
+    }
     for (int k0 = 0; k0 < n; k0 += 16) {
         const int below = n - k0 - 16;                   // rows under the diagonal block
         const bool mine = wave == 0 || 64 * wave < below;      // uniform
@@ -186,7 +226,7 @@ k_chol_inv(const CholBatch batch, int n) {
             X[p * ld + i] = 0.0;
         }
     __syncthreads();
-    chol_blocked<false>(L, ld, n, dinv, 0.0, info);
+    chol_blocked<false, true>(L, ld, n, dinv, 0.0, info);
     if (wellcond_out && tid < 64) {
         double lo = dinv[tid < n ? tid : 0], hi = lo;
         if (tid + 64 < n) { lo = fmin(lo, dinv[tid + 64]); hi = fmax(hi, dinv[tid + 64]); }
@@ -886,7 +926,7 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk, int use_pre) {
         __shared__ double rinv_sh[SM_MAX_N];
         double m = 0.0;                           // every wave finds the largest diagonal entry for itself
         for (int j = lane; j < n; j += 64) m = fmax(m, W[(size_t)j * ldc + j]);
-        chol_blocked<true>(W, ldc, n, rinv_sh, wave_max(m) * 1e-30, nullptr);
+        chol_blocked<true, NE == 1>(W, ldc, n, rinv_sh, wave_max(m) * 1e-30, nullptr);
     }
     const double tol2 = 1e-14, floor2 = 1e-28;
     double amax = 0.0;

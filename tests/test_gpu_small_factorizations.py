@@ -35,3 +35,14 @@ def test_repeated_singular_values(metis, k, p):  # noqa: F811
     assert np.abs(V.T @ V - np.eye(k)).max() < 1e-4
     An = A.double().numpy()
     assert np.linalg.norm((U * S) @ V.T - (Ur * Sr) @ Vr.T) / np.linalg.norm(An) < 1e-3
+
+
+@pytest.mark.parametrize("k,p", [(1, 1), (1, 2), (2, 2), (3, 2)])
+def test_orders_up_to_four(metis, k, p):  # noqa: F811
+    # factored on one lane up to order 4
+    A = _planted_bf16(512, 256, 50.0 * np.arange(1, 257) ** -1.5 + 0.02, seed=40 + k + p)
+    got = _run(metis, A, k, p, 1.0, seed=5)
+    _compare(A, got, odec.decompose(A.double().numpy(), k, p, 1.0, seed=5), k)
+    info = torch.zeros(1, dtype=torch.int32, device="cuda")
+    metis.decompose(torch.zeros((64, 64), dtype=torch.bfloat16, device="cuda"), k, p, 1.0, 1, info=info)
+    assert int(info.item()) != 0
