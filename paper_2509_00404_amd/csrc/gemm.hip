@@ -779,7 +779,7 @@ int launch_gemm_tile(hipStream_t s, const Fp4Operand& a, const Fp4Operand& b, in
 }
 
 // How an output of at most 256 tiles of the bounds-checked kernel is produced, by estimates (in us) that were fitted to
-// measurements at rank 64:
+// measurements at rank 64 on 256 CUs (a constant here: the workspace's size is asked for without a device, too):
 //   - small tiles (128 x 128 for large sides): a 128-deep stage takes 1.4 us (expansion bound, 1.15 per workgroup once a CU holds
 //     several; 0.85 and 0.66 for tiles with a side of 64), the rest 8.  Few tiles leave most CUs idle while each walks its whole
 //     contraction: the contraction is cut into parts where that costs less than it saves, a launch of 3.5 and 6 bytes of traffic per
@@ -789,7 +789,9 @@ int launch_gemm_tile(hipStream_t s, const Fp4Operand& a, const Fp4Operand& b, in
 //     a launch of 3 and the sum of its parts.
 // 4096 x 1024: K = 1024 43 -> 20 (small tiles, whole), K = 4096 59 -> 52, K = 14336 stays pipelined (119; small tiles 157);
 // 1024 x 1024: K = 4096 45 -> 31, K = 14336 89 -> 53 (4 parts); 1360 x 1232 x 768 35 -> 13.  Whole calls with one side below 1024:
-// 256 x 4096 x 4096 56 -> 39, 256 x 4096 x 14336 153 -> 66, 512 x 4096 x 4096 58 -> 48, 512 x 1024 x 4096 55 -> 35.
+// 256 x 4096 x 4096 56 -> 39, 256 x 4096 x 14336 153 -> 66, 512 x 4096 x 4096 58 -> 48, 512 x 1024 x 4096 55 -> 35.  The rank
+// does not enter: it costs every form about the same.  256 x 4096 x 4096 without factors 41 -> 26, at rank 16 53 -> 38, at 128
+// 61 -> 42; 512 x 1024 x 4096 41 -> 21, 53 -> 33, 61 -> 37.
 struct SmallPlan {
     bool small;              // small tiles (otherwise: too many of them, or the pipelined kernel with its own cut is faster)
     int parts;               // their contraction parts
@@ -894,14 +896,15 @@ int launch_gemm(hipStream_t s, const metis_fp4& A, const metis_fp4& B, const bf1
 // Two launches.  The first multiplies A with the rows of R_b and, as more columns, with those of V_b (T1 = A V_b^T), cut
 // along the contraction into `z` parts so that a few workgroups per CU exist however few columns there are.  A workgroup
 // owns 32 columns and all rows; its 4 waves deal the 128-deep stages of the part among themselves, so no stage
-// passes through LDS and no wave waits for another: a lane reads the 64 codes (two 16-byte loads) and 4 scales of its row and half of the stage and
-// expands them where they are.  The order of the contraction elements inside a stage is the lane's own (step s, half h =
-// elements 64 h + 8 s ..), the same for both operands.  The waves' tiles are added in wave order through LDS.
-// The second launch adds the parts in order and Y = alpha A R_b^T + (T1 S_b) U_b^T in fp32.
+// passes through LDS and no wave waits for another: a lane reads the 64 codes (two 16-byte loads) and 4 scales of its row
+// and half of the stage and expands them where they are.  The order of the contraction elements inside a stage is the
+// lane's own (step s, half h = elements 64 h + 8 s ..), the same for both operands.  The waves' tiles are added in wave
+// order through LDS.  The second launch adds the parts in order and Y = alpha A R_b^T + (T1 S_b) U_b^T in fp32.
 // Bound by latency: 16 x 4096 x 4096 at rank 64 6.6 + 5.4 us (the general path's three kernels: 8.3 + 4.5 + 31 us), the whole
-// call 42 -> 15 us; 16 x 4096 x 14336 115 -> 20 us, 64 x 4096 x 14336 117 -> 32 us.  At 128 rows a CU spends its time on
-// reading and expanding A again for every 32 columns: 128 x 14336 x 4096 60 us against the general path's 47.  (One launch whose every workgroup forms T1 again was measured too: 32 x 4096 x 4096 at rank 64 16 us,
-// 16 x 4096 x 14336 41 us; two thirds of its vector instructions expanded V_b.)
+// call 42 -> 11 us in a graph; 16 x 4096 x 14336 114 -> 20 us, 64 x 4096 x 14336 116 -> 32 us.  At 128 rows a CU spends its
+// time on reading and expanding A again for every 32 columns: 128 x 14336 x 4096 60 us against the general path's 47.
+// (One launch whose every workgroup forms T1 again was measured too: 32 x 4096 x 4096 at rank 64 16 us, 16 x 4096 x 14336
+// 41 us; two thirds of its vector instructions expanded V_b.)
 #define DC_MAX_ROWS 64
 struct DecodeRaw {
     uint4 c0, c1;
@@ -1355,8 +1358,8 @@ __device__ __forceinline__ uint4 pack8_bf16(const float (&v)[8]) {
 // NCH = ceil(kb / 64): column groups of a row that hold T1-type columns
 template <int NCH>
 __global__ void __launch_bounds__(256)
-k_assemble_ext(int64_t Ma, int64_t Nb, int ka, int kb, int Kep, Fp4Operand Ra, Fp4Operand Rb, int64_t K, int Kt, const float* __restrict__ T1, int n1,
-               const float* __restrict__ Mk, int n3, const float* __restrict__ E2, int n2,
+k_assemble_ext(int64_t Ma, int64_t Nb, int ka, int kb, int Kep, Fp4Operand Ra, Fp4Operand Rb, int64_t K, int Kt,
+               const float* __restrict__ T1, int n1, const float* __restrict__ Mk, int n3, const float* __restrict__ E2, int n2,
                const uint8_t* __restrict__ ua_codes, const uint8_t* __restrict__ ua_scales, float g_ua,
                const float* __restrict__ Sa, const uint8_t* __restrict__ ub_codes,
                const uint8_t* __restrict__ ub_scales, float g_ub, const float* __restrict__ Sb,
@@ -1523,8 +1526,9 @@ LinWs lin_layout(int64_t Ma, int64_t Nb, int ka, int kb, int64_t Kc) {
     w.off_t1 = take((size_t)w.s1 * Ma * (kb > 0 ? kb : 1) * 4);
     w.off_mk = take((size_t)w.s3 * (ka > 0 ? ka : 1) * (kb > 0 ? kb : 1) * 4);
     w.off_e2 = take((size_t)w.s2 * Nb * (ka > 0 ? ka : 1) * 4);
-    w.off_aext = take((size_t)((Ma + 31) / 32 * 32) * (w.Kep + w.Kt > 0 ? w.Kep + w.Kt : 16) * 2);       // rows padded to whole 32-row blocks
-    w.off_bext = take((size_t)((Nb + 31) / 32 * 32) * (w.Kep + w.Kt > 0 ? w.Kep + w.Kt : 16) * 2);
+    const int ext = w.Kep + w.Kt > 0 ? w.Kep + w.Kt : 16;
+    w.off_aext = take((size_t)((Ma + 31) / 32 * 32) * ext * 2);       // rows padded to whole 32-row blocks
+    w.off_bext = take((size_t)((Nb + 31) / 32 * 32) * ext * 2);
     w.decode = decode_shape(Ma, Nb, ka, kb, Kc);
     const bool large = Ma >= 1024 && Nb >= 1024, whole = Kc % G_KI == 0 || w.Kt > 0;
     const int64_t niter = w.Kt > 0 ? Kc / G_KI : ceil_div64(Kc, G_KI);
@@ -1667,7 +1671,8 @@ NtOperand nt(const metis_fp4& R, const metis_fp4& Ut, const metis_fp4& Vt, const
 extern "C" size_t metis_linear_workspace_bytes(int64_t L, int64_t N, int64_t K, int k) {
     if (L < 1 || N < 1 || K < 1 || k < 0) return 0;
     // The operands' ranks may be any two up to k.  A layout grows with each of them, except that a skinny product of up to 64
-    // columns is cut into more parts than one of 65 to 128, and that unsplit operands take other kernels: the largest is at one of these.
+    // columns is cut into more parts than one of 65 to 128, and that unsplit operands take other kernels: the largest is at
+    // one of these.
     const int ranks[3] = {0, k < 64 ? k : 64, k};
     size_t most = 0;
     for (int ka : ranks)

@@ -55,7 +55,7 @@ __device__ __forceinline__ void chol_blocked(double* __restrict__ W, int ld, int
                              int32_t* __restrict__ info) {
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = nthr >> 6;
-    if (SMALL && n <= 4) {                               // (a 2 x 2 matrix as a panel: 16 columns, 3 us; the same operations on one lane)
+    if (SMALL && n <= 4) {                               // (the same operations on one lane; a panel's 16 columns take 3 us)
         if (tid == 0) {
             double l[4][4], rv[4];
 #pragma unroll
@@ -381,7 +381,8 @@ __host__ __device__ static inline int jacobi_ld(int n, int l) {
 //      vectors are far from orthogonal (coincident or tiny eigenvalues) the preconditioner is dropped
 //   7  W0 = L P                                         (fp64 matrix cores)
 // R1 holds L on entry (column-major, odd stride lda = n | 1: rows and columns both walk all banks); the result is left in
-// R2 in the sweeps' layout (stride ld, ne + 1 columns).  gscr: n * lda doubles of global scratch for L.  sa: 10*n + 40 doubles of LDS, 16-byte aligned.
+// R2 in the sweeps' layout (stride ld, ne + 1 columns).  gscr: n * lda doubles of global scratch for L.  sa: 10*n + 40 doubles
+// of LDS, 16-byte aligned.
 // ---------------------------------------------------------------------------------------
 __device__ __forceinline__ double wave_max(double x) {
 #pragma unroll
@@ -510,9 +511,10 @@ __device__ __forceinline__ bool eig_precondition(double* __restrict__ R1, double
     gram_to_R2(true);
     __syncthreads();
     // ---- 2: tridiagonalisation (lower).  Four waves, one per SIMD: a group of 8 lanes holds the rows g, g + 32, ..., lane
-    //         q of it their columns q, q+8, ... in registers.  What a step costs is instructions, and most of them (the reflector's scalars,
-    //         v and w by columns, reductions) are the same for every row, so few waves with several rows each beat ten waves
-    //         with one (n = 80: 77 us against 100; a lone wave issues an instruction every ~6.5 cycles, 360 a step).
+    //         q of it their columns q, q+8, ... in registers.  What a step costs is instructions, and most of them (the
+    //         reflector's scalars, v and w by columns, reductions) are the same for every row, so few waves with several rows
+    //         each beat ten waves with one (n = 80: 77 us against 100; a lone wave issues an instruction every ~6.5 cycles, 360
+    //         a step).
     //         Step j, two barriers: every wave forms the reflector's scalars and its own pieces of v from
     //         column j (xx) | p_r = A[r][:] v and the wave's share of v^T A v || rank-2 update, then column j+1
     //         with its squared norm for the next step.  xx and pp are kept zero up to row j (and from n up), so
@@ -890,7 +892,7 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk, int use_pre) {
     double* __restrict__ vec = prob.vec;
     double* __restrict__ tmat = prob.tmat;
     float* __restrict__ sval = prob.sval;
-    // (orders of 72 to 88 alone: see the launch)
+    // (orders of 72 to 84 alone: see the launch)
     double* __restrict__ gscr = NE == 5 || NE == 6 ? (use_pre ? prob.gscr : nullptr) : nullptr;
     const int ne = n + (n & 1);             // even number of columns (a zero column pads odd n)
     // Column stride = 8 (mod 16) doubles spreads the columns that one LDS instruction touches over the banks.
@@ -1185,8 +1187,9 @@ int launch_jacobi_eig_batch(hipStream_t s, const JacobiProblem* probs, int count
     const size_t rsize = (size_t)(ne + 1) * ld;
     const size_t small = ((size_t)ne / 2 + ne + 1) * sizeof(double) + (size_t)(3 * ne + 4) * sizeof(int) + 16;
     // the preconditioner needs two matrix-sized regions and 10 n + 40 doubles; it pays from n ~ 72 on (about 170 us
-    // against 8 of 9 sweeps of 46 us at n = 80; at n = 64 the plain sweeps, 120 to 170 us, are no slower), and its second region fits in
-    // the 160 KB of LDS up to n = 88.  It runs when every problem of the batch brings scratch.
+    // against 8 of 9 sweeps of 46 us at n = 80; at n = 64 the plain sweeps, 120 to 170 us, are no slower), and its second
+    // region fits in the 160 KB of LDS up to n = 84 (the column stride is 112 instead of 80 beyond order 80: 161.4 kB at 84, 165.2 at
+    // 85).  It runs when every problem of the batch brings scratch.
     size_t lds = rsize * sizeof(double) + small;
     const size_t lds_pre = 2 * rsize * sizeof(double) + small + (10 * (size_t)n + 44) * sizeof(double);
     bool all_scratch = count > 0;

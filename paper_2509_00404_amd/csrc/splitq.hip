@@ -420,7 +420,8 @@ int launch_residual_quant(hipStream_t s, const bf16_t* Ap, int64_t lda, int64_t 
                           uint8_t* codes, uint8_t* scales, uint8_t* ct, uint8_t* st_, float* R_debug, bool sr, uint64_t seed) {
     // Two workgroups per CU at a time, the number of column chunks that fills the last round of workgroups best.  Every workgroup
     // walks at least four 64-column steps (whole output lines, and the factors' fragments loaded once for them) while that leaves
-    // one for each CU, fewer in small matrices: 1360 x 1232 at rank 20, both orientations, 15.8 -> 7.4 us, 1024 x 4096 at rank 64 16 -> 11.
+    // one for each CU, fewer in small matrices: 1360 x 1232 at rank 20, both orientations, 15.8 -> 7.4 us, 1024 x 4096 at rank 64
+    // 16 -> 11.
     const int64_t row_blocks = ceil_div64(M, RQ_ROWS), steps = ceil_div64(N, RQ_COLS);
     int64_t run = 4;
     while (run > 1 && row_blocks * ceil_div64(steps, run) < 256) run /= 2;

@@ -85,13 +85,19 @@ def test_all_three_products(metis, L, N, K, kx, kw, kg, out_dtype):
     assert max(e) < tol, e
 
 
-@pytest.mark.parametrize("L,N,K,k", [(1104, 1040, 1280, 16),      # fwd: pipelined kernel with ragged edge tiles
-                                     (1280, 1152, 1024, 16),      # all three products on the pipelined kernel
-                                     (1024, 1024, 384, 0)])       # no factors, three 128-deep stages
+@pytest.mark.parametrize("L,N,K,k", [(1104, 1040, 1280, 16),      # sides just above 1024, ragged: 128 x 128 tiles in parts
+                                     (1280, 1152, 1024, 16),      # the same with whole tiles
+                                     (1024, 1024, 384, 0),        # no factors, three 128-deep stages
+                                     (2176, 2304, 2048, 16),      # pipelined, half-filled edge tiles
+                                     (2064, 2080, 2096, 24),      # pipelined, ragged edges, extra columns for the last 48, 32, 16 elements
+                                     (2176, 2304, 2176, 0)])      # pipelined, no factors
 @pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
 def test_large_tiles_pipelined_kernel(metis, L, N, K, k, out_dtype):
-    """Shapes of at least 1024 x 1024 outputs take the 256x256-tile software-pipelined kernel when the
-    contraction is a multiple of 128, the 8-wave kernel otherwise; both with edge tiles."""
+    """Outputs with both sides at least 1024: of more than 256 tiles of 128 x 128 the 256x256-tile software-pipelined kernel takes
+    all three products (the last three shapes); of fewer, the estimate of small_plan in csrc/gemm.hip decides, here for 128 x 128 tiles."""
+    if L > 2048:
+        for m, n in ((L, N), (L, K), (N, K)):
+            assert -(-m // 128) * -(-n // 128) > 256
     from paper_2509_00404_amd import workloads
     X = workloads.planted(L, K, workloads.power_law(min(L, K, 256), 1.2), 4, rms=1.0, outlier_cols=1)
     W = workloads.planted(N, K, workloads.power_law(min(N, K, 256), 1.0), 5, noise_top=0.01, rms=0.02)
@@ -117,11 +123,12 @@ def test_workspace_and_shape_errors(metis):
         metis.fp4_linear_dgrad(xs, ws, Y, torch.empty((1 << 20,), dtype=torch.uint8, device="cuda"))
 
 
-def test_two_phase_form_matches_the_single_calls(metis):
+@pytest.mark.parametrize("L,N,K,k", [(1152, 1280, 1024, 16),      # 128 x 128 tiles
+                                     (2064, 2080, 2096, 24)])     # the pipelined kernel, extra columns for the partial last stage
+def test_two_phase_form_matches_the_single_calls(metis, L, N, K, k):
     """metis_fp4_linear_phase: PREPARE of all three products first (own workspaces), then APPLY, gives bit for bit
     what the three single calls give; ALL is the single call; bad product / phase are refused."""
     from paper_2509_00404_amd import workloads
-    L, N, K, k = 1152, 1280, 1024, 16
     X = workloads.planted(L, K, workloads.power_law(min(L, K, 256), 1.2), 4, rms=1.0, outlier_cols=1)
     W = workloads.planted(N, K, workloads.power_law(min(N, K, 256), 1.0), 5, noise_top=0.01, rms=0.02)
     G = workloads.planted(L, N, workloads.power_law(min(L, N, 256), 2.0, head=4, head_gain=100.0), 6, rms=1e-3)

@@ -67,21 +67,32 @@ def test_stochastic_short_cut(metis, dtype, scale, g):
     _compare(out, oq.quantize_sr(t.double().numpy(), g, 5, oq.STREAM_SR))
 
 
+# fp32 takes the generic tiles, bf16 the row kernel, bf16 in both orientations the 128 x 128 tiles
 @pytest.mark.parametrize("special", [np.inf, -np.inf, np.nan])
-def test_non_finite_values_take_the_exact_path(metis, special):
-    # fp32 takes the generic kernel, bf16 the row kernel: both must give a saturated code and leave other blocks alone
-    x = torch.randn((64, 256))
+@pytest.mark.parametrize("dtype,M,N,both", [(torch.float32, 64, 256, False), (torch.float32, 64, 256, True),
+                                            (torch.bfloat16, 64, 256, False), (torch.bfloat16, 64, 256, True),
+                                            (torch.bfloat16, 2048, 2048, True)])
+def test_non_finite_values_take_the_exact_path(metis, special, dtype, M, N, both):
+    """A non-finite element gets a saturated code and leaves every other block alone, codes and scales, in both orientations."""
+    x = torch.randn((M, N), generator=torch.Generator().manual_seed(N)).to(dtype)
     x[3, 37] = float(special)
-    ref = metis.Fp4Tensor(64, 256, 2.0 ** -9)
-    metis.quantize_sr(torch.nan_to_num(x, nan=0.0, posinf=0.0, neginf=0.0).cuda(), 11, ref)
-    got = metis.Fp4Tensor(64, 256, 2.0 ** -9)
-    metis.quantize_sr(x.cuda(), 11, got)
+    clean = torch.nan_to_num(x, nan=0.0, posinf=0.0, neginf=0.0)
+    outs = []
+    for t in (clean, x):
+        o, ot = metis.Fp4Tensor(M, N, 2.0 ** -9), metis.Fp4Tensor(N, M, 2.0 ** -9) if both else None
+        metis.quantize_sr(t.cuda(), 11, o, ot)
+        outs.append((o, ot))
     torch.cuda.synchronize()
-    a, b = got.codes.cpu().numpy(), ref.codes.cpu().numpy()
-    code = (a[3, 18] >> 4) & 7
-    assert code == 7                                          # magnitude 6
-    a[3, 16:24] = b[3, 16:24]
-    assert np.array_equal(a, b)
+    for ref, got, (r, c) in zip(*outs, ((3, 37), (37, 3))):
+        if got is None:
+            continue
+        codes, scales = got.codes.cpu().numpy(), got.scales.cpu().numpy()
+        assert (codes[r, c // 2] >> (4 * (c % 2))) & 7 == 7                   # magnitude 6
+        block = c // 16
+        codes[r, 8 * block:8 * block + 8] = ref.codes.cpu().numpy()[r, 8 * block:8 * block + 8]
+        scales[r, block] = ref.scales.cpu().numpy()[r, block]
+        assert np.array_equal(codes, ref.codes.cpu().numpy())
+        assert np.array_equal(scales, ref.scales.cpu().numpy())
 
 
 # thin matrices on both sides of the lines between the two tile kernels: 48 and 80 rows, 32 columns

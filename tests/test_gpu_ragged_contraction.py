@@ -1,6 +1,6 @@
 """GPU parity of large products whose contraction is not a multiple of the 128-deep stage: the last elements travel
-as extra bf16 columns of the pipelined kernel (exact), or, for two unsplit operands without a workspace, through the
-bounds-checked staging.  Same bars as tests/test_gpu_linear.py."""
+as extra bf16 columns (exact) of whichever kernel takes the output, the pipelined one or 128 x 128 tiles, or, for two unsplit
+operands without a workspace, through the bounds-checked staging.  Same bars as tests/test_gpu_linear.py."""
 import pytest
 import torch
 
@@ -12,10 +12,11 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("L,N,K,kx,kw,kg", [
-    (1040, 1072, 1264, 16, 24, 8),      # residues 16, 48, 112 over the three contractions
+    (1040, 1072, 1264, 16, 24, 8),      # residues 16, 48, 112 over the three contractions; 128 x 128 tiles, as the next two
     (1136, 1088, 1040, 0, 20, 0),       # one operand unsplit, 4 extra low-rank pad columns
     (1024, 1024, 144, 16, 16, 16),      # a single whole stage and one block
-    (3056, 1520, 1040, 72, 80, 64),     # more than 64 low-rank columns a side
+    (3056, 1520, 1040, 72, 80, 64),     # more than 64 low-rank columns a side; the forward product pipelined
+    (2192, 2064, 2160, 16, 0, 72),      # all three pipelined: residues 112, 16, 16, one operand unsplit
 ])
 @pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
 def test_partial_last_stage(metis, L, N, K, kx, kw, kg, out_dtype):  # noqa: F811

@@ -1,5 +1,5 @@
 """The small factorizations at the orders where their tiles end: Cholesky panels of 16 columns (one below, at, and one
-above a multiple), the eigenvector preconditioner's range of 72 to 88, its neighbours, and the largest orders; repeated and
+above a multiple), the eigenvector preconditioner's range of 72 to 84, its neighbours, and the largest orders; repeated and
 vanishing singular values (the preconditioner's fallback).  Bars of tests/test_gpu_decompose.py."""
 import numpy as np
 import pytest
@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("k,p", [(1, 1), (8, 7), (16, 1), (17, 14), (31, 2), (48, 16), (49, 16), (63, 8), (64, 8), (65, 8),
-                                 (64, 15), (65, 15), (65, 16), (72, 15), (80, 8), (81, 8), (90, 5), (95, 1)])
+                                 (64, 15), (65, 15), (65, 16), (76, 8), (77, 8), (72, 15), (80, 8), (81, 8), (90, 5), (95, 1)])
 def test_orders_at_the_edges_of_tiles(metis, k, p):  # noqa: F811
     M, N = 512, 256
     s = 50.0 * np.arange(1, N + 1) ** -1.1 + 0.02

@@ -1,6 +1,6 @@
-"""GPU parity of products with few rows (at most 64 rows of an unsplit operand) and of small outputs
-whose contraction is cut into parts; with the bars of tests/test_gpu_linear.py, at edges of the 32-row / 32-column
-tiles, the 128-deep stages and the 32-column groups of the low-rank part."""
+"""GPU parity of products with few rows (at most 64 rows of an unsplit operand, on their own kernels or past the lines to the
+general ones) and of small outputs whose contraction is cut into parts; with the bars of tests/test_gpu_linear.py, at edges of
+the 32-row / 32-column tiles, the 128-deep stages and the 32-column groups of the low-rank part, and at output widths of any size."""
 import pytest
 import torch
 
