@@ -781,10 +781,11 @@ int launch_gemm_tile(hipStream_t s, const Fp4Operand& a, const Fp4Operand& b, in
 // How an output of at most 256 tiles of the bounds-checked kernel is produced, by estimates (in us) that were fitted to
 // measurements at rank 64 on 256 CUs (a constant here: the workspace's size is asked for without a device, too):
 //   - small tiles (128 x 128 for large sides): a 128-deep stage takes 1.4 us (expansion bound, 1.15 per workgroup once a CU holds
-//     several; 0.85 and 0.66 for tiles with a side of 64), the rest 8.  Few tiles leave most CUs idle while each walks its whole
-//     contraction: the contraction is cut into parts where that costs less than it saves, a launch of 3.5 and 6 bytes of traffic per
-//     element and part at ~4 TB/s.  Where the whole call would be one short launch (lone: no extra columns; a side of 64) the second
-//     one also costs the host 2 us (64 x 4096 x 1024: cut 9.4 us in a graph, 11.5 call after call; whole 10.6 both);
+//     several; 0.82 to 0.95, and 0.66, for tiles with a side of 64), the rest 8.  Few tiles leave most CUs idle while each walks
+//     its whole contraction: the contraction is cut into parts where that costs less than it saves, a launch of 3.5 and 6 bytes of
+//     traffic per element and part at ~4 TB/s.  Where the whole call would be one short launch (lone: no extra columns; a side of
+//     64) the second one also costs the host 2.5 us (64 x 4096 x 1024: cut 9.4 us in a graph, 11.5 call after call; whole 10.6
+//     both);
 //   - both sides at least 1024: the pipelined kernel's 256 x 256 tiles, 3.3 per stage of a tile cut into `pipe_parts`, the rest 13,
 //     a launch of 3 and the sum of its parts.
 // 4096 x 1024: K = 1024 43 -> 20 (small tiles, whole), K = 4096 59 -> 52, K = 14336 stays pipelined (119; small tiles 157);
@@ -804,7 +805,7 @@ SmallPlan small_plan(int64_t M, int64_t N, int64_t niter, int pipe_parts, bool l
     const double mn = (double)M * (double)N;
     double best_t = pipe_parts > 0 ? 16.0 + 3.3 * (double)ceil_div64(niter, pipe_parts) + pipe_parts * mn * 1e-6 : 1e30;
     const bool half = bm * bn < 128 * 128;
-    const double one = half ? 0.85 : 1.4, many = half ? 0.66 : 1.15, launch = lone && half ? 5.5 : 3.5;
+    const double one = half ? 0.95 : 1.4, many = half ? 0.66 : 1.15, launch = lone && half ? 6.0 : 3.5;
     for (int p = 1; p <= 16 && (p == 1 || 2 * p <= niter); ++p) {
         const int64_t ips = ceil_div64(niter, p);
         if (ceil_div64(niter, ips) != p) continue;                       // no empty part
