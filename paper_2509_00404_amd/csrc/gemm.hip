@@ -1248,38 +1248,47 @@ __device__ __forceinline__ float fp4_elem_nog(const uint8_t* codes, const uint8_
 // Blocks [0, ceil(Ma/32)) build 32 rows of Aext each: the dequantized factor rows U_a and the small matrix
 // Sa Mk sit in LDS; thread (row t/8, column group t%8) owns the columns 64 h + 8 (t%8) + 0..7 of its row.  The
 // remaining blocks build 32 rows of Bext each the same way.  The kernel moves little data and is bound by
-// load latency: the loads of all parts of a sum are issued before the first use, and four workgroups share a CU.  Both count:
-// with the loads of T1 and Mk in one trip as well (220 registers, two workgroups per CU) 4096 rows a side at rank 64 took the
-// same 33.0 us with the skinny products before it, and 100352 rows of an output layer behind 128 tokens 24.6 instead of 18.5.
+// load latency: the loads of all parts of a sum are issued before the first use, and four workgroups share a CU.  TRIP: those of T1
+// and Mk together (220 registers, two workgroups per CU), for calls whose workgroups fit like that, see assemble_in_one_trip.
 #define AX_ROWS 32
 
 // acc[i] += sum over parts p < n <= NP of base[p * pstride + off + i], i < 8, 16-byte aligned: all loads issued, then added in
 // ascending order (a missing part re-reads the last one with weight 0)
 template <int NP>
-__device__ __forceinline__ void sum_parts8_vec(const float* __restrict__ base, size_t pstride, int n, size_t off, float (&acc)[8]) {
+struct Parts8 {
     float4 lo[NP], hi[NP];
+};
+template <int NP>
+__device__ __forceinline__ Parts8<NP> load_parts8(const float* __restrict__ base, size_t pstride, int n, size_t off) {
+    Parts8<NP> r;
 #pragma unroll
     for (int u = 0; u < NP; ++u) {
         const float* q = base + (size_t)(u < n ? u : n - 1) * pstride + off;
-        lo[u] = *reinterpret_cast<const float4*>(q);
-        hi[u] = *reinterpret_cast<const float4*>(q + 4);
+        r.lo[u] = *reinterpret_cast<const float4*>(q);
+        r.hi[u] = *reinterpret_cast<const float4*>(q + 4);
     }
+    return r;
+}
+template <int NP>
+__device__ __forceinline__ void add_parts8(const Parts8<NP>& r, int n, float (&acc)[8]) {
 #pragma unroll
     for (int u = 0; u < NP; ++u) {
         const float w = u < n ? 1.0f : 0.0f;
-        acc[0] = fmaf(w, lo[u].x, acc[0]); acc[1] = fmaf(w, lo[u].y, acc[1]);
-        acc[2] = fmaf(w, lo[u].z, acc[2]); acc[3] = fmaf(w, lo[u].w, acc[3]);
-        acc[4] = fmaf(w, hi[u].x, acc[4]); acc[5] = fmaf(w, hi[u].y, acc[5]);
-        acc[6] = fmaf(w, hi[u].z, acc[6]); acc[7] = fmaf(w, hi[u].w, acc[7]);
+        acc[0] = fmaf(w, r.lo[u].x, acc[0]); acc[1] = fmaf(w, r.lo[u].y, acc[1]);
+        acc[2] = fmaf(w, r.lo[u].z, acc[2]); acc[3] = fmaf(w, r.lo[u].w, acc[3]);
+        acc[4] = fmaf(w, r.hi[u].x, acc[4]); acc[5] = fmaf(w, r.hi[u].y, acc[5]);
+        acc[6] = fmaf(w, r.hi[u].z, acc[6]); acc[7] = fmaf(w, r.hi[u].w, acc[7]);
     }
 }
 
 // acc[i] += sum over parts p < n <= 8 of base[p * pstride + off + i], i < cnt <= 8 (vec: cnt = 8 and 16-byte aligned).
+// FOUR: sums of up to four parts load no more than those (a branch that the one-trip form, with eight parts as a rule, goes without)
+template <bool FOUR>
 __device__ __forceinline__ void sum_parts8(const float* __restrict__ base, size_t pstride, int n, size_t off, int cnt,
                                            bool vec, float (&acc)[8]) {
     if (vec) {
-        if (n <= 4) sum_parts8_vec<4>(base, pstride, n, off, acc);       // (uniform)
-        else sum_parts8_vec<8>(base, pstride, n, off, acc);
+        if (FOUR && n <= 4) add_parts8(load_parts8<4>(base, pstride, n, off), n, acc);       // (uniform)
+        else add_parts8(load_parts8<8>(base, pstride, n, off), n, acc);
         return;
     }
     for (int p0 = 0; p0 < n; p0 += 4) {
@@ -1357,7 +1366,7 @@ __device__ __forceinline__ uint4 pack8_bf16(const float (&v)[8]) {
 }
 
 // NCH = ceil(kb / 64): column groups of a row that hold T1-type columns
-template <int NCH>
+template <int NCH, bool TRIP>
 __global__ void __launch_bounds__(256)
 k_assemble_ext(int64_t Ma, int64_t Nb, int ka, int kb, int Kep, Fp4Operand Ra, Fp4Operand Rb, int64_t K, int Kt,
                const float* __restrict__ T1, int n1, const float* __restrict__ Mk, int n3, const float* __restrict__ E2, int n2,
@@ -1380,23 +1389,41 @@ k_assemble_ext(int64_t Ma, int64_t Nb, int ka, int kb, int Kep, Fp4Operand Ra, F
         for (int h = 0; h < NCH; ++h)
 #pragma unroll
             for (int i = 0; i < 8; ++i) t1[h][i] = 0.0f;
-        // this thread's sums of the T1 parts
+        if constexpr (TRIP) {
+            // every group of 8 is whole, aligned and inside one row of Mk
+            const int c0 = 8 * cg < kb ? 8 * cg : 0, ea = 8 * tid < nmk ? 8 * tid : 0, eb = 8 * tid + 2048 < nmk ? 8 * tid + 2048 : 0;
+            const Parts8<8> pt = load_parts8<8>(T1, (size_t)Ma * kb, n1, (size_t)lrow * kb + c0);
+            const Parts8<8> pa = load_parts8<8>(Mk, (size_t)nmk, n3, (size_t)ea);
+            const Parts8<8> pb = load_parts8<8>(Mk, (size_t)nmk, n3, (size_t)eb);
+            const float fa = g_ua * Sa[ea / kb], fb = g_ua * Sa[eb / kb];
+            float ma[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f}, mb[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+            add_parts8(pt, n1, t1[0]);
+            add_parts8(pa, n3, ma);
+            add_parts8(pb, n3, mb);
 #pragma unroll
-        for (int h = 0; h < NCH; ++h) {
-            const int c0 = 64 * h + 8 * cg;
-            if (c0 < kb && n1 > 0) {
-                const int cnt = kb - c0 < 8 ? kb - c0 : 8;
-                sum_parts8(T1, (size_t)Ma * kb, n1, (size_t)lrow * kb + c0, cnt, cnt == 8 && kb % 4 == 0, t1[h]);
+            for (int i = 0; i < 8; ++i) {
+                if (8 * tid < nmk) mk[ea + i] = ma[i] * fa;
+                if (8 * tid + 2048 < nmk) mk[eb + i] = mb[i] * fb;
             }
-        }
-        // Sa Mk (with U_a's tensor scale) into LDS, the parts added on the way
-        for (int e0 = 8 * tid; e0 < nmk; e0 += 8 * 256) {
-            float m[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-            const int cnt = nmk - e0 < 8 ? nmk - e0 : 8;
-            sum_parts8(Mk, (size_t)nmk, n3, (size_t)e0, cnt, cnt == 8 && nmk % 4 == 0, m);
+        } else {
+            // this thread's sums of the T1 parts
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (i < cnt) mk[e0 + i] = m[i] * g_ua * Sa[(e0 + i) / kb];
+            for (int h = 0; h < NCH; ++h) {
+                const int c0 = 64 * h + 8 * cg;
+                if (c0 < kb && n1 > 0) {
+                    const int cnt = kb - c0 < 8 ? kb - c0 : 8;
+                    sum_parts8<true>(T1, (size_t)Ma * kb, n1, (size_t)lrow * kb + c0, cnt, cnt == 8 && kb % 4 == 0, t1[h]);
+                }
+            }
+            // Sa Mk (with U_a's tensor scale) into LDS, the parts added on the way
+            for (int e0 = 8 * tid; e0 < nmk; e0 += 8 * 256) {
+                float m[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+                const int cnt = nmk - e0 < 8 ? nmk - e0 : 8;
+                sum_parts8<true>(Mk, (size_t)nmk, n3, (size_t)e0, cnt, cnt == 8 && nmk % 4 == 0, m);
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if (i < cnt) mk[e0 + i] = m[i] * g_ua * Sa[(e0 + i) / kb];
+            }
         }
         decode_factor_rows(ua_codes, ua_scales, Ma, ka, r0, ua, tid);
         __syncthreads();
@@ -1455,7 +1482,7 @@ k_assemble_ext(int64_t Ma, int64_t Nb, int ka, int kb, int Kep, Fp4Operand Ra, F
         const int lo = c0 > kb ? c0 : kb, hi = c0 + 8 < kb + ka ? c0 + 8 : kb + ka;
         if (lo < hi && n2 > 0) {
             const int cnt = hi - lo;
-            sum_parts8(E2, (size_t)Nb * ka, n2, (size_t)lrow * ka + (lo - kb), cnt,
+            sum_parts8<!TRIP>(E2, (size_t)Nb * ka, n2, (size_t)lrow * ka + (lo - kb), cnt,
                        cnt == 8 && ka % 4 == 0 && (lo - kb) % 4 == 0, e2[h]);
         }
     }
@@ -1486,6 +1513,14 @@ k_assemble_ext(int64_t Ma, int64_t Nb, int ka, int kb, int Kep, Fp4Operand Ra, F
         }
         *reinterpret_cast<uint4*>(Bext + ext_chunk(row >> 5, c0 >> 4, (c0 >> 3) & 1, rr, nsteps)) = pack8_bf16(v);
     }
+}
+
+// The form of k_assemble_ext whose loads are all in flight at once: both operands split, every group of 8 whole, aligned and inside
+// one row of Mk, and (nblk) few enough workgroups that two per CU hold them.  In a training step of 4096 x 1024 x 4096 at rank 64
+// (160 to 256 workgroups) a launch takes 15.8 us against 16.8; 128 x 50256 x 4096 at rank 64 (1575) whole 141 against 139,
+// 16 x 50256 x 4096 at rank 16 107 against 102.
+bool assemble_in_one_trip(int ka, int kb, int64_t nblk) {
+    return ka > 0 && kb > 0 && kb <= 64 && kb % 8 == 0 && ka * kb <= 2 * 8 * 256 && nblk <= 512;
 }
 
 struct NtOperand {            // one side of Abar Bbar^T: Abar = U diag(S) V^T + R, R [rows, Kc]
@@ -1630,9 +1665,10 @@ int linear_nt(hipStream_t s, const NtOperand& a, const NtOperand& b, metis_mat* 
             }
             const int64_t nblk = ceil_div64(Ma, AX_ROWS) + ceil_div64(Nb, AX_ROWS);
             const size_t ax_lds = ((size_t)(AX_ROWS * ((ka > kb ? ka : kb) + 1) + 3) / 4 * 4 + (size_t)ka * kb + 8) * sizeof(float);
-            auto assemble = kb > 64 ? k_assemble_ext<2> : k_assemble_ext<1>;
-            static LdsLimitCache ax_set[2];
-            if (ax_lds > 48 * 1024 && !ensure_dyn_lds((const void*)assemble, ax_lds, ax_set[kb > 64])) return METIS_HIP_ERROR;
+            const int form = assemble_in_one_trip(ka, kb, nblk) ? 2 : kb > 64 ? 1 : 0;
+            auto assemble = form == 2 ? k_assemble_ext<1, true> : form == 1 ? k_assemble_ext<2, false> : k_assemble_ext<1, false>;
+            static LdsLimitCache ax_set[3];
+            if (ax_lds > 48 * 1024 && !ensure_dyn_lds((const void*)assemble, ax_lds, ax_set[form])) return METIS_HIP_ERROR;
             hipLaunchKernelGGL(assemble, dim3((unsigned)nblk), dim3(256), ax_lds, s, Ma, Nb, ka, kb, w.Kep,
                                Fp4Operand{a.R.codes, a.R.scales, Ma}, Fp4Operand{b.R.codes, b.R.scales, Nb}, Kc, w.Kt, T1,
                                w.s1, Mk, w.s3, E2, w.s2, a.Ut.codes, a.Ut.scales, ka > 0 ? a.Ut.tscale : 1.0f, a.S, b.Ut.codes,
