@@ -49,13 +49,13 @@ __device__ __forceinline__ double chol_rsqrt(double x) {
     return __builtin_fma(e * y, __builtin_fma(e, 0.375, 0.5), y);
 }
 
-// SMALL: n may be 4 or less.
+// SMALL: the order is at most 4.  (Its own instances of the kernels: behind a test the path cost every order 0.5 us a launch.)
 template <bool BAD_PIVOT_ZEROES, bool SMALL>
 __device__ __forceinline__ void chol_blocked(double* __restrict__ W, int ld, int n, double* __restrict__ rinv, double floor_,
                              int32_t* __restrict__ info) {
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = nthr >> 6;
-    if (SMALL && n <= 4) {                               // (the same operations on one lane; a panel's 16 columns take 3 us)
+    if constexpr (SMALL) {                               // (the same operations on one lane; a panel's 16 columns take 3 us)
         if (tid == 0) {
             double l[4][4], rv[4];
 #pragma unroll
@@ -202,6 +202,7 @@ __device__ __forceinline__ void chol_blocked(double* __restrict__ W, int ld, int
 // LDS: L [n][n+1] doubles, X [n][n+1] doubles.
 // ---------------------------------------------------------------------------------------
 #define CI_THREADS 512               // 256 registers per lane: the panels take 140
+template <bool SMALL>
 __global__ void __launch_bounds__(CI_THREADS)
 k_chol_inv(const CholBatch batch, int n) {
     extern __shared__ double sm[];
@@ -226,7 +227,7 @@ k_chol_inv(const CholBatch batch, int n) {
             X[p * ld + i] = 0.0;
         }
     __syncthreads();
-    chol_blocked<false, true>(L, ld, n, dinv, 0.0, info);
+    chol_blocked<false, SMALL>(L, ld, n, dinv, 0.0, info);
     if (wellcond_out && tid < 64) {
         double lo = dinv[tid < n ? tid : 0], hi = lo;
         if (tid + 64 < n) { lo = fmin(lo, dinv[tid + 64]); hi = fmax(hi, dinv[tid + 64]); }
@@ -882,7 +883,8 @@ __device__ __forceinline__ bool eig_precondition(double* __restrict__ R1, double
 // Deflation: a column that met every partner of a sweep without rotating is orthogonal (to tol)
 // to all the others, and rotations among the others keep it so; it leaves the tournament, and
 // the later sweeps run over the columns that still move.
-template <int NE, int JGL>
+// SMALL: n <= 4 (see chol_blocked).
+template <int NE, int JGL, bool SMALL = false>
 __global__ void __launch_bounds__(NE <= 4 ? 512 : 128 * NE)
 k_jacobi_eig(const JacobiBatch batch, int n, int kk, int use_pre) {
     extern __shared__ double sm[];
@@ -928,7 +930,7 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk, int use_pre) {
         __shared__ double rinv_sh[SM_MAX_N];
         double m = 0.0;                           // every wave finds the largest diagonal entry for itself
         for (int j = lane; j < n; j += 64) m = fmax(m, W[(size_t)j * ldc + j]);
-        chol_blocked<true, NE == 1>(W, ldc, n, rinv_sh, wave_max(m) * 1e-30, nullptr);
+        chol_blocked<true, SMALL>(W, ldc, n, rinv_sh, wave_max(m) * 1e-30, nullptr);
     }
     const double tol2 = 1e-14, floor2 = 1e-28;
     double amax = 0.0;
@@ -1168,13 +1170,14 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk, int use_pre) {
 int launch_chol_inv_batch(hipStream_t s, const CholProblem* probs, int count, int n) {
     if (n < 1 || n > SM_MAX_CHOL || count < 0) return METIS_UNSUPPORTED;
     size_t lds = 2 * (size_t)n * (n + 1) * sizeof(double);
-    static LdsLimitCache lds_set;
-    if (!ensure_dyn_lds((const void*)k_chol_inv, lds, lds_set)) return METIS_HIP_ERROR;
+    auto kern = n <= 4 ? k_chol_inv<true> : k_chol_inv<false>;
+    static LdsLimitCache lds_set[2];
+    if (!ensure_dyn_lds((const void*)kern, lds, lds_set[n <= 4])) return METIS_HIP_ERROR;
     for (int b0 = 0; b0 < count; b0 += SM_MAX_BATCH) {
         const int nb = count - b0 < SM_MAX_BATCH ? count - b0 : SM_MAX_BATCH;
         CholBatch batch;
         for (int i = 0; i < SM_MAX_BATCH; ++i) batch.p[i] = probs[b0 + (i < nb ? i : 0)];
-        hipLaunchKernelGGL(k_chol_inv, dim3(nb), dim3(CI_THREADS), lds, s, batch, n);
+        hipLaunchKernelGGL(kern, dim3(nb), dim3(CI_THREADS), lds, s, batch, n);
         METIS_LAUNCH_CHECK();
     }
     return METIS_OK;
@@ -1206,14 +1209,14 @@ int launch_jacobi_eig_batch(hipStream_t s, const JacobiProblem* probs, int count
         const int nb = count - b0 < SM_MAX_BATCH ? count - b0 : SM_MAX_BATCH;
         JacobiBatch batch;
         for (int i = 0; i < SM_MAX_BATCH; ++i) batch.p[i] = probs[b0 + (i < nb ? i : 0)];
-#define JACOBI_CASE(NE, JGL)                                                                                  \
-    {                                                                                                         \
-        static LdsLimitCache lds_set;                                                                         \
-        if (!ensure_dyn_lds((const void*)k_jacobi_eig<NE, JGL>, lds, lds_set)) return METIS_HIP_ERROR;        \
-        hipLaunchKernelGGL((k_jacobi_eig<NE, JGL>), dim3(nb), dim3(threads), lds, s, batch, n, kk, use_pre);  \
+#define JACOBI_CASE(...)                                                                                          \
+    {                                                                                                             \
+        static LdsLimitCache lds_set;                                                                             \
+        if (!ensure_dyn_lds((const void*)k_jacobi_eig<__VA_ARGS__>, lds, lds_set)) return METIS_HIP_ERROR;        \
+        hipLaunchKernelGGL((k_jacobi_eig<__VA_ARGS__>), dim3(nb), dim3(threads), lds, s, batch, n, kk, use_pre);  \
     }
         switch ((n + 15) / 16) {
-            case 1: JACOBI_CASE(1, 16) break;
+            case 1: if (n <= 4) JACOBI_CASE(1, 16, true) else JACOBI_CASE(1, 16, false) break;
             case 2: JACOBI_CASE(2, 16) break;
             case 3: JACOBI_CASE(3, 16) break;
             case 4: JACOBI_CASE(4, 16) break;
