@@ -352,6 +352,47 @@ k_sum_output_parts(const float* __restrict__ P, int parts, int64_t MN, int64_t N
     store_out<OUT>(c, acc.x); store_out<OUT>(c + 1, acc.y); store_out<OUT>(c + 2, acc.z); store_out<OUT>(c + 3, acc.w);
 }
 
+// The block scales of both operands in fp16, in the order k_fp4_gemm_nt_stream reads them: 4 KiB for 256 rows and one unit of 128,
+// [64 rows][lane][4] dwords, the dword of lane 16 kg + r and t the scales of row 16 t + r's blocks 2 kg and 2 kg + 1.  (Fetched from the
+// rows themselves, 8 bytes from each, a unit's scales cost the address units twice what its codes do: 2922 against 2544 cycles
+// for 64 columns of a 256 x 256 tile; and the conversion of 32 pairs a unit is done once instead of in every tile.)
+// A thread takes one row and four units; rows past the end get zeros.
+#define GS_SCALES 4096                                   // bytes for 256 rows and one unit
+struct ScalePlan {
+    const uint8_t *scales_a, *scales_b;
+    int64_t rows_a, rows_b, sstride;
+    uint8_t *plan_a, *plan_b;
+    int blocks_a, blocks, niter;                         // of 256 rows: A's, both operands'; units
+    int first, count;                                    // workgroups of a shared launch
+};
+__device__ __forceinline__ void scale_plan_block(const ScalePlan& o, int index) {
+    const int by = index / o.blocks, bx = index - by * o.blocks;
+    const bool isb = bx >= o.blocks_a;
+    const uint8_t* scales = isb ? o.scales_b : o.scales_a;
+    uint8_t* plan = isb ? o.plan_b : o.plan_a;
+    const int64_t rows = isb ? o.rows_b : o.rows_a;
+    const int rb = bx - (isb ? o.blocks_a : 0), lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t row = 256 * (int64_t)rb + 64 * w + 16 * (lane & 3) + (lane >> 2);
+    uint2 x[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int u = 4 * by + i;
+        x[i] = row < rows && u < o.niter ? load8_any(scales + row * o.sstride + 8 * u) : make_uint2(0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int u = 4 * by + i;
+        if (u >= o.niter) break;
+        uint32_t* p = reinterpret_cast<uint32_t*>(plan + ((int64_t)rb * o.niter + u) * GS_SCALES + 1024 * w) + lane;
+        p[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8((int)x[i].x, 1.0f, false));
+        p[64] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8((int)x[i].x, 1.0f, true));
+        p[128] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8((int)x[i].y, 1.0f, false));
+        p[192] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8((int)x[i].y, 1.0f, true));
+    }
+}
+__global__ void __launch_bounds__(256)
+k_scale_plan(ScalePlan o) { scale_plan_block(o, (int)blockIdx.x); }
+
 // Up to three skinny products in one launch, each cut along the contraction into `splits` parts that are written
 // side by side (part z of problem q at P + z rows_a rows_b, plain stores): the consumer adds the parts in a fixed
 // order, so the result does not depend on the order in which workgroups finish.  128 x 64 tiles, 4 waves.
@@ -366,11 +407,16 @@ struct SkinnyProblem {
 struct SkinnyBatch {
     SkinnyProblem p[3];
     int count;
+    ScalePlan plan;          // workgroups plan.first .. (none if count is 0)
 };
 
 template <bool PART>
 __global__ void __launch_bounds__(256)
 k_fp4_skinny_batch(SkinnyBatch batch, int64_t K) {
+    if (batch.plan.count > 0 && (int)blockIdx.x >= batch.plan.first) {
+        scale_plan_block(batch.plan, (int)blockIdx.x - batch.plan.first);
+        return;
+    }
     int q = 0;
 #pragma unroll
     for (int i = 1; i < 3; ++i)
@@ -387,7 +433,8 @@ k_fp4_skinny_batch(SkinnyBatch batch, int64_t K) {
                                          it0, niter);
 }
 
-// Software-pipelined variant: 256 x 256 tile, 4 waves of 128 x 128 (16 accumulator tiles per wave,
+// Software-pipelined variant, for large outputs that are too few or too short for k_fp4_gemm_nt_stream, or whose caller brought no
+// room for its scale plan: 256 x 256 tile, 4 waves of 128 x 128 (16 accumulator tiles per wave,
 // one wave per SIMD).  Half as many code expansions per MFMA as the 8-wave kernel, so the matrix
 // cores rather than the vector ALUs bound it -- provided the matrix pipe never drains:
 //  * within a stage, the raw codes/scales of contraction step s+2 are read from LDS and step s+1
@@ -729,6 +776,40 @@ static size_t gemm_tail_bytes(int64_t M, int64_t N, int64_t K, int* parts_out = 
     return (size_t)tail * parts * 65536 * sizeof(float);
 }
 
+#include "gemm_stream.h"
+
+template <typename OUT>
+int launch_gemm_stream(hipStream_t s, const Fp4Operand& a, const Fp4Operand& b, int64_t K, const uint8_t* plan, const bf16_t* Aext,
+                       const bf16_t* Bext, int Ke, float alpha, OUT* C, int64_t ldc, float* partial, size_t partial_bytes) {
+    const int64_t tm = ceil_div64(a.rows, 256), tn = ceil_div64(b.rows, 256);
+    if (tm * tn > 0x7FFFFFFF) return METIS_UNSUPPORTED;
+    const int total = (int)(tm * tn);
+    int parts = 1, tail_first = total;
+    const size_t want = gemm_tail_bytes(a.rows, b.rows, K, &parts, &tail_first);
+    const bool split = want > 0 && partial && partial_bytes >= want;
+    if (!split) { parts = 1; tail_first = total; }
+    const int tail = total - tail_first;
+    const int items = tail_first + tail * parts;
+    const int cus = device_cu_count();
+    if (cus < 1) return METIS_HIP_ERROR;
+    dim3 grid((unsigned)(items < cus ? items : cus));
+    auto kern = k_fp4_gemm_nt_stream<OUT>;
+    static LdsLimitCache lds_set;
+    if (!ensure_dyn_lds((const void*)kern, GS_LDS, lds_set)) return METIS_HIP_ERROR;
+    const TileMap tmap = make_band_map(tm, tn, GS_BAND);
+    const bool vec = (uintptr_t)C % 16 == 0 && (ldc * sizeof(OUT)) % 16 == 0;
+    hipLaunchKernelGGL(kern, grid, dim3(256), GS_LDS, s, a, b, K, plan,
+                       plan + (size_t)tm * (K / G_KI) * GS_SCALES, Aext, Bext, Ke, alpha, C, ldc, vec, tmap, total, tail_first, parts,
+                       partial, items);
+    METIS_LAUNCH_CHECK();
+    if (split) {
+        hipLaunchKernelGGL(k_gemm_tail_sum<OUT>, dim3((unsigned)(tail * 8)), dim3(256), 0, s, partial, parts, tail_first, total,
+                           tmap, a.rows, b.rows, C, ldc);
+        METIS_LAUNCH_CHECK();
+    }
+    return METIS_OK;
+}
+
 template <typename OUT>
 int launch_gemm_pipe(hipStream_t s, const Fp4Operand& a, const Fp4Operand& b, int64_t K, const bf16_t* Aext,
                      const bf16_t* Bext, int Ke, float alpha, OUT* C, int64_t ldc, float* partial, size_t partial_bytes) {
@@ -855,7 +936,8 @@ bool tail_as_columns(int64_t M, int64_t N, int64_t K) { return M >= 1024 && N >=
 // ext_tail: the elements past the last whole stage are among the extra columns
 template <typename OUT>
 int launch_gemm(hipStream_t s, const metis_fp4& A, const metis_fp4& B, const bf16_t* Aext, const bf16_t* Bext, int Ke,
-                bool ext_tail, float alpha, OUT* C, int64_t ldc, float* partial = nullptr, size_t partial_bytes = 0) {
+                bool ext_tail, float alpha, OUT* C, int64_t ldc, float* partial = nullptr, size_t partial_bytes = 0,
+                const uint8_t* plan_room = nullptr) {
     const int64_t M = A.rows, N = B.rows, K = A.cols;
     const Fp4Operand a = {A.codes, A.scales, M}, b = {B.codes, B.scales, N};
     const int64_t niter = ext_tail ? K / G_KI : ceil_div64(K, G_KI);
@@ -873,6 +955,8 @@ int launch_gemm(hipStream_t s, const metis_fp4& A, const metis_fp4& B, const bf1
             if (plan.parts == 1) return launch_gemm_tile<2, 2, 2, 2, OUT>(s, a, b, K, niter, Aext, Bext, Ke, alpha, C, ldc);
             return launch_gemm_parts<2, 2, 2, 2, OUT>(s, a, b, K, niter, plan.parts, Aext, Bext, Ke, alpha, C, ldc, partial);
         }
+        if (plan_room)
+            return launch_gemm_stream<OUT>(s, a, b, K, plan_room, Aext, Bext, Ke, alpha, C, ldc, partial, partial_bytes);
         if (whole && (can_split || tiles > 128))
             return launch_gemm_pipe<OUT>(s, a, b, K, Aext, Bext, Ke, alpha, C, ldc, partial, partial_bytes);
         // an output of at most 128 tiles of 256 x 256 would leave half the CUs without work: 128 x 128 tiles
@@ -1523,6 +1607,18 @@ bool assemble_in_one_trip(int ka, int kb, int64_t nblk) {
     return ka > 0 && kb > 0 && kb <= 64 && kb % 8 == 0 && ka * kb <= 2 * 8 * 256 && nblk <= 512;
 }
 
+// Products for the streaming kernel (instead of the pipelined one).  It wants a workgroup on every CU, and work enough per CU to pay
+// for its start and the scale plan (lone: no extra columns, so that the plan is a launch of its own, ~5 us).  Measured call for call
+// against the pipelined kernel, at rank 64 / without factors: one round of tiles, 4096 x 4096, K = 2048 0.97 / 1.00 of its time, 4096
+// 0.95 / 0.98, 8192 0.92 / 0.94; two rounds, 8192 x 4096, K = 1024 1.00 / 1.04, 2048 0.95 / 0.99, 4096 0.91 / 0.96; four, 8192 x 8192,
+// K = 512 0.95 / 0.93, 4096 0.90 / 0.91; two with the second half empty, 2048 x 14336, K = 2048 0.95 / 1.02, 4096 0.95 / 1.00.  Fewer than
+// 256 tiles leave CUs idle, and the pipelined kernel then has the power to itself: 3072 x 4096, K = 4096 1.00 / 1.06.
+bool stream_shape(int64_t M, int64_t N, int64_t niter, bool lone) {
+    if (M < 1024 || N < 1024) return false;
+    const int64_t tiles = ceil_div64(M, 256) * ceil_div64(N, 256);
+    return tiles >= 256 && ceil_div64(tiles, 256) * niter >= (lone ? 64 : 32);
+}
+
 struct NtOperand {            // one side of Abar Bbar^T: Abar = U diag(S) V^T + R, R [rows, Kc]
     metis_fp4 R, Ut, Vt;      // Ut [k, rows], Vt [k, Kc]
     const float* S;
@@ -1530,7 +1626,7 @@ struct NtOperand {            // one side of Abar Bbar^T: Abar = U diag(S) V^T +
 };
 
 struct LinWs {
-    size_t off_t1, off_mk, off_e2, off_aext, off_bext, off_tail, tail_bytes, total;
+    size_t off_t1, off_mk, off_e2, off_aext, off_bext, off_tail, tail_bytes, off_plan, plan_bytes, total;
     int Kep;                 // low-rank columns, padded to 16
     int Kt;                  // columns of the last, partial contraction stage (0: none or not taken as columns)
     int s1, s2, s3;          // contraction parts of T1, E2, Mk
@@ -1553,8 +1649,16 @@ LinWs lin_layout(int64_t Ma, int64_t Nb, int ka, int kb, int64_t Kc) {
     LinWs w;
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes, 256); return at; };
-    w.Kep = (ka + kb + 15) / 16 * 16;
     w.Kt = tail_as_columns(Ma, Nb, Kc) ? (int)(Kc % G_KI) : 0;
+    const bool large = Ma >= 1024 && Nb >= 1024, whole = Kc % G_KI == 0 || w.Kt > 0;
+    const int64_t niter = w.Kt > 0 ? Kc / G_KI : ceil_div64(Kc, G_KI);
+    const SmallPlan plan = gemm_plan(Ma, Nb, niter, whole, ka + kb + w.Kt == 0);
+    w.Kep = (ka + kb + 15) / 16 * 16;
+    bool stream = whole && !plan.small && stream_shape(Ma, Nb, niter, ka + kb + w.Kt == 0);
+    if (stream && (w.Kep + w.Kt) % 32 != 0) {
+        if (w.Kep + 16 <= 256) w.Kep += 16;               // (the assembly kernel clears up to 256 columns)
+        else stream = false;
+    }
     // (the assembly kernel adds the parts up, two rounds of four loads at most)
     w.s1 = kb > 0 ? skinny_parts(Ma, kb, Kc, 8) : 1;
     w.s2 = ka > 0 ? skinny_parts(Nb, ka, Kc, 8) : 1;
@@ -1566,14 +1670,13 @@ LinWs lin_layout(int64_t Ma, int64_t Nb, int ka, int kb, int64_t Kc) {
     w.off_aext = take((size_t)((Ma + 31) / 32 * 32) * ext * 2);       // rows padded to whole 32-row blocks
     w.off_bext = take((size_t)((Nb + 31) / 32 * 32) * ext * 2);
     w.decode = decode_shape(Ma, Nb, ka, kb, Kc);
-    const bool large = Ma >= 1024 && Nb >= 1024, whole = Kc % G_KI == 0 || w.Kt > 0;
-    const int64_t niter = w.Kt > 0 ? Kc / G_KI : ceil_div64(Kc, G_KI);
-    const SmallPlan plan = gemm_plan(Ma, Nb, niter, whole, w.Kep + w.Kt == 0);
     const size_t parts_bytes = plan.parts > 1 ? (size_t)plan.parts * Ma * Nb * sizeof(float) : 0;
     if (w.decode) w.tail_bytes = decode_plan(Ma, Nb, kb, Kc).bytes;
     else if (large) w.tail_bytes = !whole ? 0 : plan.small ? parts_bytes : gemm_tail_bytes(Ma, Nb, Kc);
     else w.tail_bytes = parts_bytes;
     w.off_tail = take(w.tail_bytes);
+    w.plan_bytes = stream ? (size_t)(ceil_div64(Ma, 256) + ceil_div64(Nb, 256)) * niter * GS_SCALES : 0;
+    w.off_plan = take(w.plan_bytes);
     w.total = o;
     return w;
 }
@@ -1609,7 +1712,7 @@ int linear_nt(hipStream_t s, const NtOperand& a, const NtOperand& b, metis_mat* 
         if (!ws_fits) return METIS_WORKSPACE_TOO_SMALL;
         if (!ws_aligned) return METIS_INVALID_ARG;
     }
-    if (w.decode && workspace && workspace_bytes >= w.total && ws_aligned) {
+    if (w.decode && workspace && workspace_bytes >= w.off_plan && ws_aligned) {
         float* P = (float*)((char*)workspace + w.off_tail);
         // the kept factors, 9/16 byte per element of U_b and 4 per singular value, take the place of Bext: 2 bytes per element
         uint8_t* keep = (uint8_t*)workspace + w.off_bext;
@@ -1621,6 +1724,21 @@ int linear_nt(hipStream_t s, const NtOperand& a, const NtOperand& b, metis_mat* 
             st = launch_decode<float>(s, a.R, b.R, &b.Ut, &b.Vt, b.S, kb, P, keep, phase, (float*)out->ptr, out->ld);
         metis_prof_end(METIS_PROF_GEMM, pi, s);
         return st;
+    }
+    // room for the streaming kernel's scale plan, when the workspace has it (and the codes start on 16 bytes)
+    uint8_t* plan = nullptr;
+    ScalePlan sp{};
+    if (w.plan_bytes > 0 && workspace && workspace_bytes >= w.total && ws_aligned && (uintptr_t)a.R.codes % 16 == 0 &&
+        (uintptr_t)b.R.codes % 16 == 0) {
+        plan = (uint8_t*)workspace + w.off_plan;
+        sp.niter = (int)(Kc / G_KI);
+        sp.blocks_a = (int)ceil_div64(Ma, 256);
+        sp.blocks = sp.blocks_a + (int)ceil_div64(Nb, 256);
+        sp.scales_a = a.R.scales; sp.scales_b = b.R.scales;
+        sp.rows_a = Ma; sp.rows_b = Nb; sp.sstride = Kc / 16;
+        sp.plan_a = plan;
+        sp.plan_b = plan + (size_t)sp.blocks_a * sp.niter * GS_SCALES;
+        sp.count = sp.blocks * (int)ceil_div64(sp.niter, 4);
     }
     // (two unsplit operands work without a workspace: a partial last stage then takes the bounds-checked kernel)
     if (ka > 0 || kb > 0 || (w.Kt > 0 && ws_fits && ws_aligned)) {
@@ -1654,7 +1772,11 @@ int linear_nt(hipStream_t s, const NtOperand& a, const NtOperand& b, metis_mat* 
             if (ka > 0) add(b.R, a.Vt, E2, w.s2);
             if (ka > 0 && kb > 0) add(a.Vt, b.Vt, Mk, w.s3);
             for (int i = sb.count; i < 3; ++i) sb.p[i] = sb.count ? sb.p[0] : SkinnyProblem{};
+            sb.plan = sp;
+            sb.plan.first = wgs;
             if (sb.count > 0) {
+                wgs += sp.count;
+                sp.count = 0;                                // on its way
                 constexpr size_t lds = gemm_lds_bytes<128, 64>();
                 const bool part = Kc % G_KI != 0;
                 auto skinny = part ? k_fp4_skinny_batch<true> : k_fp4_skinny_batch<false>;
@@ -1680,19 +1802,23 @@ int linear_nt(hipStream_t s, const NtOperand& a, const NtOperand& b, metis_mat* 
         Aext = ae;
         Bext = be;
     }
+    if (plan && do_pre && sp.count > 0) {                    // no factors, no launch to share
+        hipLaunchKernelGGL(k_scale_plan, dim3((unsigned)sp.count), dim3(256), 0, s, sp);
+        METIS_LAUNCH_CHECK();
+    }
     // room for the partial tiles of a split last round, when the workspace has it
     float* partial = nullptr;
     size_t partial_bytes = 0;
-    if (w.tail_bytes > 0 && !w.decode && workspace && workspace_bytes >= w.total && ws_aligned) {
+    if (w.tail_bytes > 0 && !w.decode && workspace && workspace_bytes >= w.off_plan && ws_aligned) {
         partial = (float*)((char*)workspace + w.off_tail);
         partial_bytes = w.tail_bytes;
     }
     if (!do_main) return METIS_OK;
     const int pi = metis_prof_begin(METIS_PROF_GEMM, s);
     if (out->dtype == METIS_BF16)
-        st = launch_gemm<bf16_t>(s, a.R, b.R, Aext, Bext, Ke, ext_tail, grr, (bf16_t*)out->ptr, out->ld, partial, partial_bytes);
+        st = launch_gemm<bf16_t>(s, a.R, b.R, Aext, Bext, Ke, ext_tail, grr, (bf16_t*)out->ptr, out->ld, partial, partial_bytes, plan);
     else
-        st = launch_gemm<float>(s, a.R, b.R, Aext, Bext, Ke, ext_tail, grr, (float*)out->ptr, out->ld, partial, partial_bytes);
+        st = launch_gemm<float>(s, a.R, b.R, Aext, Bext, Ke, ext_tail, grr, (float*)out->ptr, out->ld, partial, partial_bytes, plan);
     metis_prof_end(METIS_PROF_GEMM, pi, s);
     return st;
 }
