@@ -51,8 +51,8 @@ Layout make_layout(int64_t M, int64_t N, int k, int p, int64_t Ms) {
         // one region for the partial products of whichever split contraction is running (they run one after the
         // other): the sketch, the projection and the four Gram matrices; sized for the fast and the generic kernels
         const int64_t tiles_rr = ceil_div64(L.r, 32) * ceil_div64(L.r, 32), tiles_kk = ceil_div64(k, 32) * ceil_div64(k, 32);
-        const size_t zp = std::max(sketch_parts(Ms, N), dgemm_parts<EPI_PART_F64>(Ms, L.r, N, split_for(N, ceil_div64(Ms, 32) * ceil_div64(L.r, 32))));
-        const size_t bp = std::max(project_parts(Ms, N), dgemm_parts<EPI_PART_F64>(L.r, N, Ms, split_for(Ms, ceil_div64(L.r, 32) * ceil_div64(N, 32))));
+        const size_t zp = std::max(sketch_parts(Ms, N, L.r), dgemm_parts<EPI_PART_F64>(Ms, L.r, N, split_for(N, ceil_div64(Ms, 32) * ceil_div64(L.r, 32))));
+        const size_t bp = std::max(project_parts(Ms, N, L.r), dgemm_parts<EPI_PART_F64>(L.r, N, Ms, split_for(Ms, ceil_div64(L.r, 32) * ceil_div64(N, 32))));
         const size_t g1p = dgemm_parts<EPI_PART_F64>(L.r, L.r, Ms, split_for(Ms, tiles_rr));
         const size_t g2p = dgemm_parts<EPI_PART_F64>(L.r, L.r, N, split_for(N, tiles_rr));
         const size_t g3p = std::max((int)gram_blocks(M), dgemm_parts<EPI_PART_F64>(k, k, M, split_for(M, tiles_kk)));
@@ -350,7 +350,7 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
         int zp;
         if (j.fast) {
             if ((st = launch_sketch(s, j.A, j.lda, j.idx_use, j.Ms, j.N, j.om_use, r, j.parts)) != METIS_OK) return st;
-            zp = sketch_parts(j.Ms, j.N);
+            zp = sketch_parts(j.Ms, j.N, r);
         } else {
             launch_dgemm<bf16_t, bf16_t, EPI_PART_F64>(s, op(j.A, j.lda, 1, j.idx_use), op(j.om_use, 1, r), j.Ms, r, j.N,
                                                         split_for(j.N, tiles_zr), epi_part(j.parts, j.Ms, r));
@@ -389,7 +389,7 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
         int bp;
         if (j.fast) {
             if ((st = launch_project(s, j.H, j.H1, j.wellcond, r, j.A, j.lda, j.idx_use, j.Ms, j.N, j.parts)) != METIS_OK) return st;
-            bp = project_parts(j.Ms, j.N);
+            bp = project_parts(j.Ms, j.N, r);
         } else {
             const int want = split_for(j.Ms, ceil_div64(r, 32) * ceil_div64(j.N, 32));
             launch_dgemm<double, bf16_t, EPI_PART_F64>(s, op(j.H, 1, r), op(j.A, 1, j.lda, nullptr, j.idx_use), r, j.N, j.Ms,

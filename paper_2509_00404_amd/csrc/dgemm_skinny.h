@@ -6,11 +6,29 @@
 // accumulation is fp64 throughout.  The contraction is split over blockIdx.z; chunk z stores its partial
 // strip at part z of the output (parts Ms r resp. r N elements apart), and k_sum_parts_batch adds the parts in
 // a fixed order afterwards: no atomics, so the result does not depend on the order workgroups finish in.
+//
+// Bound by the fp64 matrix cores: a register loop of the instruction with the conversions beside it takes 84 cycles each (58
+// TFLOP/s; without them 74; nominal 64), these loops 88.  What the rest was spent on, 4096 x 4096 at 80 columns, of 65 us (sketch)
+// and 63: clearing LDS for columns that 80 = 5 x 16 does not have 2, SIMDs with four waves beside others with two, and one
+// operand read at a time 8: 57 and 63 now; of fp32 weight gradients at rank 64 58 -> 48 and 63 -> 50.  The partial strips (21 MB
+// here) and the launch are the other 10.
 #pragma once
 #include "dgemm.h"
 
 __device__ __forceinline__ double skinny_to_f64(bf16_t h) { return (double)__uint_as_float(((uint32_t)h) << 16); }
 __device__ __forceinline__ double skinny_to_f64(float x) { return (double)x; }
+
+// The order of 16 contraction elements' work: a matrix instruction (64 cycles), then two LDS reads of the next 16 and up to four vector
+// instructions, so that neither a read's latency nor a conversion ever stands between two matrix instructions.
+template <int NT>
+__device__ __forceinline__ void skinny_interleave() {
+#pragma unroll
+    for (int m = 0; m < 4 * NT; ++m) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+    }
+}
 
 // ---------------------------------------------------------------------------------------
 // Sketch: Z[m][j] += sum_k A[rowmap[m]][k] * Om[k][j],  m < Ms, j < r, k in the split's chunk.
@@ -19,6 +37,9 @@ __device__ __forceinline__ double skinny_to_f64(float x) { return (double)x; }
 //   Z   fp64 [ksplit][Ms][r] partial products
 // grid (1, ceil(Ms/64), ksplit), block 256: wave w owns rows 16w..16w+15 and all NT column tiles.
 // ---------------------------------------------------------------------------------------
+// Waves per SIMD of both kernels, and no more: the contraction is cut so that two workgroups share a CU, and with room for a third
+// wave some SIMDs get three and others one.
+#define SKINNY_WAVES 2
 #define SK_ROWS 64
 #define SK_KS 64                      // unit of the contraction split
 template <int NT, typename TA>
@@ -33,7 +54,7 @@ struct SketchCfg {
 };
 
 template <int NT, typename TA>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SKINNY_WAVES, SKINNY_WAVES)))
 k_sketch(const TA* __restrict__ A, int64_t lda, const uint32_t* __restrict__ rowmap, int64_t Ms, int64_t K,
          const bf16_t* __restrict__ Om, int r, int64_t kchunk, double* __restrict__ Z) {
     typedef SketchCfg<NT, TA> Cfg;
@@ -46,9 +67,11 @@ k_sketch(const TA* __restrict__ A, int64_t lda, const uint32_t* __restrict__ row
     const int64_t kend = kbeg + kchunk < K ? kbeg + kchunk : K;
     if (kbeg >= kend) return;
 
-    // the pad columns r .. 16 NT of the Omega stage stay zero
-    for (int e = tid; e < 2 * KS * LDO; e += 256) (&Os[0][0])[e] = 0;
-    __syncthreads();
+    // the pad columns r .. 16 NT of the Omega stage, if there are any, stay zero
+    if (r < 16 * NT) {
+        for (int e = tid; e < KS * LDO / 4; e += 256) reinterpret_cast<uint4*>(&Os[0][0])[e] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+    }
 
     // A pieces: 64 rows x 8 pieces, two per thread
     const TA* arow[2];
@@ -109,15 +132,32 @@ k_sketch(const TA* __restrict__ A, int64_t lda, const uint32_t* __restrict__ row
     for (int64_t kt = kbeg; kt < kend; kt += KS) {
         const bool more = kt + KS < kend;
         if (more) fetch(kt + KS);
-#pragma unroll 4
-        for (int s = 0; s < KS / 4; ++s) {
-            const int kr = 4 * s + (lane >> 4);
-            const double a = skinny_to_f64(As[buf][arow_l + kr]);
+        // 16 elements at a time: the operands of the next 16 are read while these are multiplied (see skinny_interleave)
+        constexpr int G = KS / 16;
+        TA ar[2][4];
+        bf16_t br[2][4][NT];
+        auto read = [&](int g, int n) __attribute__((always_inline)) {
 #pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                const double b = skinny_to_f64(Os[buf][kr * LDO + 16 * j + (lane & 15)]);
-                acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[j], 0, 0, 0);
+            for (int s = 0; s < 4; ++s) {
+                const int kr = 16 * g + 4 * s + (lane >> 4);
+                ar[n][s] = As[buf][arow_l + kr];
+#pragma unroll
+                for (int j = 0; j < NT; ++j) br[n][s][j] = Os[buf][kr * LDO + 16 * j + (lane & 15)];
             }
+        };
+        read(0, 0);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (g + 1 < G) read(g + 1, (g + 1) & 1);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const double a = skinny_to_f64(ar[g & 1][s]);
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, skinny_to_f64(br[g & 1][s][j]), acc[j], 0, 0, 0);
+            }
+            skinny_interleave<NT>();
         }
         if (more) stash(buf ^ 1);
         __syncthreads();
@@ -153,7 +193,7 @@ struct ProjectCfg {
 };
 
 template <int NT, typename TA>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SKINNY_WAVES, SKINNY_WAVES)))
 k_project(const double* __restrict__ H_main, const double* __restrict__ H_alt, const int32_t* __restrict__ use_alt, int r,
           const TA* __restrict__ A, int64_t lda, const uint32_t* __restrict__ rowmap, int64_t Ms, int64_t N,
           int64_t kchunk, double* __restrict__ B) {
@@ -170,8 +210,10 @@ k_project(const double* __restrict__ H_main, const double* __restrict__ H_alt, c
     const int64_t kend = kbeg + kchunk < Ms ? kbeg + kchunk : Ms;
     if (kbeg >= kend) return;
 
-    for (int e = tid; e < 2 * PJ_KS * LDH; e += 256) Hs[e] = 0.0;      // pad columns r .. 16 NT stay zero
-    __syncthreads();
+    if (r < 16 * NT) {                                                 // pad columns r .. 16 NT stay zero
+        for (int e = tid; e < PJ_KS * LDH; e += 256) reinterpret_cast<double2*>(Hs)[e] = make_double2(0.0, 0.0);
+        __syncthreads();
+    }
 
     // H pieces: 32 k-rows x r/2 pairs of doubles
     const int rc = r >> 1;
@@ -236,15 +278,33 @@ k_project(const double* __restrict__ H_main, const double* __restrict__ H_alt, c
         if (more) fetch(kt + PJ_KS);
         const double* hs = Hs + (size_t)buf * PJ_KS * LDH;
         const TA* as = As + buf * PJ_KS * PJ_LDA;
-#pragma unroll 4
-        for (int s = 0; s < PJ_KS / 4; ++s) {
-            const int kr = 4 * s + (lane >> 4);
-            const double b = skinny_to_f64(as[kr * PJ_LDA + wave * 16 + (lane & 15)]);
+        constexpr int G = PJ_KS / 16;
+        constexpr bool AHEAD = NT <= 6;                    // (two sets of operands for more would not fit the registers)
+        double ar[AHEAD ? 2 : 1][4][NT];
+        TA br[AHEAD ? 2 : 1][4];
+        auto read = [&](int g, int n) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < NT; ++i) {
-                const double a = hs[kr * LDH + 16 * i + (lane & 15)];
-                acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[i], 0, 0, 0);
+            for (int s = 0; s < 4; ++s) {
+                const int kr = 16 * g + 4 * s + (lane >> 4);
+                br[n][s] = as[kr * PJ_LDA + wave * 16 + (lane & 15)];
+#pragma unroll
+                for (int i = 0; i < NT; ++i) ar[n][s][i] = hs[kr * LDH + 16 * i + (lane & 15)];
             }
+        };
+        if (AHEAD) read(0, 0);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int c = AHEAD ? g & 1 : 0;
+            __builtin_amdgcn_sched_barrier(0);
+            if (!AHEAD) read(g, 0);
+            else if (g + 1 < G) read(g + 1, c ^ 1);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const double b = skinny_to_f64(br[c][s]);
+#pragma unroll
+                for (int i = 0; i < NT; ++i) acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[c][s][i], b, acc[i], 0, 0, 0);
+            }
+            skinny_interleave<NT>();
         }
         if (more) stash(buf ^ 1);
         __syncthreads();
@@ -260,12 +320,25 @@ k_project(const double* __restrict__ H_main, const double* __restrict__ H_alt, c
         }
 }
 
-// contraction split for ~768 workgroups, every split at least one stage deep
-static inline int64_t skinny_kchunk(int64_t K, int64_t tiles, int stage) {
-    int64_t want = ceil_div64(768, tiles), maxs = ceil_div64(K, stage);
-    int64_t ks = want < maxs ? want : maxs;
-    if (ks < 1) ks = 1;
-    return ceil_div64(ceil_div64(K, ks), stage) * stage;
+// Contraction split: the one with the least estimated time (us).  Two workgroups share a CU (256 of them a constant here: workspace
+// sizes are asked for without a device); a round of them takes 0.067 per contraction element and 80 columns (0.045 where CUs have one
+// only), 2 us besides, and every part costs its traffic, written and read once, at 4 TB/s.
+static inline int64_t skinny_kchunk(int64_t K, int64_t tiles, int stage, int64_t outputs, int r) {
+    const double per_k = 0.067 / 80.0 * (double)((r + 15) / 16 * 16);
+    double best_t = 1e30;
+    int64_t best = stage;
+    for (int64_t n = 1; n <= 64; ++n) {
+        const int64_t chunk = ceil_div64(ceil_div64(K, n), stage) * stage, parts = ceil_div64(K, chunk), wgs = tiles * parts;
+        const int64_t rounds = ceil_div64(wgs, 512);
+        const double t = (double)rounds * ((double)chunk * per_k * (wgs <= 256 ? 0.67 : 1.0) + 2.0) +
+                         (parts > 1 ? (double)parts : 0.0) * (double)outputs * 16.0 / 4e6;
+        if (t < best_t - 1e-9) {
+            best_t = t;
+            best = chunk;
+        }
+        if (chunk == stage) break;
+    }
+    return best;
 }
 
 // true when the fast kernels' layout preconditions hold
@@ -275,18 +348,16 @@ static inline bool skinny_ok(const TA* A, int64_t lda, int64_t N, int r) {
 }
 
 // number of partial products the two kernels write
-static inline int sketch_parts(int64_t Ms, int64_t K) {
-    return (int)ceil_div64(K, skinny_kchunk(K, ceil_div64(Ms, SK_ROWS), SK_KS));
-}
-static inline int project_parts(int64_t Ms, int64_t N) {
-    return (int)ceil_div64(Ms, skinny_kchunk(Ms, ceil_div64(N, PJ_COLS), PJ_KS));
-}
+static inline int64_t sketch_kchunk(int64_t Ms, int64_t K, int r) { return skinny_kchunk(K, ceil_div64(Ms, SK_ROWS), SK_KS, Ms * r, r); }
+static inline int64_t project_kchunk(int64_t Ms, int64_t N, int r) { return skinny_kchunk(Ms, ceil_div64(N, PJ_COLS), PJ_KS, N * r, r); }
+static inline int sketch_parts(int64_t Ms, int64_t K, int r) { return (int)ceil_div64(K, sketch_kchunk(Ms, K, r)); }
+static inline int project_parts(int64_t Ms, int64_t N, int r) { return (int)ceil_div64(Ms, project_kchunk(Ms, N, r)); }
 
-// Z = sketch_parts(Ms, K) partial products [Ms][r]
+// Z = sketch_parts(Ms, K, r) partial products [Ms][r]
 template <typename TA>
 static inline int launch_sketch(hipStream_t s, const TA* A, int64_t lda, const uint32_t* rowmap, int64_t Ms, int64_t K,
                                 const bf16_t* Om, int r, double* Z) {
-    const int64_t kchunk = skinny_kchunk(K, ceil_div64(Ms, SK_ROWS), SK_KS);
+    const int64_t kchunk = sketch_kchunk(Ms, K, r);
     dim3 grid(1, (unsigned)ceil_div64(Ms, SK_ROWS), (unsigned)ceil_div64(K, kchunk));
 #define SKETCH_CASE(NT)                                                                                          \
     hipLaunchKernelGGL((k_sketch<NT, TA>), grid, dim3(256), 0, s, A, lda, rowmap, Ms, K, Om, r, kchunk, Z);
@@ -305,11 +376,11 @@ static inline int launch_sketch(hipStream_t s, const TA* A, int64_t lda, const u
     return METIS_OK;
 }
 
-// B = project_parts(Ms, N) partial products [r][N]
+// B = project_parts(Ms, N, r) partial products [r][N]
 template <typename TA>
 static inline int launch_project(hipStream_t s, const double* H, const double* H_alt, const int32_t* use_alt, int r,
                                  const TA* A, int64_t lda, const uint32_t* rowmap, int64_t Ms, int64_t N, double* B) {
-    const int64_t kchunk = skinny_kchunk(Ms, ceil_div64(N, PJ_COLS), PJ_KS);
+    const int64_t kchunk = project_kchunk(Ms, N, r);
     dim3 grid((unsigned)ceil_div64(N, PJ_COLS), 1, (unsigned)ceil_div64(Ms, kchunk));
 #define PROJECT_CASE(NT)                                                                                         \
     {                                                                                                            \

@@ -103,13 +103,13 @@ FgLayout fg_layout(int64_t N, int64_t K, int k) {
     {
         // partial products of whichever split contraction is running (fast and generic kernels), added in a fixed order
         const int64_t tk = ceil_div64(k, 32);
-        const size_t tp = std::max(sketch_parts(N, K), dgemm_parts<EPI_PART_F64>(N, k, K, splits_for(K, ceil_div64(N, 32) * tk)));
-        const size_t vp = std::max(project_parts(N, K), dgemm_parts<EPI_PART_F64>(K, k, N, splits_for(N, ceil_div64(K, 32) * tk)));
+        const size_t tp = std::max(sketch_parts(N, K, k), dgemm_parts<EPI_PART_F64>(N, k, K, splits_for(K, ceil_div64(N, 32) * tk)));
+        const size_t vp = std::max(project_parts(N, K, k), dgemm_parts<EPI_PART_F64>(K, k, N, splits_for(N, ceil_div64(K, 32) * tk)));
         const size_t sp = dgemm_parts<EPI_PART_F64>(k, k, N, splits_for(N, tk * tk));
         size_t need = std::max(tp * (size_t)N * k, vp * (size_t)K * k);
         need = std::max(need, sp * (size_t)k * k);
         L.off_parts = take(need * 8);
-        L.off_parts2 = take((size_t)project_parts(N, K) * K * k * 8);     // the second product's, side by side with the first's
+        L.off_parts2 = take((size_t)project_parts(N, K, k) * K * k * 8);     // the second product's, side by side with the first's
     }
     L.total = o;
     return L;
@@ -172,10 +172,10 @@ int run(hipStream_t s, const TW* dW, int64_t ld, int64_t N, int64_t K, int k, co
         int st;
         // T = dW Vbar                  [N,k], contraction over K
         if ((st = launch_sketch(s, dW, ld, nullptr, N, K, Vbf, k, parts)) != METIS_OK) return st;
-        sums.add(parts, sketch_parts(N, K), N * (int64_t)k, N * (int64_t)k, T);
+        sums.add(parts, sketch_parts(N, K, k), N * (int64_t)k, N * (int64_t)k, T);
         // dV^T = (Ubar S)^T dW         [k,K], contraction over N
         if ((st = launch_project(s, H64, nullptr, nullptr, k, dW, ld, nullptr, N, K, parts2)) != METIS_OK) return st;
-        sums.add(parts2, project_parts(N, K), K * (int64_t)k, K * (int64_t)k, dV64);
+        sums.add(parts2, project_parts(N, K, k), K * (int64_t)k, K * (int64_t)k, dV64);
         sums.launch(s);
     } else {
         hipLaunchKernelGGL(k_dequant_factor, dim3((unsigned)ceil_div64((int64_t)k * K, 256)), dim3(256), 0, s, W->Vt.codes,
