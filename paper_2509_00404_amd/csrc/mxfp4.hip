@@ -81,11 +81,17 @@ k_quantize_mx(const T* __restrict__ A, int64_t ld, int64_t M, int64_t nblk /* co
 //  * fragments are double-buffered in registers: step s+1 is read from LDS while step s multiplies;
 //  * a wave issues in order and a matrix instruction holds its pipe for 32 cycles, so memory instructions of one
 //    wave leave the pipe idle while they issue: the second wave on the SIMD fills those gaps (four waves of
-//    128 x 128 need fewer LDS bytes per flop but reach 10 % less).
+//    128 x 128 need fewer LDS bytes per flop but reach 10 % less);
+//  * the tiles an XCD has in work share MX_BAND panels of B and 32 / MX_BAND of A (make_band_map);
+//  * accumulator tiles are transposed (B's fragment first): a lane then holds runs of four columns of one row, which go to whole
+//    lines by way of the finished stage's LDS, 16 bytes a lane (as 2-byte stores, half a line of two rows each, a tile took 128
+//    store instructions a wave instead of 16).  With the band order, quantizers included: 8192 x 14336 x 4096 330 -> 324 us, 8192 x
+//    4096 x 4096 fp32 118.5 -> 115.5, 2047 x 4096 x 4096 50.2 -> 46.1.
 // The stage body is branch-free (stage indices are clamped; the last stage loads and stores data nobody uses).
 #define MX_KI 256
 #define MX_CROW (MX_KI / 2 + 16)      // padded code row in LDS: 144 bytes, 16-byte reads of 8 consecutive rows hit 8 bank groups
 #define MX_SROW 8                     // the row's eight scale bytes of a stage
+#define MX_BAND 4                     // tiles side by side that an XCD has in work: 4 of B's panels and 8 of A's
 
 struct MxOperand {
     const uint8_t* codes;             // [rows, K/2]
@@ -93,12 +99,24 @@ struct MxOperand {
     int64_t rows;
 };
 
+// four neighbouring outputs of a row
+__device__ __forceinline__ void mx_put4(bf16_t* p, float x, float y, float z, float w) {
+    typedef __bf16 bf2_t __attribute__((ext_vector_type(2)));
+    typedef float f2_t __attribute__((ext_vector_type(2)));
+    const f2_t lo = {x, y}, hi = {z, w};
+    *reinterpret_cast<uvec2_t*>(p) = uvec2_t{__builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf2_t)),
+                                             __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, bf2_t))};
+}
+__device__ __forceinline__ void mx_put4(float* p, float x, float y, float z, float w) {
+    *reinterpret_cast<float4*>(p) = make_float4(x, y, z, w);
+}
+
 // TAIL: K is not a multiple of the 256-deep stage.  The last stage then exists only in part: its missing blocks of 32
 // enter as zero codes under a unit scale, and because scale rows are no longer 8-byte aligned every stage's scale
 // bytes are fetched one by one.
 template <typename OUT, bool TAIL>
 __global__ void __launch_bounds__(512)
-k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_t ldc, TileMap tmap) {
+k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_t ldc, bool vec, TileMap tmap) {
     constexpr int TM = 4, TN = 2, BM = 256, BN = 256, KS = MX_KI / 64, NV = 4;   // NV: 16-byte code vectors per thread, operand and stage
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     constexpr int OFF_CB = BM * MX_CROW, OFF_SA = (BM + BN) * MX_CROW, OFF_SB = OFF_SA + BM * MX_SROW,
@@ -220,8 +238,8 @@ k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_
             for (int j = 0; j < TN; ++j) {
                 const int8v_t b = {(int)fb[slot][j].x, (int)fb[slot][j].y, (int)fb[slot][j].z, (int)fb[slot][j].w, 0, 0, 0, 0};
                 // formats 4 = FP4 (E2M1) for both operands; the scale byte is byte `sel` of the shifted word
-                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc[i][j], 4, 4, sel, (int)sa[word][i],
-                                                                             sel, (int)sb[word][j]);
+                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(b, a, acc[i][j], 4, 4, sel, (int)sb[word][j],
+                                                                             sel, (int)sa[word][i]);
             }
         }
     };
@@ -259,23 +277,44 @@ k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_
         read_scales(bufn);
     }
 
-    const bool interior = m0 + BM <= A.rows && n0 + BN <= B.rows;
+    // The last stage's buffer is free: its codes and scales were in registers before the last meeting, and that stage stored to the
+    // other one.  Every wave stages 32 rows of its 64 columns at a time in a part of its own.
+    constexpr int E = 16 / (int)sizeof(OUT), LROW = 64 * (int)sizeof(OUT) + 16, UNITS = 64 / E, ROWS = 64 / UNITS;
+    static_assert(8 * 32 * LROW <= BUF, "the staged rows fit one buffer");
+    uint8_t* sm = lds + ((niter - 1) & 1) * BUF + wave * (32 * LROW);
+    const bool whole = vec && m0 + BM <= A.rows && n0 + BN <= B.rows;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i) {
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int64_t c = n0 + wn + 32 * j + li;
-            const int64_t rbase = m0 + wm + 32 * i + 4 * half;
-            if (interior) {
-                store_tile16<OUT>(C + rbase * ldc + c, ldc, acc[i][j], 1.0f);
-            } else {
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int64_t r = rbase + 8 * (v >> 2) + (v & 3);
-                    if (r < A.rows && c < B.rows) store_out<OUT>(C + r * ldc + c, acc[i][j][v]);
+            for (int v = 0; v < 16; v += 4)
+                mx_put4(reinterpret_cast<OUT*>(sm + li * LROW) + 32 * j + 2 * v + 4 * half, acc[i][j][v], acc[i][j][v + 1],
+                        acc[i][j][v + 2], acc[i][j][v + 3]);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int t = 0; t < 32 / ROWS; ++t) {
+            const int row = ROWS * t + lane / UNITS, unit = lane % UNITS;
+            const uint8_t* q = sm + row * LROW + 16 * unit;
+            const uvec4_t w = *reinterpret_cast<const uvec4_t*>(q);
+            const int64_t r = m0 + wm + 32 * i + row, c = n0 + wn + E * unit;
+            OUT* p = C + r * ldc + c;
+            if (whole) {
+                *reinterpret_cast<uvec4_t*>(p) = w;
+            } else if (r < A.rows) {
+                const int64_t left = B.rows - c;
+                if (vec && left >= E) {
+                    *reinterpret_cast<uvec4_t*>(p) = w;
+                } else {
+#pragma unroll 1
+                    for (int e = 0; e < E && e < left; ++e) p[e] = reinterpret_cast<const OUT*>(q)[e];
                 }
             }
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
 }
 
 constexpr size_t MX_LDS = 2 * (size_t)(256 + 256) * (MX_CROW + MX_SROW);
@@ -284,16 +323,18 @@ template <typename OUT>
 int launch_mx_gemm(hipStream_t s, const MxOperand& a, const MxOperand& b, int64_t K, OUT* C, int64_t ldc) {
     const int64_t tm = ceil_div64(a.rows, 256), tn = ceil_div64(b.rows, 256);
     if (tm * tn > 0x7FFFFFFF) return METIS_UNSUPPORTED;
+    const TileMap tmap = make_band_map(tm, tn, MX_BAND);
+    const bool vec = (uintptr_t)C % 16 == 0 && (ldc * sizeof(OUT)) % 16 == 0;
     if (K % MX_KI == 0) {
         auto kern = k_mxfp4_gemm_nt<OUT, false>;
         static LdsLimitCache lds_set;
         if (!ensure_dyn_lds((const void*)kern, MX_LDS, lds_set)) return METIS_HIP_ERROR;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn)), dim3(512), MX_LDS, s, a, b, K, C, ldc, make_tile_map(tm, tn));
+        hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn)), dim3(512), MX_LDS, s, a, b, K, C, ldc, vec, tmap);
     } else {
         auto kern = k_mxfp4_gemm_nt<OUT, true>;
         static LdsLimitCache lds_set;
         if (!ensure_dyn_lds((const void*)kern, MX_LDS, lds_set)) return METIS_HIP_ERROR;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn)), dim3(512), MX_LDS, s, a, b, K, C, ldc, make_tile_map(tm, tn));
+        hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn)), dim3(512), MX_LDS, s, a, b, K, C, ldc, vec, tmap);
     }
     METIS_LAUNCH_CHECK();
     return METIS_OK;

@@ -71,3 +71,22 @@ def test_rejects_bad_arguments(metis):
         metis.mxfp4_gemm_nt(qc, metis.MxTensor(32, 512), Cm)
     with pytest.raises(metis.MetisError):
         metis.quantize_mx(torch.zeros((64, 64), dtype=torch.float32, device="cuda"), qc)
+
+
+@pytest.mark.parametrize("M,N,K,ld_extra", [(257, 255, 256, 0), (255, 261, 288, 3), (33, 67, 96, 8), (512, 1283, 512, 1), (2305, 1288, 256, 0)])
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
+def test_mxfp4_gemm_rows_that_do_not_store_in_vectors(metis, M, N, K, ld_extra, out_dtype):
+    """Odd widths, rows of C that start off 16 bytes, last bands of 1 and 2 tile columns; nothing beside the rows is written.  The bars of
+    test_mxfp4_gemm_against_oracle."""
+    a, b = _data(M, K, 3, torch.bfloat16), _data(N, K, 4, torch.bfloat16)
+    qa, qb = metis.MxTensor(M, K), metis.MxTensor(N, K)
+    metis.quantize_mx(a.cuda(), qa)
+    metis.quantize_mx(b.cuda(), qb)
+    full = torch.full((M, N + ld_extra), float("nan"), dtype=out_dtype, device="cuda")
+    metis.mxfp4_gemm_nt(qa, qb, full[:, :N])
+    torch.cuda.synchronize()
+    ref = omx.mx_gemm_nt((qa.codes.cpu().numpy(), qa.scales.cpu().numpy()), (qb.codes.cpu().numpy(), qb.scales.cpu().numpy()))
+    got = full[:, :N].double().cpu().numpy()
+    assert np.isfinite(got).all()
+    assert rel_fro(got, ref) < (1e-5 if out_dtype == torch.float32 else 4e-3)
+    assert bool(torch.isnan(full[:, N:]).all())
