@@ -111,10 +111,16 @@ __device__ __forceinline__ void mx_put4(float* p, float x, float y, float z, flo
     *reinterpret_cast<float4*>(p) = make_float4(x, y, z, w);
 }
 
-// TAIL: K is not a multiple of the 256-deep stage.  The last stage then exists only in part: its missing blocks of 32
-// enter as zero codes under a unit scale, and because scale rows are no longer 8-byte aligned every stage's scale
-// bytes are fetched one by one.
-template <typename OUT, bool TAIL>
+// MODE: MX_WHOLE for K a multiple of the 256-deep stage.  Else the last stage exists only in part, and its missing blocks of 32 enter as
+// zero codes under a unit scale.  MX_TAIL: what is missing is put in on the way to LDS, where the data has arrived, so that
+// nothing waits for a load when it is issued; scale rows are not 8-byte aligned and are fetched 8 bytes at a time all the same, from
+// up to 7 bytes before where that would cross the operand's end.  MX_SHORT: K < 256, one stage and perhaps fewer than 8
+// scale bytes in all, fetched one by one.
+// (With the zeros and the scale bytes put together behind the load, in one kernel for both, 240 registers were spilled and a stage had no
+// load in flight; quantizers included: 8192 x 4096 x 4064 915 -> 118 us, where 4096 takes 117; 1000 x 1008 x 1248 187 -> 20.6.)
+typedef uint32_t mx_uvec2_any __attribute__((ext_vector_type(2), aligned(1)));
+enum { MX_WHOLE, MX_TAIL, MX_SHORT };
+template <typename OUT, int MODE>
 __global__ void __launch_bounds__(512)
 k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_t ldc, bool vec, TileMap tmap) {
     constexpr int TM = 4, TN = 2, BM = 256, BN = 256, KS = MX_KI / 64, NV = 4;   // NV: 16-byte code vectors per thread, operand and stage
@@ -161,10 +167,17 @@ k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_
     uvec4_t ra[NV], rb[NV];
     uvec2_t rs;
     auto clampst = [&](int st) { return st < niter ? st : niter - 1; };
+    auto seg_exists = [&](int st) __attribute__((always_inline)) { return 8u * st + (tid & 7) < sstride; };
+    // where the 8 scale bytes are fetched (K > 256: an operand has more than 8)
+    const uint32_t slast = (uint32_t)(tid < 256 ? A.rows : B.rows) * sstride - 8u;
+    auto scale_offset = [&](int st) __attribute__((always_inline)) {
+        const uint32_t o = (tid < 256 ? osga : osgb) + 8u * st;
+        return o < slast ? o : slast;
+    };
     auto load_stage = [&](int st) __attribute__((always_inline)) {
         const uint8_t* ca = A.codes + (size_t)st * (MX_KI / 2);
         const uint8_t* cb = B.codes + (size_t)st * (MX_KI / 2);
-        if (!TAIL) {
+        if (MODE == MX_WHOLE) {
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
                 ra[v] = *reinterpret_cast<const uvec4_t*>(ca + oa[v]);
@@ -172,29 +185,43 @@ k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_
             }
             rs = *reinterpret_cast<const uvec2_t*>((tid < 256 ? A.scales + osga : B.scales + osgb) + (size_t)st * (MX_KI / 32));
         } else {
-            // this lane's 16-byte segment is one block of 32 contraction elements: it exists or it does not
-            const bool seg_ok = (int64_t)st * MX_KI + 32 * (tid & 7) < K;
+            // this lane's 16-byte segment is one block of 32 contraction elements: if it does not exist the row's first is read
+            const uint32_t d = seg_exists(st) ? (uint32_t)st * (MX_KI / 2) : 0u - 16u * (tid & 7);
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                ra[v] = *reinterpret_cast<const uvec4_t*>(A.codes + (uint32_t)(oa[v] + d));
+                rb[v] = *reinterpret_cast<const uvec4_t*>(B.codes + (uint32_t)(ob[v] + d));
+            }
+            const uint8_t* sp = tid < 256 ? A.scales : B.scales;
+            if (MODE == MX_TAIL) {
+                rs = *reinterpret_cast<const mx_uvec2_any*>(sp + scale_offset(st));
+            } else {
+                const uint32_t o = tid < 256 ? osga : osgb;
+                uint32_t w[2] = {0u, 0u};
+#pragma unroll
+                for (int i = 0; i < 8; ++i) w[i >> 2] |= (uint32_t)sp[o + (i < (int)sstride ? i : 0)] << (8 * (i & 3));
+                rs.x = w[0];
+                rs.y = w[1];
+            }
+        }
+    };
+    auto store_stage = [&](uint8_t* buf, int st) __attribute__((always_inline)) {       // st: the stage that the registers hold
+        if (MODE != MX_WHOLE) {
+            const bool ok = seg_exists(st);
             const uvec4_t zero4 = {0u, 0u, 0u, 0u};
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
-                const uvec4_t xa = *reinterpret_cast<const uvec4_t*>(seg_ok ? ca + oa[v] : A.codes);
-                const uvec4_t xb = *reinterpret_cast<const uvec4_t*>(seg_ok ? cb + ob[v] : B.codes);
-                ra[v] = seg_ok ? xa : zero4;
-                rb[v] = seg_ok ? xb : zero4;
+                ra[v] = ok ? ra[v] : zero4;
+                rb[v] = ok ? rb[v] : zero4;
             }
-            const uint8_t* sp = tid < 256 ? A.scales + osga : B.scales + osgb;
-            const int64_t b0 = (int64_t)st * (MX_KI / 32), nb = K / 32;
-            uint32_t w[2] = {0u, 0u};
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const uint32_t byte = b0 + i < nb ? (uint32_t)sp[b0 + i] : 127u;          // 127 = scale 1 for an absent block
-                w[i >> 2] |= byte << (8 * (i & 3));
-            }
-            rs.x = w[0];
-            rs.y = w[1];
+            uint64_t w = (uint64_t)rs.y << 32 | rs.x;
+            if (MODE == MX_TAIL) w >>= 8 * ((tid < 256 ? osga : osgb) + 8u * st - scale_offset(st));
+            const int have = (int)sstride - 8 * st;                                     // >= 1; 127 = scale 1 for an absent block
+            const uint64_t absent = have < 8 ? ~0ull << (8 * have) : 0ull;
+            w = (w & ~absent) | (0x7F7F7F7F7F7F7F7Full & absent);
+            rs.x = (uint32_t)w;
+            rs.y = (uint32_t)(w >> 32);
         }
-    };
-    auto store_stage = [&](uint8_t* buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
             const int row = (tid >> 3) + 64 * v, seg = tid & 7;
@@ -245,7 +272,7 @@ k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_
     };
 
     load_stage(0);
-    store_stage(lds);
+    store_stage(lds, 0);
     __syncthreads();
     load_stage(clampst(1));
     read_codes(lds, 0, 0);
@@ -258,7 +285,7 @@ k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_
         read_codes(bufc, 1, 1);
         __builtin_amdgcn_sched_barrier(0);
         mma(std::integral_constant<int, 0>{});
-        store_stage(bufn);                        // stage it + 1 (loaded one stage ago) to the other buffer ...
+        store_stage(bufn, clampst(it + 1));                        // stage it + 1 (loaded one stage ago) to the other buffer ...
         load_stage(clampst(it + 2));              // ... and its registers take stage it + 2
         __builtin_amdgcn_sched_barrier(0);
         read_codes(bufc, 2, 0);
@@ -325,17 +352,16 @@ int launch_mx_gemm(hipStream_t s, const MxOperand& a, const MxOperand& b, int64_
     if (tm * tn > 0x7FFFFFFF) return METIS_UNSUPPORTED;
     const TileMap tmap = make_band_map(tm, tn, MX_BAND);
     const bool vec = (uintptr_t)C % 16 == 0 && (ldc * sizeof(OUT)) % 16 == 0;
-    if (K % MX_KI == 0) {
-        auto kern = k_mxfp4_gemm_nt<OUT, false>;
-        static LdsLimitCache lds_set;
-        if (!ensure_dyn_lds((const void*)kern, MX_LDS, lds_set)) return METIS_HIP_ERROR;
+    auto launch = [&](auto kern, LdsLimitCache& lds_set) {
+        if (!ensure_dyn_lds((const void*)kern, MX_LDS, lds_set)) return false;
         hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn)), dim3(512), MX_LDS, s, a, b, K, C, ldc, vec, tmap);
-    } else {
-        auto kern = k_mxfp4_gemm_nt<OUT, true>;
-        static LdsLimitCache lds_set;
-        if (!ensure_dyn_lds((const void*)kern, MX_LDS, lds_set)) return METIS_HIP_ERROR;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn)), dim3(512), MX_LDS, s, a, b, K, C, ldc, vec, tmap);
-    }
+        return true;
+    };
+    static LdsLimitCache lds_set[3];
+    const bool ok = K % MX_KI == 0 ? launch(k_mxfp4_gemm_nt<OUT, MX_WHOLE>, lds_set[0])
+                    : K > MX_KI    ? launch(k_mxfp4_gemm_nt<OUT, MX_TAIL>, lds_set[1])
+                                   : launch(k_mxfp4_gemm_nt<OUT, MX_SHORT>, lds_set[2]);
+    if (!ok) return METIS_HIP_ERROR;
     METIS_LAUNCH_CHECK();
     return METIS_OK;
 }

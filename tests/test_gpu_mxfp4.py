@@ -90,3 +90,24 @@ def test_mxfp4_gemm_rows_that_do_not_store_in_vectors(metis, M, N, K, ld_extra, 
     assert np.isfinite(got).all()
     assert rel_fro(got, ref) < (1e-5 if out_dtype == torch.float32 else 4e-3)
     assert bool(torch.isnan(full[:, N:]).all())
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 1, 32), (3, 2, 64), (1, 7, 224), (1, 1, 288), (2, 257, 480), (3, 5, 544), (257, 3, 1024 + 32)])
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
+def test_mxfp4_gemm_partial_last_stage(metis, M, N, K, out_dtype):
+    """One partial stage and a partial stage after whole ones, 1 to 7 blocks of 32 in it, operands of a few rows: the scale bytes of the last
+    row are fetched from before where they start.  The bars of test_mxfp4_gemm_against_oracle."""
+    a, b = _data(M, K, 5, torch.bfloat16), _data(N, K, 6, torch.bfloat16)
+    qa, qb = metis.MxTensor(M, K), metis.MxTensor(N, K)
+    metis.quantize_mx(a.cuda(), qa)
+    metis.quantize_mx(b.cuda(), qb)
+    Cm = torch.full((M, N), float("nan"), dtype=out_dtype, device="cuda")
+    metis.mxfp4_gemm_nt(qa, qb, Cm)
+    torch.cuda.synchronize()
+    ref = omx.mx_gemm_nt((qa.codes.cpu().numpy(), qa.scales.cpu().numpy()), (qb.codes.cpu().numpy(), qb.scales.cpu().numpy()))
+    got = Cm.double().cpu().numpy()
+    assert np.isfinite(got).all()
+    # elementwise, for outputs of few elements: 2^-22 sqrt(K) of the sum of magnitudes (fp32 sums), and half a bf16 unit of the result
+    mag = omx.mx_gemm_nt((qa.codes.cpu().numpy() & 0x77, qa.scales.cpu().numpy()), (qb.codes.cpu().numpy() & 0x77, qb.scales.cpu().numpy()))
+    bound = (2.0 ** -22 * np.sqrt(K)) * mag + (2.0 ** -8 * np.abs(ref) if out_dtype == torch.bfloat16 else 0.0)
+    assert (np.abs(got - ref) <= bound).all()
