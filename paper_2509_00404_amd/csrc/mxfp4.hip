@@ -72,7 +72,8 @@ k_quantize_mx(const T* __restrict__ A, int64_t ld, int64_t M, int64_t nblk /* co
 }
 
 // ---- GEMM C[M,N] = A[M,K] B[N,K]^T ----
-// 256 x 256 tile, 8 waves of 128 x 64 (4 x 2 accumulator tiles of 32 x 32, two waves per SIMD).  A lane's operand of
+// 256 x 256 tile, 8 waves of 128 x 64 (4 x 2 accumulator tiles of 32 x 32, two waves per SIMD); for few tiles 128 x 128, 8 waves of 64 x
+// 32 and two workgroups a CU (BT, see launch_mx_gemm).  A lane's operand of
 // one matrix instruction is the 32 codes (16 bytes) of row lane % 32, contraction half lane / 32, and the E8M0 byte
 // of exactly that block of 32.  With no expansion work the kernel lives on operand delivery:
 //  * a stage is 256 contraction elements = 128 bytes of every row = whole cache lines (with 64-byte stages every
@@ -120,10 +121,10 @@ __device__ __forceinline__ void mx_put4(float* p, float x, float y, float z, flo
 // load in flight; quantizers included: 8192 x 4096 x 4064 915 -> 118 us, where 4096 takes 117; 1000 x 1008 x 1248 187 -> 20.6.)
 typedef uint32_t mx_uvec2_any __attribute__((ext_vector_type(2), aligned(1)));
 enum { MX_WHOLE, MX_TAIL, MX_SHORT };
-template <typename OUT, int MODE>
-__global__ void __launch_bounds__(512)
+template <typename OUT, int MODE, int BT>
+__global__ void __launch_bounds__(512, BT == 256 ? 2 : 4)
 k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_t ldc, bool vec, TileMap tmap) {
-    constexpr int TM = 4, TN = 2, BM = 256, BN = 256, KS = MX_KI / 64, NV = 4;   // NV: 16-byte code vectors per thread, operand and stage
+    constexpr int TM = BT / 64, TN = BT / 128, BM = BT, BN = BT, NV = BT / 64;   // NV: 16-byte code vectors per thread, operand and stage
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     constexpr int OFF_CB = BM * MX_CROW, OFF_SA = (BM + BN) * MX_CROW, OFF_SB = OFF_SA + BM * MX_SROW,
                   BUF = OFF_SB + BN * MX_SROW;
@@ -131,7 +132,7 @@ k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_
     int tile_m, tile_n;
     tile_coords(tmap, tile_m, tile_n);
     const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
-    const int wm = (wave >> 2) * 128, wn = (wave & 3) * 64;
+    const int wm = (wave >> 2) * (BT / 2), wn = (wave & 3) * (BT / 4);
     const int li = lane & 31, half = lane >> 5;
 
     float16_t acc[TM][TN];
@@ -143,8 +144,8 @@ k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
     const int niter = (int)((K + MX_KI - 1) / MX_KI);
-    // this thread's share of a stage: code vectors v = 0..3 of each operand (row tid/8 + 64 v, 16-byte segment
-    // tid % 8: a row's 128 bytes are read by 8 consecutive lanes) and the 8 scale bytes of rows tid (A) and tid (B);
+    // this thread's share of a stage: code vectors v of each operand (row tid/8 + 64 v, 16-byte segment
+    // tid % 8: a row's 128 bytes are read by 8 consecutive lanes) and the 8 scale bytes of one row;
     // rows past the operand's end re-read its last row.  Byte offsets fit 32 bits (checked by the host).
     uint32_t oa[NV], ob[NV], osga, osgb;
     const uint32_t cstride = (uint32_t)(K / 2), sstride = (uint32_t)(K / 32);
@@ -157,21 +158,23 @@ k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_
         ob[v] = (uint32_t)gb * cstride + 16u * (tid & 7);
     }
     {
-        // threads 0..255 carry A's scale rows, threads 256..511 B's
-        int64_t ga = m0 + (tid & 255), gb = n0 + (tid & 255);
+        int64_t ga = m0 + (tid & (BT - 1)), gb = n0 + (tid & (BT - 1));
         if (ga >= A.rows) ga = A.rows - 1;
         if (gb >= B.rows) gb = B.rows - 1;
         osga = (uint32_t)ga * sstride;
         osgb = (uint32_t)gb * sstride;
     }
+    // the first BT threads carry A's scale rows, the next BT B's (and with BT = 128 the other half the same once more)
+    const int srow = tid & (2 * BT - 1);
+    const bool sc_a = srow < BT;
     uvec4_t ra[NV], rb[NV];
     uvec2_t rs;
     auto clampst = [&](int st) { return st < niter ? st : niter - 1; };
     auto seg_exists = [&](int st) __attribute__((always_inline)) { return 8u * st + (tid & 7) < sstride; };
     // where the 8 scale bytes are fetched (K > 256: an operand has more than 8)
-    const uint32_t slast = (uint32_t)(tid < 256 ? A.rows : B.rows) * sstride - 8u;
+    const uint32_t slast = (uint32_t)(sc_a ? A.rows : B.rows) * sstride - 8u;
     auto scale_offset = [&](int st) __attribute__((always_inline)) {
-        const uint32_t o = (tid < 256 ? osga : osgb) + 8u * st;
+        const uint32_t o = (sc_a ? osga : osgb) + 8u * st;
         return o < slast ? o : slast;
     };
     auto load_stage = [&](int st) __attribute__((always_inline)) {
@@ -183,7 +186,7 @@ k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_
                 ra[v] = *reinterpret_cast<const uvec4_t*>(ca + oa[v]);
                 rb[v] = *reinterpret_cast<const uvec4_t*>(cb + ob[v]);
             }
-            rs = *reinterpret_cast<const uvec2_t*>((tid < 256 ? A.scales + osga : B.scales + osgb) + (size_t)st * (MX_KI / 32));
+            rs = *reinterpret_cast<const uvec2_t*>((sc_a ? A.scales + osga : B.scales + osgb) + (size_t)st * (MX_KI / 32));
         } else {
             // this lane's 16-byte segment is one block of 32 contraction elements: if it does not exist the row's first is read
             const uint32_t d = seg_exists(st) ? (uint32_t)st * (MX_KI / 2) : 0u - 16u * (tid & 7);
@@ -192,11 +195,11 @@ k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_
                 ra[v] = *reinterpret_cast<const uvec4_t*>(A.codes + (uint32_t)(oa[v] + d));
                 rb[v] = *reinterpret_cast<const uvec4_t*>(B.codes + (uint32_t)(ob[v] + d));
             }
-            const uint8_t* sp = tid < 256 ? A.scales : B.scales;
+            const uint8_t* sp = sc_a ? A.scales : B.scales;
             if (MODE == MX_TAIL) {
                 rs = *reinterpret_cast<const mx_uvec2_any*>(sp + scale_offset(st));
             } else {
-                const uint32_t o = tid < 256 ? osga : osgb;
+                const uint32_t o = sc_a ? osga : osgb;
                 uint32_t w[2] = {0u, 0u};
 #pragma unroll
                 for (int i = 0; i < 8; ++i) w[i >> 2] |= (uint32_t)sp[o + (i < (int)sstride ? i : 0)] << (8 * (i & 3));
@@ -215,7 +218,7 @@ k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_
                 rb[v] = ok ? rb[v] : zero4;
             }
             uint64_t w = (uint64_t)rs.y << 32 | rs.x;
-            if (MODE == MX_TAIL) w >>= 8 * ((tid < 256 ? osga : osgb) + 8u * st - scale_offset(st));
+            if (MODE == MX_TAIL) w >>= 8 * ((sc_a ? osga : osgb) + 8u * st - scale_offset(st));
             const int have = (int)sstride - 8 * st;                                     // >= 1; 127 = scale 1 for an absent block
             const uint64_t absent = have < 8 ? ~0ull << (8 * have) : 0ull;
             w = (w & ~absent) | (0x7F7F7F7F7F7F7F7Full & absent);
@@ -228,7 +231,7 @@ k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_
             *reinterpret_cast<uvec4_t*>(buf + row * MX_CROW + 16 * seg) = ra[v];
             *reinterpret_cast<uvec4_t*>(buf + OFF_CB + row * MX_CROW + 16 * seg) = rb[v];
         }
-        *reinterpret_cast<uvec2_t*>(buf + OFF_SA + tid * MX_SROW) = rs;          // B's scale rows follow A's
+        *reinterpret_cast<uvec2_t*>(buf + OFF_SA + srow * MX_SROW) = rs;          // B's scale rows follow A's
     };
 
     // per-lane byte offsets of this wave's fragment rows inside a buffer
@@ -305,8 +308,8 @@ k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_
     }
 
     // The last stage's buffer is free: its codes and scales were in registers before the last meeting, and that stage stored to the
-    // other one.  Every wave stages 32 rows of its 64 columns at a time in a part of its own.
-    constexpr int E = 16 / (int)sizeof(OUT), LROW = 64 * (int)sizeof(OUT) + 16, UNITS = 64 / E, ROWS = 64 / UNITS;
+    // other one.  Every wave stages 32 rows of its columns at a time in a part of its own.
+    constexpr int E = 16 / (int)sizeof(OUT), LROW = 32 * TN * (int)sizeof(OUT) + 16, UNITS = 32 * TN / E, ROWS = 64 / UNITS;
     static_assert(8 * 32 * LROW <= BUF, "the staged rows fit one buffer");
     uint8_t* sm = lds + ((niter - 1) & 1) * BUF + wave * (32 * LROW);
     const bool whole = vec && m0 + BM <= A.rows && n0 + BN <= B.rows;
@@ -344,26 +347,36 @@ k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_
     }
 }
 
-constexpr size_t MX_LDS = 2 * (size_t)(256 + 256) * (MX_CROW + MX_SROW);
-
-template <typename OUT>
-int launch_mx_gemm(hipStream_t s, const MxOperand& a, const MxOperand& b, int64_t K, OUT* C, int64_t ldc) {
-    const int64_t tm = ceil_div64(a.rows, 256), tn = ceil_div64(b.rows, 256);
+template <typename OUT, int BT>
+int launch_mx_tile(hipStream_t s, const MxOperand& a, const MxOperand& b, int64_t K, OUT* C, int64_t ldc) {
+    constexpr size_t LDS = 2 * (size_t)(2 * BT) * (MX_CROW + MX_SROW);
+    const int64_t tm = ceil_div64(a.rows, BT), tn = ceil_div64(b.rows, BT);
     if (tm * tn > 0x7FFFFFFF) return METIS_UNSUPPORTED;
     const TileMap tmap = make_band_map(tm, tn, MX_BAND);
     const bool vec = (uintptr_t)C % 16 == 0 && (ldc * sizeof(OUT)) % 16 == 0;
     auto launch = [&](auto kern, LdsLimitCache& lds_set) {
-        if (!ensure_dyn_lds((const void*)kern, MX_LDS, lds_set)) return false;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn)), dim3(512), MX_LDS, s, a, b, K, C, ldc, vec, tmap);
+        if (!ensure_dyn_lds((const void*)kern, LDS, lds_set)) return false;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn)), dim3(512), LDS, s, a, b, K, C, ldc, vec, tmap);
         return true;
     };
     static LdsLimitCache lds_set[3];
-    const bool ok = K % MX_KI == 0 ? launch(k_mxfp4_gemm_nt<OUT, MX_WHOLE>, lds_set[0])
-                    : K > MX_KI    ? launch(k_mxfp4_gemm_nt<OUT, MX_TAIL>, lds_set[1])
-                                   : launch(k_mxfp4_gemm_nt<OUT, MX_SHORT>, lds_set[2]);
+    const bool ok = K % MX_KI == 0 ? launch(k_mxfp4_gemm_nt<OUT, MX_WHOLE, BT>, lds_set[0])
+                    : K > MX_KI    ? launch(k_mxfp4_gemm_nt<OUT, MX_TAIL, BT>, lds_set[1])
+                                   : launch(k_mxfp4_gemm_nt<OUT, MX_SHORT, BT>, lds_set[2]);
     if (!ok) return METIS_HIP_ERROR;
     METIS_LAUNCH_CHECK();
     return METIS_OK;
+}
+
+// 128 x 128 tiles while two workgroups a CU hold them all, with an eighth of the places to spare: the chip is fuller and a stage
+// shorter.  With the quantizers, against 256 x 256 tiles, K = 4096: 27 of them 37.1 -> 22.6 us, 128 41.4 -> 26.6, 256 41.0 -> 27.0, 384
+// 43.1 -> 40.1; K = 8192: 448 81.6 -> 78.8.  512 would take 44.6 for 45.1 at K = 4096 but 139.1 for 137.6 at K = 14336, 640 57.5 for 47.2.
+template <typename OUT>
+int launch_mx_gemm(hipStream_t s, const MxOperand& a, const MxOperand& b, int64_t K, OUT* C, int64_t ldc) {
+    const int cus = device_cu_count();
+    if (cus < 1) return METIS_HIP_ERROR;
+    if (ceil_div64(a.rows, 128) * ceil_div64(b.rows, 128) <= 7 * (int64_t)cus / 4) return launch_mx_tile<OUT, 128>(s, a, b, K, C, ldc);
+    return launch_mx_tile<OUT, 256>(s, a, b, K, C, ldc);
 }
 
 bool mx_ok(const metis_mxfp4* t) { return t && t->codes && t->scales && t->rows >= 1 && t->cols >= 32 && t->cols % 32 == 0; }

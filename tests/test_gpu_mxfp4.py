@@ -111,3 +111,24 @@ def test_mxfp4_gemm_partial_last_stage(metis, M, N, K, out_dtype):
     mag = omx.mx_gemm_nt((qa.codes.cpu().numpy() & 0x77, qa.scales.cpu().numpy()), (qb.codes.cpu().numpy() & 0x77, qb.scales.cpu().numpy()))
     bound = (2.0 ** -22 * np.sqrt(K)) * mag + (2.0 ** -8 * np.abs(ref) if out_dtype == torch.bfloat16 else 0.0)
     assert (np.abs(got - ref) <= bound).all()
+
+
+@pytest.mark.parametrize("M,N", [(2048, 3584), (2176, 3584), (2049, 4090), (4100, 2433)])       # 448 tiles of 128 x 128, 476 and more
+@pytest.mark.parametrize("K", [256, 288, 96])
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
+def test_mxfp4_gemm_on_both_sides_of_the_tile_rule(metis, M, N, K, out_dtype):
+    """Outputs of up to 448 tiles of 128 x 128 and larger ones, each with whole, partial and short contractions.  The bars of
+    test_mxfp4_gemm_against_oracle, for every 256 x 256 block of the output."""
+    a, b = _data(M, K, 7, torch.bfloat16), _data(N, K, 8, torch.bfloat16)
+    qa, qb = metis.MxTensor(M, K), metis.MxTensor(N, K)
+    metis.quantize_mx(a.cuda(), qa)
+    metis.quantize_mx(b.cuda(), qb)
+    Cm = torch.full((M, N), float("nan"), dtype=out_dtype, device="cuda")
+    metis.mxfp4_gemm_nt(qa, qb, Cm)
+    torch.cuda.synchronize()
+    ref = omx.mx_gemm_nt((qa.codes.cpu().numpy(), qa.scales.cpu().numpy()), (qb.codes.cpu().numpy(), qb.scales.cpu().numpy()))
+    got = Cm.double().cpu().numpy()
+    assert np.isfinite(got).all()
+    for i in range(0, M, 256):
+        for j in range(0, N, 256):
+            assert rel_fro(got[i:i + 256, j:j + 256], ref[i:i + 256, j:j + 256]) < (1e-5 if out_dtype == torch.float32 else 4e-3), (i, j)
