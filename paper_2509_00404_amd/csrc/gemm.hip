@@ -362,7 +362,7 @@ struct ScalePlan {
     const uint8_t *scales_a, *scales_b;
     int64_t rows_a, rows_b, sstride;
     uint8_t *plan_a, *plan_b;
-    int blocks_a, blocks, niter;                         // of 256 rows: A's, both operands'; units
+    int blocks_a, blocks, niter;                         // of 256 rows: A's, all (an operand may have none to do); units
     int first, count;                                    // workgroups of a shared launch
 };
 __device__ __forceinline__ void scale_plan_block(const ScalePlan& o, int index) {
@@ -1725,19 +1725,24 @@ int linear_nt(hipStream_t s, const NtOperand& a, const NtOperand& b, metis_mat* 
         metis_prof_end(METIS_PROF_GEMM, pi, s);
         return st;
     }
-    // room for the streaming kernel's scale plan, when the workspace has it (and the codes start on 16 bytes)
+    // Room for the streaming kernel's scale plan, when the workspace has it (and the codes start on 16 bytes).  PREPARE may lay out the
+    // scales of a residual that it reads anyway (the other side's factors multiply it, or its last columns are among the extra ones);
+    // the other residual need not be there, or be the last one, before APPLY, which then lays it out in a launch of its own.
     uint8_t* plan = nullptr;
     ScalePlan sp{};
     if (w.plan_bytes > 0 && workspace && workspace_bytes >= w.total && ws_aligned && (uintptr_t)a.R.codes % 16 == 0 &&
         (uintptr_t)b.R.codes % 16 == 0) {
         plan = (uint8_t*)workspace + w.off_plan;
+        const bool early_a = kb > 0 || w.Kt > 0, early_b = ka > 0 || w.Kt > 0;
+        const bool lay_a = early_a ? do_pre : do_main, lay_b = early_b ? do_pre : do_main;
+        const int blocks_a = (int)ceil_div64(Ma, 256);
         sp.niter = (int)(Kc / G_KI);
-        sp.blocks_a = (int)ceil_div64(Ma, 256);
-        sp.blocks = sp.blocks_a + (int)ceil_div64(Nb, 256);
+        sp.blocks_a = lay_a ? blocks_a : 0;
+        sp.blocks = sp.blocks_a + (lay_b ? (int)ceil_div64(Nb, 256) : 0);
         sp.scales_a = a.R.scales; sp.scales_b = b.R.scales;
         sp.rows_a = Ma; sp.rows_b = Nb; sp.sstride = Kc / 16;
         sp.plan_a = plan;
-        sp.plan_b = plan + (size_t)sp.blocks_a * sp.niter * GS_SCALES;
+        sp.plan_b = plan + (size_t)blocks_a * sp.niter * GS_SCALES;
         sp.count = sp.blocks * (int)ceil_div64(sp.niter, 4);
     }
     // (two unsplit operands work without a workspace: a partial last stage then takes the bounds-checked kernel)
@@ -1802,7 +1807,7 @@ int linear_nt(hipStream_t s, const NtOperand& a, const NtOperand& b, metis_mat* 
         Aext = ae;
         Bext = be;
     }
-    if (plan && do_pre && sp.count > 0) {                    // no factors, no launch to share
+    if (sp.count > 0) {                                      // no skinny products in this phase, no launch to share
         hipLaunchKernelGGL(k_scale_plan, dim3((unsigned)sp.count), dim3(256), 0, s, sp);
         METIS_LAUNCH_CHECK();
     }

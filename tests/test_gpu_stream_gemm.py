@@ -46,3 +46,29 @@ def test_against_the_oracle(metis, L, N, K, kx, kw, dtype, ld_extra):  # noqa: F
     bound = elementwise_bound(operand_parts(xo), operand_parts(wo), ref, dtype)
     for out in (Y, small):
         assert (np.abs(out.double().cpu().numpy() - ref) <= bound).all()
+
+
+@pytest.mark.parametrize("kx,kw", [(0, 8), (8, 0), (0, 0), (8, 8)])
+def test_residuals_may_be_written_between_the_phases(metis, kx, kw):  # noqa: F811
+    """PREPARE uses of a residual only what the other side's factors multiply: one that meets none is read by APPLY alone, codes and
+    block scales alike.  Whole stages, so that no columns of the residuals are among the extra ones."""
+    L, N, K = 4112, 4112, 4096
+    g = torch.Generator().manual_seed(kx + 2 * kw)
+    xs = make_split(metis, torch.randn((L, K), generator=g).bfloat16(), kx, 8, 0.25, 11, want_t=False)[0]
+    ws = make_split(metis, (0.02 * torch.randn((N, K), generator=g)).bfloat16(), kw, 8, 0.25, 12, want_t=False)[0]
+    room = torch.empty((metis.linear_workspace_bytes(L, N, K, max(kx, kw)),), dtype=torch.uint8, device="cuda")
+    want, got = (torch.empty((L, N), dtype=torch.float32, device="cuda") for _ in range(2))
+    metis.fp4_linear_fwd(xs, ws, want, room)
+    room.fill_(0xA5)
+    late = [s.R for s, other in ((xs, kw), (ws, kx)) if other == 0]
+    kept = [(r.codes.clone(), r.scales.clone()) for r in late]
+    for r in late:
+        r.codes.fill_(0x33)
+        r.scales.fill_(0x38)
+    metis.fp4_linear_phase(metis.LINEAR_FWD, metis.LINEAR_PREPARE, xs, ws, None, room)
+    for r, (c, s) in zip(late, kept):
+        r.codes.copy_(c)
+        r.scales.copy_(s)
+    metis.fp4_linear_phase(metis.LINEAR_FWD, metis.LINEAR_APPLY, xs, ws, got, room)
+    torch.cuda.synchronize()
+    assert torch.equal(want, got)
