@@ -740,9 +740,9 @@ k_fp4_gemm_nt_pipe(Fp4Operand A, Fp4Operand B, int64_t K, const bf16_t* __restri
 }
 
 // adds the parts of the split tail tiles and writes them to C (see k_fp4_gemm_nt_pipe); one workgroup per 32 rows of a tile
-template <typename OUT>
+template <typename OUT, typename MAP>
 __global__ void __launch_bounds__(256)
-k_gemm_tail_sum(const float* __restrict__ partial, int parts, int tail_first, int total_tiles, TileMap tmap, int64_t M,
+k_gemm_tail_sum(const float* __restrict__ partial, int parts, int tail_first, int total_tiles, MAP tmap, int64_t M,
                 int64_t N, OUT* __restrict__ C, int64_t ldc) {
     const int tile = tail_first + (int)blockIdx.x / 8, rb = (int)blockIdx.x % 8;
     int tile_m, tile_n;
@@ -796,14 +796,14 @@ int launch_gemm_stream(hipStream_t s, const Fp4Operand& a, const Fp4Operand& b, 
     auto kern = k_fp4_gemm_nt_stream<OUT>;
     static LdsLimitCache lds_set;
     if (!ensure_dyn_lds((const void*)kern, GS_LDS, lds_set)) return METIS_HIP_ERROR;
-    const TileMap tmap = make_band_map(tm, tn, GS_BAND);
+    const BandMap tmap = make_band_map(tm, tn, GS_BAND);
     const bool vec = (uintptr_t)C % 16 == 0 && (ldc * sizeof(OUT)) % 16 == 0;
     hipLaunchKernelGGL(kern, grid, dim3(256), GS_LDS, s, a, b, K, plan,
                        plan + (size_t)tm * (K / G_KI) * GS_SCALES, Aext, Bext, Ke, alpha, C, ldc, vec, tmap, total, tail_first, parts,
                        partial, items);
     METIS_LAUNCH_CHECK();
     if (split) {
-        hipLaunchKernelGGL(k_gemm_tail_sum<OUT>, dim3((unsigned)(tail * 8)), dim3(256), 0, s, partial, parts, tail_first, total,
+        hipLaunchKernelGGL((k_gemm_tail_sum<OUT, BandMap>), dim3((unsigned)(tail * 8)), dim3(256), 0, s, partial, parts, tail_first, total,
                            tmap, a.rows, b.rows, C, ldc);
         METIS_LAUNCH_CHECK();
     }
@@ -834,7 +834,7 @@ int launch_gemm_pipe(hipStream_t s, const Fp4Operand& a, const Fp4Operand& b, in
                        partial, items);
     METIS_LAUNCH_CHECK();
     if (split) {
-        hipLaunchKernelGGL(k_gemm_tail_sum<OUT>, dim3((unsigned)(tail * 8)), dim3(256), 0, s, partial, parts, tail_first, total,
+        hipLaunchKernelGGL((k_gemm_tail_sum<OUT, TileMap>), dim3((unsigned)(tail * 8)), dim3(256), 0, s, partial, parts, tail_first, total,
                            tmap, a.rows, b.rows, C, ldc);
         METIS_LAUNCH_CHECK();
     }

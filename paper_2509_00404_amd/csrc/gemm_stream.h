@@ -172,7 +172,7 @@ template <typename OUT>
 __global__ void __launch_bounds__(256)
 k_fp4_gemm_nt_stream(Fp4Operand A, Fp4Operand B, int64_t K, const uint8_t* __restrict__ Aplan,
                      const uint8_t* __restrict__ Bplan, const bf16_t* __restrict__ Aext, const bf16_t* __restrict__ Bext,
-                     int Ke_all, float alpha, OUT* __restrict__ C, int64_t ldc, bool vec, TileMap tmap, int total_tiles,
+                     int Ke_all, float alpha, OUT* __restrict__ C, int64_t ldc, bool vec, BandMap tmap, int total_tiles,
                      int tail_first, int tail_parts, float* __restrict__ partial, int total_items) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)lds;
@@ -192,7 +192,7 @@ k_fp4_gemm_nt_stream(Fp4Operand A, Fp4Operand B, int64_t K, const uint8_t* __res
         int tile = pos, part = 0, parts = 1;
         w.cut = -1;
         // (opaque: else the reciprocals of these divisions are kept in registers through the whole kernel)
-        TileMap map = tmap;
+        BandMap map = tmap;
         int cuts = tail_parts;
         asm volatile("" : "+s"(map.tiles_m), "+s"(map.tiles_n), "+s"(cuts));
         if (tile >= tail_first) {

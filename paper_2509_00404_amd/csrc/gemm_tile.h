@@ -38,11 +38,10 @@ template <> __device__ __forceinline__ void store_tile16<bf16_t>(bf16_t* p, int6
 struct TileMap {
     int tiles_n;     // tiles along N
     int rm, rn;      // region shape in tiles, 0 = no regions
-    int tiles_m, group;      // group > 0: bands instead of regions, see make_band_map
 };
 
 static inline TileMap make_tile_map(int64_t tiles_m, int64_t tiles_n) {
-    TileMap t = {(int)tiles_n, 0, 0, (int)tiles_m, 0};
+    TileMap t = {(int)tiles_n, 0, 0};
     const int64_t total = tiles_m * tiles_n;
     if (total % 8) return t;
     const int64_t per = total / 8;
@@ -59,25 +58,20 @@ static inline TileMap make_tile_map(int64_t tiles_m, int64_t tiles_n) {
 
 // The other order: bands of `group` tile columns, each walked down, `group` tiles at a time; every XCD takes a contiguous run.  The
 // 32 tiles an XCD has in work then share `group` panels of B and 32 / group of A, whatever the grid's shape (a region of
-// 16 x 28 tiles, walked by rows, has 28 + 2).
-static inline TileMap make_band_map(int64_t tiles_m, int64_t tiles_n, int group) {
-    return {(int)tiles_n, 0, 0, (int)tiles_m, group};
+// 16 x 28 tiles, walked by rows, has 28 + 2).  (A type of its own: with one map that can be either the pipelined GEMM, which is short
+// of scalar registers, spilled 10 instead of 4 and was 1 % slower, 16384 x 8192 x 512 189.0 us in fp32 for 187.1; the streaming
+// GEMM's bf16 form spilled 6 vector registers, which it reloaded in front of every tile's stores.)
+struct BandMap {
+    int tiles_n, tiles_m, group;
+};
+
+static inline BandMap make_band_map(int64_t tiles_m, int64_t tiles_n, int group) {
+    return {(int)tiles_n, (int)tiles_m, group};
 }
 
-__device__ __forceinline__ void tile_coords_of(const TileMap& t, int b, int total, int& tm, int& tn);
-__device__ __forceinline__ void tile_coords(const TileMap& t, int& tm, int& tn) {
-    tile_coords_of(t, (int)blockIdx.x, (int)gridDim.x, tm, tn);
-}
 // b = position in launch order among `total` tiles
 __device__ __forceinline__ void tile_coords_of(const TileMap& t, int b, int total, int& tm, int& tn) {
-    if (t.group > 0) {
-        const int xcd = b & 7, rest = total & 7;
-        const int tile = xcd * (total >> 3) + (xcd < rest ? xcd : rest) + (b >> 3);
-        const int band = tile / (t.group * t.tiles_m), r = tile - band * t.group * t.tiles_m;
-        const int left = t.tiles_n - band * t.group, w = left < t.group ? left : t.group;
-        tm = r / w;
-        tn = band * t.group + (r - tm * w);
-    } else if (t.rm > 0) {
+    if (t.rm > 0) {
         const int xcd = b & 7, local = b >> 3, regions_n = t.tiles_n / t.rn;
         tm = (xcd / regions_n) * t.rm + local / t.rn;
         tn = (xcd % regions_n) * t.rn + local % t.rn;
@@ -87,6 +81,18 @@ __device__ __forceinline__ void tile_coords_of(const TileMap& t, int b, int tota
         tm = tile / t.tiles_n;
         tn = tile % t.tiles_n;
     }
+}
+__device__ __forceinline__ void tile_coords_of(const BandMap& t, int b, int total, int& tm, int& tn) {
+    const int xcd = b & 7, rest = total & 7;
+    const int tile = xcd * (total >> 3) + (xcd < rest ? xcd : rest) + (b >> 3);
+    const int band = tile / (t.group * t.tiles_m), r = tile - band * t.group * t.tiles_m;
+    const int left = t.tiles_n - band * t.group, w = left < t.group ? left : t.group;
+    tm = r / w;
+    tn = band * t.group + (r - tm * w);
+}
+template <typename MAP>
+__device__ __forceinline__ void tile_coords(const MAP& t, int& tm, int& tn) {
+    tile_coords_of(t, (int)blockIdx.x, (int)gridDim.x, tm, tn);
 }
 
 }  // namespace

@@ -123,7 +123,7 @@ typedef uint32_t mx_uvec2_any __attribute__((ext_vector_type(2), aligned(1)));
 enum { MX_WHOLE, MX_TAIL, MX_SHORT };
 template <typename OUT, int MODE, int BT>
 __global__ void __launch_bounds__(512, BT == 256 ? 2 : 4)
-k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_t ldc, bool vec, TileMap tmap) {
+k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_t ldc, bool vec, BandMap tmap) {
     constexpr int TM = BT / 64, TN = BT / 128, BM = BT, BN = BT, NV = BT / 64;   // NV: 16-byte code vectors per thread, operand and stage
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     constexpr int OFF_CB = BM * MX_CROW, OFF_SA = (BM + BN) * MX_CROW, OFF_SB = OFF_SA + BM * MX_SROW,
@@ -352,7 +352,7 @@ int launch_mx_tile(hipStream_t s, const MxOperand& a, const MxOperand& b, int64_
     constexpr size_t LDS = 2 * (size_t)(2 * BT) * (MX_CROW + MX_SROW);
     const int64_t tm = ceil_div64(a.rows, BT), tn = ceil_div64(b.rows, BT);
     if (tm * tn > 0x7FFFFFFF) return METIS_UNSUPPORTED;
-    const TileMap tmap = make_band_map(tm, tn, MX_BAND);
+    const BandMap tmap = make_band_map(tm, tn, MX_BAND);
     const bool vec = (uintptr_t)C % 16 == 0 && (ldc * sizeof(OUT)) % 16 == 0;
     auto launch = [&](auto kern, LdsLimitCache& lds_set) {
         if (!ensure_dyn_lds((const void*)kern, LDS, lds_set)) return false;
