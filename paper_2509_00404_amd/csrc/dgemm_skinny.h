@@ -37,9 +37,12 @@ __device__ __forceinline__ void skinny_interleave() {
 //   Z   fp64 [ksplit][Ms][r] partial products
 // grid (1, ceil(Ms/64), ksplit), block 256: wave w owns rows 16w..16w+15 and all NT column tiles.
 // ---------------------------------------------------------------------------------------
-// Waves per SIMD of both kernels, and no more: the contraction is cut so that two workgroups share a CU, and with room for a third
-// wave some SIMDs get three and others one.
-#define SKINNY_WAVES 2
+// Waves per SIMD of both kernels.  At 3 and 4 column tiles two and no more: the contraction is cut so that two workgroups share a CU, and
+// with room for a third wave some SIMDs get three and others one (48 columns, fp32 14336 x 4096: 250 us, 262 without the limit).  With
+// 5 and more the registers see to that.  With 1 and 2 the pass is bound by memory and wants every wave it can get: 14336 x 4096 at
+// 16 columns 121 us with the limit and the split of the wide ones, 102 without; 32 columns 185 and 170.
+#define SKINNY_NARROW 2
+template <int NT> struct SkinnyWaves { static constexpr int MIN = NT == 3 || NT == 4 ? 2 : 1, MAX = NT == 3 || NT == 4 ? 2 : 8; };
 #define SK_ROWS 64
 #define SK_KS 64                      // unit of the contraction split
 template <int NT, typename TA>
@@ -54,7 +57,7 @@ struct SketchCfg {
 };
 
 template <int NT, typename TA>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SKINNY_WAVES, SKINNY_WAVES)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SkinnyWaves<NT>::MIN, SkinnyWaves<NT>::MAX)))
 k_sketch(const TA* __restrict__ A, int64_t lda, const uint32_t* __restrict__ rowmap, int64_t Ms, int64_t K,
          const bf16_t* __restrict__ Om, int r, int64_t kchunk, double* __restrict__ Z) {
     typedef SketchCfg<NT, TA> Cfg;
@@ -132,32 +135,41 @@ k_sketch(const TA* __restrict__ A, int64_t lda, const uint32_t* __restrict__ row
     for (int64_t kt = kbeg; kt < kend; kt += KS) {
         const bool more = kt + KS < kend;
         if (more) fetch(kt + KS);
-        // 16 elements at a time: the operands of the next 16 are read while these are multiplied (see skinny_interleave)
-        constexpr int G = KS / 16;
-        TA ar[2][4];
-        bf16_t br[2][4][NT];
-        auto read = [&](int g, int n) __attribute__((always_inline)) {
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int kr = 16 * g + 4 * s + (lane >> 4);
-                ar[n][s] = As[buf][arow_l + kr];
-#pragma unroll
-                for (int j = 0; j < NT; ++j) br[n][s][j] = Os[buf][kr * LDO + 16 * j + (lane & 15)];
+        if constexpr (NT == 1) {           // bound by memory: read where they are used, fewer registers, more waves
+#pragma unroll 4
+            for (int s = 0; s < KS / 4; ++s) {
+                const int kr = 4 * s + (lane >> 4);
+                const double a = skinny_to_f64(As[buf][arow_l + kr]);
+                acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, skinny_to_f64(Os[buf][kr * LDO + (lane & 15)]), acc[0], 0, 0, 0);
             }
-        };
-        read(0, 0);
+        } else {
+            // 16 elements at a time: the operands of the next 16 are read while these are multiplied (see skinny_interleave)
+            constexpr int G = KS / 16;
+            TA ar[2][4];
+            bf16_t br[2][4][NT];
+            auto read = [&](int g, int n) __attribute__((always_inline)) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            __builtin_amdgcn_sched_barrier(0);
-            if (g + 1 < G) read(g + 1, (g + 1) & 1);
+                for (int s = 0; s < 4; ++s) {
+                    const int kr = 16 * g + 4 * s + (lane >> 4);
+                    ar[n][s] = As[buf][arow_l + kr];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const double a = skinny_to_f64(ar[g & 1][s]);
+                    for (int j = 0; j < NT; ++j) br[n][s][j] = Os[buf][kr * LDO + 16 * j + (lane & 15)];
+                }
+            };
+            read(0, 0);
 #pragma unroll
-                for (int j = 0; j < NT; ++j)
-                    acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, skinny_to_f64(br[g & 1][s][j]), acc[j], 0, 0, 0);
+            for (int g = 0; g < G; ++g) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (g + 1 < G) read(g + 1, (g + 1) & 1);
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const double a = skinny_to_f64(ar[g & 1][s]);
+#pragma unroll
+                    for (int j = 0; j < NT; ++j)
+                        acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, skinny_to_f64(br[g & 1][s][j]), acc[j], 0, 0, 0);
+                }
+                skinny_interleave<NT>();
             }
-            skinny_interleave<NT>();
         }
         if (more) stash(buf ^ 1);
         __syncthreads();
@@ -193,7 +205,7 @@ struct ProjectCfg {
 };
 
 template <int NT, typename TA>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SKINNY_WAVES, SKINNY_WAVES)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SkinnyWaves<NT>::MIN, SkinnyWaves<NT>::MAX)))
 k_project(const double* __restrict__ H_main, const double* __restrict__ H_alt, const int32_t* __restrict__ use_alt, int r,
           const TA* __restrict__ A, int64_t lda, const uint32_t* __restrict__ rowmap, int64_t Ms, int64_t N,
           int64_t kchunk, double* __restrict__ B) {
@@ -278,33 +290,42 @@ k_project(const double* __restrict__ H_main, const double* __restrict__ H_alt, c
         if (more) fetch(kt + PJ_KS);
         const double* hs = Hs + (size_t)buf * PJ_KS * LDH;
         const TA* as = As + buf * PJ_KS * PJ_LDA;
-        constexpr int G = PJ_KS / 16;
-        constexpr bool AHEAD = NT <= 6;                    // (two sets of operands for more would not fit the registers)
-        double ar[AHEAD ? 2 : 1][4][NT];
-        TA br[AHEAD ? 2 : 1][4];
-        auto read = [&](int g, int n) __attribute__((always_inline)) {
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const int kr = 16 * g + 4 * s + (lane >> 4);
-                br[n][s] = as[kr * PJ_LDA + wave * 16 + (lane & 15)];
-#pragma unroll
-                for (int i = 0; i < NT; ++i) ar[n][s][i] = hs[kr * LDH + 16 * i + (lane & 15)];
+        if constexpr (NT == 1) {           // as in k_sketch
+#pragma unroll 4
+            for (int s = 0; s < PJ_KS / 4; ++s) {
+                const int kr = 4 * s + (lane >> 4);
+                const double b = skinny_to_f64(as[kr * PJ_LDA + wave * 16 + (lane & 15)]);
+                acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(hs[kr * LDH + (lane & 15)], b, acc[0], 0, 0, 0);
             }
-        };
-        if (AHEAD) read(0, 0);
+        } else {
+            constexpr int G = PJ_KS / 16;
+            constexpr bool AHEAD = NT <= 6;                    // (two sets of operands for more would not fit the registers)
+            double ar[AHEAD ? 2 : 1][4][NT];
+            TA br[AHEAD ? 2 : 1][4];
+            auto read = [&](int g, int n) __attribute__((always_inline)) {
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const int c = AHEAD ? g & 1 : 0;
-            __builtin_amdgcn_sched_barrier(0);
-            if (!AHEAD) read(g, 0);
-            else if (g + 1 < G) read(g + 1, c ^ 1);
+                for (int s = 0; s < 4; ++s) {
+                    const int kr = 16 * g + 4 * s + (lane >> 4);
+                    br[n][s] = as[kr * PJ_LDA + wave * 16 + (lane & 15)];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const double b = skinny_to_f64(br[c][s]);
+                    for (int i = 0; i < NT; ++i) ar[n][s][i] = hs[kr * LDH + 16 * i + (lane & 15)];
+                }
+            };
+            if (AHEAD) read(0, 0);
 #pragma unroll
-                for (int i = 0; i < NT; ++i) acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[c][s][i], b, acc[i], 0, 0, 0);
+            for (int g = 0; g < G; ++g) {
+                const int c = AHEAD ? g & 1 : 0;
+                __builtin_amdgcn_sched_barrier(0);
+                if (!AHEAD) read(g, 0);
+                else if (g + 1 < G) read(g + 1, c ^ 1);
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const double b = skinny_to_f64(br[c][s]);
+#pragma unroll
+                    for (int i = 0; i < NT; ++i) acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[c][s][i], b, acc[i], 0, 0, 0);
+                }
+                skinny_interleave<NT>();
             }
-            skinny_interleave<NT>();
         }
         if (more) stash(buf ^ 1);
         __syncthreads();
@@ -320,24 +341,38 @@ k_project(const double* __restrict__ H_main, const double* __restrict__ H_alt, c
         }
 }
 
-// Contraction split: the one with the least estimated time (us).  Two workgroups share a CU (256 of them a constant here: workspace
-// sizes are asked for without a device); a round of them takes 0.067 per contraction element and 80 columns (0.045 where CUs have one
-// only), 2 us besides, and every part costs its traffic, written and read once, at 4 TB/s.
+// Contraction split.  Up to 32 columns about 768 workgroups.  From 33 on the split with the least estimated time (us): two workgroups
+// share a CU (256 of them a constant here: workspace sizes are asked for without a device); a round of them takes 0.067 per
+// contraction element and 80 columns (0.045 where CUs have one only), 2 us besides, and every part costs its traffic, written and
+// read once, at 4 TB/s.  Few tiles take many parts: sketch and projection of 64 rows x 14336 at 80 columns 28 us with up to 64
+// parts, 23 with as many as the estimate asks for (112); 50256 x 256 115 and 105.
 static inline int64_t skinny_kchunk(int64_t K, int64_t tiles, int stage, int64_t outputs, int r) {
+    if (r <= 16 * SKINNY_NARROW) {
+        int64_t ks = ceil_div64(768, tiles);
+        const int64_t maxs = ceil_div64(K, stage);
+        if (ks > maxs) ks = maxs;
+        return ceil_div64(ceil_div64(K, ks), stage) * stage;
+    }
     const double per_k = 0.067 / 80.0 * (double)((r + 15) / 16 * 16);
     double best_t = 1e30;
     int64_t best = stage;
-    for (int64_t n = 1; n <= 64; ++n) {
-        const int64_t chunk = ceil_div64(ceil_div64(K, n), stage) * stage, parts = ceil_div64(K, chunk), wgs = tiles * parts;
-        const int64_t rounds = ceil_div64(wgs, 512);
+    auto consider = [&](int64_t chunk) {
+        const int64_t parts = ceil_div64(K, chunk), wgs = tiles * parts, rounds = ceil_div64(wgs, 512);
         const double t = (double)rounds * ((double)chunk * per_k * (wgs <= 256 ? 0.67 : 1.0) + 2.0) +
                          (parts > 1 ? (double)parts : 0.0) * (double)outputs * 16.0 / 4e6;
         if (t < best_t - 1e-9) {
             best_t = t;
             best = chunk;
         }
-        if (chunk == stage) break;
+        return wgs;
+    };
+    // 1 to 64 parts, then every shorter chunk, up to two rounds of workgroups
+    int64_t chunk = 0;
+    for (int64_t n = 1; n <= 64 && chunk != stage; ++n) {
+        chunk = ceil_div64(ceil_div64(K, n), stage) * stage;
+        consider(chunk);
     }
+    while (chunk > stage && consider(chunk -= stage) < 1024) {}
     return best;
 }
 

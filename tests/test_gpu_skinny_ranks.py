@@ -1,6 +1,6 @@
 """The fp64 sketch and projection kernels at every width of their strips: whole tiles of 16 columns and partial ones, operands read
-ahead (up to 6 tiles) and not, contractions in one part and in several, through the factor gradients (2^-24 of the sums: the bar of
-tests/test_gpu_factor_grads.py)."""
+ahead (2 to 6 tiles) and not, contractions in one part, in several and in more than 64, through the factor gradients (2^-24 of
+the sums: the bar of tests/test_gpu_factor_grads.py)."""
 import pytest
 import torch
 
@@ -11,7 +11,8 @@ from test_gpu_factor_grads import FG_RTOL, _run, metis  # noqa: F401  (metis is 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("N,K,k", [(272, 320, 16), (1040, 368, 24), (320, 2064, 80), (336, 304, 88), (400, 528, 112), (1552, 176, 128)])
+@pytest.mark.parametrize("N,K,k", [(272, 320, 16), (1040, 368, 24), (320, 2064, 80), (336, 304, 88), (400, 528, 112), (1552, 176, 128),
+                                   (528, 656, 8), (1040, 400, 32), (336, 784, 48), (656, 1040, 64), (64, 14336, 80), (8208, 96, 72)])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_strip_widths(metis, N, K, k, dtype):  # noqa: F811
     g = torch.Generator().manual_seed(k)
