@@ -83,16 +83,20 @@ k_quantize_mx(const T* __restrict__ A, int64_t ld, int64_t M, int64_t nblk /* co
 //  * a wave issues in order and a matrix instruction holds its pipe for 32 cycles, so memory instructions of one
 //    wave leave the pipe idle while they issue: the second wave on the SIMD fills those gaps (four waves of
 //    128 x 128 need fewer LDS bytes per flop but reach 10 % less);
-//  * the tiles an XCD has in work share MX_BAND panels of B and 32 / MX_BAND of A (make_band_map);
+//  * the tiles an XCD has in work share few panels of both operands (mx_order);
 //  * accumulator tiles are transposed (B's fragment first): a lane then holds runs of four columns of one row, which go to whole
 //    lines by way of the finished stage's LDS, 16 bytes a lane (as 2-byte stores, half a line of two rows each, a tile took 128
-//    store instructions a wave instead of 16).  With the band order, quantizers included: 8192 x 14336 x 4096 330 -> 324 us, 8192 x
-//    4096 x 4096 fp32 118.5 -> 115.5, 2047 x 4096 x 4096 50.2 -> 46.1.
+//    store instructions a wave instead of 16).
 // The stage body is branch-free (stage indices are clamped; the last stage loads and stores data nobody uses).
 #define MX_KI 256
 #define MX_CROW (MX_KI / 2 + 16)      // padded code row in LDS: 144 bytes, 16-byte reads of 8 consecutive rows hit 8 bank groups
 #define MX_SROW 8                     // the row's eight scale bytes of a stage
-#define MX_BAND 4                     // tiles side by side that an XCD has in work: 4 of B's panels and 8 of A's
+#define MX_BAND 4                     // tiles side by side in a band: an XCD has 4 of B's panels and 8 of A's in work
+
+struct MxOrder {
+    TileMap regions;
+    BandMap bands;                    // bands.group == 0: regions
+};
 
 struct MxOperand {
     const uint8_t* codes;             // [rows, K/2]
@@ -123,14 +127,15 @@ typedef uint32_t mx_uvec2_any __attribute__((ext_vector_type(2), aligned(1)));
 enum { MX_WHOLE, MX_TAIL, MX_SHORT };
 template <typename OUT, int MODE, int BT>
 __global__ void __launch_bounds__(512, BT == 256 ? 2 : 4)
-k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_t ldc, bool vec, BandMap tmap) {
+k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_t ldc, bool vec, MxOrder order) {
     constexpr int TM = BT / 64, TN = BT / 128, BM = BT, BN = BT, NV = BT / 64;   // NV: 16-byte code vectors per thread, operand and stage
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     constexpr int OFF_CB = BM * MX_CROW, OFF_SA = (BM + BN) * MX_CROW, OFF_SB = OFF_SA + BM * MX_SROW,
                   BUF = OFF_SB + BN * MX_SROW;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int tile_m, tile_n;
-    tile_coords(tmap, tile_m, tile_n);
+    if (order.bands.group > 0) tile_coords(order.bands, tile_m, tile_n);
+    else tile_coords(order.regions, tile_m, tile_n);
     const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
     const int wm = (wave >> 2) * (BT / 2), wn = (wave & 3) * (BT / 4);
     const int li = lane & 31, half = lane >> 5;
@@ -347,16 +352,30 @@ k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_
     }
 }
 
+// Regions or bands.  An XCD's tiles in work should share few panels: a region near square sees to that and writes longer runs of
+// C's rows, which counts while a tile's contraction is short; bands see to it whatever the grid, and over many tiles of a long contraction
+// share better than a wide region walked by rows.  Multiplication alone, us, regions / bands: 16384 x 14336 x 4096 597 / 569, x 2048
+// 329 / 313, x 1056 255 / 241, x 1024 fp32 256 / 260, x 512 fp32 196 / 205; 8192 x 14336 x 512 fp32 100 / 107; 16384 x 4096 x 512
+// 39.0 / 40.9, x 4096 162 / 160; no region (8448 x 8448 x 2048) 112 / 100; one of 47 x 7 (12000 x 14336 x 4096) 438 / 432.  128 x 128
+// tiles are all in work at once: regions where there are any, 512 x 7168 x 4096 15.6 / 17.3, 2048 x 3584 x 14336 95.9 / 97.6.
+MxOrder mx_order(int64_t tiles_m, int64_t tiles_n, int64_t K, int bt) {
+    MxOrder o = {make_tile_map(tiles_m, tiles_n), {0, 0, 0}};
+    const int rm = o.regions.rm, rn = o.regions.rn;
+    const bool near_square = rm > 0 && rm <= 4 * rn && rn <= 4 * rm;
+    if (bt == 256 ? !near_square || (K > 1024 && tiles_m * tiles_n >= 1536) : rm == 0) o.bands = make_band_map(tiles_m, tiles_n, MX_BAND);
+    return o;
+}
+
 template <typename OUT, int BT>
 int launch_mx_tile(hipStream_t s, const MxOperand& a, const MxOperand& b, int64_t K, OUT* C, int64_t ldc) {
     constexpr size_t LDS = 2 * (size_t)(2 * BT) * (MX_CROW + MX_SROW);
     const int64_t tm = ceil_div64(a.rows, BT), tn = ceil_div64(b.rows, BT);
     if (tm * tn > 0x7FFFFFFF) return METIS_UNSUPPORTED;
-    const BandMap tmap = make_band_map(tm, tn, MX_BAND);
+    const MxOrder order = mx_order(tm, tn, K, BT);
     const bool vec = (uintptr_t)C % 16 == 0 && (ldc * sizeof(OUT)) % 16 == 0;
     auto launch = [&](auto kern, LdsLimitCache& lds_set) {
         if (!ensure_dyn_lds((const void*)kern, LDS, lds_set)) return false;
-        hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn)), dim3(512), LDS, s, a, b, K, C, ldc, vec, tmap);
+        hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn)), dim3(512), LDS, s, a, b, K, C, ldc, vec, order);
         return true;
     };
     static LdsLimitCache lds_set[3];
@@ -370,7 +389,8 @@ int launch_mx_tile(hipStream_t s, const MxOperand& a, const MxOperand& b, int64_
 
 // 128 x 128 tiles while two workgroups a CU hold them all, with an eighth of the places to spare: the chip is fuller and a stage
 // shorter.  With the quantizers, against 256 x 256 tiles, K = 4096: 27 of them 37.1 -> 22.6 us, 128 41.4 -> 26.6, 256 41.0 -> 27.0, 384
-// 43.1 -> 40.1; K = 8192: 448 81.6 -> 78.8.  512 would take 44.6 for 45.1 at K = 4096 but 139.1 for 137.6 at K = 14336, 640 57.5 for 47.2.
+// 43.1 -> 40.1.  448, multiplication alone: K = 4096 32.3 -> 30.4, 14336 96.1 -> 95.9.  With the quantizers, 512 would take 44.6 for 45.1
+// at K = 4096 but 139.1 for 137.6 at K = 14336, 640 57.5 for 47.2.
 template <typename OUT>
 int launch_mx_gemm(hipStream_t s, const MxOperand& a, const MxOperand& b, int64_t K, OUT* C, int64_t ldc) {
     const int cus = device_cu_count();

@@ -113,7 +113,8 @@ def test_mxfp4_gemm_partial_last_stage(metis, M, N, K, out_dtype):
     assert (np.abs(got - ref) <= bound).all()
 
 
-@pytest.mark.parametrize("M,N", [(2048, 3584), (2176, 3584), (2049, 4090), (4100, 2433)])       # 448 tiles of 128 x 128, 476 and more
+# 448 tiles of 128 x 128, 476 and more; a grid of 256 x 256 tiles that splits into near-square regions and ones that do not
+@pytest.mark.parametrize("M,N", [(2048, 3584), (2176, 3584), (2049, 4090), (4100, 2433), (4090, 2048)])
 @pytest.mark.parametrize("K", [256, 288, 96])
 @pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
 def test_mxfp4_gemm_on_both_sides_of_the_tile_rule(metis, M, N, K, out_dtype):
