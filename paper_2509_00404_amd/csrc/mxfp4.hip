@@ -84,9 +84,11 @@ k_quantize_mx(const T* __restrict__ A, int64_t ld, int64_t M, int64_t nblk /* co
 //    wave leave the pipe idle while they issue: the second wave on the SIMD fills those gaps (four waves of
 //    128 x 128 need fewer LDS bytes per flop but reach 10 % less);
 //  * the tiles an XCD has in work share few panels of both operands (mx_order);
-//  * accumulator tiles are transposed (B's fragment first): a lane then holds runs of four columns of one row, which go to whole
+//  * bf16 accumulator tiles are transposed (B's fragment first): a lane then holds runs of four columns of one row, which go to whole
 //    lines by way of the finished stage's LDS, 16 bytes a lane (as 2-byte stores, half a line of two rows each, a tile took 128
-//    store instructions a wave instead of 16).
+//    store instructions a wave instead of 16).  An fp32 row of 32 is a whole line as it is: by way of LDS 16384 x 14336 x 512 takes 197
+//    us instead of 188, 6144 x 6144 x 1024 47 for 45, 4352 x 4352 x 512 23.8 for 22.5 (128 x 128 tiles, where it makes no difference,
+//    use the one path).
 // The stage body is branch-free (stage indices are clamped; the last stage loads and stores data nobody uses).
 #define MX_KI 256
 #define MX_CROW (MX_KI / 2 + 16)      // padded code row in LDS: 144 bytes, 16-byte reads of 8 consecutive rows hit 8 bank groups
@@ -128,6 +130,7 @@ enum { MX_WHOLE, MX_TAIL, MX_SHORT };
 template <typename OUT, int MODE, int BT>
 __global__ void __launch_bounds__(512, BT == 256 ? 2 : 4)
 k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_t ldc, bool vec, MxOrder order) {
+    constexpr bool LINES = sizeof(OUT) == 2 || BT == 128;              // outputs by way of LDS, accumulator tiles transposed
     constexpr int TM = BT / 64, TN = BT / 128, BM = BT, BN = BT, NV = BT / 64;   // NV: 16-byte code vectors per thread, operand and stage
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     constexpr int OFF_CB = BM * MX_CROW, OFF_SA = (BM + BN) * MX_CROW, OFF_SB = OFF_SA + BM * MX_SROW,
@@ -273,8 +276,12 @@ k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_
             for (int j = 0; j < TN; ++j) {
                 const int8v_t b = {(int)fb[slot][j].x, (int)fb[slot][j].y, (int)fb[slot][j].z, (int)fb[slot][j].w, 0, 0, 0, 0};
                 // formats 4 = FP4 (E2M1) for both operands; the scale byte is byte `sel` of the shifted word
-                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(b, a, acc[i][j], 4, 4, sel, (int)sb[word][j],
-                                                                             sel, (int)sa[word][i]);
+                if constexpr (LINES)
+                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(b, a, acc[i][j], 4, 4, sel, (int)sb[word][j],
+                                                                                 sel, (int)sa[word][i]);
+                else
+                    acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc[i][j], 4, 4, sel, (int)sa[word][i],
+                                                                                 sel, (int)sb[word][j]);
             }
         }
     };
@@ -312,6 +319,26 @@ k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_
         read_scales(bufn);
     }
 
+    if constexpr (!LINES) {
+        const bool interior = m0 + BM <= A.rows && n0 + BN <= B.rows;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int64_t c = n0 + wn + 32 * j + li;
+                const int64_t rbase = m0 + wm + 32 * i + 4 * half;
+                if (interior) {
+                    store_tile16<OUT>(C + rbase * ldc + c, ldc, acc[i][j], 1.0f);
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int64_t r = rbase + 8 * (v >> 2) + (v & 3);
+                        if (r < A.rows && c < B.rows) store_out<OUT>(C + r * ldc + c, acc[i][j][v]);
+                    }
+                }
+            }
+        return;
+    }
     // The last stage's buffer is free: its codes and scales were in registers before the last meeting, and that stage stored to the
     // other one.  Every wave stages 32 rows of its columns at a time in a part of its own.
     constexpr int E = 16 / (int)sizeof(OUT), LROW = 32 * TN * (int)sizeof(OUT) + 16, UNITS = 32 * TN / E, ROWS = 64 / UNITS;
