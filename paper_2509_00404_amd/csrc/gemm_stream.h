@@ -7,10 +7,18 @@ typedef uint32_t gs_u32x2 __attribute__((ext_vector_type(2)));
 typedef float gs_acc_t __attribute__((ext_vector_type(4)));
 
 // Transfers global memory -> LDS that pass through no register: the lane's 16 bytes go to lds + 16 lane.  lds and base
-// are uniform.
+// are uniform.  Two hazards that the compiler does not look for inside asm are closed here: m0 must have been written two
+// instructions before, and a base that a vector instruction wrote (v_readfirstlane, or v_readlane where it was spilled) may be read by
+// a memory instruction only five wait states later.  The scalar copy waits for either writer by itself, and stands where m0 needs an
+// instruction in between.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"          // m0 is one of the compiler's reserved registers, and is to be clobbered
 __device__ __forceinline__ void gs_dma16(uint32_t lds, uint32_t voff, const uint8_t* base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds), "v"(voff), "s"(base) : "memory");
+    const uint8_t* copy;
+    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
+                 : "=&s"(copy) : "s"(lds), "v"(voff), "s"(base) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 // all but the N youngest of the wave's transfers have arrived and its LDS reads are done; then the workgroup meets
 template <int N>
 __device__ __forceinline__ void gs_meet() {
