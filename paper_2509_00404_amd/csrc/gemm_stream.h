@@ -110,6 +110,12 @@ template <> struct GsStage<float> {
         *reinterpret_cast<float4*>(sm + row * 128 + (((4 * z + kg) ^ (row >> 1)) * 16)) = w;
     }
 };
+// Lanes exchange what they staged: the compiler may order one lane's read and write of different addresses as it likes, and LDS keeps
+// the wave's order.  (No instruction.)
+__device__ __forceinline__ void gs_wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 // the 16 staged rows to C (first row r0, first column c0); whole: inside the matrix and 16-byte aligned
 template <typename OUT>
 __device__ __forceinline__ void gs_store_rows(const uint8_t* sm, OUT* C, int64_t ldc, int64_t r0, int64_t c0, int64_t M, int64_t N,
@@ -144,6 +150,7 @@ __device__ __forceinline__ void gs_store_tile(uint8_t* sm, const gs_acc_t (&acc)
     const int row = lane & 15, kg = lane >> 4;
 #pragma unroll
     for (int z = 0; z < Z; ++z) GsStage<OUT>::put(sm, row, kg, z, acc[0][z], alpha);
+    gs_wave_order();
 #pragma unroll
     for (int q = 0; q < CHUNKS; ++q) {
         const int n = q + 1;
@@ -152,6 +159,7 @@ __device__ __forceinline__ void gs_store_tile(uint8_t* sm, const gs_acc_t (&acc)
             for (int z = 0; z < Z; ++z) GsStage<OUT>::put(sm + (n & 1) * 2048, row, kg, z, acc[n / CT][(n % CT) * Z + z], alpha);
         }
         gs_store_rows<OUT>(sm + (q & 1) * 2048, C, ldc, r0 + 16 * (q / CT), c0 + 16 * Z * (q % CT), M, N, whole, vec, lane);
+        gs_wave_order();                                 // both for the rows staged above and for the half just read
     }
 }
 
