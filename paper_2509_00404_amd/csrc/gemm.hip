@@ -1613,8 +1613,9 @@ bool assemble_in_one_trip(int ka, int kb, int64_t nblk) {
 // 0.95 / 0.98, 8192 0.92 / 0.94; two rounds, 8192 x 4096, K = 1024 1.00 / 1.04, 2048 0.95 / 0.99, 4096 0.91 / 0.96; four, 8192 x 8192,
 // K = 512 0.95 / 0.93, 4096 0.90 / 0.91; two with the second half empty, 2048 x 14336, K = 2048 0.95 / 1.02, 4096 0.95 / 1.00.  Fewer than
 // 256 tiles leave CUs idle, and the pipelined kernel then has the power to itself: 3072 x 4096, K = 4096 1.00 / 1.06.
-bool stream_shape(int64_t M, int64_t N, int64_t niter, bool lone) {
-    if (M < 1024 || N < 1024) return false;
+// (Its offsets within a tile's 256 rows of codes are 32 bits wide: rows of up to 2^32 / 255 bytes, 16.8 MB.)
+bool stream_shape(int64_t M, int64_t N, int64_t niter, int64_t row_bytes, bool lone) {
+    if (M < 1024 || N < 1024 || row_bytes > 0xFFFFFFFFll / 255) return false;
     const int64_t tiles = ceil_div64(M, 256) * ceil_div64(N, 256);
     return tiles >= 256 && ceil_div64(tiles, 256) * niter >= (lone ? 64 : 32);
 }
@@ -1654,7 +1655,7 @@ LinWs lin_layout(int64_t Ma, int64_t Nb, int ka, int kb, int64_t Kc) {
     const int64_t niter = w.Kt > 0 ? Kc / G_KI : ceil_div64(Kc, G_KI);
     const SmallPlan plan = gemm_plan(Ma, Nb, niter, whole, ka + kb + w.Kt == 0);
     w.Kep = (ka + kb + 15) / 16 * 16;
-    bool stream = whole && !plan.small && stream_shape(Ma, Nb, niter, ka + kb + w.Kt == 0);
+    bool stream = whole && !plan.small && stream_shape(Ma, Nb, niter, Kc / 2, ka + kb + w.Kt == 0);
     if (stream && (w.Kep + w.Kt) % 32 != 0) {
         if (w.Kep + 16 <= 256) w.Kep += 16;               // (the assembly kernel clears up to 256 columns)
         else stream = false;

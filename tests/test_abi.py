@@ -82,6 +82,19 @@ def test_linear_workspace_covers_every_smaller_rank(L, N, K):
                     assert st == -1, (fn.__name__, k, ka, kb, st)
 
 
+def test_streaming_gemm_leaves_rows_that_its_offsets_cannot_span():
+    """The streaming GEMM addresses a tile's 256 rows of codes with 32-bit offsets: 255 rows of K / 2 bytes and 64 more have to fit.  Seen
+    in the room for its scale plan (4 KiB per 256 rows and 128 elements), which is most of the workspace at these sizes."""
+    from paper_2509_00404_amd import metis
+    if not os.path.exists(metis.LIB_PATH):
+        pytest.skip("library not built")
+    K = 33686016                                             # a multiple of 128
+    assert 255 * (K // 2) + 64 <= 2 ** 32 < 255 * ((K + 128) // 2) + 64
+    plan = 2 * 16 * (K // 128) * 4096
+    assert metis.linear_workspace_bytes(4096, 4096, K, 0) > plan
+    assert metis.linear_workspace_bytes(4096, 4096, K + 128, 0) < 0.6 * plan
+
+
 def test_tensor_scale_helper_is_the_smallest_covering_power_of_two():
     from paper_2509_00404_amd import metis
     if not os.path.exists(metis.LIB_PATH):
