@@ -6,6 +6,7 @@
 // significant bits: exact) and multiplied on the fp16 matrix cores with fp32 accumulation.
 // The low-rank terms of the split enter as extra contraction columns (bf16, same
 // accumulators):  Abar Bbar^T = Ra Rb^T + [(Ra Vb + Ua Sa Va^T Vb) Sb] Ub^T + (Ua Sa)(Rb Va)^T.
+#include <algorithm>
 #include <stdlib.h>
 #include "common.h"
 #include "gemm_tile.h"
@@ -1839,15 +1840,22 @@ NtOperand nt(const metis_fp4& R, const metis_fp4& Ut, const metis_fp4& Vt, const
 
 extern "C" size_t metis_linear_workspace_bytes(int64_t L, int64_t N, int64_t K, int k) {
     if (L < 1 || N < 1 || K < 1 || k < 0) return 0;
-    // The operands' ranks may be any two up to k.  A layout grows with each of them, except that a skinny product of up to 64
-    // columns is cut into more parts than one of 65 to 128, and that unsplit operands take other kernels: the largest is at
-    // one of these.
+    // The operands' ranks may be any two up to k.  A layout without the streaming kernel's scale plan grows with each of them, except
+    // that a skinny product of up to 64 columns is cut into more parts than one of 65 to 128, and that unsplit operands take other
+    // kernels: the largest is at one of these.  The plan, the same for all ranks, may be there for some and not for others.
     const int ranks[3] = {0, k < 64 ? k : 64, k};
+    const int64_t shapes[3][3] = {{L, N, K}, {L, K, N}, {N, K, L}};
     size_t most = 0;
-    for (int ka : ranks)
-        for (int kb : ranks)
-            for (size_t b : {lin_layout(L, N, ka, kb, K).total, lin_layout(L, K, ka, kb, N).total, lin_layout(N, K, ka, kb, L).total})
-                if (b > most) most = b;
+    for (const auto& p : shapes) {
+        size_t rest = 0, plan = 0;
+        for (int ka : ranks)
+            for (int kb : ranks) {
+                const LinWs w = lin_layout(p[0], p[1], ka, kb, p[2]);
+                rest = std::max(rest, w.off_plan);
+                plan = std::max(plan, w.total - w.off_plan);
+            }
+        most = std::max(most, rest + plan);
+    }
     return most;
 }
 

@@ -82,6 +82,17 @@ def test_linear_workspace_covers_every_smaller_rank(L, N, K):
                     assert st == -1, (fn.__name__, k, ka, kb, st)
 
 
+@pytest.mark.parametrize("L,N,K", [(16384, 4112, 4112), (4112, 4112, 4112), (8208, 14352, 4112), (4096, 4096, 8192), (4112, 8192, 2064)])
+def test_linear_workspace_grows_with_the_rank(L, N, K):
+    """Room for operands of ranks up to k is room for operands of ranks up to any smaller one: the optional regions (parts of a cut last
+    round, the streaming GEMM's scale plan) included, without which a call runs on another kernel."""
+    from paper_2509_00404_amd import metis
+    if not os.path.exists(metis.LIB_PATH):
+        pytest.skip("library not built")
+    sizes = [metis.linear_workspace_bytes(L, N, K, k) for k in range(129)]
+    assert all(a <= b for a, b in zip(sizes[1:], sizes[2:]))
+
+
 def test_streaming_gemm_leaves_rows_that_its_offsets_cannot_span():
     """The streaming GEMM addresses a tile's 256 rows of codes with 32-bit offsets: 255 rows of K / 2 bytes and 64 more have to fit.  Seen
     in the room for its scale plan (4 KiB per 256 rows and 128 elements), which is most of the workspace at these sizes."""
