@@ -6,17 +6,18 @@ typedef uint32_t gs_u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t gs_u32x2 __attribute__((ext_vector_type(2)));
 typedef float gs_acc_t __attribute__((ext_vector_type(4)));
 
-// Transfers global memory -> LDS that pass through no register: the lane's 16 bytes go to lds + 16 lane.  lds and base
+// Transfers global memory -> LDS that pass through no register: the lane's 16 bytes go to lds + AT + 16 lane.  lds and base
 // are uniform.  Two hazards that the compiler does not look for inside asm are closed here: m0 must have been written two
 // instructions before, and a base that a vector instruction wrote (v_readfirstlane, or v_readlane where it was spilled) may be read by
 // a memory instruction only five wait states later.  The scalar copy waits for either writer by itself, and stands where m0 needs an
 // instruction in between.
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"          // m0 is one of the compiler's reserved registers, and is to be clobbered
+template <int AT>
 __device__ __forceinline__ void gs_dma16(uint32_t lds, uint32_t voff, const uint8_t* base) {
     const uint8_t* copy;
-    asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
-                 : "=&s"(copy) : "s"(lds), "v"(voff), "s"(base) : "memory", "m0");
+    asm volatile("s_add_u32 m0, %1, %4\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
+                 : "=&s"(copy) : "s"(lds), "v"(voff), "s"(base), "n"(AT) : "memory", "m0", "scc");
 }
 #pragma clang diagnostic pop
 // all but the N youngest of the wave's transfers have arrived and its LDS reads are done; then the workgroup meets
@@ -167,8 +168,10 @@ __device__ __forceinline__ void gs_store_tile(uint8_t* sm, const gs_acc_t (&acc)
 // What bounds it: the issue of a lone wave per SIMD.  64 contraction elements of a tile are 128 matrix instructions of 16 cycles
 // and 256 expansion instructions a wave; in the order M V V they take 2227 cycles where the matrix instructions alone take
 // 2060 (a register loop of the same), with the reads of the codes 2311, with the transfers 2544 (a transfer costs the wave ~45
-// cycles, whatever its place), and a tile's 8 units of extra columns, its stores and its start another 17000: 180500 cycles
-// for K = 4096 + 128 against a matrix core's 135200.  Why so:
+// cycles, whatever its place), and a tile's 4 units of extra columns, its stores and its start another 17000: 180500 cycles
+// for K = 4096 + 128 against a matrix core's 135200.  (As built now, by the counter of wave cycles over products of 4096 and 14336
+// elements at rank 64 on both sides: 2486 for 64 elements, 28600 for the rest of a tile.  57 of a unit's 920 instructions are s_nops
+// that the compiler puts between a matrix instruction and a multiplication of two asm statements.)  Why so:
 //  * 16 x 16 x 32 matrix instructions, not 32 x 32 x 16: an accumulator is read and written half as often, and in long runs,
 //    where the card holds its power and not its clock, the same loop on random codes runs at 1.97 PFLOP/s instead of 1.78;
 //  * accumulators in the accumulation registers, everything that is ordered in volatile asm (above);
@@ -180,7 +183,7 @@ __device__ __forceinline__ void gs_store_tile(uint8_t* sm, const gs_acc_t (&acc)
 //    128 x 64) is no faster: its panel is four times the bytes to move through L2 and LDS, 2680 cycles, and the expansion ahead
 //    costs 8 to 30 us a product.
 // Where it stands against the pipelined kernel it took these products from (fp32 partial sums in the same order, so mostly the same
-// bits), alone: 16384 x 4096 x 4096 430 -> 372 us, 16384 x 14336 x 4096 1505 -> 1295, 16384 x 4096 x 14336 1386 -> 1210, 2048 x 14336 x
+// bits), alone: 16384 x 4096 x 4096 430 -> 372 us, 16384 x 14336 x 4096 1505 -> 1270, 16384 x 4096 x 14336 1386 -> 1210, 2048 x 14336 x
 // 4096 200 -> 179.  (What was tried before: M V V with the expansions as ordinary code, which the compiler sinks to where they are
 // used, 3215 cycles; the block scales fetched from the rows; a wave-dependent delay behind the meeting, no effect.)
 // The tiles of a last round that fills few CUs are cut along the contraction (tail_first, tail_parts), as there.
@@ -308,11 +311,11 @@ k_fp4_gemm_nt_stream(Fp4Operand A, Fp4Operand B, int64_t K, const uint8_t* __res
     // again, unused, where leaving them out would cost a branch)
     auto issue = [&](uint32_t buf, auto kc) GS_INLINE {
         constexpr int k = decltype(kc)::value;
-        const uint32_t d = lds0 + buf;
-        if constexpr (k < 4) gs_dma16(d + 4096u * wave + 1024u * k, va[k], qa);
-        else if constexpr (k < 8) gs_dma16(d + GS_CODES + 4096u * wave + 1024u * (k - 4), vb[k - 4], qb);
-        else if constexpr (k == 8) gs_dma16(d + 2 * GS_CODES + 1024u * wave, vlane, qsa);
-        else gs_dma16(d + 2 * GS_CODES + GS_SCALES + 1024u * wave, vlane, qsb);
+        const uint32_t dc = lds0 + buf + 4096u * wave, ds = lds0 + buf + 1024u * wave;
+        if constexpr (k < 4) gs_dma16<1024 * k>(dc, va[k], qa);
+        else if constexpr (k < 8) gs_dma16<GS_CODES + 1024 * (k - 4)>(dc, vb[k - 4], qb);
+        else if constexpr (k == 8) gs_dma16<2 * GS_CODES>(ds, vlane, qsa);
+        else gs_dma16<2 * GS_CODES + GS_SCALES>(ds, vlane, qsb);
         if constexpr (k == 7) {
             qa += qstep;
             qb += qstep;

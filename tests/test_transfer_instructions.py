@@ -28,5 +28,5 @@ def test_every_transfer_takes_its_base_from_a_scalar_copy(tmp_path):
             if m:
                 transfers += 1
                 assert lines[i - 1].startswith(f"s_mov_b64 {m.group(1)}, s["), lines[i - 2:i + 1]
-                assert lines[i - 2].startswith("s_mov_b32 m0, s"), lines[i - 2:i + 1]
+                assert lines[i - 2].startswith("s_add_u32 m0, s"), lines[i - 2:i + 1]
     assert transfers > 0
