@@ -325,9 +325,10 @@ def main():
     gd = timers["gemm"].durations_ms(args.steps * n_gemm)
     gemm_ms = sum(gd) / len(gd)
     gemm_tflops = useful_flops * args.steps / (sum(gd) * 1e-3) / 1e12
-    roofline = {"kernel": "k_fp4_gemm_nt_pipe", "bound": "mfma", "achieved": round(gemm_tflops, 2),
+    gemm_kernel, gemm_traffic = gemm_from_profile(args.workload)
+    roofline = {"kernel": gemm_kernel, "bound": "mfma", "achieved": round(gemm_tflops, 2),
                 "peak": PEAK_MFMA_TFLOPS, "unit": "TFLOP/s", "frac": round(gemm_tflops / PEAK_MFMA_TFLOPS, 4),
-                "traffic": traffic_from_profile(args.workload), "avg_launch_ms": round(gemm_ms, 4),
+                "traffic": gemm_traffic, "avg_launch_ms": round(gemm_ms, 4),
                 "launches_per_step": n_gemm, "flop_per_launch": useful_flops / n_gemm,
                 "frac_of_fp8_peak": round(gemm_tflops / 5000.0, 4), "frac_of_fp4_peak": round(gemm_tflops / PEAK_FP4_TFLOPS, 4),
                 "timing": "HIP events on the launch stream around every launch of the timed steps"}
@@ -591,18 +592,21 @@ def extras(out, args, torch, metis, linears, all_ops, step, multi, useful_flops)
         out["quantize_plain"] = {"error": repr(e)[:200]}
 
 
-def traffic_from_profile(workload):
-    """HBM bytes per launch of the dominant kernel from the committed rocprofv3 counter summary
-    (FETCH_SIZE + WRITE_SIZE, scaled by the copy-kernel calibration); None if there is none."""
+def gemm_from_profile(workload):
+    """The FP4 GEMM kernel with the most launches of the workload and its HBM bytes per launch, from the committed rocprofv3 counter
+    summary (FETCH_SIZE + WRITE_SIZE, scaled by the copy-kernel calibration; kernel in the first 52 columns, then launches and MiB
+    read and written per launch).  Without one: the kernels' common name and None."""
     path = os.path.join(ROOT, "profiles", f"bench_config{workload[1]}_hbm_traffic.txt")
+    most, kernel, traffic = 0, "k_fp4_gemm_nt*", None
     try:
         for line in open(path):
-            if line.startswith("k_fp4_gemm_nt_pipe<unsigned short>"):
-                tail = line[52:].split()
-                return round((float(tail[0]) + float(tail[1])) * 2 ** 20)
+            if line.startswith("k_fp4_gemm_nt"):
+                launches, read, written = (float(x) for x in line[52:].split()[:3])
+                if launches > most:
+                    most, kernel, traffic = launches, line.split("<")[0], round((read + written) * 2 ** 20)
     except OSError:
         pass
-    return None
+    return kernel, traffic
 
 
 def cpu_baseline(np, torch, workloads, host, workload):
