@@ -380,8 +380,7 @@ int metis_quantize_mx(void* stream, const metis_mat* A, metis_mxfp4* out);
 
 /*
  * C[M,N] = A[M,K] B[N,K]^T on the block-scaled FP4 matrix instruction (the scales are applied by
- * the hardware, fp32 accumulation).  K % 32 == 0 (whole blocks; a K that is not a multiple of 256 takes a
- * somewhat slower variant of the kernel); C device, bf16 or fp32, row stride ld >= N.
+ * the hardware, fp32 accumulation).  K % 32 == 0 (whole blocks); C device, bf16 or fp32, row stride ld >= N.
  * Errors: METIS_INVALID_ARG, METIS_BAD_SHAPE, METIS_UNSUPPORTED (an operand larger than 4 GiB of codes).
  */
 int metis_mxfp4_gemm_nt(void* stream, const metis_mxfp4* A, const metis_mxfp4* B, metis_mat* C);

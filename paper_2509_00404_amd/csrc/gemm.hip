@@ -1610,10 +1610,12 @@ bool assemble_in_one_trip(int ka, int kb, int64_t nblk) {
 
 // Products for the streaming kernel (instead of the pipelined one).  It wants a workgroup on every CU, and work enough per CU to pay
 // for its start and the scale plan (lone: no extra columns, so that the plan is a launch of its own, ~5 us).  Measured call for call
-// against the pipelined kernel, at rank 64 / without factors: one round of tiles, 4096 x 4096, K = 2048 0.97 / 1.00 of its time, 4096
-// 0.95 / 0.98, 8192 0.92 / 0.94; two rounds, 8192 x 4096, K = 1024 1.00 / 1.04, 2048 0.95 / 0.99, 4096 0.91 / 0.96; four, 8192 x 8192,
-// K = 512 0.95 / 0.93, 4096 0.90 / 0.91; two with the second half empty, 2048 x 14336, K = 2048 0.95 / 1.02, 4096 0.95 / 1.00.  Fewer than
-// 256 tiles leave CUs idle, and the pipelined kernel then has the power to itself: 3072 x 4096, K = 4096 1.00 / 1.06.
+// against the pipelined kernel, parts of its time.  With factors, at the line of 32 units: 8192 x 4096, K = 2048 0.92; 8192 x 8192,
+// K = 1024 0.90; 16384 x 16384, K = 256 0.79 to 0.85; 32768 x 32768, K = 128 0.79; above it 4096 x 4096, K = 4096 0.90.  Without, at 64:
+// 4096 x 4096, K = 8192 0.88; 8192 x 8192, K = 2048 0.88; 16384 x 16384, K = 512 0.82.  Below the line it depends on the shape, and the
+// pipelined kernel keeps them all: 8192 x 8192, K = 512 0.95 / 0.93 (with factors / without), 4096 x 4096, K = 2048 0.97 / 1.00,
+// 8192 x 4096, K = 1024 1.00 / 1.04, 2048 x 14336, K = 2048 0.95 / 1.02.  Fewer than 256 tiles leave CUs idle, and the pipelined kernel
+// then has the power to itself: 3072 x 4096, K = 4096 1.00 / 1.06 (with so few that their contractions are cut: not measured).
 // (Its offsets within a tile's 256 rows of codes are 32 bits wide: rows of up to 2^32 / 255 bytes, 16.8 MB.)
 bool stream_shape(int64_t M, int64_t N, int64_t niter, int64_t row_bytes, bool lone) {
     if (M < 1024 || N < 1024 || row_bytes > 0xFFFFFFFFll / 255) return false;
