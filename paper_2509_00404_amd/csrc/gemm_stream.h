@@ -169,9 +169,9 @@ __device__ __forceinline__ void gs_store_tile(uint8_t* sm, const gs_acc_t (&acc)
 // and 256 expansion instructions a wave; in the order M V V they take 2227 cycles where the matrix instructions alone take
 // 2060 (a register loop of the same), with the reads of the codes 2311, with the transfers 2544 (a transfer costs the wave ~45
 // cycles, whatever its place), and a tile's 4 units of extra columns, its stores and its start another 17000: 180500 cycles
-// for K = 4096 + 128 against a matrix core's 135200.  (As built now, by the counter of wave cycles over products of 4096 and 14336
-// elements at rank 64 on both sides: 2486 for 64 elements, 28600 for the rest of a tile.  57 of a unit's 920 instructions are s_nops
-// that the compiler puts between a matrix instruction and a multiplication of two asm statements.)  Why so:
+// for K = 4096 + 128 against a matrix core's 135200.  (With all that is below, by the counter of wave cycles over products of 4096
+// and 14336 elements at rank 64 on both sides: 2486 for 64 elements, 28600 for the rest of a tile.  57 of a unit's 920 instructions
+// are s_nops that the compiler puts between a matrix instruction and a multiplication of two asm statements.)  Why so:
 //  * 16 x 16 x 32 matrix instructions, not 32 x 32 x 16: an accumulator is read and written half as often, and in long runs,
 //    where the card holds its power and not its clock, the same loop on random codes runs at 1.97 PFLOP/s instead of 1.78;
 //  * accumulators in the accumulation registers, everything that is ordered in volatile asm (above);
