@@ -32,14 +32,22 @@ __device__ __forceinline__ uint32_t pk_umax16(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, r);
 }
 
-// grid: (ceil(M/256), nsplit); block 512.  KT = number of 32-column tiles of V0 (k <= 32*KT).
+// One workgroup of 512 per 256 rows and contraction range.  KT = number of 32-column tiles of V0 (k <= 32*KT).
 // A is read with fully coalesced 16-byte loads (8 lanes cover one 128-byte row piece) and passes
 // through a per-wave LDS slice to reach the MFMA operand layout; loading each lane's operand
 // fragment directly would touch every cache line 4-8 times with 16 bytes each.
 template <int KT>
 __global__ void __launch_bounds__(64 * BC_WAVES)
-k_broadcast(const bf16_t* __restrict__ A, int64_t lda, int64_t M, int64_t N, const bf16_t* __restrict__ V0hi,
-            const bf16_t* __restrict__ V0lo, int k, float* __restrict__ Cpart, uint32_t* __restrict__ amax_bits) {
+k_broadcast(const CallBatch<BroadcastCall> batch) {
+    uint32_t local;
+    const BroadcastCall call = batch_call(batch, local);
+    const bf16_t* __restrict__ A = call.A;
+    const bf16_t* __restrict__ V0hi = call.V0hi;
+    const bf16_t* __restrict__ V0lo = call.V0lo;
+    uint32_t* __restrict__ amax_bits = call.amax_bits;
+    const int64_t lda = call.lda, M = call.M, N = call.N;
+    const int k = call.k;
+    const uint32_t ranges = call.wgs / call.row_blocks, range = local / call.row_blocks;
     constexpr int NT = 64 * BC_WAVES;
     constexpr int BVEC = 2 * 32 * KT * (BC_NC / 8) / NT;                     // 16-byte V0 vectors per thread
     static_assert(BVEC * NT == 2 * 32 * KT * (BC_NC / 8), "a V0 stage is a whole number of vectors per thread");
@@ -47,11 +55,11 @@ k_broadcast(const bf16_t* __restrict__ A, int64_t lda, int64_t M, int64_t N, con
     __shared__ __attribute__((aligned(16))) bf16_t Bs[2][2][32 * KT][BC_LDB];  // [buffer][hi/lo][column][n]
     __shared__ __attribute__((aligned(16))) bf16_t As[BC_WAVES][32][BC_LDB];   // per-wave slice of A
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t row0 = (int64_t)blockIdx.x * BC_ROWS + wave * 32;
-    // contraction stages are dealt round-robin to the gridDim.y workgroups of a row block, so that the
+    const int64_t row0 = (int64_t)(local - range * call.row_blocks) * BC_ROWS + wave * 32;
+    // contraction stages are dealt round-robin to the `ranges` workgroups of a row block, so that the
     // workgroups running side by side read neighbouring pieces of the same rows (DRAM page locality)
-    const int64_t nstride = (int64_t)gridDim.y * BC_NC;
-    const int64_t nbeg = (int64_t)blockIdx.y * BC_NC;
+    const int64_t nstride = (int64_t)ranges * BC_NC;
+    const int64_t nbeg = (int64_t)range * BC_NC;
     const int li = lane & 31, half = lane >> 5;
     const int lrow = lane >> 3, piece = lane & 7;           // coalesced load: 8 rows x 128 B per instruction
 
@@ -179,7 +187,7 @@ k_broadcast(const bf16_t* __restrict__ A, int64_t lda, int64_t M, int64_t N, con
     }
     // D layout 32x32: lane l, element v -> row 8*(v/4) + 4*(l/32) + v%4, column l%32.
     // Each contraction split writes its own partial C (plain stores); the consumers add the parts.
-    float* __restrict__ P = Cpart + (size_t)blockIdx.y * (size_t)M * k;
+    float* __restrict__ P = call.Cpart + (size_t)range * (size_t)M * k;
 #pragma unroll
     for (int t = 0; t < KT; ++t) {
         int c = 32 * t + li;
@@ -189,7 +197,7 @@ k_broadcast(const bf16_t* __restrict__ A, int64_t lda, int64_t M, int64_t N, con
             if (r < M && c < k) P[r * k + c] = acc[t][v];
         }
     }
-    if (amax_bits) {                          // kernel argument: the branch is uniform
+    if (amax_bits) {                          // of the call: the branch is uniform
         uint32_t m = (amax2 & 0xFFFFu) > (amax2 >> 16) ? (amax2 & 0xFFFFu) : (amax2 >> 16);
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
@@ -220,18 +228,28 @@ int broadcast_splits(int64_t M, int64_t N) {
     return (int)balanced_split(row_blocks, max_split, 256);
 }
 
-int launch_broadcast(hipStream_t s, const bf16_t* A, int64_t lda, int64_t M, int64_t N, const bf16_t* V0hi,
-                     const bf16_t* V0lo, int k, float* Cpart, uint32_t* amax_bits) {
-    const int kt = (k + 31) / 32;
-    dim3 grid((unsigned)ceil_div64(M, BC_ROWS), (unsigned)broadcast_splits(M, N));
-    dim3 block(64 * BC_WAVES);
-    switch (kt) {
-        case 1: hipLaunchKernelGGL(k_broadcast<1>, grid, block, 0, s, A, lda, M, N, V0hi, V0lo, k, Cpart, amax_bits); break;
-        case 2: hipLaunchKernelGGL(k_broadcast<2>, grid, block, 0, s, A, lda, M, N, V0hi, V0lo, k, Cpart, amax_bits); break;
-        case 3: hipLaunchKernelGGL(k_broadcast<3>, grid, block, 0, s, A, lda, M, N, V0hi, V0lo, k, Cpart, amax_bits); break;
-        case 4: hipLaunchKernelGGL(k_broadcast<4>, grid, block, 0, s, A, lda, M, N, V0hi, V0lo, k, Cpart, amax_bits); break;
-        default: return METIS_UNSUPPORTED;
+BroadcastCall broadcast_call(const bf16_t* A, int64_t lda, int64_t M, int64_t N, const bf16_t* V0hi, const bf16_t* V0lo, int k,
+                             float* Cpart, uint32_t* amax_bits) {
+    const uint32_t row_blocks = (uint32_t)ceil_div64(M, BC_ROWS);
+    return {A, lda, M, N, V0hi, V0lo, k, row_blocks * (uint32_t)broadcast_splits(M, N), row_blocks, Cpart, amax_bits};
+}
+
+// calls of up to 128 columns each
+int launch_broadcast(hipStream_t s, const std::vector<BroadcastCall>& calls) {
+    for (int kt = 1; kt <= 4; ++kt) {
+        std::vector<BroadcastCall> g;
+        for (const BroadcastCall& c : calls)
+            if ((c.k + 31) / 32 == kt) g.push_back(c);
+        const int st = launch_calls(g.data(), g.size(), [&](const CallBatch<BroadcastCall>& b, uint32_t wgs) {
+            const dim3 grid(wgs), block(64 * BC_WAVES);
+            switch (kt) {
+                case 1: hipLaunchKernelGGL(k_broadcast<1>, grid, block, 0, s, b); break;
+                case 2: hipLaunchKernelGGL(k_broadcast<2>, grid, block, 0, s, b); break;
+                case 3: hipLaunchKernelGGL(k_broadcast<3>, grid, block, 0, s, b); break;
+                default: hipLaunchKernelGGL(k_broadcast<4>, grid, block, 0, s, b); break;
+            }
+        });
+        if (st != METIS_OK) return st;
     }
-    METIS_LAUNCH_CHECK();
     return METIS_OK;
 }

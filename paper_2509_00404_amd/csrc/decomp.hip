@@ -112,24 +112,37 @@ FusedLayout make_fused_layout(size_t base, int64_t M, int64_t N, int k) {
 // flag word (a fill kernel, not a memset node, so the call can be graph-captured) and the two optional
 // output words, the next idx_blocks blocks draw the row sample, the rest draw Omega (a null idx / omega means
 // the caller supplied it).
+struct SetupCall {
+    uint32_t* zero;
+    size_t nwords;
+    uint32_t* amax_out;
+    int32_t* info;
+    uint32_t wgs;
+    int zero_blocks, idx_blocks;
+    uint64_t seed;
+    int64_t M, Ms, group;
+    uint32_t* idx;
+    int64_t omega_count;
+    bf16_t* omega;
+};
 __global__ void __launch_bounds__(256)
-k_decomp_setup(uint32_t* __restrict__ zero, size_t nwords, uint32_t* __restrict__ amax_out, int32_t* __restrict__ info,
-               int zero_blocks, int idx_blocks, uint64_t seed, int64_t M, int64_t Ms, int64_t group,
-               uint32_t* __restrict__ idx, int64_t omega_count, bf16_t* __restrict__ omega) {
-    const int b = blockIdx.x;
+k_decomp_setup(const CallBatch<SetupCall> batch) {
+    uint32_t local;
+    const SetupCall call = batch_call(batch, local);
+    const int b = (int)local, zero_blocks = call.zero_blocks, idx_blocks = call.idx_blocks;
     if (b < zero_blocks) {
         size_t i = (size_t)b * 256 + threadIdx.x;
         const size_t st = (size_t)zero_blocks * 256;
-        for (; i < nwords; i += st) zero[i] = 0u;
+        for (; i < call.nwords; i += st) call.zero[i] = 0u;
         if (b == 0 && threadIdx.x == 0) {
-            if (amax_out) *amax_out = 0u;
-            if (info) *info = 0;
+            if (call.amax_out) *call.amax_out = 0u;
+            if (call.info) *call.info = 0;
         }
     } else if (b < zero_blocks + idx_blocks) {
         const int64_t j = (int64_t)(b - zero_blocks) * 256 + threadIdx.x;
-        if (j < Ms) idx[j] = sample_row_grouped(seed, M, Ms, group, j);
+        if (j < call.Ms) call.idx[j] = sample_row_grouped(call.seed, call.M, call.Ms, call.group, j);
     } else {
-        gaussian_pair(seed, (int64_t)(b - zero_blocks - idx_blocks) * 256 + threadIdx.x, omega_count, omega);
+        gaussian_pair(call.seed, (int64_t)(b - zero_blocks - idx_blocks) * 256 + threadIdx.x, call.omega_count, call.omega);
     }
 }
 
@@ -313,14 +326,20 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
     // ---- flag and status words to zero, the draws the caller did not supply, sketch Z = A_s Omega, Gram of Z ----
     // (every split contraction writes its partial products to the job's `parts` region and a batched kernel adds
     // them in a fixed order: no floating-point atomics anywhere, so a decomposition is reproducible bit for bit)
-    for (const Job& j : jobs) {
-        const int zero_blocks = 1, idx_blocks = j.idx_in ? 0 : (int)ceil_div64(j.Ms, 256);
-        const int64_t omega_count = j.N * (int64_t)j.r;
-        const int64_t omega_blocks = j.omega_in ? 0 : ceil_div64(ceil_div64(omega_count, 2), 256);
-        hipLaunchKernelGGL(k_decomp_setup, dim3((unsigned)(zero_blocks + idx_blocks + omega_blocks)), dim3(256), 0, s,
-                           (uint32_t*)j.ws, j.L.zero_bytes / 4, (uint32_t*)j.amax_out, j.info, zero_blocks, idx_blocks, j.seed,
-                           j.M, j.Ms, j.group, j.idx_in ? nullptr : j.idx, omega_count, j.omega_in ? nullptr : j.omega);
-        METIS_LAUNCH_CHECK();
+    {
+        std::vector<SetupCall> calls;
+        for (const Job& j : jobs) {
+            const int zero_blocks = 1, idx_blocks = j.idx_in ? 0 : (int)ceil_div64(j.Ms, 256);
+            const int64_t omega_count = j.N * (int64_t)j.r;
+            const int64_t omega_blocks = j.omega_in ? 0 : ceil_div64(ceil_div64(omega_count, 2), 256);
+            calls.push_back({(uint32_t*)j.ws, j.L.zero_bytes / 4, (uint32_t*)j.amax_out, j.info,
+                             (uint32_t)(zero_blocks + idx_blocks + omega_blocks), zero_blocks, idx_blocks, j.seed, j.M, j.Ms, j.group,
+                             j.idx_in ? nullptr : j.idx, omega_count, j.omega_in ? nullptr : j.omega});
+        }
+        st = launch_calls(calls.data(), calls.size(), [&](const CallBatch<SetupCall>& b, uint32_t wgs) {
+            hipLaunchKernelGGL(k_decomp_setup, dim3(wgs), dim3(256), 0, s, b);
+        });
+        if (st != METIS_OK) return st;
     }
     // products of the same kind and step of all jobs go out together (DgemmList): the small ones are latency-bound
     DgemmList<double, double, EPI_PART_F64> gram;
@@ -344,12 +363,13 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
         gram.launch(s);
         sums.launch(s);
     };
+    std::vector<SketchCall<bf16_t>> sketches;
     for (const Job& j : jobs) {
         const int r = j.r;
         const int64_t tiles_zr = ceil_div64(j.Ms, 32) * ceil_div64(r, 32);
         int zp;
         if (j.fast) {
-            if ((st = launch_sketch(s, j.A, j.lda, j.idx_use, j.Ms, j.N, j.om_use, r, j.parts)) != METIS_OK) return st;
+            sketches.push_back(sketch_call(j.A, j.lda, j.idx_use, j.Ms, j.N, j.om_use, r, j.parts));
             zp = sketch_parts(j.Ms, j.N, r);
         } else {
             launch_dgemm<bf16_t, bf16_t, EPI_PART_F64>(s, op(j.A, j.lda, 1, j.idx_use), op(j.om_use, 1, r), j.Ms, r, j.N,
@@ -359,6 +379,7 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
         METIS_LAUNCH_CHECK();
         sums.add(j.parts, zp, j.Ms * (int64_t)r, j.Ms * (int64_t)r, j.Zacc);
     }
+    if ((st = launch_sketch(s, sketches)) != METIS_OK) return st;
     sums.launch(s);
     METIS_LAUNCH_CHECK();
     gram_of(&Job::Zacc, &Job::G1, [](const Job& j) { return j.Ms; }, false);
@@ -384,11 +405,12 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
     for (const Job& j : jobs) mul.add(op(j.H1, j.r, 1), op(j.Linv, j.r, 1), j.Ms, j.r, j.r, 1, epi_skip(j.H, j.r, j.wellcond));
     mul.launch(s);
     METIS_LAUNCH_CHECK();
+    std::vector<ProjectCall<bf16_t>> projections;
     for (const Job& j : jobs) {
         const int r = j.r;
         int bp;
         if (j.fast) {
-            if ((st = launch_project(s, j.H, j.H1, j.wellcond, r, j.A, j.lda, j.idx_use, j.Ms, j.N, j.parts)) != METIS_OK) return st;
+            projections.push_back(project_call(j.H, j.H1, j.wellcond, r, j.A, j.lda, j.idx_use, j.Ms, j.N, j.parts));
             bp = project_parts(j.Ms, j.N, r);
         } else {
             const int want = split_for(j.Ms, ceil_div64(r, 32) * ceil_div64(j.N, 32));
@@ -399,6 +421,7 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
         METIS_LAUNCH_CHECK();
         sums.add(j.parts, bp, (int64_t)r * j.N, (int64_t)r * j.N, j.B);
     }
+    if ((st = launch_project(s, projections)) != METIS_OK) return st;
     sums.launch(s);
     METIS_LAUNCH_CHECK();
     gram_of(&Job::B, &Job::G2, [](const Job& j) { return j.N; }, false);
@@ -420,6 +443,7 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
         v0mul.add(op(j.B, 1, j.N), op(j.T, 1, j.k), j.N, j.k, j.r, 1, epi(j.V0f, j.k, j.V0hi, j.V0lo, j.N));
     v0mul.launch(s);
     METIS_LAUNCH_CHECK();
+    std::vector<BroadcastCall> broadcasts;
     for (const Job& j : jobs) {
         const int k = j.k;
         if (j.split) {
@@ -439,7 +463,7 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
                 const int parts = broadcast_splits(rows, j.N);
                 const bf16_t* Ab = j.A + r0 * j.lda;
                 const int pi = metis_prof_begin(METIS_PROF_BROADCAST, s);
-                st = launch_broadcast(s, Ab, j.lda, rows, j.N, j.V0hi, j.V0lo, k, band, (uint32_t*)j.amax_out);
+                st = launch_broadcast(s, {broadcast_call(Ab, j.lda, rows, j.N, j.V0hi, j.V0lo, k, band, (uint32_t*)j.amax_out)});
                 metis_prof_end(METIS_PROF_BROADCAST, pi, s);
                 if (st != METIS_OK) return st;
                 if ((st = launch_band_factors(s, band, parts, rows * (int64_t)k, rows, k, F.kp, j.C + r0 * k,
@@ -453,16 +477,23 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
                     return st;
             }
         } else {
-            const int pi = metis_prof_begin(METIS_PROF_BROADCAST, s);
-            st = launch_broadcast(s, j.A, j.lda, j.M, j.N, j.V0hi, j.V0lo, k, j.C, (uint32_t*)j.amax_out);
-            metis_prof_end(METIS_PROF_BROADCAST, pi, s);
-            if (st != METIS_OK) return st;
+            broadcasts.push_back(broadcast_call(j.A, j.lda, j.M, j.N, j.V0hi, j.V0lo, k, j.C, (uint32_t*)j.amax_out));
         }
+    }
+    if (!broadcasts.empty()) {
+        const int pi = metis_prof_begin(METIS_PROF_BROADCAST, s);
+        st = launch_broadcast(s, broadcasts);
+        metis_prof_end(METIS_PROF_BROADCAST, pi, s);
+        if (st != METIS_OK) return st;
+    }
+    std::vector<GramCall> grams;
+    for (const Job& j : jobs) {
+        const int k = j.k;
         const int64_t tiles_kk = ceil_div64(k, 32) * ceil_div64(k, 32);
         const int64_t cstride = j.M * (int64_t)k;
         if (j.gram_fast) {
             // sums the broadcast's partial products into C (part 0) on the way
-            if ((st = launch_gram_parts(s, j.C, k, j.M, j.cparts, cstride, j.C, j.parts)) != METIS_OK) return st;
+            grams.push_back(gram_call(j.C, k, j.M, j.cparts, cstride, j.C, j.parts));
             sums.add(j.parts, (int)gram_blocks(j.M), (int64_t)k * k, (int64_t)k * k, j.G3);
         } else {
             const int want = split_for(j.M, tiles_kk);
@@ -472,6 +503,7 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
         }
         METIS_LAUNCH_CHECK();
     }
+    if ((st = launch_gram_parts(s, grams)) != METIS_OK) return st;
     sums.launch(s);
     METIS_LAUNCH_CHECK();
     // ---- singular-value form: C = U S W^T, V = V0 W ----

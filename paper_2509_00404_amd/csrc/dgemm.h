@@ -4,6 +4,7 @@
 // operands of type bf16, fp32 or fp64; several epilogues.
 #pragma once
 #include "common.h"
+#include <utility>
 #include <vector>
 
 typedef double double4_t __attribute__((ext_vector_type(4)));
@@ -152,29 +153,19 @@ k_dgemm(DOperand A, DOperand B, int64_t M, int64_t N, int64_t K, int64_t kchunk,
     dgemm_tile<TA, TB, EPI>(A, B, M, N, K, kchunk, ep, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
-// Several independent small products in one launch (the same step of several decompositions): the calls travel
-// by value in the kernel arguments, call c owns the blocks [off[c], off[c+1]) of a one-dimensional grid.
-#define DG_MAX_BATCH 16
+// Several independent small products in one launch (the same step of several decompositions).
 struct DgemmCall {
     DOperand A, B;
     int64_t M, N, K, kchunk;
     DEpilogue ep;
-    uint32_t gx, gy, gz;
-};
-struct DgemmBatch {
-    int n;
-    uint32_t off[DG_MAX_BATCH + 1];
-    DgemmCall c[DG_MAX_BATCH];
+    uint32_t gx, gy, wgs;
 };
 
 template <typename TA, typename TB, int EPI>
 __global__ void __launch_bounds__(256)
-k_dgemm_batch(const DgemmBatch b) {
-    const uint32_t blk = blockIdx.x;
-    int c = 0;
-    while (c + 1 < b.n && blk >= b.off[c + 1]) ++c;
-    const DgemmCall& call = b.c[c];
-    const uint32_t local = blk - b.off[c];
+k_dgemm_batch(const CallBatch<DgemmCall> b) {
+    uint32_t local;
+    const DgemmCall call = batch_call(b, local);
     const uint32_t bx = local % call.gx, by = (local / call.gx) % call.gy, bz = local / (call.gx * call.gy);
     dgemm_tile<TA, TB, EPI>(call.A, call.B, call.M, call.N, call.K, call.kchunk, call.ep, bx, by, bz);
 }
@@ -329,8 +320,7 @@ static inline void launch_dgemm(hipStream_t s, DOperand A, DOperand B, int64_t M
 }
 
 
-// A list of products of one kind: the small ones go out in launches of up to DG_MAX_BATCH calls, a large one
-// (see launch_dgemm) on its own.
+// A list of products of one kind: the small ones go out together, a large one (see launch_dgemm) on its own.
 template <typename TA, typename TB, int EPI>
 struct DgemmList {
     struct Item { DOperand A, B; int64_t M, N, K; int ksplit; DEpilogue ep; };
@@ -338,16 +328,8 @@ struct DgemmList {
     void add(DOperand A, DOperand B, int64_t M, int64_t N, int64_t K, int ksplit, DEpilogue ep) {
         items.push_back({A, B, M, N, K, ksplit, ep});
     }
-    void launch(hipStream_t s) {
-        DgemmBatch b;
-        b.n = 0;
-        b.off[0] = 0;
-        auto flush = [&]() {
-            if (b.n == 0) return;
-            for (int i = b.n; i < DG_MAX_BATCH; ++i) { b.c[i] = b.c[0]; b.off[i + 1] = b.off[b.n]; }
-            hipLaunchKernelGGL((k_dgemm_batch<TA, TB, EPI>), dim3(b.off[b.n]), dim3(256), 0, s, b);
-            b.n = 0;
-        };
+    int launch(hipStream_t s) {
+        std::vector<DgemmCall> calls;
         for (const Item& it : items) {
             if (dgemm_is_big(it.M, it.N, it.K)) {
                 launch_dgemm<TA, TB, EPI>(s, it.A, it.B, it.M, it.N, it.K, it.ksplit, it.ep);
@@ -355,16 +337,14 @@ struct DgemmList {
             }
             int64_t kchunk;
             const int ksplit = dgemm_parts<EPI>(it.M, it.N, it.K, it.ksplit, &kchunk);
-            DgemmCall& c = b.c[b.n];
-            c.A = it.A; c.B = it.B; c.M = it.M; c.N = it.N; c.K = it.K; c.kchunk = kchunk; c.ep = it.ep;
-            c.gx = (uint32_t)ceil_div64(it.N, DG_BN);
-            c.gy = (uint32_t)ceil_div64(it.M, DG_BM);
-            c.gz = (uint32_t)ksplit;
-            b.off[b.n + 1] = b.off[b.n] + c.gx * c.gy * c.gz;
-            if (++b.n == DG_MAX_BATCH) flush();
+            const uint32_t gx = (uint32_t)ceil_div64(it.N, DG_BN), gy = (uint32_t)ceil_div64(it.M, DG_BM);
+            calls.push_back({it.A, it.B, it.M, it.N, it.K, kchunk, it.ep, gx, gy, gx * gy * (uint32_t)ksplit});
         }
-        flush();
         items.clear();
+        METIS_LAUNCH_CHECK();
+        return launch_calls(calls.data(), calls.size(), [&](const CallBatch<DgemmCall>& b, uint32_t wgs) {
+            hipLaunchKernelGGL((k_dgemm_batch<TA, TB, EPI>), dim3(wgs), dim3(256), 0, s, b);
+        });
     }
 };
 
@@ -377,31 +357,24 @@ struct DgemmList {
 #define SUM_EB 32
 #define SUM_PG 8
 #define SUM_WIDE 512             // elements per workgroup in the few-parts shape
-#define SUM_MAX_BATCH 24
 struct SumCall {
     const double* parts;
     double* out;
     int64_t n, stride;
     int nparts;
     int wide;                    // 1: few parts of a large array
+    uint32_t wgs;
     const int32_t* skip;         // optional device flag: nonzero -> nothing is written
-};
-struct SumBatch {
-    int n;
-    uint32_t off[SUM_MAX_BATCH + 1];
-    SumCall c[SUM_MAX_BATCH];
 };
 
 static __global__ void __launch_bounds__(256)
-k_sum_parts_batch(const SumBatch b) {
+k_sum_parts_batch(const CallBatch<SumCall> b) {
     __shared__ double red[SUM_PG][SUM_EB];
-    const uint32_t blk = blockIdx.x;
-    int c = 0;
-    while (c + 1 < b.n && blk >= b.off[c + 1]) ++c;
-    const SumCall& call = b.c[c];
+    uint32_t local;
+    const SumCall call = batch_call(b, local);
     if (call.skip && *call.skip) return;
     if (call.wide) {
-        const int64_t i = ((int64_t)(blk - b.off[c]) * 256 + threadIdx.x) * 2;
+        const int64_t i = ((int64_t)local * 256 + threadIdx.x) * 2;
         if (i >= call.n) return;
         const double* __restrict__ src = call.parts + i;
         double a0 = 0.0, a1 = 0.0;
@@ -426,7 +399,7 @@ k_sum_parts_batch(const SumBatch b) {
         return;
     }
     const int e = threadIdx.x % SUM_EB, g = threadIdx.x / SUM_EB;
-    const int64_t i = (int64_t)(blk - b.off[c]) * SUM_EB + e;
+    const int64_t i = (int64_t)local * SUM_EB + e;
     const int per = (call.nparts + SUM_PG - 1) / SUM_PG;
     const int p0 = g * per, p1 = p0 + per < call.nparts ? p0 + per : call.nparts;
     double acc = 0.0;
@@ -450,24 +423,13 @@ struct SumList {
     void add(const double* parts, int nparts, int64_t stride, int64_t n, double* out, const int32_t* skip = nullptr) {
         // few parts of a large array: one thread adds them all; many parts: thread groups share them
         const int wide = nparts <= 24 || n >= ((int64_t)1 << 18);
-        items.push_back({parts, out, n, stride, nparts, wide, skip});
+        items.push_back({parts, out, n, stride, nparts, wide, (uint32_t)ceil_div64(n, wide ? SUM_WIDE : SUM_EB), skip});
     }
-    void launch(hipStream_t s) {
-        SumBatch b;
-        b.n = 0;
-        b.off[0] = 0;
-        auto flush = [&]() {
-            if (b.n == 0) return;
-            for (int i = b.n; i < SUM_MAX_BATCH; ++i) { b.c[i] = b.c[0]; b.off[i + 1] = b.off[b.n]; }
-            hipLaunchKernelGGL(k_sum_parts_batch, dim3(b.off[b.n]), dim3(256), 0, s, b);
-            b.n = 0;
-        };
-        for (const SumCall& it : items) {
-            b.c[b.n] = it;
-            b.off[b.n + 1] = b.off[b.n] + (uint32_t)ceil_div64(it.n, it.wide ? SUM_WIDE : SUM_EB);
-            if (++b.n == SUM_MAX_BATCH) flush();
-        }
-        flush();
+    int launch(hipStream_t s) {
+        const std::vector<SumCall> calls = std::move(items);
         items.clear();
+        return launch_calls(calls.data(), calls.size(), [&](const CallBatch<SumCall>& b, uint32_t wgs) {
+            hipLaunchKernelGGL(k_sum_parts_batch, dim3(wgs), dim3(256), 0, s, b);
+        });
     }
 };

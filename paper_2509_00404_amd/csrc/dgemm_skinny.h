@@ -14,6 +14,7 @@
 // here) and the launch are the other 10.
 #pragma once
 #include "dgemm.h"
+#include <algorithm>
 
 __device__ __forceinline__ double skinny_to_f64(bf16_t h) { return (double)__uint_as_float(((uint32_t)h) << 16); }
 __device__ __forceinline__ double skinny_to_f64(float x) { return (double)x; }
@@ -35,7 +36,7 @@ __device__ __forceinline__ void skinny_interleave() {
 //   A   bf16 (or fp32: the weight gradient of the factor gradients), rows of whole 16-byte pieces, 16-byte aligned, K % 8 == 0
 //   Om  bf16 [K][r] row-major, r % 8 == 0, base 16-byte aligned
 //   Z   fp64 [ksplit][Ms][r] partial products
-// grid (1, ceil(Ms/64), ksplit), block 256: wave w owns rows 16w..16w+15 and all NT column tiles.
+// one workgroup of 256 per 64 rows and chunk: wave w owns rows 16w..16w+15 and all NT column tiles.
 // ---------------------------------------------------------------------------------------
 // Waves per SIMD of both kernels.  At 3 and 4 column tiles two and no more: the contraction is cut so that two workgroups share a CU, and
 // with room for a third wave some SIMDs get three and others one (48 columns, fp32 14336 x 4096: 250 us, 262 without the limit).  With
@@ -56,18 +57,39 @@ struct SketchCfg {
     static constexpr int OM_LOADS = (KS * NT * 2 + 255) / 256;    // 16-byte pieces per thread and stage
 };
 
+template <typename TA>
+struct SketchCall {
+    const TA* A;
+    int64_t lda;
+    const uint32_t* rowmap;
+    int64_t Ms, K;
+    const bf16_t* Om;
+    int r;
+    uint32_t wgs, tiles;              // workgroups; of one chunk
+    int64_t kchunk;
+    double* Z;
+};
+
 template <int NT, typename TA>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SkinnyWaves<NT>::MIN, SkinnyWaves<NT>::MAX)))
-k_sketch(const TA* __restrict__ A, int64_t lda, const uint32_t* __restrict__ rowmap, int64_t Ms, int64_t K,
-         const bf16_t* __restrict__ Om, int r, int64_t kchunk, double* __restrict__ Z) {
+k_sketch(const CallBatch<SketchCall<TA>> batch) {
+    uint32_t local;
+    const SketchCall<TA> call = batch_call(batch, local);
+    const TA* __restrict__ A = call.A;
+    const uint32_t* __restrict__ rowmap = call.rowmap;
+    const bf16_t* __restrict__ Om = call.Om;
+    const int64_t lda = call.lda, Ms = call.Ms, K = call.K, kchunk = call.kchunk;
+    const int r = call.r;
+    const uint32_t chunk = local / call.tiles;
     typedef SketchCfg<NT, TA> Cfg;
     constexpr int LDO = Cfg::LDO, OML = Cfg::OM_LOADS, KS = Cfg::KS, LDA = Cfg::LDA;
     __shared__ __align__(16) TA As[2][SK_ROWS * LDA];
     __shared__ __align__(16) uint16_t Os[2][KS * LDO];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t m0 = (int64_t)blockIdx.y * SK_ROWS;
-    const int64_t kbeg = (int64_t)blockIdx.z * kchunk;
+    const int64_t m0 = (int64_t)(local - chunk * call.tiles) * SK_ROWS;
+    const int64_t kbeg = (int64_t)chunk * kchunk;
     const int64_t kend = kbeg + kchunk < K ? kbeg + kchunk : K;
+    double* __restrict__ Z = call.Z + (int64_t)chunk * Ms * r;
     if (kbeg >= kend) return;
 
     // the pad columns r .. 16 NT of the Omega stage, if there are any, stay zero
@@ -182,7 +204,7 @@ k_sketch(const TA* __restrict__ A, int64_t lda, const uint32_t* __restrict__ row
         for (int v = 0; v < 4; ++v) {
             const int64_t m = m0 + wave * 16 + 4 * v + (lane >> 4);
             const int col = 16 * j + (lane & 15);
-            if (m < Ms && col < r) Z[(int64_t)blockIdx.z * Ms * r + m * r + col] = acc[j][v];
+            if (m < Ms && col < r) Z[m * r + col] = acc[j][v];
         }
 }
 
@@ -191,7 +213,7 @@ k_sketch(const TA* __restrict__ A, int64_t lda, const uint32_t* __restrict__ row
 //   H   fp64 [Ms][r] row-major, r even
 //   A   bf16 as above, N % 8 == 0
 //   B   fp64 [ksplit][r][N] partial products
-// grid (ceil(N/64), 1, ksplit), block 256: wave w owns columns 16w..16w+15 and all NT row tiles.
+// one workgroup of 256 per 64 columns and chunk: wave w owns columns 16w..16w+15 and all NT row tiles.
 // Dynamic LDS: 2 H stages (fp64) + 2 A stages (bf16).
 // ---------------------------------------------------------------------------------------
 #define PJ_COLS 64
@@ -204,22 +226,41 @@ struct ProjectCfg {
     static constexpr size_t LDS = 2 * (size_t)PJ_KS * LDH * sizeof(double) + 2 * (size_t)PJ_KS * PJ_LDA * sizeof(TA);
 };
 
+template <typename TA>
+struct ProjectCall {
+    const double *H, *H_alt;
+    const int32_t* use_alt;
+    int r;
+    uint32_t wgs, tiles;              // workgroups; of one chunk
+    const TA* A;
+    int64_t lda;
+    const uint32_t* rowmap;
+    int64_t Ms, N, kchunk;
+    double* B;
+};
+
 template <int NT, typename TA>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SkinnyWaves<NT>::MIN, SkinnyWaves<NT>::MAX)))
-k_project(const double* __restrict__ H_main, const double* __restrict__ H_alt, const int32_t* __restrict__ use_alt, int r,
-          const TA* __restrict__ A, int64_t lda, const uint32_t* __restrict__ rowmap, int64_t Ms, int64_t N,
-          int64_t kchunk, double* __restrict__ B) {
+k_project(const CallBatch<ProjectCall<TA>> batch) {
+    uint32_t local;
+    const ProjectCall<TA> call = batch_call(batch, local);
     // the orthonormal basis: the second CholeskyQR pass's output, or the first pass's when that was enough
-    const double* __restrict__ H = (use_alt && *use_alt) ? H_alt : H_main;
+    const double* __restrict__ H = (call.use_alt && *call.use_alt) ? call.H_alt : call.H;
+    const TA* __restrict__ A = call.A;
+    const uint32_t* __restrict__ rowmap = call.rowmap;
+    const int64_t lda = call.lda, Ms = call.Ms, N = call.N, kchunk = call.kchunk;
+    const int r = call.r;
+    const uint32_t chunk = local / call.tiles;
     constexpr int LDH = ProjectCfg<NT, TA>::LDH;
     constexpr int HL = ProjectCfg<NT, TA>::H_LOADS;
     extern __shared__ __align__(16) unsigned char pj_smem[];
     double* Hs = reinterpret_cast<double*>(pj_smem);                                   // [2][PJ_KS * LDH]
     TA* As = reinterpret_cast<TA*>(pj_smem + 2 * (size_t)PJ_KS * LDH * sizeof(double));   // [2][PJ_KS * PJ_LDA]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t n0 = (int64_t)blockIdx.x * PJ_COLS;
-    const int64_t kbeg = (int64_t)blockIdx.z * kchunk;
+    const int64_t n0 = (int64_t)(local - chunk * call.tiles) * PJ_COLS;
+    const int64_t kbeg = (int64_t)chunk * kchunk;
     const int64_t kend = kbeg + kchunk < Ms ? kbeg + kchunk : Ms;
+    double* __restrict__ B = call.B + (int64_t)chunk * r * N;
     if (kbeg >= kend) return;
 
     if (r < 16 * NT) {                                                 // pad columns r .. 16 NT stay zero
@@ -337,7 +378,7 @@ k_project(const double* __restrict__ H_main, const double* __restrict__ H_alt, c
         for (int v = 0; v < 4; ++v) {
             const int j = 16 * i + 4 * v + (lane >> 4);
             const int64_t n = n0 + wave * 16 + (lane & 15);
-            if (j < r && n < N) B[((int64_t)blockIdx.z * r + j) * N + n] = acc[i][v];
+            if (j < r && n < N) B[(int64_t)j * N + n] = acc[i][v];
         }
 }
 
@@ -390,54 +431,69 @@ static inline int project_parts(int64_t Ms, int64_t N, int r) { return (int)ceil
 
 // Z = sketch_parts(Ms, K, r) partial products [Ms][r]
 template <typename TA>
-static inline int launch_sketch(hipStream_t s, const TA* A, int64_t lda, const uint32_t* rowmap, int64_t Ms, int64_t K,
-                                const bf16_t* Om, int r, double* Z) {
+static inline SketchCall<TA> sketch_call(const TA* A, int64_t lda, const uint32_t* rowmap, int64_t Ms, int64_t K, const bf16_t* Om, int r,
+                                         double* Z) {
     const int64_t kchunk = sketch_kchunk(Ms, K, r);
-    dim3 grid(1, (unsigned)ceil_div64(Ms, SK_ROWS), (unsigned)ceil_div64(K, kchunk));
-#define SKETCH_CASE(NT)                                                                                          \
-    hipLaunchKernelGGL((k_sketch<NT, TA>), grid, dim3(256), 0, s, A, lda, rowmap, Ms, K, Om, r, kchunk, Z);
-    switch ((r + 15) / 16) {
-        case 1: SKETCH_CASE(1) break;
-        case 2: SKETCH_CASE(2) break;
-        case 3: SKETCH_CASE(3) break;
-        case 4: SKETCH_CASE(4) break;
-        case 5: SKETCH_CASE(5) break;
-        case 6: SKETCH_CASE(6) break;
-        case 7: SKETCH_CASE(7) break;
-        case 8: SKETCH_CASE(8) break;
-        default: return METIS_UNSUPPORTED;
-    }
-#undef SKETCH_CASE
-    return METIS_OK;
+    const uint32_t tiles = (uint32_t)ceil_div64(Ms, SK_ROWS);
+    return {A, lda, rowmap, Ms, K, Om, r, tiles * (uint32_t)ceil_div64(K, kchunk), tiles, kchunk, Z};
 }
-
 // B = project_parts(Ms, N, r) partial products [r][N]
 template <typename TA>
-static inline int launch_project(hipStream_t s, const double* H, const double* H_alt, const int32_t* use_alt, int r,
-                                 const TA* A, int64_t lda, const uint32_t* rowmap, int64_t Ms, int64_t N, double* B) {
+static inline ProjectCall<TA> project_call(const double* H, const double* H_alt, const int32_t* use_alt, int r, const TA* A, int64_t lda,
+                                           const uint32_t* rowmap, int64_t Ms, int64_t N, double* B) {
     const int64_t kchunk = project_kchunk(Ms, N, r);
-    dim3 grid((unsigned)ceil_div64(N, PJ_COLS), 1, (unsigned)ceil_div64(Ms, kchunk));
-#define PROJECT_CASE(NT)                                                                                         \
-    {                                                                                                            \
-        const size_t lds = ProjectCfg<NT, TA>::LDS;                                                                  \
-        static LdsLimitCache lds_set;                                                                            \
-        if (!ensure_dyn_lds((const void*)k_project<NT, TA>, lds, lds_set)) return METIS_HIP_ERROR;                   \
-        hipLaunchKernelGGL((k_project<NT, TA>), grid, dim3(256), lds, s, H, H_alt, use_alt, r, A, lda, rowmap, Ms, N, kchunk, B);      \
-    }
-    switch ((r + 15) / 16) {
-        case 1: PROJECT_CASE(1) break;
-        case 2: PROJECT_CASE(2) break;
-        case 3: PROJECT_CASE(3) break;
-        case 4: PROJECT_CASE(4) break;
-        case 5: PROJECT_CASE(5) break;
-        case 6: PROJECT_CASE(6) break;
-        case 7: PROJECT_CASE(7) break;
-        case 8: PROJECT_CASE(8) break;
-        default: return METIS_UNSUPPORTED;
-    }
-#undef PROJECT_CASE
-    return METIS_OK;
+    const uint32_t tiles = (uint32_t)ceil_div64(N, PJ_COLS);
+    return {H, H_alt, use_alt, r, tiles * (uint32_t)ceil_div64(Ms, kchunk), tiles, A, lda, rowmap, Ms, N, kchunk, B};
 }
+
+// The calls whose width is NT column tiles, those with the longest workgroups first (the short ones fill the last round).
+template <typename Call>
+static inline std::vector<Call> skinny_of_width(const std::vector<Call>& calls, int nt) {
+    std::vector<Call> g;
+    for (const Call& c : calls)
+        if ((c.r + 15) / 16 == nt) g.push_back(c);
+    std::stable_sort(g.begin(), g.end(), [](const Call& a, const Call& b) { return a.kchunk > b.kchunk; });
+    return g;
+}
+
+template <int NT, typename TA>
+static inline int launch_sketch_width(hipStream_t s, const std::vector<SketchCall<TA>>& calls) {
+    const std::vector<SketchCall<TA>> g = skinny_of_width(calls, NT);
+    return launch_calls(g.data(), g.size(), [&](const CallBatch<SketchCall<TA>>& b, uint32_t wgs) {
+        hipLaunchKernelGGL((k_sketch<NT, TA>), dim3(wgs), dim3(256), 0, s, b);
+    });
+}
+template <int NT, typename TA>
+static inline int launch_project_width(hipStream_t s, const std::vector<ProjectCall<TA>>& calls) {
+    const std::vector<ProjectCall<TA>> g = skinny_of_width(calls, NT);
+    if (g.empty()) return METIS_OK;
+    const size_t lds = ProjectCfg<NT, TA>::LDS;
+    static LdsLimitCache lds_set;
+    if (!ensure_dyn_lds((const void*)k_project<NT, TA>, lds, lds_set)) return METIS_HIP_ERROR;
+    return launch_calls(g.data(), g.size(), [&](const CallBatch<ProjectCall<TA>>& b, uint32_t wgs) {
+        hipLaunchKernelGGL((k_project<NT, TA>), dim3(wgs), dim3(256), lds, s, b);
+    });
+}
+#define SKINNY_WIDTHS(LAUNCH)                                                                                   \
+    for (int nt = 1, st; nt <= 8; ++nt) {                                                                       \
+        switch (nt) {                                                                                           \
+            case 1: st = LAUNCH<1>(s, calls); break;                                                            \
+            case 2: st = LAUNCH<2>(s, calls); break;                                                            \
+            case 3: st = LAUNCH<3>(s, calls); break;                                                            \
+            case 4: st = LAUNCH<4>(s, calls); break;                                                            \
+            case 5: st = LAUNCH<5>(s, calls); break;                                                            \
+            case 6: st = LAUNCH<6>(s, calls); break;                                                            \
+            case 7: st = LAUNCH<7>(s, calls); break;                                                            \
+            default: st = LAUNCH<8>(s, calls); break;                                                           \
+        }                                                                                                       \
+        if (st != METIS_OK) return st;                                                                          \
+    }                                                                                                           \
+    return METIS_OK;
+// (r <= 128, skinny_ok)
+template <typename TA>
+static inline int launch_sketch(hipStream_t s, const std::vector<SketchCall<TA>>& calls) { SKINNY_WIDTHS(launch_sketch_width) }
+template <typename TA>
+static inline int launch_project(hipStream_t s, const std::vector<ProjectCall<TA>>& calls) { SKINNY_WIDTHS(launch_project_width) }
 
 // ---------------------------------------------------------------------------------------
 // Gram matrix of a tall skinny matrix given as a sum of partial arrays (the broadcast's per-split
@@ -445,23 +501,37 @@ static inline int launch_project(hipStream_t s, const double* H, const double* H
 // G holds gram_blocks(M) partial Gram matrices, added in a fixed order afterwards (k_sum_parts_batch).
 // The summed matrix is written back as fp32 (sum_out, may alias part 0) for the later U = S T.
 //   r % 4 == 0, C 16-byte aligned.
-// grid gram_blocks(M), block 256; wave w owns row tiles w, w+4 of G and all NT column tiles.
+// gram_blocks(M) workgroups of 256; wave w owns row tiles w, w+4 of G and all NT column tiles.
 // ---------------------------------------------------------------------------------------
 #define GR_KS 32                      // rows per stage
 // Rows of C per workgroup: one stage while that leaves at most 256 partial matrices (bound by the latency of the parts'
 // loads), two beyond, where the partial matrices' own traffic counts (k = 64: 32 KB each).  4096 rows: 11.5 -> 7.2 us against two.
 static inline int gram_rows(int64_t M) { return M <= 256 * GR_KS ? GR_KS : 2 * GR_KS; }
 static inline int64_t gram_blocks(int64_t M) { return ceil_div64(M, gram_rows(M)); }
+struct GramCall {
+    const float* C;
+    int r, rows, nparts;
+    uint32_t wgs;
+    int64_t M, part_stride;
+    float* sum_out;
+    double* G;
+};
 template <int NT>
 __global__ void __launch_bounds__(256)
-k_gram_parts(const float* C, int r, int64_t M, int rows, int nparts, int64_t part_stride, float* sum_out,
-             double* __restrict__ G) {
+k_gram_parts(const CallBatch<GramCall> batch) {
+    uint32_t local;
+    const GramCall call = batch_call(batch, local);
+    const float* C = call.C;
+    float* sum_out = call.sum_out;
+    const int r = call.r, rows = call.rows, nparts = call.nparts;
+    const int64_t M = call.M, part_stride = call.part_stride;
     constexpr int LDC = NT * 16 + ((NT * 16) % 32 == 16 ? 0 : 16);      // doubles, = 16 (mod 32)
     constexpr int PIECES = (GR_KS * NT * 4 + 255) / 256;                // float4 pieces per thread and stage
     constexpr int RT = (NT + 3) / 4;                                     // row tiles per wave
     __shared__ double Cs[GR_KS * LDC];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t m0 = (int64_t)blockIdx.x * rows;
+    const int64_t m0 = (int64_t)local * rows;
+    double* __restrict__ G = call.G + (int64_t)local * r * r;
     const int rc = r >> 2;
     for (int e = tid; e < GR_KS * LDC; e += 256) Cs[e] = 0.0;           // pad columns r .. 16 NT stay zero
     double4_t acc[RT][NT];
@@ -538,26 +608,22 @@ k_gram_parts(const float* C, int r, int64_t M, int rows, int nparts, int64_t par
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int a = 16 * it + 4 * v + (lane >> 4), b = 16 * j + (lane & 15);
-                if (a < r && b < r) G[((int64_t)blockIdx.x * r + a) * r + b] = acc[i][j][v];
+                if (a < r && b < r) G[a * r + b] = acc[i][j][v];
             }
     }
 }
 
-static inline int launch_gram_parts(hipStream_t s, const float* C, int r, int64_t M, int nparts, int64_t part_stride,
-                                    float* sum_out, double* G) {
-    dim3 grid((unsigned)gram_blocks(M));
-#define GRAM_CASE(NT) hipLaunchKernelGGL(k_gram_parts<NT>, grid, dim3(256), 0, s, C, r, M, gram_rows(M), nparts, part_stride, sum_out, G);
-    switch ((r + 15) / 16) {
-        case 1: GRAM_CASE(1) break;
-        case 2: GRAM_CASE(2) break;
-        case 3: GRAM_CASE(3) break;
-        case 4: GRAM_CASE(4) break;
-        case 5: GRAM_CASE(5) break;
-        case 6: GRAM_CASE(6) break;
-        case 7: GRAM_CASE(7) break;
-        case 8: GRAM_CASE(8) break;
-        default: return METIS_UNSUPPORTED;
-    }
-#undef GRAM_CASE
-    return METIS_OK;
+static inline GramCall gram_call(const float* C, int r, int64_t M, int nparts, int64_t part_stride, float* sum_out, double* G) {
+    return {C, r, gram_rows(M), nparts, (uint32_t)gram_blocks(M), M, part_stride, sum_out, G};
 }
+template <int NT>
+static inline int launch_gram_width(hipStream_t s, const std::vector<GramCall>& calls) {
+    std::vector<GramCall> g;
+    for (const GramCall& c : calls)
+        if ((c.r + 15) / 16 == NT) g.push_back(c);
+    return launch_calls(g.data(), g.size(), [&](const CallBatch<GramCall>& b, uint32_t wgs) {
+        hipLaunchKernelGGL(k_gram_parts<NT>, dim3(wgs), dim3(256), 0, s, b);
+    });
+}
+// (r <= 128)
+static inline int launch_gram_parts(hipStream_t s, const std::vector<GramCall>& calls) { SKINNY_WIDTHS(launch_gram_width) }
