@@ -29,7 +29,7 @@ struct Layout {
     int64_t M, N, Ms;
     int k, r;
     size_t off_zacc, off_g1, off_g1b, off_g2, off_g3, off_flag, off_c, off_b, off_parts, zero_bytes;
-    size_t off_idx, off_omega, off_linv, off_h1, off_h, off_lam, off_t, off_v0f, off_v0hi, off_v0lo,
+    size_t off_idx, off_omega, off_linv, off_h1, off_lam, off_t, off_v0f, off_v0hi, off_v0lo,
         off_lam3, off_w3, off_t3, off_jscr, total;
 };
 
@@ -58,7 +58,7 @@ Layout make_layout(int64_t M, int64_t N, int k, int p, int64_t Ms) {
         const size_t g3p = std::max((int)gram_blocks(M), dgemm_parts<EPI_PART_F64>(k, k, M, split_for(M, tiles_kk)));
         size_t need = zp * (size_t)Ms * r;
         need = std::max(need, bp * r * (size_t)N);
-        need = std::max(need, std::max(g1p, g2p) * r * r);
+        need = std::max(need, (g1p + g2p) * r * r);      // (the second pass's two at once)
         need = std::max(need, g3p * kk * kk);
         L.off_parts = take(need * 8);
     }
@@ -67,7 +67,6 @@ Layout make_layout(int64_t M, int64_t N, int k, int p, int64_t Ms) {
     L.off_omega = take((size_t)N * r * 2);
     L.off_linv = take(r * r * 8);
     L.off_h1 = take((size_t)Ms * r * 8);
-    L.off_h = take((size_t)Ms * r * 8);
     L.off_lam = take(r * 8);
     L.off_t = take(r * kk * 8);
     L.off_v0f = take((size_t)N * kk * 4);
@@ -172,11 +171,6 @@ DEpilogue epi_part(double* parts, int64_t M, int64_t N, const int32_t* skip = nu
     e.skip = skip;
     return e;
 }
-DEpilogue epi_skip(void* c, int64_t ldc, const int32_t* skip) {
-    DEpilogue e = epi(c, ldc);
-    e.skip = skip;
-    return e;
-}
 
 }  // namespace
 
@@ -205,7 +199,7 @@ struct Job {
     int cparts;
     char* ws;
     Layout L;
-    double *Zacc, *G1, *G1b, *G2, *G3, *Linv, *H1, *H, *B, *lam, *T, *lam3, *W3, *T3, *jscr, *parts;
+    double *Zacc, *G1, *G1b, *G2, *G3, *Linv, *H1, *B, *lam, *T, *lam3, *W3, *T3, *jscr, *parts;
     float *C, *V0f;
     uint32_t* idx;
     bf16_t *omega, *V0hi, *V0lo;
@@ -258,7 +252,6 @@ int make_job(const metis_decompose_job& a, Job& j) {
     j.omega = (bf16_t*)(ws + L.off_omega);
     j.Linv = (double*)(ws + L.off_linv);
     j.H1 = (double*)(ws + L.off_h1);
-    j.H = (double*)(ws + L.off_h);
     j.B = (double*)(ws + L.off_b);
     j.lam = (double*)(ws + L.off_lam);
     j.T = (double*)(ws + L.off_t);
@@ -277,7 +270,9 @@ int make_job(const metis_decompose_job& a, Job& j) {
     j.fast = skinny_ok(j.A, j.lda, j.N, j.r) && reinterpret_cast<uintptr_t>(j.om_use) % 16 == 0;
     // The second CholeskyQR pass only repairs the orthogonality the first one lost to cond(Z)^2 eps.  When the
     // first factor's diagonal shows a well-conditioned sketch the first pass's H1 is orthonormal to ~1e-10
-    // already: a device flag then turns the second pass's kernels into no-ops and the projection reads H1.
+    // already: a device flag then turns the second pass's kernel into a no-op.  The projection reads H1 either way: with H1 = H R2
+    // the pass's factor X = R2^-T turns B1 = H1^T A_s into B = X B1, and only B B^T = X (B1 B1^T) X^T and V0 = B1^T (X^T T)
+    // are ever needed, so that it costs one launch and not four when there is nothing to repair (4.5 us each).
     j.wellcond = j.fast ? (int32_t*)(ws + L.off_flag) : nullptr;
     j.gram_fast = a.k % 4 == 0;
     j.cparts = a.split ? 1 : broadcast_splits(j.M, j.N);      // the fused path sums each band's parts at once
@@ -348,20 +343,16 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
     DgemmList<float, double, EPI_STORE_F32> outmul;
     SumList sums;
     auto tiles_rr = [](const Job& j) { return ceil_div64(j.r, 32) * ceil_div64(j.r, 32); };
-    // Gram matrix of X (K x r, row-major, ld r) for every job: partial products, then their sum
-    auto gram_of = [&](double* Job::*X, double* Job::*G, auto K_of, bool skippable) {
-        for (const Job& j : jobs) {
-            const int r = j.r;
-            const int64_t K = K_of(j);
-            const bool by_rows = X != &Job::B;           // Z, H1: contraction over rows; B (r x N): over columns
-            const DOperand o = by_rows ? op(j.*X, 1, r) : op(j.*X, K, 1);
-            const int32_t* skip = skippable ? j.wellcond : nullptr;
-            gram.add(o, o, r, r, K, split_for(K, tiles_rr(j)), epi_part(j.parts, r, r, skip));
-            sums.add(j.parts, dgemm_parts<EPI_PART_F64>(r, r, K, split_for(K, tiles_rr(j))), (int64_t)r * r, (int64_t)r * r,
-                     j.*G, skip);
-        }
-        gram.launch(s);
-        sums.launch(s);
+    // Gram matrix of an r-wide operand over a contraction of K: partial products at `parts`, to be summed into G; returns their number
+    auto gram_of = [&](const Job& j, const DOperand& o, int64_t K, double* parts, double* G, const int32_t* skip) {
+        const int r = j.r, n = dgemm_parts<EPI_PART_F64>(r, r, K, split_for(K, tiles_rr(j)));
+        gram.add(o, o, r, r, K, split_for(K, tiles_rr(j)), epi_part(parts, r, r, skip));
+        sums.add(parts, n, (int64_t)r * r, (int64_t)r * r, G, skip);
+        return n;
+    };
+    auto grams_launch = [&]() {
+        const int e = gram.launch(s);
+        return e != METIS_OK ? e : sums.launch(s);
     };
     std::vector<SketchCall<bf16_t>> sketches;
     for (const Job& j : jobs) {
@@ -380,41 +371,29 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
         sums.add(j.parts, zp, j.Ms * (int64_t)r, j.Ms * (int64_t)r, j.Zacc);
     }
     if ((st = launch_sketch(s, sketches)) != METIS_OK) return st;
-    sums.launch(s);
-    METIS_LAUNCH_CHECK();
-    gram_of(&Job::Zacc, &Job::G1, [](const Job& j) { return j.Ms; }, false);
-    METIS_LAUNCH_CHECK();
+    if ((st = sums.launch(s)) != METIS_OK) return st;
+    for (const Job& j : jobs) gram_of(j, op(j.Zacc, 1, j.r), j.Ms, j.parts, j.G1, nullptr);
+    if ((st = grams_launch()) != METIS_OK) return st;
     // ---- CholeskyQR2: Z = H R ----
     {
         std::vector<CholProblem> pr;
-        for (const Job& j : jobs) pr.push_back({j.G1, j.Linv, j.info, j.wellcond, nullptr});
+        for (const Job& j : jobs) pr.push_back({j.G1, j.Linv, j.info, j.wellcond, nullptr, nullptr});
         if ((st = launch_grouped<CholProblem>(jobs, [](const Job& j) { return j.r; }, chol_launch, s, pr, zeros)) != METIS_OK)
             return st;
     }
     for (const Job& j : jobs) mul.add(op(j.Zacc, j.r, 1), op(j.Linv, j.r, 1), j.Ms, j.r, j.r, 1, epi(j.H1, j.r));
-    mul.launch(s);
-    gram_of(&Job::H1, &Job::G1b, [](const Job& j) { return j.Ms; }, true);
-    METIS_LAUNCH_CHECK();
-    {
-        std::vector<CholProblem> pr;
-        for (const Job& j : jobs) pr.push_back({j.G1b, j.Linv, j.info, nullptr, j.wellcond});
-        if ((st = launch_grouped<CholProblem>(jobs, [](const Job& j) { return j.r; }, chol_launch, s, pr, zeros)) != METIS_OK)
-            return st;
-    }
-    // ---- reduced matrix B = H^T A_s (r x N) and its Gram matrix ----
-    for (const Job& j : jobs) mul.add(op(j.H1, j.r, 1), op(j.Linv, j.r, 1), j.Ms, j.r, j.r, 1, epi_skip(j.H, j.r, j.wellcond));
-    mul.launch(s);
-    METIS_LAUNCH_CHECK();
+    if ((st = mul.launch(s)) != METIS_OK) return st;
+    // ---- reduced matrix B1 = H1^T A_s (r x N), its Gram matrix, and the second pass ----
     std::vector<ProjectCall<bf16_t>> projections;
     for (const Job& j : jobs) {
         const int r = j.r;
         int bp;
         if (j.fast) {
-            projections.push_back(project_call(j.H, j.H1, j.wellcond, r, j.A, j.lda, j.idx_use, j.Ms, j.N, j.parts));
+            projections.push_back(project_call(j.H1, r, j.A, j.lda, j.idx_use, j.Ms, j.N, j.parts));
             bp = project_parts(j.Ms, j.N, r);
         } else {
             const int want = split_for(j.Ms, ceil_div64(r, 32) * ceil_div64(j.N, 32));
-            launch_dgemm<double, bf16_t, EPI_PART_F64>(s, op(j.H, 1, r), op(j.A, 1, j.lda, nullptr, j.idx_use), r, j.N, j.Ms,
+            launch_dgemm<double, bf16_t, EPI_PART_F64>(s, op(j.H1, 1, r), op(j.A, 1, j.lda, nullptr, j.idx_use), r, j.N, j.Ms,
                                                         want, epi_part(j.parts, r, j.N));
             bp = dgemm_parts<EPI_PART_F64>(r, j.N, j.Ms, want);
         }
@@ -422,16 +401,24 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
         sums.add(j.parts, bp, (int64_t)r * j.N, (int64_t)r * j.N, j.B);
     }
     if ((st = launch_project(s, projections)) != METIS_OK) return st;
-    sums.launch(s);
-    METIS_LAUNCH_CHECK();
-    gram_of(&Job::B, &Job::G2, [](const Job& j) { return j.N; }, false);
-    METIS_LAUNCH_CHECK();
+    if ((st = sums.launch(s)) != METIS_OK) return st;
+    for (const Job& j : jobs) {
+        const int n = gram_of(j, op(j.B, j.N, 1), j.N, j.parts, j.G2, nullptr);
+        gram_of(j, op(j.H1, 1, j.r), j.Ms, j.parts + (int64_t)n * j.r * j.r, j.G1b, j.wellcond);
+    }
+    if ((st = grams_launch()) != METIS_OK) return st;
+    {
+        std::vector<CholProblem> pr;
+        for (const Job& j : jobs) pr.push_back({j.G1b, j.Linv, j.info, nullptr, j.wellcond, j.G2});
+        if ((st = launch_grouped<CholProblem>(jobs, [](const Job& j) { return j.r; }, chol_launch, s, pr, zeros)) != METIS_OK)
+            return st;
+    }
     // ---- top-k right singular vectors of B from the eigen-decomposition of B B^T ----
     {
         std::vector<JacobiProblem> pr;
         std::vector<int> kks;
         for (const Job& j : jobs) {
-            pr.push_back({j.G2, j.lam, nullptr, j.T, nullptr, j.jscr});
+            pr.push_back({j.G2, j.lam, nullptr, j.T, nullptr, j.jscr, j.Linv, j.wellcond});
             kks.push_back(j.k);
         }
         if ((st = launch_grouped<JacobiProblem>(jobs, [](const Job& j) { return j.r; }, launch_jacobi_eig_batch, s, pr, kks)) !=
@@ -441,8 +428,7 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
     // ---- broadcast to the full batch: C = A V0, and its Gram matrix ----
     for (const Job& j : jobs)
         v0mul.add(op(j.B, 1, j.N), op(j.T, 1, j.k), j.N, j.k, j.r, 1, epi(j.V0f, j.k, j.V0hi, j.V0lo, j.N));
-    v0mul.launch(s);
-    METIS_LAUNCH_CHECK();
+    if ((st = v0mul.launch(s)) != METIS_OK) return st;
     std::vector<BroadcastCall> broadcasts;
     for (const Job& j : jobs) {
         const int k = j.k;
@@ -504,14 +490,13 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
         METIS_LAUNCH_CHECK();
     }
     if ((st = launch_gram_parts(s, grams)) != METIS_OK) return st;
-    sums.launch(s);
-    METIS_LAUNCH_CHECK();
+    if ((st = sums.launch(s)) != METIS_OK) return st;
     // ---- singular-value form: C = U S W^T, V = V0 W ----
     {
         std::vector<JacobiProblem> pr;
         std::vector<int> kks;
         for (const Job& j : jobs) {
-            pr.push_back({j.G3, j.lam3, j.W3, j.T3, j.S, nullptr});
+            pr.push_back({j.G3, j.lam3, j.W3, j.T3, j.S, nullptr, nullptr, nullptr});
             kks.push_back(j.k);
         }
         if ((st = launch_grouped<JacobiProblem>(jobs, [](const Job& j) { return j.k; }, launch_jacobi_eig_batch, s, pr, kks)) !=
@@ -527,8 +512,7 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
             outmul.add(op_parts(j.C, k, 1, j.cparts, cstride), op(j.T3, 1, k), j.M, k, k, 1, epi(j.U, k));
         outmul.add(op(j.V0f, k, 1), op(j.W3, 1, k), j.N, k, k, 1, epi(j.V, k));
     }
-    outmul.launch(s);
-    METIS_LAUNCH_CHECK();
+    if ((st = outmul.launch(s)) != METIS_OK) return st;
     for (const Job& j : jobs)
         if (j.split && (st = quantize_factors(s, j.U, j.S, j.V, j.M, j.N, j.k, j.split, false, 0)) != METIS_OK) return st;
     return METIS_OK;

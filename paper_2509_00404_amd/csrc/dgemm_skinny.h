@@ -228,8 +228,7 @@ struct ProjectCfg {
 
 template <typename TA>
 struct ProjectCall {
-    const double *H, *H_alt;
-    const int32_t* use_alt;
+    const double* H;
     int r;
     uint32_t wgs, tiles;              // workgroups; of one chunk
     const TA* A;
@@ -244,8 +243,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Skinny
 k_project(const CallBatch<ProjectCall<TA>> batch) {
     uint32_t local;
     const ProjectCall<TA> call = batch_call(batch, local);
-    // the orthonormal basis: the second CholeskyQR pass's output, or the first pass's when that was enough
-    const double* __restrict__ H = (call.use_alt && *call.use_alt) ? call.H_alt : call.H;
+    const double* __restrict__ H = call.H;
     const TA* __restrict__ A = call.A;
     const uint32_t* __restrict__ rowmap = call.rowmap;
     const int64_t lda = call.lda, Ms = call.Ms, N = call.N, kchunk = call.kchunk;
@@ -439,11 +437,11 @@ static inline SketchCall<TA> sketch_call(const TA* A, int64_t lda, const uint32_
 }
 // B = project_parts(Ms, N, r) partial products [r][N]
 template <typename TA>
-static inline ProjectCall<TA> project_call(const double* H, const double* H_alt, const int32_t* use_alt, int r, const TA* A, int64_t lda,
-                                           const uint32_t* rowmap, int64_t Ms, int64_t N, double* B) {
+static inline ProjectCall<TA> project_call(const double* H, int r, const TA* A, int64_t lda, const uint32_t* rowmap, int64_t Ms, int64_t N,
+                                           double* B) {
     const int64_t kchunk = project_kchunk(Ms, N, r);
     const uint32_t tiles = (uint32_t)ceil_div64(N, PJ_COLS);
-    return {H, H_alt, use_alt, r, tiles * (uint32_t)ceil_div64(Ms, kchunk), tiles, A, lda, rowmap, Ms, N, kchunk, B};
+    return {H, r, tiles * (uint32_t)ceil_div64(Ms, kchunk), tiles, A, lda, rowmap, Ms, N, kchunk, B};
 }
 
 // The calls whose width is NT column tiles, those with the longest workgroups first (the short ones fill the last round).

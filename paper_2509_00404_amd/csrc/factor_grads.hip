@@ -174,7 +174,7 @@ int run(hipStream_t s, const TW* dW, int64_t ld, int64_t N, int64_t K, int k, co
         if ((st = launch_sketch<TW>(s, {sketch_call(dW, ld, nullptr, N, K, Vbf, k, parts)})) != METIS_OK) return st;
         sums.add(parts, sketch_parts(N, K, k), N * (int64_t)k, N * (int64_t)k, T);
         // dV^T = (Ubar S)^T dW         [k,K], contraction over N
-        if ((st = launch_project<TW>(s, {project_call<TW>(H64, nullptr, nullptr, k, dW, ld, nullptr, N, K, parts2)})) != METIS_OK) return st;
+        if ((st = launch_project<TW>(s, {project_call(H64, k, dW, ld, nullptr, N, K, parts2)})) != METIS_OK) return st;
         sums.add(parts2, project_parts(N, K, k), K * (int64_t)k, K * (int64_t)k, dV64);
         sums.launch(s);
     } else {

@@ -12,7 +12,8 @@ struct CholProblem {
     int32_t* info;            // optional: index + 1 of a pivot that was not positive
     int32_t* wellcond_out;    // optional: set to 1 when the factor's diagonal spans less than 1e3 (the QR pass that
                               // used it is then orthonormal to ~1e-10)
-    const int32_t* skip_in;   // optional: nonzero -> Linv = identity without factoring
+    const int32_t* skip_in;   // optional: nonzero -> nothing is done
+    double* transform;        // optional: n x n, replaced by Linv transform Linv^T
 };
 struct CholBatch { CholProblem p[SM_MAX_BATCH]; };
 
@@ -24,20 +25,11 @@ struct JacobiProblem {
     float* sval;              // optional kk square roots of the eigenvalues
     double* gscr;             // optional jacobi_scratch_doubles(n) doubles of device scratch; when given (and the order
                               // allows it) the sweeps start from columns preconditioned with approximate eigenvectors
+    const double* post;       // optional n x n lower triangular X: tmat becomes X^T tmat
+    const int32_t* post_skip; // optional: nonzero -> it does not
 };
 struct JacobiBatch { JacobiProblem p[SM_MAX_BATCH]; };
 
 int launch_chol_inv_batch(hipStream_t s, const CholProblem* probs, int count, int n);
 int launch_jacobi_eig_batch(hipStream_t s, const JacobiProblem* probs, int count, int n, int kk);
 size_t jacobi_scratch_doubles(int n);
-
-static inline int launch_chol_inv(hipStream_t s, const double* G, int n, double* Linv, int32_t* info,
-                                  int32_t* wellcond_out = nullptr, const int32_t* skip_in = nullptr) {
-    const CholProblem p = {G, Linv, info, wellcond_out, skip_in};
-    return launch_chol_inv_batch(s, &p, 1, n);
-}
-static inline int launch_jacobi_eig(hipStream_t s, const double* G, int n, int kk, double* lam, double* vec, double* tmat,
-                                    float* sval, double* gscr = nullptr) {
-    const JacobiProblem p = {G, lam, vec, tmat, sval, gscr};
-    return launch_jacobi_eig_batch(s, &p, 1, n, kk);
-}

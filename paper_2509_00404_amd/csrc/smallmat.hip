@@ -197,8 +197,37 @@ __device__ __forceinline__ void chol_blocked(double* __restrict__ W, int ld, int
     __syncthreads();                                     // the last panel is visible to the caller
 }
 
+// One 16x16 tile of sum_{kbeg <= k < kend} a(i, k) b(k, j) on the fp64 matrix cores (kbeg a multiple of 16); lane supplies
+// row/column (lane & 15) and the k offset lane >> 4.  fa / fb read in-bounds elements; out-of-range rows, columns and k
+// contribute zero.
+template <class FA, class FB>
+__device__ __forceinline__ double4_t tile_mma(int n, int ia, int jb, int kq, FA fa, FB fb, int kbeg, int kend) {
+    const int ic = min(ia, n - 1), jc = min(jb, n - 1);
+    const bool iok = ia < n, jok = jb < n;
+    double4_t acc = {0.0, 0.0, 0.0, 0.0};
+    if ((n & 15) == 0 && (kend & 15) == 0) {      // whole tiles: no guards, operands of four steps loaded ahead
+        for (int k0 = kbeg; k0 < kend; k0 += 16) {
+            double a[4], b[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                a[u] = fa(ia, k0 + 4 * u + kq);
+                b[u] = fb(k0 + 4 * u + kq, jb);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[u], acc, 0, 0, 0);
+        }
+        return acc;
+    }
+    for (int k0 = kbeg; k0 < kend; k0 += 4) {
+        const int k = k0 + kq, kc = min(k, n - 1);
+        const double a = fa(ic, kc), b = fb(kc, jc);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64((iok && k < kend) ? a : 0.0, (jok && k < kend) ? b : 0.0, acc, 0, 0, 0);
+    }
+    return acc;
+}
+
 // ---------------------------------------------------------------------------------------
-// Cholesky G = L L^T and Linv = L^-1 (lower triangular), n <= SM_MAX_N.
+// Cholesky G = L L^T and Linv = L^-1 (lower triangular), n <= SM_MAX_CHOL; optionally a second matrix F <- Linv F Linv^T.
 // LDS: L [n][n+1] doubles, X [n][n+1] doubles.
 // ---------------------------------------------------------------------------------------
 #define CI_THREADS 512               // 256 registers per lane: the panels take 140
@@ -212,10 +241,7 @@ k_chol_inv(const CholBatch batch, int n) {
     int32_t* __restrict__ info = prob.info;
     int32_t* __restrict__ wellcond_out = prob.wellcond_out;
     const int32_t* __restrict__ skip_in = prob.skip_in;
-    if (skip_in && *skip_in) {
-        for (int e = threadIdx.x; e < n * n; e += CI_THREADS) Linv[e] = (e / n == e % n) ? 1.0 : 0.0;
-        return;
-    }
+    if (skip_in && *skip_in) return;
     const int ld = n + 1;
     double* L = sm;                              // column-major: L(i, c) at L[c*ld + i]
     double* X = sm + (size_t)n * ld;             // L^-1, row-major: X(t, c) at X[t*ld + c]
@@ -300,6 +326,46 @@ k_chol_inv(const CholBatch batch, int n) {
     __syncthreads();
     for (int i = tid >> 4; i < n; i += CI_THREADS >> 4)
         for (int j = tid & 15; j < n; j += 16) Linv[(size_t)i * n + j] = X[i * ld + j];
+    if (prob.transform) {                        // F <- X F X^T, by way of L's place: X F first, row-major
+        double* __restrict__ F = prob.transform;
+        constexpr int TW = (((SM_MAX_CHOL + 15) / 16) * ((SM_MAX_CHOL + 15) / 16) + 7) / 8;      // tiles a wave
+        const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = CI_THREADS >> 6;
+        const int T = (n + 15) / 16, r16 = lane & 15, kq = lane >> 4;
+        double4_t acc[TW];
+        auto product = [&](auto fb) {
+#pragma unroll
+            for (int t = 0; t < TW; ++t) {
+                const int tile = wave + t * nwaves;
+                if (tile >= T * T) continue;     // (uniform)
+                const int ti = tile / T, tj = tile - ti * T;
+                acc[t] = tile_mma(n, 16 * ti + r16, 16 * tj + r16, kq, [&](int i, int k) { return fb(i, k, true); },
+                                  [&](int k, int j) { return fb(k, j, false); }, 0, n);
+            }
+        };
+        auto each = [&](auto put) {
+#pragma unroll
+            for (int t = 0; t < TW; ++t) {
+                const int tile = wave + t * nwaves;
+                if (tile >= T * T) continue;
+                const int ti = tile / T, tj = tile - ti * T;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int i = 16 * ti + 4 * v + kq, j = 16 * tj + r16;
+                    if (i < n && j < n) put(i, j, acc[t][v]);
+                }
+            }
+        };
+        __syncthreads();
+        for (int i = tid >> 4; i < n; i += CI_THREADS >> 4)
+            for (int j = tid & 15; j < n; j += 16) L[i * ld + j] = F[(size_t)i * n + j];
+        __syncthreads();
+        product([&](int i, int j, bool left) { return left ? X[i * ld + j] : L[i * ld + j]; });
+        __syncthreads();
+        each([&](int i, int j, double v) { L[i * ld + j] = v; });
+        __syncthreads();
+        product([&](int i, int j, bool left) { return left ? L[i * ld + j] : X[j * ld + i]; });
+        each([&](int i, int j, double v) { F[(size_t)i * n + j] = v; });
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -411,35 +477,6 @@ __device__ __forceinline__ double rcp_nr2(double x) {          // 1/x to ~1e-15 
 // ~1e-5 before the polish, which one Newton-Schulz step brings to ~1e-10
 #define PRE_ROUNDS 19
 #define PRE_MAX_ROUNDS 32
-
-// One 16x16 tile of sum_{kbeg <= k < kend} a(i, k) b(k, j) on the fp64 matrix cores (kbeg a multiple of 16); lane supplies
-// row/column (lane & 15) and the k offset lane >> 4.  fa / fb read in-bounds elements; out-of-range rows, columns and k
-// contribute zero.
-template <class FA, class FB>
-__device__ __forceinline__ double4_t tile_mma(int n, int ia, int jb, int kq, FA fa, FB fb, int kbeg, int kend) {
-    const int ic = min(ia, n - 1), jc = min(jb, n - 1);
-    const bool iok = ia < n, jok = jb < n;
-    double4_t acc = {0.0, 0.0, 0.0, 0.0};
-    if ((n & 15) == 0 && (kend & 15) == 0) {      // whole tiles: no guards, operands of four steps loaded ahead
-        for (int k0 = kbeg; k0 < kend; k0 += 16) {
-            double a[4], b[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                a[u] = fa(ia, k0 + 4 * u + kq);
-                b[u] = fb(k0 + 4 * u + kq, jb);
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[u], acc, 0, 0, 0);
-        }
-        return acc;
-    }
-    for (int k0 = kbeg; k0 < kend; k0 += 4) {
-        const int k = k0 + kq, kc = min(k, n - 1);
-        const double a = fa(ic, kc), b = fb(kc, jc);
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64((iok && k < kend) ? a : 0.0, (jok && k < kend) ? b : 0.0, acc, 0, 0, 0);
-    }
-    return acc;
-}
 
 // Reflectors j with (j+1)/8 == E0, highest first, applied to the column piece zr (rows q + 8 e); then the lower blocks.
 template <int NR, int E0>
@@ -1159,6 +1196,20 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk, int use_pre) {
                 if (vec) vec[(size_t)i * n + j] = v;
                 if (tmat && j < kk) tmat[(size_t)i * kk + j] = v * rl[q];
             }
+        // G stood for X F X^T, X lower triangular: what multiplies F's basis is X^T tmat
+        const double* __restrict__ X = prob.post;
+        if (X && !(prob.post_skip && *prob.post_skip)) {
+            for (int i = tid >> 4; i < n; i += nthr >> 4)
+#pragma unroll
+                for (int q = 0; q < NJ; ++q) {
+                    const int j = (tid & 15) + 16 * q;
+                    if (j >= min(n, kk)) continue;
+                    double v = 0.0;
+                    for (int t = i; t < n; ++t)
+                        v = __builtin_fma(X[(size_t)t * n + i], zero[q] ? (t == j ? rl[q] : 0.0) : W[(size_t)pp[q] * ld + t] * rl[q], v);
+                    tmat[(size_t)i * kk + j] = v * rl[q];
+                }
+        }
     }
     if (tid < n) {
         double l = nrm[order[tid]];              // sigma_j = sqrt(lambda_j)
