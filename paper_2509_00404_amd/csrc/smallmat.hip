@@ -419,8 +419,10 @@ template <> __device__ __forceinline__ double group_sum<16>(double x) {
 }
 
 // lanes per column pair: a step is bound by the latency of its chain of dependent operations, so the
-// widest group (shortest per-lane column pieces) wins even though it needs the most waves
-__host__ __device__ static inline int jacobi_lanes(int n) { (void)n; return 16; }
+// widest group (shortest per-lane column pieces) wins even though it needs the most waves; behind the preconditioner the
+// workgroup keeps to 512 threads
+#define JGL_PLAIN 16
+#define PRE_JGL 8
 // Column stride in doubles: at least n rounded up to 16 (the rows from n up exist and stay zero, so the
 // column loads and stores need no bounds checks), and = l (mod 2 l), which shifts neighbouring columns
 // by one group's width in the banks.
@@ -440,15 +442,21 @@ __host__ __device__ static inline int jacobi_ld(int n, int l) {
 // eigenvalue by 1e-10 relative).  P comes from the classical dense symmetric path, all inside this
 // workgroup:
 //   1  A = L^T L                                       (fp64 matrix cores)
-//   2  Householder tridiagonalisation  Q^T A Q = T     (rows in registers, 8 lanes a row, four waves)
-//   3  eigenvalues of T by multisection on Sturm counts (3 probes per eigenvalue and round)
-//   4  eigenvectors of T by twisted factorisation       (one thread per eigenvector)
-//   5  back-transformation  P = Q Z                     (one column per 8 lanes, no barriers)
+//   2  Householder tridiagonalisation  Q^T A Q = T     (a column a lane, the rows dealt over four waves, one barrier a step)
+//   3  eigenvalues of T by multisection on Sturm counts (5 to 10 probes per eigenvalue and round)
+//   4  eigenvectors of T by twisted factorisation       (two lanes per eigenvector, one from either end)
+//   5  back-transformation  P = Q Z                     (blocks of 16 reflectors on the fp64 matrix cores)
 //   6  Newton-Schulz polish  P <- P (I - (P^T P - I) / 2)  until orthogonal to 1e-10; if the computed
 //      vectors are far from orthogonal (coincident or tiny eigenvalues) the preconditioner is dropped
 //   7  W0 = L P                                         (fp64 matrix cores)
+// What bounds all but 5 to 7 is one wave's issue (a dependent fp64 operation every 8.8 cycles, an independent one every
+// 6.5, with a row broadcast or without; a second wave on the SIMD issues in between for nothing).  Thousands of cycles (2.4
+// GHz) at order 80, and what the phase took before it was written this way:
+//   2  141 (184: 8 lanes a row on four waves, two barriers a step)       3  64 (79: 3 probes, coefficients from LDS)
+//   4  21 (53: one thread an eigenvector)      5  31 (48: 8 lanes a column and one reflector at a time)
+//   6  30 (35)      7 and the check 29 (35)      the whole eigenproblem 375 (498)
 // R1 holds L on entry (column-major, odd stride lda = n | 1: rows and columns both walk all banks); the result is left in
-// R2 in the sweeps' layout (stride ld, ne + 1 columns).  gscr: n * lda doubles of global scratch for L.  sa: 10*n + 40 doubles
+// R2 in the sweeps' layout (stride ld, ne + 1 columns).  gscr: n * lda doubles of global scratch for L.  sa: pre_doubles(n) doubles
 // of LDS, 16-byte aligned.
 // ---------------------------------------------------------------------------------------
 __device__ __forceinline__ double wave_max(double x) {
@@ -456,15 +464,9 @@ __device__ __forceinline__ double wave_max(double x) {
     for (int o = 32; o >= 1; o >>= 1) x = fmax(x, __shfl_xor(x, o));
     return x;
 }
+// the sum over the wave, in every lane
 __device__ __forceinline__ double wave_sum(double x) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o);
-    return x;
-}
-
-// x is the same in the 8 lanes of every group: the sum over the wave's 8 groups, in every lane
-__device__ __forceinline__ double wave_sum_of_groups8(double x) {
-    x += dpp_mov64<0x140>(x);     // row_mirror: the other group of this row of 16 lanes
+    x = group_sum<16>(x);
     return (readlane64(x, 0) + readlane64(x, 16)) + (readlane64(x, 32) + readlane64(x, 48));
 }
 __device__ __forceinline__ double rcp_nr2(double x) {          // 1/x to ~1e-15 relative
@@ -472,224 +474,239 @@ __device__ __forceinline__ double rcp_nr2(double x) {          // 1/x to ~1e-15 
     y = y * (2.0 - x * y);
     return y * (2.0 - x * y);
 }
+// acc += (x of lane N of the row of 16 lanes) * m.  A lane's own write of x needs two wait states before another lane of the row
+// reads it: the caller puts dpp_settle(x) between the two.
+template <int N>
+__device__ __forceinline__ void fmac_row(double& acc, double x, double m) {
+    asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(x), "v"(m), "n"(N));
+}
+__device__ __forceinline__ void dpp_settle(double& x) { asm volatile("s_nop 1" : "+v"(x)); }
 
-// 4^19 = 2.7e11 sections of the scaled spectrum: eigenvalues to ~1e-11 ||T||, eigenvectors orthogonal to
-// ~1e-5 before the polish, which one Newton-Schulz step brings to ~1e-10
-#define PRE_ROUNDS 19
-#define PRE_MAX_ROUNDS 32
+// eigenvalues to 2^-38 of ||T||, eigenvectors orthogonal to ~1e-5 before the polish, which one Newton-Schulz step brings to
+// ~1e-10; small ones of a graded spectrum go on to at most 2^-64
+#define PRE_BITS 38
+#define PRE_MAX_BITS 64
 
-// Reflectors j with (j+1)/8 == E0, highest first, applied to the column piece zr (rows q + 8 e); then the lower blocks.
-template <int NR, int E0>
-__device__ __forceinline__ void back_blocks(double (&zr)[NR], const double* __restrict__ V, int lda, int n, int q,
-                                            const double* __restrict__ tauv) {
-    const int jhi = min(8 * E0 + 6, n - 3), jlo = max(8 * E0 - 1, 0);
-    for (int j = jhi; j >= jlo; --j) {
-        const double tau = tauv[j];
-        double v[NR], dot = 0.0;
-#pragma unroll
-        for (int e = E0; e < NR; ++e) {
-            const int i = q + 8 * e;
-            v[e] = i < n ? V[(size_t)i * lda + j] : 0.0;
-            dot += v[e] * zr[e];
-        }
-        dot = tau * group8_sum(dot);
-#pragma unroll
-        for (int e = E0; e < NR; ++e) zr[e] -= dot * v[e];
-    }
-    if constexpr (E0 > 0) back_blocks<NR, E0 - 1>(zr, V, lda, n, q, tauv);
+// row length of the tridiagonalisation's published vectors: a place for every lane's column, and one more
+__host__ __device__ static constexpr int pre_row(int n16) { return (n16 > 64 ? n16 : 64) + 1; }
+// doubles of LDS for the vectors of the phases below (the largest of what they keep one after the other)
+__host__ __device__ static inline size_t pre_doubles(int n) {
+    const size_t n16 = (n + 15) / 16 * 16, tri = 16 * pre_row((int)n16) + 128 * ((n16 + 63) / 64) + 4 + 65;
+    return 4 * n16 + (tri > 17 * n16 ? tri : 17 * n16) + 1;  // dd, ee, tau, lam | the tridiagonalisation's; twisted pairs; T of the block reflectors
 }
 
 template <int NE>
 __device__ __forceinline__ bool eig_precondition(double* __restrict__ R1, double* __restrict__ R2, int ld, int lda, int n, int ne,
                                  double* __restrict__ gscr, double* __restrict__ sa) {
-    constexpr int NR = 2 * NE;                    // entries of a row (or column) per lane of an 8-lane group
-    const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63;
+    constexpr int N16 = 16 * NE;                  // the order in whole tiles
+    const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, r16 = lane & 15, kq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = nthr >> 6;
     const int T16 = (n + 15) / 16, ntiles = T16 * T16;
-    const size_t rsize = (size_t)(ne + 1) * ld;
-    const int n8 = (n + 7) & ~7;
-    double* dd = sa;            // [n] diagonal of T
-    double* ee = dd + n;        // [n] ee[j] couples j and j+1
-    double* de = ee + n;        // [2 n8] scaled T for the Sturm counts: d_k at [k], e_{k-1}^2 at [n8 + k]; padded with (4, 0): no sign change
-    double* tauv = de + 2 * n8; // [n] Householder tau
-    double* scl = tauv + n;     // [n] v_i = A[i][j] * scl[j] for i > j+1, v_{j+1} = 1
-    double* lamv = scl + n;     // [n] eigenvalues of T, ascending
-    const int n32 = (n + 31) & ~31;
-    double* xx = lamv + n;      // [n32] current column below the diagonal, zero up to the current row and from n up
-    double* pp = xx + n32;      // [n32] A v, zero up to the current row and from n up
-    __shared__ double part_k[4], part_s[2][4];    // per-wave partial sums: v^T A v, and sigma by step parity
+    double* dd = sa;                              // [N16] diagonal of T; past n: 4, outside the scaled spectrum
+    double* ee = dd + N16;                        // [N16] ee[j] couples j and j+1; past n - 2: 0
+    double* tauv = ee + N16;                      // [N16] Householder tau; past n - 3: 0
+    double* lamv = tauv + N16;                    // [N16] eigenvalues of T, ascending
+    double* scr = lamv + N16;                     // of the phase at work
     __shared__ unsigned long long err_s;
     __shared__ int fail_s;
 
     // ---- 0: L to global scratch (R1 is reused for the eigenvectors) ----
     for (int e = tid; e < n * lda; e += nthr) gscr[e] = R1[e];
-    if (tid == 0) fail_s = 0;
+    if (tid == 0) { fail_s = 0; err_s = 0ull; }
 
-    // Gram of the columns of R1 into R2 (row-major, lda): lower tiles, mirrored.  k_from: the columns are zero above row
+    // lower tiles of the Gram matrix of the columns of R1, each to put(ti, tj, tile).  lower: the columns are zero above row
     // 16 floor(column / 16) (a triangular factor), so the sum starts there
-    auto gram_to_R2 = [&](bool lower) {
+    auto gram = [&](bool lower, auto put) {
         for (int tile = wave; tile < T16 * (T16 + 1) / 2; tile += nwaves) {    // `wave` is a scalar: a uniform loop
             int ti = 0, tj = tile;
             while (tj > ti) { tj -= ti + 1; ++ti; }
-            const int ci = 16 * ti + (lane & 15), cj = 16 * tj + (lane & 15), kq = lane >> 4;
-            const double4_t acc = tile_mma(n, ci, cj, kq, [&](int i, int k) { return R1[(size_t)i * lda + k]; },
-                                           [&](int k, int c) { return R1[(size_t)c * lda + k]; }, lower ? 16 * ti : 0, n);
+            const int ci = 16 * ti + r16, cj = 16 * tj + r16;
+            put(ti, tj, tile_mma(n, ci, cj, kq, [&](int i, int k) { return R1[(size_t)i * lda + k]; },
+                                 [&](int k, int c) { return R1[(size_t)c * lda + k]; }, lower ? 16 * ti : 0, n));
+        }
+    };
+    // a symmetric matrix's lower tile to both halves of R2
+    auto mirror = [&](int ti, int tj, double4_t acc) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int i = 16 * ti + 4 * v + kq;
-                if (i < n && cj < n) {
-                    R2[(size_t)i * lda + cj] = acc[v];
-                    R2[(size_t)cj * lda + i] = acc[v];
-                }
+        for (int v = 0; v < 4; ++v) {
+            const int i = 16 * ti + 4 * v + kq, j = 16 * tj + r16;
+            if (i < n && j < n) {
+                R2[(size_t)i * lda + j] = acc[v];
+                R2[(size_t)j * lda + i] = acc[v];
             }
         }
     };
 
     // ---- 1: A = L^T L ----
-    gram_to_R2(true);
+    gram(true, mirror);
+    for (int i = tid; i < N16; i += nthr) {
+        tauv[i] = 0.0;
+        if (i >= n) { dd[i] = 4.0; ee[i] = 0.0; }
+    }
     __syncthreads();
-    // ---- 2: tridiagonalisation (lower).  Four waves, one per SIMD: a group of 8 lanes holds the rows g, g + 32, ..., lane
-    //         q of it their columns q, q+8, ... in registers.  What a step costs is instructions, and most of them (the
-    //         reflector's scalars, v and w by columns, reductions) are the same for every row, so few waves with several rows
-    //         each beat ten waves with one (n = 80: 77 us against 100; a lone wave issues an instruction every ~6.5 cycles, 360
-    //         a step).
-    //         Step j, two barriers: every wave forms the reflector's scalars and its own pieces of v from
-    //         column j (xx) | p_r = A[r][:] v and the wave's share of v^T A v || rank-2 update, then column j+1
-    //         with its squared norm for the next step.  xx and pp are kept zero up to row j (and from n up), so
-    //         dead columns of a block update by exactly zero without any test; whole dead blocks of rows and columns are
-    //         skipped (one instantiation of the step per block of 8 columns). ----
+    // ---- 2: tridiagonalisation.  Lane l holds column o + l (o = n - 64, or 0) and wave w of the first four its rows w, w + 4, ...; the
+    //         first o columns sit in lanes of the other four waves, which retire with them.  Step j eliminates column j below its
+    //         subdiagonal with u = (column j below row j+1, and g = alpha - beta at row j+1), A <- H A H, H = I - t u u^T.
+    //         Row j (x) and row j+1 (ra) are known to every wave at work, so that vectors by columns are formed by each for
+    //         itself, and one barrier a step is enough: a wave publishes its rows' share of A x and its candidate for row
+    //         j+2 as it is before this step, wave 4 the reflector's scalars g and t, and the two rows the next step starts from follow from
+    //             row' = row - u[row] (t p - t^2 (u^T p) u) - p[row] t u,   p = A u.
+    //         The scalars' chain (a sum over the wave, a square root, a reciprocal) runs on wave 4 while the others form A x.  u and p
+    //         reach the rows' products by row broadcasts from registers that hold 16 of a wave's rows.  Columns up to j go
+    //         through the update as well (u is zero there, they keep their norm) and are not read again.  Lanes past the last
+    //         column write to places of their own: no branch in a step.
     {
-        constexpr int RWS = (16 * NE + 31) / 32;               // rows per lane group
-        const int g = tid >> 3, q = tid & 7;
-        const bool part = wave < 4;                            // uniform
-        double areg[RWS][NR];
-        if (part) {
+        const int o = n > 64 ? n - 64 : 0, wr = wave & 3;
+        constexpr int NT = 4 * NE, NB = (NT + 15) / 16;        // rows a wave; registers of 16 rows
+        constexpr int PS = pre_row(N16);
+        const int c0 = o + lane, c1 = lane;
+        const bool ok0 = c0 < n, ok1 = c1 < o;
+        const bool second = wave >= 4;                         // uniform: holds the first o columns
+        double* parts = scr;                                   // [2][4][PS] shares of A x by column
+        double* row2s = parts + 8 * PS;                        // [2][4][PS]
+        double* ub = row2s + 8 * PS;                           // [4][16 NB] u by row, the 16 rows of a register next to each other
+        double* pb = ub + 64 * NB;                             // same for p
+        double* scal = pb + 64 * NB;                           // [2][2] g, t
+        double* dummy = scal + 4;                              // [64 + 1]
+        auto slot = [](int r) { return (r & 3) * (16 * NB) + (r >> 2); };
+        const int s0 = slot(c0), s1 = ok1 ? slot(c1) : (int)(dummy - ub) + 64;
+        const int s1p = ok1 ? slot(c1) : (int)(dummy - pb) + 64;
+        const int cown = second ? (ok1 ? c1 : PS - 1) : c0;    // (column PS - 1 is nobody's)
+        double a[NT];
 #pragma unroll
-            for (int i = 0; i < RWS; ++i)
+        for (int t = 0; t < NT; ++t)
+            a[t] = (second ? ok1 : ok0) && 4 * t + wr < n ? R2[(size_t)(4 * t + wr) * lda + cown] : 0.0;
+        double x0 = ok0 ? R2[c0] : 0.0, x1 = ok1 ? R2[c1] : 0.0, ra0 = ok0 ? R2[lda + c0] : 0.0, ra1 = ok1 ? R2[lda + c1] : 0.0;
+        double d0 = 0.0, d1 = 0.0;                             // the diagonal, of wave 4
+        for (int e = tid; e < 128 * NB; e += nthr) ub[e] = 0.0;
+        __syncthreads();                                       // the matrix is in registers: the reflectors take its place
+        for (int r = tid >> 4; r < o; r += nthr >> 4)          // zeros above the reflectors of the later columns
+            for (int c = o + r16; c < n; c += 16) R2[(size_t)r * lda + c] = 0.0;
+        auto step = [&](int j, auto ES, auto SETS, auto ROLE) {
+            constexpr int es = decltype(ES)::value;            // (j + 2) / 16: rows below 16 es are dead
+            constexpr bool two = decltype(SETS)::value == 2;   // columns of the second set are alive
+            constexpr int role = decltype(ROLE)::value;        // 0: rows of set 0; 1: rows of set 1; 2: the scalars; 3: both
+            constexpr bool rows = role != 2, scalars = role >= 2;
+            const int par = j & 1;
+            auto at = [&](double v0, double v1, int c) {
+                if constexpr (!two) return readlane64(v0, c - o);
+                const double l1 = readlane64(v1, min(c, 63)), l0 = readlane64(v0, max(c - o, 0));
+                return c >= o ? l0 : l1;
+            };
+            const double m0 = c0 > j + 1 ? x0 : 0.0, m1 = two && c1 > j + 1 ? x1 : 0.0;
+            double u16[NB];
+            if constexpr (rows) {
+                double q[4] = {0.0, 0.0, 0.0, 0.0};
+                ub[s0] = m0;
+                if constexpr (two) ub[s1] = m1;
 #pragma unroll
-                for (int e = 0; e < NR; ++e) {
-                    const int r = g + 32 * i, c = q + 8 * e;
-                    areg[i][e] = (r < n && c < n) ? R2[(size_t)r * lda + c] : 0.0;
-                }
-        }
-        for (int c = tid; c < n32; c += nthr) { pp[c] = 0.0; xx[c] = 0.0; }
-        __syncthreads();
-        if (part) {
-            double y = 0.0;
+                for (int b = es / 4; b < NB; ++b) u16[b] = ub[wr * 16 * NB + 16 * b + r16];
+                const int ts = ((j + 2) >> 2) & 3;
+                const double lo = ts & 1 ? a[4 * es + 1] : a[4 * es], hi = ts & 1 ? a[4 * es + 3] : a[4 * es + 2];
+                row2s[(par * 4 + wr) * PS + cown] = ts & 2 ? hi : lo;
 #pragma unroll
-            for (int i = 0; i < RWS; ++i) {
-                const int r = g + 32 * i;
-                if (q == 0 && r < n) {
-                    if (r >= 1) xx[r] = areg[i][0];
-                    if (r >= 2) y += areg[i][0] * areg[i][0];
-                }
+                for (int b = es / 4; b < NB; ++b) dpp_settle(u16[b]);
+                for_each_block<NT - 4 * es>([&](auto I) {
+                    constexpr int t = 4 * es + decltype(I)::value;
+                    fmac_row<t % 16>(q[t % 4], u16[t / 16], a[t]);
+                });
+                parts[(par * 4 + wr) * PS + cown] = (q[0] + q[1]) + (q[2] + q[3]);
             }
-            const double t = wave_sum_of_groups8(group8_sum(y));
-            if (lane == 0) part_s[0][wave] = t;
-        }
-        auto step = [&](int j, auto ES) {
-            constexpr int es = decltype(ES)::value;            // (j + 1) / 8: the register block of column j + 1
-            constexpr int i0 = es / 4;                         // rows below 32 i0 are dead
-            __syncthreads();                      // column j (xx) and the partial sums of its sigma are complete
-            double vreg[NR], vr[RWS], p[RWS], tau = 0.0;
-            if (part) {
-                // every wave works out the reflector's scalars for itself: cheaper than a third barrier
-                const double sg = (part_s[j & 1][0] + part_s[j & 1][1]) + (part_s[j & 1][2] + part_s[j & 1][3]);
-                const double alpha = xx[j + 1];
-                double scale = 0.0, beta = alpha;
-                if (sg > 0.0) {
-                    const double h = alpha * alpha + sg;
-                    const double ri = chol_rsqrt(h);
-                    const double nr = h * ri;
-                    beta = alpha >= 0.0 ? -nr : nr;
-                    tau = (beta - alpha) * (alpha >= 0.0 ? -ri : ri);
-                    scale = rcp_nr2(alpha - beta);
+            double g, t;
+            if constexpr (scalars) {
+                // t = -1 / (beta g)
+                const double sg = wave_sum(two ? __builtin_fma(m1, m1, m0 * m0) : m0 * m0);
+                const double alpha = at(x0, x1, j + 1);
+                const bool some = sg > 0.0, pos = alpha >= 0.0;
+                const double h = some ? __builtin_fma(alpha, alpha, sg) : 1.0, ri = chol_rsqrt(h), nr = h * ri;
+                const double beta = some ? (pos ? -nr : nr) : alpha, rb = pos ? -ri : ri;      // rb = 1 / beta
+                const double gg = some ? alpha - beta : 1.0, sc = rcp_nr2(gg);
+                g = some ? gg : 0.0;
+                t = some ? -(rb * sc) : 0.0;
+                scal[2 * par] = g;
+                scal[2 * par + 1] = t;
+                ee[j] = beta;
+                tauv[j] = some ? -(gg * rb) : 0.0;
+                // the reflector, zeros down to the diagonal
+                const double scale = some ? sc : 0.0;
+                (ok0 ? R2 + (size_t)c0 * lda + j : dummy + lane)[0] = (c0 == j + 1 ? g : m0) * scale;
+                d0 = c0 == j ? x0 : d0;
+                if constexpr (two) {
+                    (ok1 ? R2 + (size_t)c1 * lda + j : dummy + lane)[0] = (c1 == j + 1 ? g : m1) * scale;
+                    d1 = c1 == j ? x1 : d1;
                 }
-                if (tid == 0) { pp[j] = 0.0; ee[j] = beta; tauv[j] = tau; scl[j] = scale; }
-                // v_c = x_c * scale below row j+1 (xx is zero up to row j), 1 at row j+1
-                const int qj = (j + 1) & 7;
-#pragma unroll
-                for (int e = es; e < NR; ++e) vreg[e] = xx[q + 8 * e] * scale;
-                vreg[es] = q == qj ? 1.0 : vreg[es];
-                double s = 0.0;
-#pragma unroll
-                for (int i = i0; i < RWS; ++i) {               // p_r = sum_c A[r][c] v_c
-                    const int r = g + 32 * i;
-                    const double x = xx[r] * scale;
-                    vr[i] = r == j + 1 ? 1.0 : x;
-                    double p0 = 0.0, p1 = 0.0;
-#pragma unroll
-                    for (int e = es; e < NR; e += 2) {
-                        p0 = __builtin_fma(areg[i][e], vreg[e], p0);
-                        if (e + 1 < NR) p1 = __builtin_fma(areg[i][e + 1], vreg[e + 1], p1);
-                    }
-                    const double pr = group8_sum(p0 + p1);
-                    p[i] = r > j ? pr : 0.0;
-                    pp[r] = p[i];                     // (the 8 lanes write the same value)
-                    s = __builtin_fma(p[i], vr[i], s);
-                }
-                s = wave_sum_of_groups8(s);
-                if (lane == 0) part_k[wave] = s;
             }
             __syncthreads();
-            if (part) {
-                const double ks = (part_k[0] + part_k[1]) + (part_k[2] + part_k[3]);
-                const double K = 0.5 * tau * tau * ks;
-                double wc[NR], y = 0.0;
-#pragma unroll
-                for (int e = es; e < NR; ++e) wc[e] = __builtin_fma(tau, pp[q + 8 * e], -K * vreg[e]);
-                double xn[RWS];
-#pragma unroll
-                for (int i = i0; i < RWS; ++i) {
-                    const int r = g + 32 * i;
-                    const double wr = __builtin_fma(tau, p[i], -K * vr[i]);
-#pragma unroll
-                    for (int e = es; e < NR; ++e)
-                        areg[i][e] = __builtin_fma(-wr, vreg[e], __builtin_fma(-vr[i], wc[e], areg[i][e]));
-                    // column j+1 below its diagonal for the next step, and the partial sums of its sigma
-                    xn[i] = r >= j + 2 ? areg[i][es] : 0.0;
-                    const double z = r >= j + 3 ? xn[i] : 0.0;
-                    y = __builtin_fma(z, z, y);
+            {
+                const double* pp = parts + par * 4 * PS;
+                const double* r2 = row2s + (par * 4 + ((j + 2) & 3)) * PS;
+                if constexpr (!scalars) { g = scal[2 * par]; t = scal[2 * par + 1]; }
+                const double rb0 = r2[c0];
+                const double p0 = __builtin_fma(g, ra0, (pp[c0] + pp[PS + c0]) + (pp[2 * PS + c0] + pp[3 * PS + c0]));
+                double p1 = 0.0, rb1 = 0.0;
+                if constexpr (two) {
+                    rb1 = r2[c1];
+                    p1 = __builtin_fma(g, ra1, (pp[c1] + pp[PS + c1]) + (pp[2 * PS + c1] + pp[3 * PS + c1]));
+                    if (!ok1) { p1 = 0.0; rb1 = 0.0; }
                 }
-                // rows up to j+1 (the spent head of the column) read as zero from now on
-                if (tid == 0) xx[j + 1] = 0.0;
-                if (q == ((j + 1) & 7)) {
+                double p16[NB];
+                if constexpr (rows) {
+                    pb[s0] = p0;
+                    if constexpr (two) pb[s1p] = p1;
 #pragma unroll
-                    for (int i = i0; i < RWS; ++i) xx[g + 32 * i] = xn[i];
-                } else {
-                    y = 0.0;
+                    for (int b = es / 4; b < NB; ++b) p16[b] = pb[wr * 16 * NB + 16 * b + r16];
                 }
-                const double t = wave_sum_of_groups8(group8_sum(y));
-                if (lane == 0) part_s[(j + 1) & 1][wave] = t;
+                const double u0 = c0 == j + 1 ? g : m0, u1 = two && c1 == j + 1 ? g : m1;
+                const double ks = wave_sum(two ? __builtin_fma(u1, p1, u0 * p0) : u0 * p0);
+                const double pj1 = at(p0, p1, j + 1), pj2 = at(p0, p1, j + 2), uj2 = at(m0, m1, j + 2);
+                const double tk = t * t * ks;
+                const double al0 = __builtin_fma(-tk, u0, t * p0), be0 = t * u0;
+                const double al1 = __builtin_fma(-tk, u1, t * p1), be1 = t * u1;
+                x0 = __builtin_fma(-pj1, be0, __builtin_fma(-g, al0, ra0));
+                ra0 = __builtin_fma(-pj2, be0, __builtin_fma(-uj2, al0, rb0));
+                if constexpr (two) {
+                    x1 = __builtin_fma(-pj1, be1, __builtin_fma(-g, al1, ra1));
+                    ra1 = __builtin_fma(-pj2, be1, __builtin_fma(-uj2, al1, rb1));
+                }
+                if constexpr (rows) {
+                    const double na = role == 0 ? -al0 : -al1, nb = role == 0 ? -be0 : -be1;
+#pragma unroll
+                    for (int b = es / 4; b < NB; ++b) dpp_settle(p16[b]);
+                    for_each_block<NT - 4 * es>([&](auto I) {
+                        constexpr int t = 4 * es + decltype(I)::value;
+                        fmac_row<t % 16>(a[t], u16[t / 16], na);
+                        fmac_row<t % 16>(a[t], p16[t / 16], nb);
+                    });
+                }
             }
         };
-        for_each_block<NR>([&](auto ES) {
-            constexpr int es = decltype(ES)::value;
-            const int jlo = es == 0 ? 0 : 8 * es - 1, jhi = min(8 * es + 6, n - 3);
-            for (int j = jlo; j <= jhi; ++j) step(j, ES);
-        });
-        __syncthreads();
-        // the reflectors, normalised, stay in the strict lower triangle: v^(j)_i = R2[i][j] for every i (zeros down
-        // to the diagonal, 1 below it); the diagonal and the subdiagonal move to dd, ee first
-        if (part) {
-#pragma unroll
-            for (int i = 0; i < RWS; ++i)
-#pragma unroll
-                for (int e = 0; e < NR; ++e) {
-                    const int r = g + 32 * i, c = q + 8 * e;
-                    if (r < n && c < n) {
-                        if (c == r) dd[r] = areg[i][e];
-                        if (c == r - 1 && r == n - 1) ee[n - 2] = areg[i][e];
-                        double v = 0.0;
-                        if (c + 2 < n) v = r == c + 1 ? 1.0 : (r > c + 1 ? areg[i][e] * scl[c] : 0.0);
-                        R2[(size_t)r * lda + c] = v;
-                    }
+        auto reduce = [&](auto ROLE1, auto ROLE2) {            // a wave's role while the second set is alive, and after
+            for_each_block<NE>([&](auto ES) {
+                constexpr int es = decltype(ES)::value;
+                const int jlo = es == 0 ? 0 : 16 * es - 2, jhi = min(16 * es + 13, n - 3);
+                int j = jlo;
+                if constexpr (NE > 4 && 16 * es - 2 < N16 - 64)
+                    for (; j <= min(jhi, o - 1); ++j) step(j, ES, std::integral_constant<int, 2>{}, ROLE1);
+                for (; j <= jhi; ++j) {
+                    if constexpr (decltype(ROLE2)::value < 0) __syncthreads();
+                    else step(j, ES, std::integral_constant<int, 1>{}, ROLE2);
                 }
+            });
+        };
+        if (wave < 4) reduce(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
+        else if (wave == 4) reduce(std::integral_constant<int, 3>{}, std::integral_constant<int, 2>{});
+        else reduce(std::integral_constant<int, 1>{}, std::integral_constant<int, -1>{});
+        // what is left: rows n - 2 (x) and n - 1, in set 0
+        if (wave == 4) {
+            if (c0 == n - 1) { ee[n - 2] = x0; ee[n - 1] = 0.0; }
+            d0 = c0 == n - 2 ? x0 : (c0 == n - 1 ? ra0 : d0);
+            if (ok0) dd[c0] = d0;
+            if (ok1) dd[c1] = d1;
         }
-        if (tid == 0) { tauv[n - 2] = 0.0; tauv[n - 1] = 0.0; ee[n - 1] = 0.0; }
         __syncthreads();
     }
     // ---- 3: eigenvalues of T.  Scale T by a power of two so that |d| + 2|e| <= 1, then multisection ----
+    double* tw = scr;                             // [2][N16][2] the twisted factorisation's (d, coupling to the next row), from either end
     {
         if (wave == 0) {
             double g = 0.0;
@@ -697,53 +714,70 @@ __device__ __forceinline__ bool eig_precondition(double* __restrict__ R1, double
                 g = fmax(g, fabs(dd[i]) + fabs(ee[i]) + (i ? fabs(ee[i - 1]) : 0.0));
             g = wave_max(g);
             const double s = g > 0.0 ? ldexp(1.0, -ilogb(g) - 1) : 1.0;
-            for (int i = lane; i < n8; i += 64) {
-                const double d = i < n ? dd[i] * s : 4.0, e = i < n ? ee[i] * s : 0.0;
-                if (i < n) { dd[i] = d; ee[i] = e; }
-                de[i] = d;
-                if (i + 1 < n8) de[n8 + i + 1] = e * e;
-                if (i == 0) de[n8] = 0.0;
-            }
+            for (int i = lane; i < n; i += 64) { dd[i] *= s; ee[i] *= s; }
         }
         __syncthreads();
-        // 21 eigenvalues per wave, 3 probes each: four sections, 2 bits per round.  (Eight probes, 3.17 bits, need ten waves
-        // for n = 80 and cost what ten waves issue: 44 us against 33.)
-        const int idx = lane / 3, q = lane - 3 * idx, i = 21 * wave + idx;
-        if (21 * wave < n) {
+        for (int i = tid; i < N16; i += nthr) {
+            tw[2 * i] = dd[i];
+            tw[2 * i + 1] = ee[i];
+            tw[2 * N16 + 2 * i] = dd[N16 - 1 - i];
+            tw[2 * N16 + 2 * i + 1] = i < N16 - 1 ? ee[N16 - 2 - i] : 0.0;
+        }
+        // The eigenvalues are dealt over all waves and the lanes over a wave's eigenvalues: n = 80: 10 and 6, sections of 1/7; n = 64: 8
+        // and 8, sections of 1/9.  The coefficients are row broadcasts.
+        const int epw = (n + nwaves - 1) / nwaves, G = min(64 / epw, 16);
+        const int idx = lane / G, q = lane - G * idx, i = epw * wave + idx;
+        const bool mine = idx < epw && i < n;
+        double dreg[NE], nereg[NE];
+#pragma unroll
+        for (int b = 0; b < NE; ++b) {
+            const int k = 16 * b + r16;
+            const double e = k ? ee[k - 1] : 0.0;
+            dreg[b] = dd[k];
+            nereg[b] = -(e * e);
+        }
+        if (epw * wave < n) {                                   // uniform
+            const double rs = 1.0 / (double)(G + 1);
+            const float bits = __log2f((float)(G + 1));
+            const int rounds = (int)ceilf(PRE_BITS / bits), max_rounds = (int)ceilf(PRE_MAX_BITS / bits);
             double lo = -1.0 - 1e-9, hi = 1.0 + 1e-9;       // Gershgorin after scaling
-            for (int round = 0; round < PRE_MAX_ROUNDS; ++round) {
-                // enough once the interval is below 1e-11 of the spectrum's scale and 1e-6 of the eigenvalue itself
+            for (int round = 0; round < max_rounds; ++round) {
+                // enough once the interval is below 2^-38 of the spectrum's scale and 1e-9 of the eigenvalue itself
                 // (small eigenvalues of a graded matrix keep going); the lanes of a wave leave together
-                const bool done = i >= n || idx > 20 || (round >= PRE_ROUNDS && (hi - lo) <= 1e-6 * fmax(fabs(lo), fabs(hi)));
+                const bool done = !mine || (round >= rounds && (hi - lo) <= 1e-9 * fmax(fabs(lo), fabs(hi)));
                 if (__ballot(!done) == 0ull) break;
-                const double w = (hi - lo) * 0.25;
-                const double mu = lo + w * (double)(q + 1);
+                const double w = (hi - lo) * rs;
+                const double nmu = -(lo + w * (double)(q + 1));
                 // Sturm count: sign changes in the sequence of leading principal minors of T - mu,
                 // p_k = (d_k - mu) p_{k-1} - e_{k-1}^2 p_{k-2}; the pair is renormalised, and the signs of the last
-                // 8 steps, one bit each, are counted every 8 steps
+                // 8 steps, one bit each, are counted every 8 steps (rows past n change no sign)
                 double p2 = 0.0, p1 = 1.0;
                 uint32_t signs = 0;
                 int cnt = 0;
-                for (int k0 = 0; k0 < n8; k0 += 8) {
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const double p = (de[k0 + u] - mu) * p1 - de[n8 + k0 + u] * p2;
-                        signs = __builtin_amdgcn_alignbit(signs, (uint32_t)__double2hiint(p), 31);     // signs << 1 | sign(p)
-                        p2 = p1; p1 = p;
+                for (int b = 0; b < NE; ++b) { dpp_settle(dreg[b]); dpp_settle(nereg[b]); }
+                for_each_block<N16>([&](auto K) {
+                    constexpr int k = decltype(K)::value;
+                    double p = nmu * p1;
+                    fmac_row<k % 16>(p, dreg[k / 16], p1);
+                    fmac_row<k % 16>(p, nereg[k / 16], p2);
+                    signs = __builtin_amdgcn_alignbit(signs, (uint32_t)__double2hiint(p), 31);     // signs << 1 | sign(p)
+                    p2 = p1; p1 = p;
+                    if constexpr (k % 8 == 7) {
+                        cnt += __popc((signs ^ (signs >> 1)) & 0xFFu);
+                        const int ex = max((__double2hiint(p1) >> 20) & 0x7ff, (__double2hiint(p2) >> 20) & 0x7ff);
+                        p1 = ldexp(p1, 1023 - ex);
+                        p2 = ldexp(p2, 1023 - ex);
                     }
-                    cnt += __popc((signs ^ (signs >> 1)) & 0xFFu);
-                    const int ex = max((__double2hiint(p1) >> 20) & 0x7ff, (__double2hiint(p2) >> 20) & 0x7ff);
-                    p1 = ldexp(p1, 1023 - ex);
-                    p2 = ldexp(p2, 1023 - ex);
-                }
-                // probes at or below lambda_i have cnt <= i; they form a prefix of the group's 3 lanes
+                });
+                // probes at or below lambda_i have cnt <= i; they form a prefix of the group's lanes
                 const unsigned long long b = __ballot(cnt <= i);
-                const int k0 = __popc((unsigned)((b >> (3 * idx)) & 0x7ull));
+                const int k0 = __popc((unsigned)(b >> (G * idx)) & ((1u << G) - 1u));
                 const double nlo = k0 > 0 ? lo + w * (double)k0 : lo;
-                const double nhi = k0 < 3 ? lo + w * (double)(k0 + 1) : hi;
+                const double nhi = k0 < G ? lo + w * (double)(k0 + 1) : hi;
                 lo = nlo; hi = nhi;
             }
-            if (q == 0 && i < n && idx < 21) lamv[i] = 0.5 * (lo + hi);
+            if (q == 0 && mine) lamv[i] = 0.5 * (lo + hi);
         }
         __syncthreads();
         // eigenvalues closer than the accuracy of the vectors that follow (repeated eigenvalues, rank deficiency):
@@ -754,158 +788,231 @@ __device__ __forceinline__ bool eig_precondition(double* __restrict__ R1, double
         }
         __syncthreads();
     }
-    // ---- 4: eigenvectors of T by twisted factorisation, thread i -> column i of Z (R1, column-major, lda) ----
+    // ---- 4: eigenvectors of T by twisted factorisation into R1 (column-major, lda).  Even lanes factor T - lambda from the top, odd
+    //         lanes from the bottom, in the same instructions (t counts rows from the lane's end); what is kept of a row is
+    //         m = coupling to the next row / pivot, both the next pivot's correction and the factor of the vector's recurrence.
+    //         The twist is where |gamma_k| = |D+_k + D-_k - (d_k - lambda)| is smallest; each lane looks at its own half ----
     const bool early_fail = fail_s != 0;          // uniform: read after a barrier
-    if (tid < n && !early_fail) {
-        double* z = R1 + (size_t)tid * lda;
-        const double lam = lamv[tid], pm = 1e-100;
-        auto e2_ = [&](int k) { return de[n8 + k + 1]; };    // e_k^2, k = 0 .. n-2
-        auto piv = [&](double D) { return fabs(D) < pm ? -pm : D; };
-        // forward pivots D+ into z
-        double D = dd[0] - lam;
-        z[0] = D;
-        for (int k = 1; k < n; ++k) {
-            D = (dd[k] - lam) - e2_(k - 1) * rcp_nr(piv(D));
-            z[k] = D;
+    constexpr int TW_WAVES = 4;                   // one a SIMD
+    if (wave < TW_WAVES && !early_fail) {
+        const int i = wave + TW_WAVES * (lane >> 1), side = lane & 1;
+        const bool mine = i < n;
+        const double lam = lamv[mine ? i : 0], pm = 1e-100;
+        const double* co = tw + side * 2 * N16;
+        double m[N16];
+        {
+            double prev = 0.0, ein = 0.0;
+#pragma unroll
+            for (int t = 0; t < N16; ++t) {
+                const double e = co[2 * t + 1];
+                double D = __builtin_fma(-ein, prev, co[2 * t] - lam);
+                D = fabs(D) < pm ? -pm : D;
+                prev = e * rcp_nr(D);
+                m[t] = prev;
+                ein = e;
+                if (t % 8 == 7) __builtin_amdgcn_sched_barrier(0);      // (m takes 2 N16 registers: no load far ahead of its use)
+            }
         }
-        // backward pivots D- over z, remembering where |gamma_k| = |D+_k + D-_k - (d_k - lam)| is smallest
-        double Dm = dd[n - 1] - lam;
-        double best = fabs(z[n - 1]);                        // gamma_{n-1} = D+_{n-1}
-        int rr = n - 1;
-        z[n - 1] = Dm;
-        for (int k = n - 2; k >= 0; --k) {
-            const double a = dd[k] - lam;
-            Dm = a - e2_(k) * rcp_nr(piv(Dm));
-            const double gam = fabs(z[k] + Dm - a);
-            if (gam < best) { best = gam; rr = k; }
-            z[k] = Dm;
+        asm volatile("" ::: "memory");            // (nor the pairs kept from above)
+        double best = 1e300;
+        int rr = 0;                               // in rows from this lane's end
+#pragma unroll
+        for (int t = 0; t < N16 / 2; ++t) {
+            double gam = co[2 * t] - lam;
+            if (t > 0) gam = __builtin_fma(-co[2 * t - 1], m[t > 0 ? t - 1 : 0], gam);
+            gam = fabs(__builtin_fma(-co[2 * t + 1], dpp_mov64<0xB1>(m[N16 - 2 - t]), gam));
+            const bool less = gam < best;
+            best = less ? gam : best;
+            rr = less ? t : rr;
+            if (t % 8 == 7) __builtin_amdgcn_sched_barrier(0);
         }
-        // forward pivots again for the rows above the twist
-        D = dd[0] - lam;
-        if (rr > 0) z[0] = D;
-        for (int k = 1; k < rr; ++k) {
-            D = (dd[k] - lam) - e2_(k - 1) * rcp_nr(piv(D));
-            z[k] = D;
+        {
+            const double ob = dpp_mov64<0xB1>(best);
+            const int orr = __builtin_amdgcn_mov_dpp(rr, 0xB1, 0xF, 0xF, true);
+            const bool other = ob < best || (ob == best && side == 1);
+            rr = other ? N16 - 1 - orr : rr;
         }
-        // z_rr = 1; upwards z_k = -e_k z_{k+1} / D+_k; downwards z_{k+1} = -e_k z_k / D-_{k+1}
-        double zz = 1.0, nrm2 = 1.0;
-        for (int k = rr - 1; k >= 0; --k) {
-            zz = -ee[k] * zz * rcp_nr(piv(z[k]));
-            z[k] = zz;
-            nrm2 += zz * zz;
+        // z at the twist is 1; from there towards this lane's end z_t = -m_t z_{t+1}
+        double zz = 1.0, n0 = 0.0, n1 = 0.0;
+#pragma unroll
+        for (int t = N16 - 2; t >= 0; --t) {
+            zz *= t < rr ? -m[t] : 1.0;
+            m[t] = zz;
+            if (t & 1) n1 = __builtin_fma(zz, zz, n1); else n0 = __builtin_fma(zz, zz, n0);
         }
-        zz = 1.0;
-        for (int k = rr; k + 1 < n; ++k) {
-            zz = -ee[k] * zz * rcp_nr(piv(z[k + 1]));
-            z[k + 1] = zz;
-            nrm2 += zz * zz;
-        }
-        z[rr] = 1.0;
-        if (!(nrm2 < 1e300)) atomicOr(&fail_s, 1);
+        double nrm2 = (n0 + n1) - (double)(N16 - 1 - rr);      // without the ones past the twist
+        nrm2 = 1.0 + (nrm2 + dpp_mov64<0xB1>(nrm2));
+        if (mine && !(nrm2 < 1e300)) atomicOr(&fail_s, 1);
         const double rn = rsqrt_nr(nrm2);
-        for (int k = 0; k < n; ++k) z[k] *= rn;
+        // rows from n up sit at the start of the odd lanes' count
+        double* z = R1 + (size_t)(mine ? i : 0) * lda + (side ? N16 - 1 : 0);
+        const int dir = side ? -1 : 1, t0 = side ? N16 - n : 0;
+        const unsigned rows = mine && rr > t0 ? rr - t0 : 0;
+#pragma unroll
+        for (int t = 0; t < N16 - 1; ++t)
+            if ((unsigned)(t - t0) < rows) z[dir * t] = m[t] * rn;
+        if (mine && side == 0 && rr < n) z[rr] = rn;
     }
-    __syncthreads();
-    // ---- 5: P = H_0 H_1 ... H_{n-3} Z, column c on lanes q = 0..7.  Reflector j is zero in rows 0 .. j, so the
-    //         register blocks e < (j+1)/8 are skipped (one instantiation of the inner loop per first block) ----
+    // ---- 5: P = H_0 H_1 ... H_{n-3} Z.  16 reflectors at a time are I - V T V^T with T upper triangular: T_jj = tau_j and
+    //         T_rj = -tau_j sum_{r <= u < j} T_ru v_u^T v_j.  A wave takes 16 columns of Z through all of them in registers: the
+    //         accumulators of one product are the right operand of the next (element v of a tile is its contraction chunk v) ----
     {
-        const int c = tid >> 3, q = tid & 7;
-        if (c < n && !early_fail) {
-            double* z = R1 + (size_t)c * lda;
-            double zr[NR];
+        double* Tb = scr;                         // [T16][16][17]; the products v_u^T v_j first
+        __syncthreads();                          // (the twisted pairs have been read)
+        for (int b = wave; b < T16; b += nwaves) {
+            const double4_t S = tile_mma(n, 16 * b + r16, 16 * b + r16, kq, [&](int i, int k) { return R2[(size_t)k * lda + i]; },
+                                         [&](int k, int c) { return R2[(size_t)k * lda + c]; }, 16 * b, n);
 #pragma unroll
-            for (int e = 0; e < NR; ++e) zr[e] = (q + 8 * e < n) ? z[q + 8 * e] : 0.0;
-            back_blocks<NR, NR - 1>(zr, R2, lda, n, q, tauv);
+            for (int v = 0; v < 4; ++v) Tb[(b * 16 + 4 * v + kq) * 17 + r16] = S[v];
+        }
+        __syncthreads();
+        if (tid < 16 * T16) {
+            const int b = tid >> 4, r = tid & 15;
+            const double* S = Tb + b * 16 * 17;
+            double x[16];
 #pragma unroll
-            for (int e = 0; e < NR; ++e)
-                if (q + 8 * e < n) z[q + 8 * e] = zr[e];
+            for (int j = 0; j < 16; ++j) {
+                const double tj = tauv[16 * b + j];
+                double v = 0.0;
+#pragma unroll
+                for (int u = 0; u < j; ++u) v = __builtin_fma(x[u], S[u * 17 + j], v);      // (x[u] = 0 for u < r)
+                x[j] = j == r ? tj : (j > r ? -tj * v : 0.0);
+            }
+            // (the block's 16 threads are of one wave: all have read the products before any stores)
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int j = 0; j < 16; ++j) Tb[(b * 16 + r) * 17 + j] = x[j];
+        }
+        __syncthreads();
+        for (int tc = wave; tc < T16 && !early_fail; tc += nwaves) {
+            const int c = min(16 * tc + r16, n - 1);
+            double* zc = R1 + (size_t)c * lda;
+            double4_t Z[NE];
+#pragma unroll
+            for (int ti = 0; ti < NE; ++ti)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int i = 16 * ti + 4 * v + kq;
+                    Z[ti][v] = i < n ? zc[i] : 0.0;
+                }
+            for_each_block<NE>([&](auto B) {
+                constexpr int b = NE - 1 - decltype(B)::value;
+                // columns past n - 3 hold no reflector and their tau is zero, but what they hold has to be finite: it is the matrix
+                const int j = min(16 * b + r16, n - 1);
+                double4_t Y = {0.0, 0.0, 0.0, 0.0}, Y2 = {0.0, 0.0, 0.0, 0.0};
+                asm volatile("" ::: "memory");    // (a block's operands are fetched with the block: all of them do not fit)
+                __builtin_amdgcn_sched_barrier(0);
+                for_each_block<NE - b>([&](auto I) {
+                    constexpr int ti = b + decltype(I)::value;
+                    double va[4];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) va[v] = R2[(size_t)min(16 * ti + 4 * v + kq, n - 1) * lda + j];   // (Z is zero past n)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) Y = __builtin_amdgcn_mfma_f64_16x16x4f64(va[v], Z[ti][v], Y, 0, 0, 0);
+                });
+                double ta[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) ta[v] = -Tb[(b * 16 + r16) * 17 + 4 * v + kq];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) Y2 = __builtin_amdgcn_mfma_f64_16x16x4f64(ta[v], Y[v], Y2, 0, 0, 0);
+                for_each_block<NE - b>([&](auto I) {
+                    constexpr int ti = b + decltype(I)::value;
+                    const int i = min(16 * ti + r16, n - 1);
+                    double va[4];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) va[v] = R2[(size_t)i * lda + min(16 * b + 4 * v + kq, n - 1)];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) Z[ti] = __builtin_amdgcn_mfma_f64_16x16x4f64(va[v], Y2[v], Z[ti], 0, 0, 0);
+                    if (16 * ti + 16 > n) {       // rows past n took a copy of the last row's update: they stay zero
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) Z[ti][v] = 16 * ti + 4 * v + kq < n ? Z[ti][v] : 0.0;
+                    }
+                });
+            });
+            if (16 * tc + r16 < n) {
+#pragma unroll
+                for (int ti = 0; ti < NE; ++ti)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int i = 16 * ti + 4 * v + kq;
+                        if (i < n) zc[i] = Z[ti][v];
+                    }
+            }
         }
     }
     __syncthreads();
+    // a product of n x n matrices, tile t of this wave into acc[t]: formed by every wave before any of them stores
+    constexpr int TWAVE = (NE * NE + 7) / 8;
+    double4_t acc[TWAVE];
+    auto product = [&](auto fa, auto fb, bool lower) {      // lower: the left factor is lower triangular
+#pragma unroll
+        for (int t = 0; t < TWAVE; ++t) {
+            const int tile = wave + t * nwaves;
+            if (tile >= ntiles) continue;         // (uniform)
+            const int ti = tile / T16, tj = tile - ti * T16;
+            acc[t] = tile_mma(n, 16 * ti + r16, 16 * tj + r16, kq, fa, fb, 0, lower ? min(16 * ti + 16, n) : n);
+        }
+    };
+    auto each = [&](auto put) {
+#pragma unroll
+        for (int t = 0; t < TWAVE; ++t) {
+            const int tile = wave + t * nwaves;
+            if (tile >= ntiles) continue;
+            const int ti = tile / T16, tj = tile - ti * T16, j = 16 * tj + r16;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = 16 * ti + 4 * v + kq;
+                if (i < n && j < n) put(i, j, acc[t][v]);
+            }
+        }
+    };
     // ---- 6: orthogonality check and Newton-Schulz polish ----
     bool ok = fail_s == 0;
     for (int it = 0; it < 4 && ok; ++it) {
-        if (tid == 0) err_s = 0ull;
-        gram_to_R2(false);                        // E + I = P^T P
-        __syncthreads();
         double m = 0.0;
-        for (int e = tid; e < n * n; e += nthr) {
-            const int i = e / n, j = e - i * n;
-            m = fmax(m, fabs(R2[(size_t)i * lda + j] - (i == j ? 1.0 : 0.0)));
-        }
-        m = wave_max(m);
+        bool bad = false;
+        gram(false, [&](int ti, int tj, double4_t E) {       // E = P^T P - I
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = 16 * ti + 4 * v + kq, j = 16 * tj + r16;
+                if (i == j) E[v] -= 1.0;
+                if (i < n && j < n) { m = fmax(m, fabs(E[v])); bad = bad || !(fabs(E[v]) < 0.03); }      // (a NaN is bad)
+            }
+            mirror(ti, tj, E);
+        });
+        m = __ballot(bad) ? 1.0 : wave_max(m);
         if (lane == 0) atomicMax(&err_s, (unsigned long long)__double_as_longlong(m));
         __syncthreads();
         const double err = __longlong_as_double((long long)err_s);
-        __syncthreads();
         if (!(err < 0.03)) { ok = false; break; }
         if (err < 1e-10) break;
         if (it == 3) { ok = false; break; }
         const bool last = err < 1e-4;             // one step squares the error (to < 1e-8): no need to look again
-        // P <- P - P E / 2: every wave first forms its output tiles, then all store
-        double4_t acc[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int tile = wave + t * nwaves;
-            if (tile >= ntiles) continue;
-            const int ti = tile / T16, tj = tile - ti * T16;
-            const int ia = 16 * ti + (lane & 15), jb = 16 * tj + (lane & 15), kq = lane >> 4;
-            acc[t] = tile_mma(n, ia, jb, kq, [&](int i, int k) { return R1[(size_t)k * lda + i]; },
-                              [&](int k, int c) { return R2[(size_t)k * lda + c] - (k == c ? 1.0 : 0.0); }, 0, n);
-        }
+        // P <- P - P E / 2
+        product([&](int i, int k) { return R1[(size_t)k * lda + i]; }, [&](int k, int c) { return R2[(size_t)k * lda + c]; }, false);
         __syncthreads();
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int tile = wave + t * nwaves;
-            if (tile < ntiles) {
-                const int ti = tile / T16, tj = tile - ti * T16;
-                const int jb = 16 * tj + (lane & 15), kq = lane >> 4;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int i = 16 * ti + 4 * v + kq;
-                    if (i < n && jb < n) R1[(size_t)jb * lda + i] -= 0.5 * acc[t][v];
-                }
-            }
-        }
+        if (tid == 0) err_s = 0ull;
+        each([&](int i, int j, double v) { R1[(size_t)j * lda + i] -= 0.5 * v; });
         __syncthreads();
         if (last) break;
     }
     // ---- 7: W0 = L P into R2 (or L itself when the preconditioner was dropped) ----
-    __syncthreads();
-    for (size_t e = tid; e < rsize; e += nthr) {
-        const int c = (int)(e / ld), i = (int)(e - (size_t)c * ld);
-        R2[e] = (!ok && c < n && i < n) ? gscr[(size_t)c * lda + i] : 0.0;
-    }
-    __syncthreads();
-    if (!ok) return false;
-    double4_t acc[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const int tile = wave + t * nwaves;
-        if (tile >= ntiles) continue;             // (uniform)
-        const int ti = tile / T16, tj = tile - ti * T16;
-        const int ia = 16 * ti + (lane & 15), jb = 16 * tj + (lane & 15), kq = lane >> 4;
-        acc[t] = tile_mma(n, ia, jb, kq, [&](int i, int k) { return gscr[(size_t)k * lda + i]; },           // L[i][k], k <= i
-                          [&](int k, int c) { return R1[(size_t)c * lda + k]; }, 0, min(16 * ti + 16, n));  // P[k][c]
-    }
-    __syncthreads();                              // P has been read: R1 takes a copy of W0 in its own stride for the check below
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const int tile = wave + t * nwaves;
-        if (tile >= ntiles) continue;
-        const int ti = tile / T16, tj = tile - ti * T16;
-        const int jb = 16 * tj + (lane & 15), kq = lane >> 4;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int i = 16 * ti + 4 * v + kq;
-            if (i < n && jb < n) {
-                R2[(size_t)jb * ld + i] = acc[t][v];
-                R1[(size_t)jb * lda + i] = acc[t][v];
-            }
+    if (ok)
+        product([&](int i, int k) { return gscr[(size_t)k * lda + i]; },           // L[i][k], k <= i
+                [&](int k, int c) { return R1[(size_t)c * lda + k]; }, true);      // P[k][c]
+    __syncthreads();                              // P and E have been read: R1 takes a copy of W0 in its own stride for the check below
+    for (int c = tid >> 4; c <= ne; c += nthr >> 4)
+        for (int i = r16; i < ld; i += 16) {
+            const bool in = c < n && i < n;
+            if (!in || !ok) R2[(size_t)c * ld + i] = in ? gscr[(size_t)c * lda + i] : 0.0;
         }
-    }
+    if (ok)
+        each([&](int i, int j, double v) {
+            R2[(size_t)j * ld + i] = v;
+            R1[(size_t)j * lda + i] = v;
+        });
     __syncthreads();
-    return true;
+    return ok;
 }
 
 // One-sided Jacobi on the Cholesky factor of G.  JGL lanes share a pair of columns, NE = ceil(n / JGL)
@@ -921,9 +1028,10 @@ __device__ __forceinline__ bool eig_precondition(double* __restrict__ R1, double
 // to all the others, and rotations among the others keep it so; it leaves the tournament, and
 // the later sweeps run over the columns that still move.
 // SMALL: n <= 4 (see chol_blocked).
-template <int NE, int JGL, bool SMALL = false>
-__global__ void __launch_bounds__(NE <= 4 ? 512 : 128 * NE)
-k_jacobi_eig(const JacobiBatch batch, int n, int kk, int use_pre) {
+// PRE: the preconditioner runs, for orders of PRE 16-row tiles.
+template <int NE, int JGL, bool SMALL = false, int PRE = 0>
+__global__ void __launch_bounds__(NE * JGL <= 64 || PRE ? 512 : 8 * NE * JGL)
+k_jacobi_eig(const JacobiBatch batch, int n, int kk) {
     extern __shared__ double sm[];
     const JacobiProblem& prob = batch.p[blockIdx.x];
     const double* __restrict__ G = prob.G;
@@ -931,8 +1039,7 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk, int use_pre) {
     double* __restrict__ vec = prob.vec;
     double* __restrict__ tmat = prob.tmat;
     float* __restrict__ sval = prob.sval;
-    // (orders of 72 to 84 alone: see the launch)
-    double* __restrict__ gscr = NE == 5 || NE == 6 ? (use_pre ? prob.gscr : nullptr) : nullptr;
+    double* __restrict__ gscr = PRE ? prob.gscr : nullptr;
     const int ne = n + (n & 1);             // even number of columns (a zero column pads odd n)
     // Column stride = 8 (mod 16) doubles spreads the columns that one LDS instruction touches over the banks.
     const int ld = jacobi_ld(n, JGL);
@@ -944,7 +1051,7 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk, int use_pre) {
     int* order = (int*)(nrm + ne + 1);           // [ne]
     int* colmap = order + ne;                    // [ne + 1] slot -> column of the columns still rotating
     int* rotf = colmap + ne + 1;                 // [ne + 1] column took part in a rotation this sweep
-    // [10 n + 40] the preconditioner's vectors, past the int arrays, on an even double index (16-byte loads)
+    // [pre_doubles(n)] the preconditioner's vectors, past the int arrays, on an even double index (16-byte loads)
     double* pre_sa = sm + (((gscr ? 2 : 1) * rsize + ne / 2 + ne + 1 + (3 * ne + 4) / 2 + 2) & ~(size_t)1);
     __shared__ int nact_sh, wcnt[2];
     const int tid = threadIdx.x, nthr = blockDim.x, grp = tid / JGL, gl = tid % JGL;
@@ -992,11 +1099,9 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk, int use_pre) {
         return total;
     };
     bool checked = false;
-    if constexpr (NE == 5 || NE == 6) {
-        if (gscr) {
-            W = sm + rsize;
-            checked = eig_precondition<NE>(sm, W, ld, ldc, n, ne, gscr, pre_sa);
-        }
+    if constexpr (PRE > 0) {
+        W = sm + rsize;
+        checked = eig_precondition<PRE>(sm, W, ld, ldc, n, ne, gscr, pre_sa);
     }
     if (checked) {
         // The preconditioned columns are (nearly) orthogonal: which of them still have to rotate is decided on their
@@ -1234,28 +1339,29 @@ int launch_chol_inv_batch(hipStream_t s, const CholProblem* probs, int count, in
     return METIS_OK;
 }
 
+// The orders from which on the preconditioner runs.  (It pays from 32 on: a lone decomposition with eigenproblems of order 36 and 28
+// takes 287 us with it and 316 with plain sweeps, of 72 and 56 435 and 616.  But a singular vector's sign is the one that the
+// method leaves it with, callers keep their factors from one build to the next, and below 72, and for the second problem of
+// every decomposition, it has always been the plain sweeps'.)
+#define PRE_MIN_N 72
 int launch_jacobi_eig_batch(hipStream_t s, const JacobiProblem* probs, int count, int n, int kk) {
     if (n < 1 || n > 128 || count < 0) return METIS_UNSUPPORTED;
-    const int jgl = jacobi_lanes(n);
-    const int ne = n + (n & 1), ld = jacobi_ld(n, jgl);
-    const size_t rsize = (size_t)(ne + 1) * ld;
+    const int ne = n + (n & 1);
+    auto region = [&](int jgl) { return (size_t)(ne + 1) * jacobi_ld(n, jgl); };
     const size_t small = ((size_t)ne / 2 + ne + 1) * sizeof(double) + (size_t)(3 * ne + 4) * sizeof(int) + 16;
-    // the preconditioner needs two matrix-sized regions and 10 n + 40 doubles; it pays from n ~ 72 on (about 170 us
-    // against 8 of 9 sweeps of 46 us at n = 80; at n = 64 the plain sweeps, 120 to 170 us, are no slower), and its second
-    // region fits in the 160 KB of LDS up to n = 84 (the column stride is 112 instead of 80 beyond order 80: 161.4 kB at 84, 165.2 at
-    // 85).  It runs when every problem of the batch brings scratch.
-    size_t lds = rsize * sizeof(double) + small;
-    const size_t lds_pre = 2 * rsize * sizeof(double) + small + (10 * (size_t)n + 44) * sizeof(double);
-    bool all_scratch = count > 0;
-    for (int i = 0; i < count; ++i) all_scratch = all_scratch && probs[i].gscr != nullptr;
-    const int use_pre = all_scratch && n >= 72 && lds_pre <= 160 * 1024;
-    if (use_pre) lds = lds_pre;
+    // the preconditioner needs two matrix-sized regions and its vectors, which fit in the 160 KB of LDS (2 KB of them for static
+    // arrays) up to n = 84.  It runs when every problem of the batch brings scratch.
+    bool pre = count > 0 && n >= PRE_MIN_N;
+    for (int i = 0; i < count; ++i) pre = pre && probs[i].gscr != nullptr;
+    const size_t lds_pre = (2 * region(PRE_JGL) + pre_doubles(n) + 2) * sizeof(double) + small;
+    pre = pre && lds_pre <= 158 * 1024;
     // one group of jgl lanes per column pair, in whole waves and at least 512 threads (the Cholesky pre-pass, the
-    // bookkeeping and the preconditioner's 8 lanes per row use them); no idle waves beyond that: every wave of
-    // the workgroup takes part in every barrier
+    // bookkeeping and the preconditioner use them); no idle waves beyond that: every wave of the workgroup takes part in every
+    // barrier.  After the preconditioner few columns still move, and 512 threads leave its phases 256 registers.
+    const int jgl = pre ? PRE_JGL : JGL_PLAIN;
+    const size_t lds = pre ? lds_pre : region(jgl) * sizeof(double) + small;
     const int need = (ne / 2 * jgl + 63) / 64 * 64;               // at most 128 ceil(n / 16): the kernel's launch bound
     const int threads = need > 512 ? need : 512;
-    if (ne / 2 * jgl > threads) return METIS_UNSUPPORTED;
     for (int b0 = 0; b0 < count; b0 += SM_MAX_BATCH) {
         const int nb = count - b0 < SM_MAX_BATCH ? count - b0 : SM_MAX_BATCH;
         JacobiBatch batch;
@@ -1264,25 +1370,24 @@ int launch_jacobi_eig_batch(hipStream_t s, const JacobiProblem* probs, int count
     {                                                                                                             \
         static LdsLimitCache lds_set;                                                                             \
         if (!ensure_dyn_lds((const void*)k_jacobi_eig<__VA_ARGS__>, lds, lds_set)) return METIS_HIP_ERROR;        \
-        hipLaunchKernelGGL((k_jacobi_eig<__VA_ARGS__>), dim3(nb), dim3(threads), lds, s, batch, n, kk, use_pre);  \
+        hipLaunchKernelGGL((k_jacobi_eig<__VA_ARGS__>), dim3(nb), dim3(threads), lds, s, batch, n, kk);           \
     }
+#define JACOBI_PRE(T) if (pre) JACOBI_CASE(16 / PRE_JGL * T, PRE_JGL, false, T) else JACOBI_CASE(T, JGL_PLAIN)
         switch ((n + 15) / 16) {
-            case 1: if (n <= 4) JACOBI_CASE(1, 16, true) else JACOBI_CASE(1, 16, false) break;
-            case 2: JACOBI_CASE(2, 16) break;
-            case 3: JACOBI_CASE(3, 16) break;
-            case 4: JACOBI_CASE(4, 16) break;
-            case 5: JACOBI_CASE(5, 16) break;
-            case 6: JACOBI_CASE(6, 16) break;
-            case 7: JACOBI_CASE(7, 16) break;
-            default: JACOBI_CASE(8, 16) break;
+            case 1: if (n <= 4) JACOBI_CASE(1, JGL_PLAIN, true) else JACOBI_CASE(1, JGL_PLAIN) break;
+            case 2: JACOBI_CASE(2, JGL_PLAIN) break;
+            case 3: JACOBI_CASE(3, JGL_PLAIN) break;
+            case 4: JACOBI_CASE(4, JGL_PLAIN) break;
+            case 5: JACOBI_PRE(5) break;
+            case 6: JACOBI_PRE(6) break;
+            case 7: JACOBI_CASE(7, JGL_PLAIN) break;
+            default: JACOBI_CASE(8, JGL_PLAIN) break;
         }
+#undef JACOBI_PRE
 #undef JACOBI_CASE
         METIS_LAUNCH_CHECK();
     }
     return METIS_OK;
 }
 
-size_t jacobi_scratch_doubles(int n) {
-    const int ne = n + (n & 1);
-    return (size_t)(ne + 1) * jacobi_ld(n, jacobi_lanes(n));
-}
+size_t jacobi_scratch_doubles(int n) { return (size_t)n * (n | 1); }       // the Cholesky factor while its place is in use

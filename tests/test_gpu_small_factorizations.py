@@ -21,6 +21,16 @@ def test_orders_at_the_edges_of_tiles(metis, k, p):  # noqa: F811
     _compare(A, got, odec.decompose(A.double().numpy(), k, p, 0.5, seed=5), k)
 
 
+@pytest.mark.parametrize("k,p", [(63, 8), (64, 8), (40, 33), (66, 13), (66, 14), (67, 14), (82, 2), (84, 1)])
+@pytest.mark.parametrize("alpha", [1.1, 1.5])
+def test_orders_of_the_eigenvector_preconditioner(metis, k, p, alpha):  # noqa: F811
+    # its least and largest order (72, 84) and their neighbours, whole and ragged tiles, the spectra of the tests above
+    s = 50.0 * np.arange(1, 257) ** -alpha + 0.02
+    A = _planted_bf16(512, 256, s, seed=k + 5 * p)
+    got = _run(metis, A, k, p, 1.0, seed=9)
+    _compare(A, got, odec.decompose(A.double().numpy(), k, p, 1.0, seed=9), k)
+
+
 @pytest.mark.parametrize("k,p", [(20, 12), (60, 20), (72, 16)])
 def test_repeated_singular_values(metis, k, p):  # noqa: F811
     # pairs of equal singular values down to the last kept one: the subspaces are determined up to the pair, so compare
