@@ -10,6 +10,7 @@
 #include <stdlib.h>
 #include "common.h"
 #include "gemm_tile.h"
+#include "stream_dev.h"
 
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));

@@ -1,30 +1,10 @@
 // The main FP4 GEMM kernel for large outputs (included by gemm.hip, inside its namespace).
 #pragma once
-#include <utility>
 
 typedef uint32_t gs_u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t gs_u32x2 __attribute__((ext_vector_type(2)));
 typedef float gs_acc_t __attribute__((ext_vector_type(4)));
 
-// Transfers global memory -> LDS that pass through no register: the lane's 16 bytes go to lds + AT + 16 lane.  lds and base
-// are uniform.  Two hazards that the compiler does not look for inside asm are closed here: m0 must have been written two
-// instructions before, and a base that a vector instruction wrote (v_readfirstlane, or v_readlane where it was spilled) may be read by
-// a memory instruction only five wait states later.  The scalar copy waits for either writer by itself, and stands where m0 needs an
-// instruction in between.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"          // m0 is one of the compiler's reserved registers, and is to be clobbered
-template <int AT>
-__device__ __forceinline__ void gs_dma16(uint32_t lds, uint32_t voff, const uint8_t* base) {
-    const uint8_t* copy;
-    asm volatile("s_add_u32 m0, %1, %4\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
-                 : "=&s"(copy) : "s"(lds), "v"(voff), "s"(base), "n"(AT) : "memory", "m0", "scc");
-}
-#pragma clang diagnostic pop
-// all but the N youngest of the wave's transfers have arrived and its LDS reads are done; then the workgroup meets
-template <int N>
-__device__ __forceinline__ void gs_meet() {
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
-}
 // acc += X Y^T, 16 x 16 over 32 columns, the accumulator in place in the accumulation registers (left to itself the compiler keeps
 // it in vector registers, moves it about and runs out of them; the instruction is also 40 % slower on those: 3375 cycles
 // against 2060 for 64 x 2).  The hazards that the compiler then does not see: X or Y written by a vector instruction
@@ -61,28 +41,6 @@ __device__ __forceinline__ void gs_settle(gs_acc_t (&a)[8]) {
     asm volatile("s_nop %8\n\ts_nop %8" : "+a"(a[0]), "+a"(a[1]), "+a"(a[2]), "+a"(a[3]), "+a"(a[4]), "+a"(a[5]), "+a"(a[6]), "+a"(a[7])
                  : "n"(N));
 }
-// The lane's number, computed where it is used: what is derived from it is then not kept in registers over the whole kernel.
-__device__ __forceinline__ int gs_fresh_lane() {
-    int l;
-    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
-    return l;
-}
-
-#define GS_INLINE __attribute__((always_inline))
-// f(0), f(1), ... f(N - 1) with constants (a loop of this size with the bodies below is not unrolled by pragma)
-template <int... I, typename F>
-__device__ __forceinline__ void gs_each(std::integer_sequence<int, I...>, const F& f) {
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void gs_for(const F& f) { gs_each(std::make_integer_sequence<int, N>{}, f); }
-
-// a uniform pointer that stays in scalar registers
-__device__ __forceinline__ const uint8_t* gs_uniform(const uint8_t* p) {
-    const uint64_t v = (uint64_t)p;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return (const uint8_t*)((uint64_t)hi << 32 | lo);
-}
 // LDS: four buffers of one unit: the codes of A's and of B's 256 rows, 128 elements each, then the block scales of both as
 // k_scale_plan lays them out.  The stores use the buffer of the unit just finished.
 #define GS_BAND 4                                        // tiles side by side that an XCD has in work, see make_band_map
@@ -111,12 +69,6 @@ template <> struct GsStage<float> {
         *reinterpret_cast<float4*>(sm + row * 128 + (((4 * z + kg) ^ (row >> 1)) * 16)) = w;
     }
 };
-// Lanes exchange what they staged: the compiler may order one lane's read and write of different addresses as it likes, and LDS keeps
-// the wave's order.  (No instruction.)
-__device__ __forceinline__ void gs_wave_order() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
 // the 16 staged rows to C (first row r0, first column c0); whole: inside the matrix and 16-byte aligned
 template <typename OUT>
 __device__ __forceinline__ void gs_store_rows(const uint8_t* sm, OUT* C, int64_t ldc, int64_t r0, int64_t c0, int64_t M, int64_t N,

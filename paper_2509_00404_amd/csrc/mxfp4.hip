@@ -6,6 +6,7 @@
 #include <type_traits>
 #include "common.h"
 #include "gemm_tile.h"
+#include "stream_dev.h"
 #include "../../include/metis.h"
 
 typedef int int8v_t __attribute__((ext_vector_type(8)));
@@ -72,6 +73,7 @@ k_quantize_mx(const T* __restrict__ A, int64_t ld, int64_t M, int64_t nblk /* co
 }
 
 // ---- GEMM C[M,N] = A[M,K] B[N,K]^T ----
+// Large outputs of whole units of 256 go to the streaming kernel (mx_stream.h, rule at launch_mx_tile); this one takes the rest.
 // 256 x 256 tile, 8 waves of 128 x 64 (4 x 2 accumulator tiles of 32 x 32, two waves per SIMD); for few tiles 128 x 128, 8 waves of 64 x
 // 32 and two workgroups a CU (BT, see launch_mx_gemm).  A lane's operand of
 // one matrix instruction is the 32 codes (16 bytes) of row lane % 32, contraction half lane / 32, and the E8M0 byte
@@ -116,6 +118,66 @@ __device__ __forceinline__ void mx_put4(bf16_t* p, float x, float y, float z, fl
 }
 __device__ __forceinline__ void mx_put4(float* p, float x, float y, float z, float w) {
     *reinterpret_cast<float4*>(p) = make_float4(x, y, z, w);
+}
+
+// A wave's TM x TN accumulator tiles to memory.  LINES: 32 rows of its columns at a time are staged at sm (mx_wave_rows bytes), else
+// straight from the registers.  whole: the workgroup's tile is inside the matrix (LINES: and C allows 16-byte stores, as vec says).
+template <typename OUT, int TN>
+constexpr int mx_wave_rows() { return 32 * (32 * TN * (int)sizeof(OUT) + 16); }
+template <typename OUT, bool LINES, int TM, int TN>
+__device__ __forceinline__ void mx_store_wave(const float16_t (&acc)[TM][TN], uint8_t* sm, OUT* __restrict__ C, int64_t ldc, int64_t m0,
+                                              int64_t n0, int64_t M, int64_t N, bool vec, bool whole, int lane) {
+    const int li = lane & 31, half = lane >> 5;
+    if constexpr (!LINES) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int64_t c = n0 + 32 * j + li;
+                const int64_t rbase = m0 + 32 * i + 4 * half;
+                if (whole) {
+                    store_tile16<OUT>(C + rbase * ldc + c, ldc, acc[i][j], 1.0f);
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int64_t r = rbase + 8 * (v >> 2) + (v & 3);
+                        if (r < M && c < N) store_out<OUT>(C + r * ldc + c, acc[i][j][v]);
+                    }
+                }
+            }
+    } else {
+        constexpr int E = 16 / (int)sizeof(OUT), LROW = 32 * TN * (int)sizeof(OUT) + 16, UNITS = 32 * TN / E, ROWS = 64 / UNITS;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; v += 4)
+                    mx_put4(reinterpret_cast<OUT*>(sm + li * LROW) + 32 * j + 2 * v + 4 * half, acc[i][j][v], acc[i][j][v + 1],
+                            acc[i][j][v + 2], acc[i][j][v + 3]);
+            gs_wave_order();
+#pragma unroll
+            for (int t = 0; t < 32 / ROWS; ++t) {
+                const int row = ROWS * t + lane / UNITS, unit = lane % UNITS;
+                const uint8_t* q = sm + row * LROW + 16 * unit;
+                const uvec4_t w = *reinterpret_cast<const uvec4_t*>(q);
+                const int64_t r = m0 + 32 * i + row, c = n0 + E * unit;
+                OUT* p = C + r * ldc + c;
+                if (whole) {
+                    *reinterpret_cast<uvec4_t*>(p) = w;
+                } else if (r < M) {
+                    const int64_t left = N - c;
+                    if (vec && left >= E) {
+                        *reinterpret_cast<uvec4_t*>(p) = w;
+                    } else {
+#pragma unroll 1
+                        for (int e = 0; e < E && e < left; ++e) p[e] = reinterpret_cast<const OUT*>(q)[e];
+                    }
+                }
+            }
+            gs_wave_order();
+        }
+    }
 }
 
 // MODE: MX_WHOLE for K a multiple of the 256-deep stage.  Else the last stage exists only in part, and its missing blocks of 32 enter as
@@ -319,65 +381,15 @@ k_mxfp4_gemm_nt(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C, int64_
         read_scales(bufn);
     }
 
-    if constexpr (!LINES) {
-        const bool interior = m0 + BM <= A.rows && n0 + BN <= B.rows;
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int64_t c = n0 + wn + 32 * j + li;
-                const int64_t rbase = m0 + wm + 32 * i + 4 * half;
-                if (interior) {
-                    store_tile16<OUT>(C + rbase * ldc + c, ldc, acc[i][j], 1.0f);
-                } else {
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const int64_t r = rbase + 8 * (v >> 2) + (v & 3);
-                        if (r < A.rows && c < B.rows) store_out<OUT>(C + r * ldc + c, acc[i][j][v]);
-                    }
-                }
-            }
-        return;
-    }
+    if constexpr (LINES) static_assert(8 * mx_wave_rows<OUT, TN>() <= BUF, "the staged rows fit one buffer");
     // The last stage's buffer is free: its codes and scales were in registers before the last meeting, and that stage stored to the
-    // other one.  Every wave stages 32 rows of its columns at a time in a part of its own.
-    constexpr int E = 16 / (int)sizeof(OUT), LROW = 32 * TN * (int)sizeof(OUT) + 16, UNITS = 32 * TN / E, ROWS = 64 / UNITS;
-    static_assert(8 * 32 * LROW <= BUF, "the staged rows fit one buffer");
-    uint8_t* sm = lds + ((niter - 1) & 1) * BUF + wave * (32 * LROW);
-    const bool whole = vec && m0 + BM <= A.rows && n0 + BN <= B.rows;
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; v += 4)
-                mx_put4(reinterpret_cast<OUT*>(sm + li * LROW) + 32 * j + 2 * v + 4 * half, acc[i][j][v], acc[i][j][v + 1],
-                        acc[i][j][v + 2], acc[i][j][v + 3]);
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int t = 0; t < 32 / ROWS; ++t) {
-            const int row = ROWS * t + lane / UNITS, unit = lane % UNITS;
-            const uint8_t* q = sm + row * LROW + 16 * unit;
-            const uvec4_t w = *reinterpret_cast<const uvec4_t*>(q);
-            const int64_t r = m0 + wm + 32 * i + row, c = n0 + wn + E * unit;
-            OUT* p = C + r * ldc + c;
-            if (whole) {
-                *reinterpret_cast<uvec4_t*>(p) = w;
-            } else if (r < A.rows) {
-                const int64_t left = B.rows - c;
-                if (vec && left >= E) {
-                    *reinterpret_cast<uvec4_t*>(p) = w;
-                } else {
-#pragma unroll 1
-                    for (int e = 0; e < E && e < left; ++e) p[e] = reinterpret_cast<const OUT*>(q)[e];
-                }
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-    }
+    // other one.
+    const bool inside = m0 + BM <= A.rows && n0 + BN <= B.rows;
+    mx_store_wave<OUT, LINES, TM, TN>(acc, lds + ((niter - 1) & 1) * BUF + wave * mx_wave_rows<OUT, TN>(), C, ldc, m0 + wm, n0 + wn, A.rows,
+                                      B.rows, vec, LINES ? vec && inside : inside, lane);
 }
+
+#include "mx_stream.h"
 
 // Regions or bands.  An XCD's tiles in work should share few panels: a region near square sees to that and writes longer runs of
 // C's rows, which counts while a tile's contraction is short; bands see to it whatever the grid, and over many tiles of a long contraction
@@ -405,6 +417,20 @@ int launch_mx_tile(hipStream_t s, const MxOperand& a, const MxOperand& b, int64_
         hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn)), dim3(512), LDS, s, a, b, K, C, ldc, vec, order);
         return true;
     };
+    // The streaming kernel: whole units, two at least (its transfers are two ahead of the products), and several tiles a CU or a long
+    // contraction.  A lone tile a CU gains nothing from a stream that crosses tiles: us, the kernel above / streaming, 4096 x 4096 x
+    // 512 13.0 / 13.2, x 1024 15.4 / 15.7, x 4096 (with quantizers) 56.6 / 55.9; 4352 x 4352 x 512 17.7 / 17.0, 8192 x 8192 x 512 39.6 / 35.5.
+    const int cus = device_cu_count();
+    if (cus < 1) return METIS_HIP_ERROR;
+    if (BT == 256 && K % MX_KI == 0 && K >= 2 * MX_KI && (tm * tn > cus || K >= 8 * MX_KI)) {
+        auto kern = k_mxfp4_gemm_nt_stream<OUT>;
+        static LdsLimitCache stream_set;
+        if (!ensure_dyn_lds((const void*)kern, MXS_LDS, stream_set)) return METIS_HIP_ERROR;
+        hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn < cus ? tm * tn : cus)), dim3(512), MXS_LDS, s, a, b, K, C, ldc, vec, order,
+                           (int)(tm * tn));
+        METIS_LAUNCH_CHECK();
+        return METIS_OK;
+    }
     static LdsLimitCache lds_set[3];
     const bool ok = K % MX_KI == 0 ? launch(k_mxfp4_gemm_nt<OUT, MX_WHOLE, BT>, lds_set[0])
                     : K > MX_KI    ? launch(k_mxfp4_gemm_nt<OUT, MX_TAIL, BT>, lds_set[1])

@@ -133,3 +133,26 @@ def test_mxfp4_gemm_on_both_sides_of_the_tile_rule(metis, M, N, K, out_dtype):
     for i in range(0, M, 256):
         for j in range(0, N, 256):
             assert rel_fro(got[i:i + 256, j:j + 256], ref[i:i + 256, j:j + 256]) < (1e-5 if out_dtype == torch.float32 else 4e-3), (i, j)
+
+
+# 256 x 256 tiles of whole units of 256: two units, three, more; fewer tiles than CUs, more than one a CU, ragged last rows and columns
+@pytest.mark.parametrize("M,N,K", [(3000, 3000, 2304), (2817, 6399, 768), (4200, 4399, 512), (4352, 4100, 768), (2600, 2900, 2048)])
+@pytest.mark.parametrize("ld_extra", [0, 1])
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
+def test_mxfp4_gemm_streamed(metis, M, N, K, ld_extra, out_dtype):
+    """The bars of test_mxfp4_gemm_against_oracle for every 256 x 256 block; rows of C that start off 16 bytes, nothing written beside them."""
+    a, b = _data(M, K, 9, torch.bfloat16), _data(N, K, 10, torch.bfloat16)
+    qa, qb = metis.MxTensor(M, K), metis.MxTensor(N, K)
+    metis.quantize_mx(a.cuda(), qa)
+    metis.quantize_mx(b.cuda(), qb)
+    full = torch.full((M, N + ld_extra), float("nan"), dtype=out_dtype, device="cuda")
+    for _ in range(2):                     # the second launch finds other data in LDS
+        metis.mxfp4_gemm_nt(qa, qb, full[:, :N])
+    torch.cuda.synchronize()
+    ref = omx.mx_gemm_nt((qa.codes.cpu().numpy(), qa.scales.cpu().numpy()), (qb.codes.cpu().numpy(), qb.scales.cpu().numpy()))
+    got = full[:, :N].double().cpu().numpy()
+    assert np.isfinite(got).all()
+    for i in range(0, M, 256):
+        for j in range(0, N, 256):
+            assert rel_fro(got[i:i + 256, j:j + 256], ref[i:i + 256, j:j + 256]) < (1e-5 if out_dtype == torch.float32 else 4e-3), (i, j)
+    assert bool(torch.isnan(full[:, N:]).all())
