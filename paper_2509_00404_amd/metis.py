@@ -6,6 +6,7 @@ fallback: a missing library or a non-zero status raises.
 """
 import ctypes as C
 import os
+import struct
 
 import torch
 
@@ -143,12 +144,17 @@ class Fp4Tensor:
         self.codes = torch.empty((rows, cols // 2), dtype=torch.uint8, device=device)
         self.scales = torch.empty((rows, cols // 16), dtype=torch.uint8, device=device)
 
+    def fields(self):
+        return self.codes.data_ptr(), self.scales.data_ptr(), self.tscale, self.rows, self.cols
+
     def c(self):
-        return Fp4(self.codes.data_ptr(), self.scales.data_ptr(), self.tscale, self.rows, self.cols)
+        return Fp4(*self.fields())
 
 
-def _null_fp4():
-    return Fp4(None, None, 1.0, 0, 0)
+# A Split is packed in one go: built from four nested structures it took 3.5 us on the host, of the 7 that a small product's call took.
+_SPLIT = struct.Struct("@" + 4 * "PPfqq" + "Pi0P")
+_NULL_FP4 = (0, 0, 1.0, 0, 0)
+assert _SPLIT.size == C.sizeof(Split)
 
 
 class MxTensor:
@@ -175,8 +181,8 @@ class SplitTensor:
         self.S = torch.empty((max(k, 1),), dtype=torch.float32, device=device)
 
     def c(self):
-        return Split(self.Ut.c() if self.Ut else _null_fp4(), self.Vt.c() if self.Vt else _null_fp4(),
-                     self.R.c(), self.Rt.c() if self.Rt else _null_fp4(), self.S.data_ptr(), self.k)
+        fields = [t.fields() if t else _NULL_FP4 for t in (self.Ut, self.Vt, self.R, self.Rt)]
+        return Split.from_buffer_copy(_SPLIT.pack(*fields[0], *fields[1], *fields[2], *fields[3], self.S.data_ptr(), self.k))
 
 
 def tensor_scale(amax):
