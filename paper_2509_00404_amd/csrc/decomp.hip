@@ -272,7 +272,8 @@ int make_job(const metis_decompose_job& a, Job& j) {
     // first factor's diagonal shows a well-conditioned sketch the first pass's H1 is orthonormal to ~1e-10
     // already: a device flag then turns the second pass's kernel into a no-op.  The projection reads H1 either way: with H1 = H R2
     // the pass's factor X = R2^-T turns B1 = H1^T A_s into B = X B1, and only B B^T = X (B1 B1^T) X^T and V0 = B1^T (X^T T)
-    // are ever needed, so that it costs one launch and not four when there is nothing to repair (4.5 us each).
+    // are ever needed, so that it costs no launch and not four when there is nothing to repair (4.5 us each): the
+    // eigensolver does it where the flag is not set.
     j.wellcond = j.fast ? (int32_t*)(ws + L.off_flag) : nullptr;
     j.gram_fast = a.k % 4 == 0;
     j.cparts = a.split ? 1 : broadcast_splits(j.M, j.N);      // the fused path sums each band's parts at once
@@ -377,7 +378,7 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
     // ---- CholeskyQR2: Z = H R ----
     {
         std::vector<CholProblem> pr;
-        for (const Job& j : jobs) pr.push_back({j.G1, j.Linv, j.info, j.wellcond, nullptr, nullptr});
+        for (const Job& j : jobs) pr.push_back({j.G1, j.Linv, j.info, j.wellcond});
         if ((st = launch_grouped<CholProblem>(jobs, [](const Job& j) { return j.r; }, chol_launch, s, pr, zeros)) != METIS_OK)
             return st;
     }
@@ -407,18 +408,12 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
         gram_of(j, op(j.H1, 1, j.r), j.Ms, j.parts + (int64_t)n * j.r * j.r, j.G1b, j.wellcond);
     }
     if ((st = grams_launch()) != METIS_OK) return st;
-    {
-        std::vector<CholProblem> pr;
-        for (const Job& j : jobs) pr.push_back({j.G1b, j.Linv, j.info, nullptr, j.wellcond, j.G2});
-        if ((st = launch_grouped<CholProblem>(jobs, [](const Job& j) { return j.r; }, chol_launch, s, pr, zeros)) != METIS_OK)
-            return st;
-    }
     // ---- top-k right singular vectors of B from the eigen-decomposition of B B^T ----
     {
         std::vector<JacobiProblem> pr;
         std::vector<int> kks;
         for (const Job& j : jobs) {
-            pr.push_back({j.G2, j.lam, nullptr, j.T, nullptr, j.jscr, j.Linv, j.wellcond});
+            pr.push_back({j.G2, j.lam, nullptr, j.T, nullptr, j.jscr, j.G1b, j.Linv, j.wellcond, j.info});
             kks.push_back(j.k);
         }
         if ((st = launch_grouped<JacobiProblem>(jobs, [](const Job& j) { return j.r; }, launch_jacobi_eig_batch, s, pr, kks)) !=
@@ -496,7 +491,7 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
         std::vector<JacobiProblem> pr;
         std::vector<int> kks;
         for (const Job& j : jobs) {
-            pr.push_back({j.G3, j.lam3, j.W3, j.T3, j.S, nullptr, nullptr, nullptr});
+            pr.push_back({j.G3, j.lam3, j.W3, j.T3, j.S, nullptr, nullptr, nullptr, nullptr, nullptr});
             kks.push_back(j.k);
         }
         if ((st = launch_grouped<JacobiProblem>(jobs, [](const Job& j) { return j.k; }, launch_jacobi_eig_batch, s, pr, kks)) !=

@@ -12,21 +12,23 @@ struct CholProblem {
     int32_t* info;            // optional: index + 1 of a pivot that was not positive
     int32_t* wellcond_out;    // optional: set to 1 when the factor's diagonal spans less than 1e3 (the QR pass that
                               // used it is then orthonormal to ~1e-10)
-    const int32_t* skip_in;   // optional: nonzero -> nothing is done
-    double* transform;        // optional: n x n, replaced by Linv transform Linv^T
 };
 struct CholBatch { CholProblem p[SM_MAX_BATCH]; };
 
 struct JacobiProblem {
-    const double* G;          // n x n symmetric positive semi-definite
+    double* G;                // n x n symmetric positive semi-definite
     double* lam;              // n eigenvalues, descending
     double* vec;              // optional n x kk eigenvectors
     double* tmat;             // optional n x kk eigenvectors scaled by 1 / sqrt(lambda)
     float* sval;              // optional kk square roots of the eigenvalues
     double* gscr;             // optional jacobi_scratch_doubles(n) doubles of device scratch; when given (and the order
                               // allows it) the sweeps start from columns preconditioned with approximate eigenvectors
-    const double* post;       // optional n x n lower triangular X: tmat becomes X^T tmat
-    const int32_t* post_skip; // optional: nonzero -> it does not
+    // CholeskyQR's second pass, unless *wellcond is set: gram = Gram matrix of the first pass's basis (n x n, null: no second pass),
+    // post = the inverse X of its Cholesky factor (out), G becomes X G X^T and tmat X^T tmat
+    const double* gram;
+    double* post;
+    const int32_t* wellcond;  // optional
+    int32_t* info;            // optional: as of CholProblem
 };
 struct JacobiBatch { JacobiProblem p[SM_MAX_BATCH]; };
 

@@ -2,6 +2,7 @@
 // (Sec. 3.1): Cholesky + triangular inverse for CholeskyQR2 (thin QR Z = H R), and a
 // one-sided Jacobi eigensolver for the Gram matrices of the reduced problem.
 #include "smallmat.h"
+#include <algorithm>
 #include <cstdlib>
 #include <utility>
 
@@ -227,27 +228,19 @@ __device__ __forceinline__ double4_t tile_mma(int n, int ia, int jb, int kq, FA 
 }
 
 // ---------------------------------------------------------------------------------------
-// Cholesky G = L L^T and Linv = L^-1 (lower triangular), n <= SM_MAX_CHOL; optionally a second matrix F <- Linv F Linv^T.
+// Cholesky G = L L^T and Linv = L^-1 (lower triangular), n <= SM_MAX_CHOL; optionally a second matrix F <- Linv F Linv^T (transform).
 // LDS: L [n][n+1] doubles, X [n][n+1] doubles.
 // ---------------------------------------------------------------------------------------
 #define CI_THREADS 512               // 256 registers per lane: the panels take 140
+// dinv: SM_MAX_CHOL doubles of LDS.  The workgroup's size is a multiple of 64, at least 512.
 template <bool SMALL>
-__global__ void __launch_bounds__(CI_THREADS)
-k_chol_inv(const CholBatch batch, int n) {
-    extern __shared__ double sm[];
-    const CholProblem& prob = batch.p[blockIdx.x];
-    const double* __restrict__ G = prob.G;
-    double* __restrict__ Linv = prob.Linv;
-    int32_t* __restrict__ info = prob.info;
-    int32_t* __restrict__ wellcond_out = prob.wellcond_out;
-    const int32_t* __restrict__ skip_in = prob.skip_in;
-    if (skip_in && *skip_in) return;
+__device__ __forceinline__ void chol_inverse(const double* G, double* Linv, int32_t* info, int32_t* wellcond_out, double* transform, int n,
+                                             double* __restrict__ sm, double* __restrict__ dinv) {
     const int ld = n + 1;
     double* L = sm;                              // column-major: L(i, c) at L[c*ld + i]
     double* X = sm + (size_t)n * ld;             // L^-1, row-major: X(t, c) at X[t*ld + c]
-    __shared__ double dinv[SM_MAX_CHOL];
-    const int tid = threadIdx.x;
-    for (int p = tid >> 4; p < n; p += CI_THREADS >> 4)             // G is symmetric: its row p is column p of L
+    const int tid = threadIdx.x, nthr = blockDim.x;
+    for (int p = tid >> 4; p < n; p += nthr >> 4)             // G is symmetric: its row p is column p of L
         for (int i = tid & 15; i < n; i += 16) {
             L[p * ld + i] = G[(size_t)p * n + i];
             X[p * ld + i] = 0.0;
@@ -267,7 +260,7 @@ k_chol_inv(const CholBatch batch, int n) {
     // the second product wants for its right operand (accumulator element v = contraction chunk v), so it never
     // touches memory.  Rows and columns past n act as an identity.
     {
-        const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = CI_THREADS >> 6;
+        const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = nthr >> 6;
         const int T = (n + 15) / 16;
         const bool whole = (n & 15) == 0;             // no padding: the accessors need no tests
         auto Lat = [&](int i, int c2) { return (whole || (i < n && c2 < n)) ? L[min(c2, n - 1) * ld + min(i, n - 1)] : (i == c2 ? 1.0 : 0.0); };
@@ -324,12 +317,12 @@ k_chol_inv(const CholBatch batch, int n) {
         }
     }
     __syncthreads();
-    for (int i = tid >> 4; i < n; i += CI_THREADS >> 4)
+    for (int i = tid >> 4; i < n; i += nthr >> 4)
         for (int j = tid & 15; j < n; j += 16) Linv[(size_t)i * n + j] = X[i * ld + j];
-    if (prob.transform) {                        // F <- X F X^T, by way of L's place: X F first, row-major
-        double* __restrict__ F = prob.transform;
+    if (transform) {                             // F <- X F X^T, by way of L's place: X F first, row-major
+        double* F = transform;
         constexpr int TW = (((SM_MAX_CHOL + 15) / 16) * ((SM_MAX_CHOL + 15) / 16) + 7) / 8;      // tiles a wave
-        const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = CI_THREADS >> 6;
+        const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = nthr >> 6;
         const int T = (n + 15) / 16, r16 = lane & 15, kq = lane >> 4;
         double4_t acc[TW];
         auto product = [&](auto fb) {
@@ -356,7 +349,7 @@ k_chol_inv(const CholBatch batch, int n) {
             }
         };
         __syncthreads();
-        for (int i = tid >> 4; i < n; i += CI_THREADS >> 4)
+        for (int i = tid >> 4; i < n; i += nthr >> 4)
             for (int j = tid & 15; j < n; j += 16) L[i * ld + j] = F[(size_t)i * n + j];
         __syncthreads();
         product([&](int i, int j, bool left) { return left ? X[i * ld + j] : L[i * ld + j]; });
@@ -366,6 +359,15 @@ k_chol_inv(const CholBatch batch, int n) {
         product([&](int i, int j, bool left) { return left ? L[i * ld + j] : X[j * ld + i]; });
         each([&](int i, int j, double v) { F[(size_t)i * n + j] = v; });
     }
+}
+
+template <bool SMALL>
+__global__ void __launch_bounds__(CI_THREADS)
+k_chol_inv(const CholBatch batch, int n) {
+    extern __shared__ double sm[];
+    __shared__ double dinv[SM_MAX_CHOL];
+    const CholProblem& prob = batch.p[blockIdx.x];
+    chol_inverse<SMALL>(prob.G, prob.Linv, prob.info, prob.wellcond_out, nullptr, n, sm, dinv);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1034,7 +1036,7 @@ __global__ void __launch_bounds__(NE * JGL <= 64 || PRE ? 512 : 8 * NE * JGL)
 k_jacobi_eig(const JacobiBatch batch, int n, int kk) {
     extern __shared__ double sm[];
     const JacobiProblem& prob = batch.p[blockIdx.x];
-    const double* __restrict__ G = prob.G;
+    const double* G = prob.G;                // (repaired in place, below)
     double* __restrict__ lam = prob.lam;
     double* __restrict__ vec = prob.vec;
     double* __restrict__ tmat = prob.tmat;
@@ -1059,8 +1061,23 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk) {
     // the preconditioner works on an odd column stride (and on n columns alone), the sweeps on theirs; only the lower triangle
     // is loaded (G is symmetric: column p of it is the rest of row p), so that L comes out with zeros above its diagonal
     const int ldc = gscr ? n | 1 : ld;
-    for (int p = tid >> 4; p < (gscr ? n : ne + 1); p += nthr >> 4)
-        for (int i = tid & 15; i < ldc; i += 16) W[(size_t)p * ldc + i] = (p < n && i < n && i >= p) ? G[(size_t)p * n + i] : 0.0;
+    auto load = [&]() {
+        for (int p = tid >> 4; p < (gscr ? n : ne + 1); p += nthr >> 4)
+            for (int i = tid & 15; i < ldc; i += 16) W[(size_t)p * ldc + i] = (p < n && i < n && i >= p) ? G[(size_t)p * n + i] : 0.0;
+    };
+    load();
+    // CholeskyQR's second pass, where the first one's factor was not well conditioned: its inverse X, and G <- X G X^T.  (In a
+    // launch of its own before this one it cost 4.5 us with nothing to repair; here the flag arrives with G.)
+    const bool repair = NE * JGL <= 96 && prob.gram && !(prob.wellcond && *prob.wellcond);
+    __shared__ double rinv_sh[SM_MAX_N];
+    if constexpr (NE * JGL <= 96) {
+        if (repair) {
+            __syncthreads();
+            chol_inverse<SMALL>(prob.gram, prob.post, prob.info, nullptr, prob.G, n, sm, rinv_sh);
+            __syncthreads();
+            load();
+        }
+    }
     if (tid <= ne) { colmap[tid] = tid; rotf[tid] = 0; nrm[tid] = 0.0; }
     if (tid == 0) { nact_sh = ne; wcnt[0] = 0; wcnt[1] = 0; }
     __syncthreads();
@@ -1071,7 +1088,6 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk) {
     // sigma_j^2 = lambda_j, u_j the eigenvector of G.  A pivot at rounding level (semi-definite G)
     // zeroes its column.
     {
-        __shared__ double rinv_sh[SM_MAX_N];
         double m = 0.0;                           // every wave finds the largest diagonal entry for itself
         for (int j = lane; j < n; j += 64) m = fmax(m, W[(size_t)j * ldc + j]);
         chol_blocked<true, SMALL>(W, ldc, n, rinv_sh, wave_max(m) * 1e-30, nullptr);
@@ -1302,8 +1318,8 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk) {
                 if (tmat && j < kk) tmat[(size_t)i * kk + j] = v * rl[q];
             }
         // G stood for X F X^T, X lower triangular: what multiplies F's basis is X^T tmat
-        const double* __restrict__ X = prob.post;
-        if (X && !(prob.post_skip && *prob.post_skip)) {
+        const double* X = prob.post;
+        if (repair) {
             for (int i = tid >> 4; i < n; i += nthr >> 4)
 #pragma unroll
                 for (int q = 0; q < NJ; ++q) {
@@ -1359,7 +1375,9 @@ int launch_jacobi_eig_batch(hipStream_t s, const JacobiProblem* probs, int count
     // bookkeeping and the preconditioner use them); no idle waves beyond that: every wave of the workgroup takes part in every
     // barrier.  After the preconditioner few columns still move, and 512 threads leave its phases 256 registers.
     const int jgl = pre ? PRE_JGL : JGL_PLAIN;
-    const size_t lds = pre ? lds_pre : region(jgl) * sizeof(double) + small;
+    size_t lds = pre ? lds_pre : region(jgl) * sizeof(double) + small;
+    for (int i = 0; i < count; ++i)
+        if (probs[i].gram) lds = std::max(lds, 2 * (size_t)n * (n + 1) * sizeof(double));      // (n <= SM_MAX_CHOL)
     const int need = (ne / 2 * jgl + 63) / 64 * 64;               // at most 128 ceil(n / 16): the kernel's launch bound
     const int threads = need > 512 ? need : 512;
     for (int b0 = 0; b0 < count; b0 += SM_MAX_BATCH) {
