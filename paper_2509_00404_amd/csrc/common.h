@@ -131,7 +131,7 @@ __device__ __forceinline__ Call batch_call(const CallBatch<Call>& b, uint32_t& l
 }
 // n calls of one kernel instance, call.wgs workgroups each, in as few launches as hold them: launch(batch, workgroups)
 template <typename Call, typename F>
-static inline int launch_calls(const Call* calls, size_t n, F launch) {
+[[nodiscard]] static inline int launch_calls(const Call* calls, size_t n, F launch) {
     CallBatch<Call> b;
     b.n = 0;
     b.off[0] = 0;

@@ -328,7 +328,7 @@ struct DgemmList {
     void add(DOperand A, DOperand B, int64_t M, int64_t N, int64_t K, int ksplit, DEpilogue ep) {
         items.push_back({A, B, M, N, K, ksplit, ep});
     }
-    int launch(hipStream_t s) {
+    [[nodiscard]] int launch(hipStream_t s) {
         std::vector<DgemmCall> calls;
         for (const Item& it : items) {
             if (dgemm_is_big(it.M, it.N, it.K)) {
@@ -425,7 +425,7 @@ struct SumList {
         const int wide = nparts <= 24 || n >= ((int64_t)1 << 18);
         items.push_back({parts, out, n, stride, nparts, wide, (uint32_t)ceil_div64(n, wide ? SUM_WIDE : SUM_EB), skip});
     }
-    int launch(hipStream_t s) {
+    [[nodiscard]] int launch(hipStream_t s) {
         const std::vector<SumCall> calls = std::move(items);
         items.clear();
         return launch_calls(calls.data(), calls.size(), [&](const CallBatch<SumCall>& b, uint32_t wgs) {

@@ -157,6 +157,7 @@ int run(hipStream_t s, const TW* dW, int64_t ld, int64_t N, int64_t K, int k, co
     float* UdS = (float*)(ws + L.off_uds);
     double* parts = (double*)(ws + L.off_parts);
     SumList sums;
+    int st;
     const int64_t tk = ceil_div64(k, 32);
     // A dW of aligned rows takes the decomposition's skinny kernels (same shapes as its sketch and projection): fp32 4096 x 4096
     // at rank 64, the two products 262 us on the generic kernel, 120 us there; the whole call in 7 launches instead of 14
@@ -169,14 +170,13 @@ int run(hipStream_t s, const TW* dW, int64_t ld, int64_t N, int64_t K, int k, co
         hipLaunchKernelGGL(k_fg_prepare, dim3((unsigned)ceil_div64((N + K) * k, 256)), dim3(256), 0, s, W->Vt.codes, W->Vt.scales,
                            W->Vt.tscale, K, W->Ut.codes, W->Ut.scales, W->Ut.tscale, N, k, W->S, Vbf, H64, Ud);
         METIS_LAUNCH_CHECK();
-        int st;
         // T = dW Vbar                  [N,k], contraction over K
         if ((st = launch_sketch<TW>(s, {sketch_call(dW, ld, nullptr, N, K, Vbf, k, parts)})) != METIS_OK) return st;
         sums.add(parts, sketch_parts(N, K, k), N * (int64_t)k, N * (int64_t)k, T);
         // dV^T = (Ubar S)^T dW         [k,K], contraction over N
         if ((st = launch_project<TW>(s, {project_call(H64, k, dW, ld, nullptr, N, K, parts2)})) != METIS_OK) return st;
         sums.add(parts2, project_parts(N, K, k), K * (int64_t)k, K * (int64_t)k, dV64);
-        sums.launch(s);
+        if ((st = sums.launch(s)) != METIS_OK) return st;
     } else {
         hipLaunchKernelGGL(k_dequant_factor, dim3((unsigned)ceil_div64((int64_t)k * K, 256)), dim3(256), 0, s, W->Vt.codes,
                            W->Vt.scales, k, K, W->Vt.tscale, (const float*)nullptr, Vd);
@@ -189,12 +189,12 @@ int run(hipStream_t s, const TW* dW, int64_t ld, int64_t N, int64_t K, int k, co
         int want = splits_for(K, ceil_div64(N, 32) * tk);
         launch_dgemm<TW, float, EPI_PART_F64>(s, opnd(dW, ld, 1), opnd(Vd, K, 1), N, k, K, want, epi_part(parts, N, k));
         sums.add(parts, dgemm_parts<EPI_PART_F64>(N, k, K, want), N * (int64_t)k, N * (int64_t)k, T);
-        sums.launch(s);
+        if ((st = sums.launch(s)) != METIS_OK) return st;
         // dV = dW^T (Ubar S)           [K,k], contraction over N
         want = splits_for(N, ceil_div64(K, 32) * tk);
         launch_dgemm<TW, float, EPI_PART_F64>(s, opnd(dW, 1, ld), opnd(UdS, N, 1), K, k, N, want, epi_part(parts, K, k));
         sums.add(parts, dgemm_parts<EPI_PART_F64>(K, k, N, want), K * (int64_t)k, K * (int64_t)k, dV64);
-        sums.launch(s);
+        if ((st = sums.launch(s)) != METIS_OK) return st;
     }
     METIS_LAUNCH_CHECK();
     // dS = Ubar^T T                    [k,k], contraction over N
@@ -203,7 +203,7 @@ int run(hipStream_t s, const TW* dW, int64_t ld, int64_t N, int64_t K, int k, co
         launch_dgemm<float, double, EPI_PART_F64>(s, fast ? opnd(Ud, 1, k) : opnd(Ud, N, 1), opnd(T, 1, k), k, k, N, want,
                                                   epi_part(parts, k, k));
         sums.add(parts, dgemm_parts<EPI_PART_F64>(k, k, N, want), (int64_t)k * k, (int64_t)k * k, dS64);
-        sums.launch(s);
+        if ((st = sums.launch(s)) != METIS_OK) return st;
     }
     METIS_LAUNCH_CHECK();
     if (fast) {
