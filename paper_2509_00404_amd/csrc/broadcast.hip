@@ -41,10 +41,10 @@ __global__ void __launch_bounds__(64 * BC_WAVES)
 k_broadcast(const CallBatch<BroadcastCall> batch) {
     uint32_t local;
     const BroadcastCall call = batch_call(batch, local);
-    const bf16_t* __restrict__ A = call.A;
-    const bf16_t* __restrict__ V0hi = call.V0hi;
-    const bf16_t* __restrict__ V0lo = call.V0lo;
-    uint32_t* __restrict__ amax_bits = call.amax_bits;
+    const bf16_t* __restrict__ A = in_global(call.A);
+    const bf16_t* __restrict__ V0hi = in_global(call.V0hi);
+    const bf16_t* __restrict__ V0lo = in_global(call.V0lo);
+    uint32_t* __restrict__ amax_bits = in_global(call.amax_bits);
     const int64_t lda = call.lda, M = call.M, N = call.N;
     const int k = call.k;
     const uint32_t ranges = call.wgs / call.row_blocks, range = local / call.row_blocks;
@@ -187,7 +187,7 @@ k_broadcast(const CallBatch<BroadcastCall> batch) {
     }
     // D layout 32x32: lane l, element v -> row 8*(v/4) + 4*(l/32) + v%4, column l%32.
     // Each contraction split writes its own partial C (plain stores); the consumers add the parts.
-    float* __restrict__ P = call.Cpart + (size_t)range * (size_t)M * k;
+    float* __restrict__ P = in_global(call.Cpart) + (size_t)range * (size_t)M * k;
 #pragma unroll
     for (int t = 0; t < KT; ++t) {
         int c = 32 * t + li;

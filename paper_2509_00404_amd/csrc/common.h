@@ -103,7 +103,7 @@ struct CallBatch {
     Call c[MAX_CALLS];
 };
 // The call that a workgroup belongs to, and its number there.  The first call's words are fetched together with the offsets, and the
-// empty asm keeps them so (the compiler would choose between the calls' addresses first, and a lone call would wait for one trip to the
+// empty asm, which changes nothing and writes no memory, keeps them so (the compiler would choose between the calls' addresses first, and a lone call would wait for one trip to the
 // arguments after the other, 0.5 us a launch).
 template <typename Call>
 __device__ __forceinline__ Call batch_call(const CallBatch<Call>& b, uint32_t& local) {
@@ -115,7 +115,7 @@ __device__ __forceinline__ Call batch_call(const CallBatch<Call>& b, uint32_t& l
     for (int i = 0; i < W; ++i) w[i] = first[i];
     const uint32_t end = b.off[1];
 #pragma unroll
-    for (int i = 0; i < W; ++i) asm volatile("" : "+s"(w[i]));
+    for (int i = 0; i < W; ++i) asm("" : "+s"(w[i]));
     local = blockIdx.x;
     if (local >= end) {
         int c = 1;
@@ -129,6 +129,11 @@ __device__ __forceinline__ Call batch_call(const CallBatch<Call>& b, uint32_t& l
     __builtin_memcpy(&call, w, sizeof(Call));
     return call;
 }
+// A pointer that came through batch_call is global memory's again: put together from words, it would be reached by flat instructions,
+// which count as LDS accesses too, so that every wait for LDS and every counted wait for loads became one for everything in flight
+// (k_broadcast of a lone 14336 x 4096 41.4 us, so 39.6, with arguments of its own 38.2; of 4096 x 4096 23.8, 22.8, 22.3).
+template <typename T>
+__device__ __forceinline__ T* in_global(T* p) { return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p; }
 // n calls of one kernel instance, call.wgs workgroups each, in as few launches as hold them: launch(batch, workgroups)
 template <typename Call, typename F>
 [[nodiscard]] static inline int launch_calls(const Call* calls, size_t n, F launch) {

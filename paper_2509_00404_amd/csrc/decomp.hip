@@ -127,7 +127,12 @@ struct SetupCall {
 __global__ void __launch_bounds__(256)
 k_decomp_setup(const CallBatch<SetupCall> batch) {
     uint32_t local;
-    const SetupCall call = batch_call(batch, local);
+    SetupCall call = batch_call(batch, local);
+    call.zero = in_global(call.zero);
+    call.amax_out = in_global(call.amax_out);
+    call.info = in_global(call.info);
+    call.idx = in_global(call.idx);
+    call.omega = in_global(call.omega);
     const int b = (int)local, zero_blocks = call.zero_blocks, idx_blocks = call.idx_blocks;
     if (b < zero_blocks) {
         size_t i = (size_t)b * 256 + threadIdx.x;

@@ -33,6 +33,20 @@ struct DEpilogue {
     int64_t part_stride;         // PART_F64: elements between the partial products of consecutive chunks
 };
 
+__device__ __forceinline__ DOperand in_global(DOperand o) {
+    o.p = in_global(o.p);
+    o.map_outer = in_global(o.map_outer);
+    o.map_k = in_global(o.map_k);
+    return o;
+}
+__device__ __forceinline__ DEpilogue in_global(DEpilogue e) {
+    e.c = in_global(e.c);
+    e.hi_t = in_global(e.hi_t);
+    e.lo_t = in_global(e.lo_t);
+    e.skip = in_global(e.skip);
+    return e;
+}
+
 template <typename T> __device__ __forceinline__ double dload(const void* p, int64_t off);
 template <> __device__ __forceinline__ double dload<bf16_t>(const void* p, int64_t off) {
     return (double)bf16_to_f32(((const bf16_t*)p)[off]);
@@ -165,7 +179,10 @@ template <typename TA, typename TB, int EPI>
 __global__ void __launch_bounds__(256)
 k_dgemm_batch(const CallBatch<DgemmCall> b) {
     uint32_t local;
-    const DgemmCall call = batch_call(b, local);
+    DgemmCall call = batch_call(b, local);
+    call.A = in_global(call.A);
+    call.B = in_global(call.B);
+    call.ep = in_global(call.ep);
     const uint32_t bx = local % call.gx, by = (local / call.gx) % call.gy, bz = local / (call.gx * call.gy);
     dgemm_tile<TA, TB, EPI>(call.A, call.B, call.M, call.N, call.K, call.kchunk, call.ep, bx, by, bz);
 }
@@ -371,7 +388,10 @@ static __global__ void __launch_bounds__(256)
 k_sum_parts_batch(const CallBatch<SumCall> b) {
     __shared__ double red[SUM_PG][SUM_EB];
     uint32_t local;
-    const SumCall call = batch_call(b, local);
+    SumCall call = batch_call(b, local);
+    call.parts = in_global(call.parts);
+    call.out = in_global(call.out);
+    call.skip = in_global(call.skip);
     if (call.skip && *call.skip) return;
     if (call.wide) {
         const int64_t i = ((int64_t)local * 256 + threadIdx.x) * 2;

@@ -75,9 +75,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Skinny
 k_sketch(const CallBatch<SketchCall<TA>> batch) {
     uint32_t local;
     const SketchCall<TA> call = batch_call(batch, local);
-    const TA* __restrict__ A = call.A;
-    const uint32_t* __restrict__ rowmap = call.rowmap;
-    const bf16_t* __restrict__ Om = call.Om;
+    const TA* __restrict__ A = in_global(call.A);
+    const uint32_t* __restrict__ rowmap = in_global(call.rowmap);
+    const bf16_t* __restrict__ Om = in_global(call.Om);
     const int64_t lda = call.lda, Ms = call.Ms, K = call.K, kchunk = call.kchunk;
     const int r = call.r;
     const uint32_t chunk = local / call.tiles;
@@ -89,7 +89,7 @@ k_sketch(const CallBatch<SketchCall<TA>> batch) {
     const int64_t m0 = (int64_t)(local - chunk * call.tiles) * SK_ROWS;
     const int64_t kbeg = (int64_t)chunk * kchunk;
     const int64_t kend = kbeg + kchunk < K ? kbeg + kchunk : K;
-    double* __restrict__ Z = call.Z + (int64_t)chunk * Ms * r;
+    double* __restrict__ Z = in_global(call.Z) + (int64_t)chunk * Ms * r;
     if (kbeg >= kend) return;
 
     // the pad columns r .. 16 NT of the Omega stage, if there are any, stay zero
@@ -243,9 +243,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(Skinny
 k_project(const CallBatch<ProjectCall<TA>> batch) {
     uint32_t local;
     const ProjectCall<TA> call = batch_call(batch, local);
-    const double* __restrict__ H = call.H;
-    const TA* __restrict__ A = call.A;
-    const uint32_t* __restrict__ rowmap = call.rowmap;
+    const double* __restrict__ H = in_global(call.H);
+    const TA* __restrict__ A = in_global(call.A);
+    const uint32_t* __restrict__ rowmap = in_global(call.rowmap);
     const int64_t lda = call.lda, Ms = call.Ms, N = call.N, kchunk = call.kchunk;
     const int r = call.r;
     const uint32_t chunk = local / call.tiles;
@@ -258,7 +258,7 @@ k_project(const CallBatch<ProjectCall<TA>> batch) {
     const int64_t n0 = (int64_t)(local - chunk * call.tiles) * PJ_COLS;
     const int64_t kbeg = (int64_t)chunk * kchunk;
     const int64_t kend = kbeg + kchunk < Ms ? kbeg + kchunk : Ms;
-    double* __restrict__ B = call.B + (int64_t)chunk * r * N;
+    double* __restrict__ B = in_global(call.B) + (int64_t)chunk * r * N;
     if (kbeg >= kend) return;
 
     if (r < 16 * NT) {                                                 // pad columns r .. 16 NT stay zero
@@ -519,8 +519,8 @@ __global__ void __launch_bounds__(256)
 k_gram_parts(const CallBatch<GramCall> batch) {
     uint32_t local;
     const GramCall call = batch_call(batch, local);
-    const float* C = call.C;
-    float* sum_out = call.sum_out;
+    const float* C = in_global(call.C);
+    float* sum_out = in_global(call.sum_out);
     const int r = call.r, rows = call.rows, nparts = call.nparts;
     const int64_t M = call.M, part_stride = call.part_stride;
     constexpr int LDC = NT * 16 + ((NT * 16) % 32 == 16 ? 0 : 16);      // doubles, = 16 (mod 32)
@@ -529,7 +529,7 @@ k_gram_parts(const CallBatch<GramCall> batch) {
     __shared__ double Cs[GR_KS * LDC];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t m0 = (int64_t)local * rows;
-    double* __restrict__ G = call.G + (int64_t)local * r * r;
+    double* __restrict__ G = in_global(call.G) + (int64_t)local * r * r;
     const int rc = r >> 2;
     for (int e = tid; e < GR_KS * LDC; e += 256) Cs[e] = 0.0;           // pad columns r .. 16 NT stay zero
     double4_t acc[RT][NT];
