@@ -103,8 +103,8 @@ struct CallBatch {
     Call c[MAX_CALLS];
 };
 // The call that a workgroup belongs to, and its number there.  The first call's words are fetched together with the offsets, and the
-// empty asm, which changes nothing and writes no memory, keeps them so (the compiler would choose between the calls' addresses first, and a lone call would wait for one trip to the
-// arguments after the other, 0.5 us a launch).
+// empty asm, which changes nothing and writes no memory, keeps them so (the compiler would choose between the calls' addresses first,
+// and a lone call would wait for one trip to the arguments after the other, 0.5 us a launch).
 template <typename Call>
 __device__ __forceinline__ Call batch_call(const CallBatch<Call>& b, uint32_t& local) {
     constexpr int W = sizeof(Call) / 4;

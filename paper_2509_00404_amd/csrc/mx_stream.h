@@ -193,7 +193,7 @@ k_mxfp4_gemm_nt_stream(MxOperand A, MxOperand B, int64_t K, OUT* __restrict__ C,
         int m0, n0;
         tile_of(pos, m0, n0);
         mx_store_wave<OUT, LINES, 4, 2>(acc, lds + bl + wave * mx_wave_rows<OUT, 2>(), C, ldc, m0 + 128 * wa, n0 + 64 * wb, A.rows, B.rows,
-                                        vec, vec && m0 + 256 <= A.rows && n0 + 256 <= B.rows, gs_fresh_lane());
+                                        vec, mx_whole<LINES>(m0 + 256 <= A.rows && n0 + 256 <= B.rows, vec), gs_fresh_lane());
         pos += (int)gridDim.x;
         if (pos >= total) break;
         // every wave has its rows out of the buffer before any transfers into it
