@@ -156,3 +156,23 @@ def test_mxfp4_gemm_streamed(metis, M, N, K, ld_extra, out_dtype):
         for j in range(0, N, 256):
             assert rel_fro(got[i:i + 256, j:j + 256], ref[i:i + 256, j:j + 256]) < (1e-5 if out_dtype == torch.float32 else 4e-3), (i, j)
     assert bool(torch.isnan(full[:, N:]).all())
+
+
+# three and more tiles a workgroup (256 of them), two units a tile, three and five: the staging buffers change hands several times, an odd
+# number of units swaps them from tile to tile; the last one walks its tiles in bands (1536 tiles and more, a contraction beyond 1024)
+@pytest.mark.parametrize("M,N,K", [(5900, 6100, 512), (5900, 6100, 768), (10200, 9800, 1280)])
+@pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16])
+def test_mxfp4_gemm_streamed_over_many_tiles(metis, M, N, K, out_dtype):
+    """The bars of test_mxfp4_gemm_against_oracle for every 256 x 256 block, against the fp64 product of the oracle's dequantized operands."""
+    a, b = _data(M, K, 11, torch.bfloat16), _data(N, K, 12, torch.bfloat16)
+    qa, qb = metis.MxTensor(M, K), metis.MxTensor(N, K)
+    metis.quantize_mx(a.cuda(), qa)
+    metis.quantize_mx(b.cuda(), qb)
+    C = torch.full((M, N), float("nan"), dtype=out_dtype, device="cuda")
+    metis.mxfp4_gemm_nt(qa, qb, C)
+    fa, fb = (torch.from_numpy(omx.dequantize_mx(q.codes.cpu().numpy(), q.scales.cpu().numpy())).cuda() for q in (qa, qb))
+    ref = fa @ fb.T
+    err = C.double() - ref
+    tiles = lambda x: torch.nn.functional.pad(x, (0, -N % 256, 0, -M % 256)).unflatten(1, (-1, 256)).unflatten(0, (-1, 256)).pow(2).sum((1, 3))
+    worst = (tiles(err) / tiles(ref)).sqrt().max()
+    assert float(worst) < (1e-5 if out_dtype == torch.float32 else 4e-3)
