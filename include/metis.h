@@ -391,7 +391,8 @@ int metis_mxfp4_gemm_nt(void* stream, const metis_mxfp4* A, const metis_mxfp4* B
  * Bracket every launch of one hot kernel with caller-owned HIP events (hipEvent_t passed as
  * void*), recorded on the stream the kernel is launched on: launch i uses start[i % n] and
  * stop[i % n].  kernel_id: 0 main FP4 GEMM kernel of the three linear calls (the kernel that
- * writes Y / dX / dW), 1 broadcast C = A V0, 2 fused residual + quantize, 3 plain row
+ * writes Y / dX / dW), 1 broadcast C = A V0 (a launch serves all jobs of a batch whose ranks
+ * round up to the same multiple of 32), 2 fused residual + quantize, 3 plain row
  * quantizer.  n = 0 switches it off.  The arrays (host memory) must stay valid while set.
  * Host-side state, not thread-safe; for benchmarks only.
  */

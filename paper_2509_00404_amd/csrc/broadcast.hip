@@ -242,12 +242,14 @@ int launch_broadcast(hipStream_t s, const std::vector<BroadcastCall>& calls) {
             if ((c.k + 31) / 32 == kt) g.push_back(c);
         const int st = launch_calls(g.data(), g.size(), [&](const CallBatch<BroadcastCall>& b, uint32_t wgs) {
             const dim3 grid(wgs), block(64 * BC_WAVES);
+            const int pi = metis_prof_begin(METIS_PROF_BROADCAST, s);
             switch (kt) {
                 case 1: hipLaunchKernelGGL(k_broadcast<1>, grid, block, 0, s, b); break;
                 case 2: hipLaunchKernelGGL(k_broadcast<2>, grid, block, 0, s, b); break;
                 case 3: hipLaunchKernelGGL(k_broadcast<3>, grid, block, 0, s, b); break;
                 default: hipLaunchKernelGGL(k_broadcast<4>, grid, block, 0, s, b); break;
             }
+            metis_prof_end(METIS_PROF_BROADCAST, pi, s);
         });
         if (st != METIS_OK) return st;
     }

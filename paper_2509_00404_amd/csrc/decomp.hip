@@ -448,9 +448,7 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
                 const int64_t rows = j.M - r0 < F.band_rows ? j.M - r0 : F.band_rows;
                 const int parts = broadcast_splits(rows, j.N);
                 const bf16_t* Ab = j.A + r0 * j.lda;
-                const int pi = metis_prof_begin(METIS_PROF_BROADCAST, s);
                 st = launch_broadcast(s, {broadcast_call(Ab, j.lda, rows, j.N, j.V0hi, j.V0lo, k, band, (uint32_t*)j.amax_out)});
-                metis_prof_end(METIS_PROF_BROADCAST, pi, s);
                 if (st != METIS_OK) return st;
                 if ((st = launch_band_factors(s, band, parts, rows * (int64_t)k, rows, k, F.kp, j.C + r0 * k,
                                               us_hi + r0 * F.kp, us_lo + r0 * F.kp)) != METIS_OK)
@@ -466,12 +464,7 @@ extern "C" int metis_decompose_batch(void* stream, int n_jobs, const metis_decom
             broadcasts.push_back(broadcast_call(j.A, j.lda, j.M, j.N, j.V0hi, j.V0lo, k, j.C, (uint32_t*)j.amax_out));
         }
     }
-    if (!broadcasts.empty()) {
-        const int pi = metis_prof_begin(METIS_PROF_BROADCAST, s);
-        st = launch_broadcast(s, broadcasts);
-        metis_prof_end(METIS_PROF_BROADCAST, pi, s);
-        if (st != METIS_OK) return st;
-    }
+    if ((st = launch_broadcast(s, broadcasts)) != METIS_OK) return st;
     std::vector<GramCall> grams;
     for (const Job& j : jobs) {
         const int k = j.k;

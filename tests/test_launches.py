@@ -1,7 +1,9 @@
-"""Every kernel launch that fails is reported by the call that made it (no GPU needed).
+"""What the library asks of the HIP runtime, without a GPU: every kernel launch that fails is reported by the call that made it, and every
+launch of a profiled kernel has a pair of events of its own.
 
-The library is loaded in a process of its own behind a stand-in for the HIP runtime's entry points that launches nothing, counts the
-launches and lets one of them fail: a status that is taken and dropped on the way shows as METIS_OK."""
+The library is loaded in a process of its own behind a stand-in for the runtime's entry points that launches nothing, counts the launches,
+lets one of them fail (a status that is taken and dropped on the way shows as METIS_OK) and notes between which launches an event was
+recorded."""
 import ctypes as C
 import os
 import shutil
@@ -29,7 +31,15 @@ int hipGetLastError(void) { int e = error; error = 0; return e; }
 int hipGetDevice(int* d) { *d = 0; return 0; }
 int hipDeviceGetAttribute(int* v, int a, int d) { *v = 256; return 0; }
 int hipFuncSetAttribute(const void* f, int a, int v) { return 0; }
-int hipEventRecord(void* e, void* s) { return 0; }
+static int records, event_at[64], event_id[64];
+int hipEventRecord(void* e, void* s) {
+    if (records < 64) { event_at[records] = launches; event_id[records] = (int)(size_t)e; }
+    ++records;
+    return 0;
+}
+int record_count(void) { return records; }
+int recorded_at(int i) { return event_at[i]; }
+int recorded_event(int i) { return event_id[i]; }
 """
 
 FAKE = 1 << 30                                   # an aligned address that is never read
@@ -80,10 +90,7 @@ def _calls(metis):
     }
 
 
-def _child(runtime):
-    stub = C.CDLL(runtime, mode=C.RTLD_GLOBAL)
-    sys.path.insert(0, ROOT)
-    from paper_2509_00404_amd import metis
+def _failed_launches(stub, metis):
     for name, call in _calls(metis).items():
         stub.fail_at(0)
         assert call() == 0, name
@@ -96,16 +103,38 @@ def _child(runtime):
         print(name, n)
 
 
-def test_a_failed_launch_is_reported(tmp_path):
+def _brackets(stub, metis):
+    n = 16
+    start, stop = (C.c_void_p * n)(*range(101, 101 + n)), (C.c_void_p * n)(*range(201, 201 + n))
+    for name, launches in (("decomposition", 1), ("decompositions of several orders", 2)):
+        assert metis.lib().metis_profile_events(metis.PROF_BROADCAST, start, stop, n) == 0
+        first = stub.record_count()
+        stub.fail_at(0)
+        assert _calls(metis)[name]() == 0
+        pairs = [(stub.recorded_event(i), stub.recorded_at(i), stub.recorded_event(i + 1), stub.recorded_at(i + 1))
+                 for i in range(first, stub.record_count(), 2)]
+        assert [(a, c) for a, _, c, _ in pairs] == [(101 + i, 201 + i) for i in range(launches)], (name, pairs)
+        assert all(after == before + 1 for _, before, _, after in pairs), (name, pairs)
+
+
+def _child(check, runtime):
+    stub = C.CDLL(runtime, mode=C.RTLD_GLOBAL)
+    sys.path.insert(0, ROOT)
+    from paper_2509_00404_amd import metis
+    {"failed_launches": _failed_launches, "brackets": _brackets}[check](stub, metis)
+
+
+@pytest.mark.parametrize("check", ["failed_launches", "brackets"])
+def test_behind_a_stand_in_for_the_runtime(tmp_path, check):
     from paper_2509_00404_amd import metis
     if not os.path.exists(metis.LIB_PATH) or not shutil.which("gcc"):
         pytest.skip("library not built, or no C compiler")
     src, runtime = tmp_path / "runtime.c", tmp_path / "runtime.so"
     src.write_text(RUNTIME)
     subprocess.run(["gcc", "-shared", "-fPIC", "-o", str(runtime), str(src)], check=True)
-    r = subprocess.run([sys.executable, os.path.abspath(__file__), str(runtime)], capture_output=True, text=True, timeout=300)
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), check, str(runtime)], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stdout + r.stderr
 
 
 if __name__ == "__main__":
-    _child(sys.argv[1])
+    _child(*sys.argv[1:])
