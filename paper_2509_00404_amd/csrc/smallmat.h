@@ -24,7 +24,8 @@ struct JacobiProblem {
     double* gscr;             // optional jacobi_scratch_doubles(n) doubles of device scratch; when given (and the order
                               // allows it) the sweeps start from columns preconditioned with approximate eigenvectors
     // CholeskyQR's second pass, unless *wellcond is set: gram = Gram matrix of the first pass's basis (n x n, null: no second pass),
-    // post = the inverse X of its Cholesky factor (out), G becomes X G X^T and tmat X^T tmat
+    // post = the inverse X of its Cholesky factor (out), G becomes X G X^T (its 16 x 16 tiles on and
+    // right of the diagonal) and tmat X^T tmat
     const double* gram;
     double* post;
     const int32_t* wellcond;  // optional

@@ -219,10 +219,17 @@ __device__ __forceinline__ double4_t tile_mma(int n, int ia, int jb, int kq, FA 
         }
         return acc;
     }
-    for (int k0 = kbeg; k0 < kend; k0 += 4) {
-        const int k = k0 + kq, kc = min(k, n - 1);
-        const double a = fa(ic, kc), b = fb(kc, jc);
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64((iok && k < kend) ? a : 0.0, (jok && k < kend) ? b : 0.0, acc, 0, 0, 0);
+    for (int k0 = kbeg; k0 < kend; k0 += 16) {    // (a step at a time, its loads awaited, CHFIG)
+        double a[4], b[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = k0 + 4 * u + kq, kc = min(k, n - 1);
+            const double x = fa(ic, kc), y = fb(kc, jc);
+            a[u] = iok && k < kend ? x : 0.0;
+            b[u] = jok && k < kend ? y : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[u], acc, 0, 0, 0);
     }
     return acc;
 }
@@ -319,28 +326,32 @@ __device__ __forceinline__ void chol_inverse(const double* G, double* Linv, int3
     __syncthreads();
     for (int i = tid >> 4; i < n; i += nthr >> 4)
         for (int j = tid & 15; j < n; j += 16) Linv[(size_t)i * n + j] = X[i * ld + j];
-    if (transform) {                             // F <- X F X^T, by way of L's place: X F first, row-major
+    // F <- X F X^T, by way of L's place: X F first, row-major.  X is lower triangular: neither sum goes past its diagonal; F is
+    // symmetric, and only its tiles on and right of the diagonal are written.
+    if (transform) {
         double* F = transform;
         constexpr int TW = (((SM_MAX_CHOL + 15) / 16) * ((SM_MAX_CHOL + 15) / 16) + 7) / 8;      // tiles a wave
         const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = nthr >> 6;
         const int T = (n + 15) / 16, r16 = lane & 15, kq = lane >> 4;
         double4_t acc[TW];
-        auto product = [&](auto fb) {
+        auto product = [&](bool second, auto fb) {
 #pragma unroll
             for (int t = 0; t < TW; ++t) {
                 const int tile = wave + t * nwaves;
                 if (tile >= T * T) continue;     // (uniform)
                 const int ti = tile / T, tj = tile - ti * T;
+                if (second && tj < ti) continue;
                 acc[t] = tile_mma(n, 16 * ti + r16, 16 * tj + r16, kq, [&](int i, int k) { return fb(i, k, true); },
-                                  [&](int k, int j) { return fb(k, j, false); }, 0, n);
+                                  [&](int k, int j) { return fb(k, j, false); }, 0, min(16 * (second ? tj : ti) + 16, n));
             }
         };
-        auto each = [&](auto put) {
+        auto each = [&](bool second, auto put) {
 #pragma unroll
             for (int t = 0; t < TW; ++t) {
                 const int tile = wave + t * nwaves;
                 if (tile >= T * T) continue;
                 const int ti = tile / T, tj = tile - ti * T;
+                if (second && tj < ti) continue;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int i = 16 * ti + 4 * v + kq, j = 16 * tj + r16;
@@ -352,12 +363,12 @@ __device__ __forceinline__ void chol_inverse(const double* G, double* Linv, int3
         for (int i = tid >> 4; i < n; i += nthr >> 4)
             for (int j = tid & 15; j < n; j += 16) L[i * ld + j] = F[(size_t)i * n + j];
         __syncthreads();
-        product([&](int i, int j, bool left) { return left ? X[i * ld + j] : L[i * ld + j]; });
+        product(false, [&](int i, int j, bool left) { return left ? X[i * ld + j] : L[i * ld + j]; });
         __syncthreads();
-        each([&](int i, int j, double v) { L[i * ld + j] = v; });
+        each(false, [&](int i, int j, double v) { L[i * ld + j] = v; });
         __syncthreads();
-        product([&](int i, int j, bool left) { return left ? L[i * ld + j] : X[j * ld + i]; });
-        each([&](int i, int j, double v) { F[(size_t)i * n + j] = v; });
+        product(true, [&](int i, int j, bool left) { return left ? L[i * ld + j] : X[j * ld + i]; });
+        each(true, [&](int i, int j, double v) { F[(size_t)i * n + j] = v; });
     }
 }
 
@@ -1030,8 +1041,10 @@ __device__ __forceinline__ bool eig_precondition(double* __restrict__ R1, double
 // to all the others, and rotations among the others keep it so; it leaves the tournament, and
 // the later sweeps run over the columns that still move.
 // SMALL: n <= 4 (see chol_blocked).
-// PRE: the preconditioner runs, for orders of PRE 16-row tiles.
-template <int NE, int JGL, bool SMALL = false, int PRE = 0>
+// PRE: the preconditioner runs, for orders of PRE 16-row tiles.  REPAIR: the problems bring CholeskyQR's second pass (JacobiProblem::gram);
+// instances of their own, for the code that never runs costs registers and its place all the same (16 columns 21.7 us with it, 21.2
+// without; 32 51.4, 50.1; the second eigenproblem of 4096 x 1024 x 4096 in training 203, 194).
+template <int NE, int JGL, bool REPAIR, bool SMALL = false, int PRE = 0>
 __global__ void __launch_bounds__(NE * JGL <= 64 || PRE ? 512 : 8 * NE * JGL)
 k_jacobi_eig(const JacobiBatch batch, int n, int kk) {
     extern __shared__ double sm[];
@@ -1068,9 +1081,9 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk) {
     load();
     // CholeskyQR's second pass, where the first one's factor was not well conditioned: its inverse X, and G <- X G X^T.  (In a
     // launch of its own before this one it cost 4.5 us with nothing to repair; here the flag arrives with G.)
-    const bool repair = NE * JGL <= 96 && prob.gram && !(prob.wellcond && *prob.wellcond);
+    const bool repair = REPAIR && prob.gram && !(prob.wellcond && *prob.wellcond);
     __shared__ double rinv_sh[SM_MAX_N];
-    if constexpr (NE * JGL <= 96) {
+    if constexpr (REPAIR) {
         if (repair) {
             __syncthreads();
             chol_inverse<SMALL>(prob.gram, prob.post, prob.info, nullptr, prob.G, n, sm, rinv_sh);
@@ -1315,21 +1328,27 @@ k_jacobi_eig(const JacobiBatch batch, int n, int kk) {
                 if (j >= n) continue;
                 const double v = zero[q] ? (i == j ? 1.0 : 0.0) : W[(size_t)pp[q] * ld + i] * rl[q];
                 if (vec) vec[(size_t)i * n + j] = v;
-                if (tmat && j < kk) tmat[(size_t)i * kk + j] = v * rl[q];
+                if (tmat && j < kk && !repair) tmat[(size_t)i * kk + j] = v * rl[q];
             }
-        // G stood for X F X^T, X lower triangular: what multiplies F's basis is X^T tmat
-        const double* X = prob.post;
+    }
+    // G stood for X F X^T, X lower triangular: what multiplies F's basis is X^T tmat.  (On the matrix cores: as sums of a thread each over X in
+    // global memory it was most of the repair.  The batch of a layer's 21 operands, gradients repaired, order 80: 307 -> 226 us.)
+    if constexpr (REPAIR) {
         if (repair) {
-            for (int i = tid >> 4; i < n; i += nthr >> 4)
+            const double* X = prob.post;
+            const int T16 = (n + 15) / 16, TK = (kk + 15) / 16, r16 = lane & 15, kq = lane >> 4;
+            for (int tile = wave; tile < T16 * TK; tile += nthr >> 6) {        // (uniform)
+                const int tj = tile / T16, ti = tile - tj * T16, j = 16 * tj + r16, p = order[min(j, n - 1)];
+                const double* w = W + (size_t)p * ld;
+                const double l = nrm[p], rl = l > 0.0 ? rcp_nr2(l) : 0.0;
+                const double4_t acc = tile_mma(n, 16 * ti + r16, j, kq, [&](int i, int k) { return X[(size_t)k * n + i]; },
+                                               [&](int k, int) { return w[k]; }, 16 * ti, n);
 #pragma unroll
-                for (int q = 0; q < NJ; ++q) {
-                    const int j = (tid & 15) + 16 * q;
-                    if (j >= min(n, kk)) continue;
-                    double v = 0.0;
-                    for (int t = i; t < n; ++t)
-                        v = __builtin_fma(X[(size_t)t * n + i], zero[q] ? (t == j ? rl[q] : 0.0) : W[(size_t)pp[q] * ld + t] * rl[q], v);
-                    tmat[(size_t)i * kk + j] = v * rl[q];
+                for (int v = 0; v < 4; ++v) {
+                    const int i = 16 * ti + 4 * v + kq;
+                    if (i < n && j < kk) tmat[(size_t)i * kk + j] = l > 0.0 ? (acc[v] * rl) * rl : 0.0;
                 }
+            }
         }
     }
     if (tid < n) {
@@ -1376,8 +1395,10 @@ int launch_jacobi_eig_batch(hipStream_t s, const JacobiProblem* probs, int count
     // barrier.  After the preconditioner few columns still move, and 512 threads leave its phases 256 registers.
     const int jgl = pre ? PRE_JGL : JGL_PLAIN;
     size_t lds = pre ? lds_pre : region(jgl) * sizeof(double) + small;
-    for (int i = 0; i < count; ++i)
-        if (probs[i].gram) lds = std::max(lds, 2 * (size_t)n * (n + 1) * sizeof(double));      // (n <= SM_MAX_CHOL)
+    bool repair = false;
+    for (int i = 0; i < count; ++i) repair = repair || probs[i].gram;
+    if (repair && n > SM_MAX_CHOL) return METIS_UNSUPPORTED;
+    if (repair) lds = std::max(lds, 2 * (size_t)n * (n + 1) * sizeof(double));
     const int need = (ne / 2 * jgl + 63) / 64 * 64;               // at most 128 ceil(n / 16): the kernel's launch bound
     const int threads = need > 512 ? need : 512;
     for (int b0 = 0; b0 < count; b0 += SM_MAX_BATCH) {
@@ -1390,18 +1411,20 @@ int launch_jacobi_eig_batch(hipStream_t s, const JacobiProblem* probs, int count
         if (!ensure_dyn_lds((const void*)k_jacobi_eig<__VA_ARGS__>, lds, lds_set)) return METIS_HIP_ERROR;        \
         hipLaunchKernelGGL((k_jacobi_eig<__VA_ARGS__>), dim3(nb), dim3(threads), lds, s, batch, n, kk);           \
     }
-#define JACOBI_PRE(T) if (pre) JACOBI_CASE(16 / PRE_JGL * T, PRE_JGL, false, T) else JACOBI_CASE(T, JGL_PLAIN)
+#define JACOBI_REPAIR(T, ...) if (repair) JACOBI_CASE(T, JGL_PLAIN, true, __VA_ARGS__) else JACOBI_CASE(T, JGL_PLAIN, false, __VA_ARGS__)
+#define JACOBI_PRE(T) if (pre) JACOBI_CASE(16 / PRE_JGL * T, PRE_JGL, true, false, T) else JACOBI_REPAIR(T, false)
         switch ((n + 15) / 16) {
-            case 1: if (n <= 4) JACOBI_CASE(1, JGL_PLAIN, true) else JACOBI_CASE(1, JGL_PLAIN) break;
-            case 2: JACOBI_CASE(2, JGL_PLAIN) break;
-            case 3: JACOBI_CASE(3, JGL_PLAIN) break;
-            case 4: JACOBI_CASE(4, JGL_PLAIN) break;
+            case 1: if (n <= 4) JACOBI_REPAIR(1, true) else JACOBI_REPAIR(1, false) break;
+            case 2: JACOBI_REPAIR(2, false) break;
+            case 3: JACOBI_REPAIR(3, false) break;
+            case 4: JACOBI_REPAIR(4, false) break;
             case 5: JACOBI_PRE(5) break;
             case 6: JACOBI_PRE(6) break;
-            case 7: JACOBI_CASE(7, JGL_PLAIN) break;
-            default: JACOBI_CASE(8, JGL_PLAIN) break;
+            case 7: JACOBI_CASE(7, JGL_PLAIN, false) break;
+            default: JACOBI_CASE(8, JGL_PLAIN, false) break;
         }
 #undef JACOBI_PRE
+#undef JACOBI_REPAIR
 #undef JACOBI_CASE
         METIS_LAUNCH_CHECK();
     }

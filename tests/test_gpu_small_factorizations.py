@@ -47,6 +47,20 @@ def test_repeated_singular_values(metis, k, p):  # noqa: F811
     assert np.linalg.norm((U * S) @ V.T - (Ur * Sr) @ Vr.T) / np.linalg.norm(An) < 1e-3
 
 
+@pytest.mark.parametrize("k,p", [(1, 1), (2, 2), (5, 4), (8, 8), (24, 8), (33, 8), (40, 24), (61, 10), (64, 8), (64, 16), (65, 16),
+                                 (66, 18), (72, 16), (80, 16)])
+def test_ill_conditioned_sketch(metis, k, p):  # noqa: F811
+    # the kept directions within a factor of 16, the others 2^-18 of them: the first orthogonalisation leaves its basis orthonormal to
+    # ~2^-52 2^36 only, and the second pass repairs it; orders that are multiples of 8, and the generic kernels' that are not
+    g = torch.Generator().manual_seed(100 * k + p)
+    A = torch.randn((512, 256), generator=g)
+    A[:, :k] *= 2.0 ** -torch.div(4 * torch.arange(k), k, rounding_mode="floor")
+    A[:, k:] *= 2.0 ** -18
+    A = A.to(torch.bfloat16)
+    got = _run(metis, A, k, p, 1.0, seed=9)
+    _compare(A, got, odec.decompose(A.double().numpy(), k, p, 1.0, seed=9), k)
+
+
 @pytest.mark.parametrize("k,p", [(1, 1), (1, 2), (2, 2), (3, 2)])
 def test_orders_up_to_four(metis, k, p):  # noqa: F811
     # factored on one lane up to order 4
