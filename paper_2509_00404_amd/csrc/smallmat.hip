@@ -1042,8 +1042,8 @@ __device__ __forceinline__ bool eig_precondition(double* __restrict__ R1, double
 // the later sweeps run over the columns that still move.
 // SMALL: n <= 4 (see chol_blocked).
 // PRE: the preconditioner runs, for orders of PRE 16-row tiles.  REPAIR: the problems bring CholeskyQR's second pass (JacobiProblem::gram);
-// instances of their own, for the code that never runs costs registers and its place all the same (16 columns 21.7 us with it, 21.2
-// without; 32 51.4, 50.1; the second eigenproblem of 4096 x 1024 x 4096 in training 203, 194).
+// instances of their own: inlined everywhere, its code left 36 bytes of scratch a lane also where it never runs (eigenproblems of order 32
+// and 20, us on average: 50.4 without the code, 51.3 with it, 50.6 so; of 64 and more no difference).
 template <int NE, int JGL, bool REPAIR, bool SMALL = false, int PRE = 0>
 __global__ void __launch_bounds__(NE * JGL <= 64 || PRE ? 512 : 8 * NE * JGL)
 k_jacobi_eig(const JacobiBatch batch, int n, int kk) {
@@ -1378,9 +1378,10 @@ int launch_chol_inv_batch(hipStream_t s, const CholProblem* probs, int count, in
 }
 
 // The orders from which on the preconditioner runs.  (It pays from 32 on: a lone decomposition with eigenproblems of order 36 and 28
-// takes 287 us with it and 316 with plain sweeps, of 72 and 56 435 and 616.  But a singular vector's sign is the one that the
-// method leaves it with, callers keep their factors from one build to the next, and below 72, and for the second problem of
-// every decomposition, it has always been the plain sweeps'.)
+// takes 287 us with it and 316 with plain sweeps, of 72 and 56 435 and 616.  A singular vector's sign is the one that the method leaves
+// it with.  No sign is promised, and those of orders 72 to 84 may change with this method's code; but below 72, and for the second problem
+// of every decomposition, which sets the signs of U and V, it has always been the plain sweeps', and callers keep their factors from one
+// build to the next.)
 #define PRE_MIN_N 72
 int launch_jacobi_eig_batch(hipStream_t s, const JacobiProblem* probs, int count, int n, int kk) {
     if (n < 1 || n > 128 || count < 0) return METIS_UNSUPPORTED;
