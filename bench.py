@@ -570,8 +570,8 @@ def extras(out, args, torch, metis, linears, all_ops, step, multi, useful_flops)
             mx_g = timed(torch, lambda: metis.mxfp4_gemm_nt(qx, qw, Ymx))
             tf = 2.0 * l.L * l.K * l.N / (mx_g["median_ms"] * 1e-3) / 1e12
             large = l.K % 256 == 0 and l.K >= 2048 and l.L * l.N > 448 * 128 * 128      # the streaming kernel's (csrc/mxfp4.hip)
-            out["mxfp4_variant"] = {"kernel": "k_mxfp4_gemm_nt_stream" if large else "k_mxfp4_gemm_nt", "linear": l.name, "quantize_both_ms": mx_q["median_ms"],
-                                    "gemm_ms": mx_g["median_ms"], "achieved": round(tf, 1), "peak": PEAK_FP4_TFLOPS,
+            out["mxfp4_variant"] = {"kernel": "k_mxfp4_gemm_nt_stream" if large else "k_mxfp4_gemm_nt", "linear": l.name,
+                                    "quantize_both_ms": mx_q["median_ms"], "gemm_ms": mx_g["median_ms"], "achieved": round(tf, 1), "peak": PEAK_FP4_TFLOPS,
                                     "unit": "TFLOP/s", "frac": round(tf / PEAK_FP4_TFLOPS, 4)}
         except Exception as e:                                     # an extra figure must never cost the main line
             out["mxfp4_variant"] = {"error": repr(e)[:200]}
